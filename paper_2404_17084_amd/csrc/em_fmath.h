@@ -1,4 +1,5 @@
-// FP32 elementary functions of the mixed-precision edge terms (device only).
+// Elementary functions of the edge terms (device only), FP32 for the mixed path
+// and FP64 for the double-precision path.
 //
 // The FP32 terms are accumulated in FP64 and checked against an FP64 oracle at
 // 1e-5 relative per cell, so a few ulp per function are enough; these forms
@@ -65,6 +66,100 @@ __device__ __forceinline__ float log1p_f32(float u)
     p = fmaf(p, s2, 1.0f);
     const float corr = v < 2.0f ? (u - (v - 1.0f)) * rcp_f32(v) : 0.0f;
     return fmaf((float)k, 0.6931471805599453f, fmaf(s + s, p, corr));
+}
+
+// ---------------------------------------------------------------- FP64
+// The library's double functions cost several times these (argument classes
+// the edge terms never meet, correctly rounded divisions, extended-precision
+// intermediate sums).  Each form below is within 3 ulp over its stated domain.
+
+// p z + c with c kept in its register.  The compiler forms the steps of a
+// Horner sum as a move of the coefficient and a two-operand v_fmac_f64, one
+// instruction more per coefficient than the three-operand form.
+__device__ __forceinline__ double horner_f64(double p, double z, double c)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(p), "v"(z), "v"(c));
+    return r;
+}
+
+// n / d for d of ordinary size (no overflow of 1/d): the hardware reciprocal
+// (24 bits), one Newton step (48 bits) and a residual correction.
+__device__ __forceinline__ double div_f64(double n, double d)
+{
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(fma(-d, y, 1.0), y, y);
+    const double q = n * y;
+    return fma(fma(-d, q, n), y, q);
+}
+
+// sqrt(x), x >= 0 and not denormal (0 gives 0): the hardware reciprocal square
+// root and two coupled Newton steps.
+__device__ __forceinline__ double sqrt_f64(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : 0.0;
+}
+
+// atan2(y, x) for y >= 0, result in [0, pi]; (0, 0) gives 0.  Three ranges of
+// y / |x|, cut at tan(pi/8) and tan(3 pi/8): the angle is k pi/4 + atan(q) with
+// q = y / |x|, (y - |x|) / (y + |x|) or -|x| / y, |q| <= tan(pi/8), one division
+// for all three; x < 0 mirrors it to (4 - k) pi/4 - atan(q).  atan q = q + q z
+// P(z), z = q^2, P fitted for least maximum relative error (Remez; 4e-17).
+__device__ __forceinline__ double atan2_f64(double y, double x)
+{
+    const double ax = fabs(x);
+    const bool low = y <= 0.41421356237309503 * ax, steep = y > 2.4142135623730951 * ax;
+    const double num = low ? y : (steep ? -ax : y - ax);
+    const double den = (low ? ax : (steep ? y : y + ax)) + 1e-300;  // (0, 0): 0 / 1e-300
+    double k = low ? 0.0 : (steep ? 2.0 : 1.0);
+    k = x < 0.0 ? 4.0 - k : k;
+    const double q = div_f64(x < 0.0 ? -num : num, den), z = q * q;
+    double p = 0.021169054961637412741;
+    p = horner_f64(p, z, -0.043509553233083249925);
+    p = horner_f64(p, z, 0.056894129577670176396);
+    p = horner_f64(p, z, -0.06640449782644454278);
+    p = horner_f64(p, z, 0.076899799748101054266);
+    p = horner_f64(p, z, -0.090907750859824370933);
+    p = horner_f64(p, z, 0.11111106273502896402);
+    p = horner_f64(p, z, -0.14285714183450741756);
+    p = horner_f64(p, z, 0.19999999998888552392);
+    p = horner_f64(p, z, -0.33333333333328614107);
+    return fma(k, 0.78539816339744831, fma(q * z, p, q));
+}
+
+// log(1 + n / d) for n >= 0, d > 0: the ratio of N = d + n and d as 2^k M / D
+// with M / D in [sqrt(1/2), sqrt(2)], log(M / D) = 2 atanh(s), s = (M - D) /
+// (M + D), |s| <= 0.1716 (n / (N + d), with n exact, when k = 0); atanh s =
+// s + s^3 P(s^2), P fitted for least maximum relative error (Remez; 2e-18).
+// One division for the ratio and the logarithm.
+__device__ __forceinline__ double log1p_ratio_f64(double n, double d)
+{
+    const double N = d + n;
+    int k = __builtin_amdgcn_frexp_exp(N) - __builtin_amdgcn_frexp_exp(d);
+    double M = __builtin_amdgcn_frexp_mant(N), D = __builtin_amdgcn_frexp_mant(d);
+    if (M > 1.4142135623730951 * D) {
+        D += D;
+        k += 1;
+    } else if (D > 1.4142135623730951 * M) {
+        M += M;
+        k -= 1;
+    }
+    const double s = div_f64(k == 0 ? n : M - D, k == 0 ? N + d : M + D), z = s * s;
+    double p = 0.074054223133321661683;
+    p = horner_f64(p, z, 0.07656206821538370732);
+    p = horner_f64(p, z, 0.090918181095641508513);
+    p = horner_f64(p, z, 0.11111098483779897497);
+    p = horner_f64(p, z, 0.14285714380770156303);
+    p = horner_f64(p, z, 0.19999999999649014241);
+    p = horner_f64(p, z, 0.33333333333333826701);
+    const double s2 = s + s;
+    return fma((double)k, 0.69314718055994531, fma(s2 * z, p, s2));
 }
 
 }  // namespace em

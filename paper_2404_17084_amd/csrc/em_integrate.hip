@@ -24,7 +24,7 @@
 // and the angular moments P_n = int S^n dalpha are evaluated in closed form
 // from l (t = l/R0, S = sqrt(c^2 + l^2), c^2 = r0^2 + R0^2):
 //   r0 P_-1 = atan2(r0 l, R0 S),  P_0 = atan2(l, R0),  P_2 = r0^2 P_0 + R0 l,
-//   P_3 = (R0 l S + R0 c^2 a)/2 + r0^2 R0 a + r0^2 (r0 P_-1),  a = asinh(l/c),
+//   P_3 = (R0 l S + R0 c^2 a)/2 + r0^2 R0 a + r0^3 (r0 P_-1),  a = asinh(l/c),
 //   P_4 = r0^4 P_0 + 2 r0^2 R0 l + R0^3 l + R0 l^3/3,
 //   P_5 = R0 l (S^3/4 + 3 c^2 S/8) + 3 R0 c^4 a/8 + r0^2 P_3.
 // The M4 piece radii s = 1, 2 split the edge at l_k = sqrt(k^2 - c^2).
@@ -38,15 +38,6 @@
 namespace em {
 
 namespace {
-
-__device__ __forceinline__ double f_log1p(double x) { return log1p(x); }
-__device__ __forceinline__ float f_log1p(float x) { return log1p_f32(x); }  // x >= 0 in the edge terms
-__device__ __forceinline__ double f_atan2(double y, double x) { return atan2(y, x); }
-__device__ __forceinline__ float f_atan2(float y, float x) { return atan2_f32(y, x); }  // y >= 0 in the edge terms
-__device__ __forceinline__ double f_sqrt(double x) { return sqrt(x); }
-__device__ __forceinline__ float f_sqrt(float x) { return sqrt_f32(x); }
-__device__ __forceinline__ double f_rcp(double x) { return 1.0 / x; }
-__device__ __forceinline__ float f_rcp(float x) { return rcp_f32(x); }
 
 // Work counters of one thread (feed the algorithmic flop model).
 struct Work {
@@ -78,30 +69,27 @@ __device__ __forceinline__ R pi_dH(R r0)
 }
 
 // angle atan(b/R0) - atan(a/R0) subtended at the foot point by the part [a, b] of the edge line
-template <typename R>
-__device__ __forceinline__ R seg_angle(R R0, R a, R b, Work &wk)
+__device__ __forceinline__ float seg_angle(float R0, float a, float b, Work &wk)
 {
     wk.angles++;
-    return f_atan2(R0 * (b - a), R0 * R0 + a * b);
+    return atan2_f32(R0 * (b - a), R0 * R0 + a * b);
 }
 
-// Transcendentals of the closed form at x >= 0 with S = sqrt(c^2 + x^2):
+// Transcendentals of the FP32 closed form at x >= 0 with S = sqrt(c^2 + x^2):
 //   a = asinh(x/c), beta = P_0 - r0 P_-1 = atan(x/R0) - atan(r0 x/(R0 S)).
-template <typename R>
 struct Trans {
-    R x, S, a, beta;
+    float x, S, a, beta;
 };
 
-template <typename R>
-__device__ __forceinline__ Trans<R> trans(R r0, R R0, R c2, R c, R x, R S, Work &wk)
+__device__ __forceinline__ Trans trans(float r0, float R0, float c2, float c, float x, float S, Work &wk)
 {
     wk.moments++;
-    Trans<R> t;
+    Trans t;
     t.x = x;
     t.S = S;
-    t.a = f_log1p(x * (R(1) + x * f_rcp(S + c)) * f_rcp(c));
-    const R R02 = R0 * R0;
-    t.beta = f_atan2(x * R0 * (R02 + x * x), (S + r0) * (R02 * S + r0 * x * x));
+    t.a = log1p_f32(x * (1.0f + x * rcp_f32(S + c)) * rcp_f32(c));
+    const float R02 = R0 * R0;
+    t.beta = atan2_f32(x * R0 * (R02 + x * x), (S + r0) * (R02 * S + r0 * x * x));
     return t;
 }
 
@@ -111,27 +99,16 @@ __device__ __forceinline__ Trans<R> trans(R r0, R R0, R c2, R c, R x, R S, Work 
 //   T = g_2 x + g_3 P3' + g_4 (2 r0^2 x + R0^2 x + x^3/3)
 //       + g_5 (x (S^3/4 + 3 c^2 S/8) + 3 c^4 a/8 + r0^2 P3'),
 //   P3' = (x S + c^2 a)/2 + r0^2 a.
-template <typename R>
-__device__ __forceinline__ R core(const Trans<R> &t, R r0, R R0, R A, R c2, R gm1, R g2, R g3, R g4, R g5)
+// FP32, the inner piece only (g_3 = 0).
+__device__ __forceinline__ float core_inner(const Trans &t, float r0, float R0, float A, float c2)
 {
-    const R x = t.x, S = t.S, a = t.a;
-    const R Hodd = gm1 + g3 * A * A + g5 * A * A * A;
-    const R P3r = R(0.5) * (x * S + c2 * a) + A * a;
-    const R T = g2 * x + g3 * P3r + g4 * (R(2) * A * x + R0 * R0 * x + x * x * x * R(1.0 / 3.0)) +
-                g5 * (x * (S * S * S * R(0.25) + R(0.375) * c2 * S) + R(0.375) * c2 * c2 * a + A * P3r);
+    const float gm1 = -0.25f, g2 = -1.0f / 6.0f, g3 = 0.0f, g4 = 0.075f, g5 = -0.025f;
+    const float x = t.x, S = t.S, a = t.a;
+    const float Hodd = gm1 + g3 * A * A + g5 * A * A * A;
+    const float P3r = 0.5f * (x * S + c2 * a) + A * a;
+    const float T = g2 * x + g3 * P3r + g4 * (2.0f * A * x + R0 * R0 * x + x * x * x * (1.0f / 3.0f)) +
+                    g5 * (x * (S * S * S * 0.25f + 0.375f * c2 * S) + 0.375f * c2 * c2 * a + A * P3r);
     return -t.beta * Hodd + r0 * R0 * T;
-}
-
-template <typename R>
-__device__ __forceinline__ R core_inner(const Trans<R> &t, R r0, R R0, R A, R c2)
-{
-    return core<R>(t, r0, R0, A, c2, R(-0.25), R(-1.0 / 6.0), R(0), R(0.075), R(-0.025));
-}
-
-template <typename R>
-__device__ __forceinline__ R core_shell(const Trans<R> &t, R r0, R R0, R A, R c2)
-{
-    return core<R>(t, r0, R0, A, c2, R(-4.0 / 15.0), R(-1.0 / 3.0), R(0.25), R(-0.075), R(1.0 / 120.0));
 }
 
 __constant__ float kGLx[4] = {0.1834346424956498f, 0.5255324099163290f, 0.7966664774136267f, 0.9602898564975363f};
@@ -176,56 +153,39 @@ __device__ __forceinline__ float shell_quad(float r0, float R0, float c2, float 
     return tot * R0 * (1.0f / 120.0f);
 }
 
-__device__ __forceinline__ float shell_quad_t(float r0, float R0, float c2, float dsing, float a, float b, Work &wk)
-{
-    return shell_quad(r0, R0, c2, dsing, a, b, wk);
-}
-
-__device__ __forceinline__ double shell_quad_t(double, double, double, double, double, double, Work &)
-{
-    return 0.0;
-}
-
 // pi [Qt(l_b) - Qt(l_a)] for one directed edge (R0 > 0), lengths in units of h:
 // the edge's whole share of pi int (G_c(S) - G_c(r0)) dalpha.  The signed edge
 // interval is cut at the support crossings +-l2 and (when c < 1) the inner
 // crossings +-l1 into parts beyond the support (-H times their angle), shell
-// parts and an inner part (closed forms at their endpoints, odd in l; the
-// FP32 path integrates shell parts by quadrature instead), plus the piece
-// correction dH times the angle of the shell parts when r0 < 1.
+// parts and an inner part, plus the piece correction dH times the angle of the
+// shell parts when r0 < 1.
 //
-// All cases are expressed as one fixed list of tasks - up to 4 angles, 3
-// closed-form points (|l_a|, |l_b| clamped, and l1; each point serves both
-// piece polynomials with its own weights) and 2 quadrature intervals - so that
-// the lanes of a wavefront, which hold different particles, run each task
-// type in the same code instead of one branch per geometric case.
-template <typename R>
-__device__ __forceinline__ R sgnr(R x)
-{
-    return x > R(0) ? R(1) : (x < R(0) ? R(-1) : R(0));
-}
+// FP32 form (distributions 0-2 of the mixed path): all cases are expressed as
+// one fixed list of tasks - up to 4 angles, 3 closed-form points of the inner
+// piece (|l_a|, |l_b| clamped, and l1) and 2 quadrature intervals of the shell
+// piece - so that the lanes of a wavefront, which hold different particles, run
+// each task type in the same code instead of one branch per geometric case.
+__device__ __forceinline__ float sgnr(float x) { return x > 0.0f ? 1.0f : (x < 0.0f ? -1.0f : 0.0f); }
 
-template <typename R>
-__device__ __forceinline__ R edge_term(R r0, R R0, R la, R lb, R Ht, R dH, Work &wk)
+__device__ __forceinline__ float edge_term(float r0, float R0, float la, float lb, float, float Ht, float dH, Work &wk)
 {
-    constexpr bool kQuad = std::is_same<R, float>::value;
-    const R A = r0 * r0;
-    const R c2 = A + R0 * R0;
+    const float A = r0 * r0;
+    const float c2 = A + R0 * R0;
     // angle tasks: (a, b, weight)
-    R aa0 = la, ab0 = lb, aw0 = R(0), aa1 = R(0), ab1 = R(0), aw1 = R(0);
-    R aa2 = R(0), ab2 = R(0), aw2 = R(0), aa3 = R(0), ab3 = R(0), aw3 = R(0);
-    // closed-form point weights (inner, shell) at |ca|, |cb| and l1
-    R wi0 = R(0), wi1 = R(0), wi2 = R(0), ws0 = R(0), ws1 = R(0), ws2 = R(0);
+    float aa0 = la, ab0 = lb, aw0 = 0.0f, aa1 = 0.0f, ab1 = 0.0f, aw1 = 0.0f;
+    float aa2 = 0.0f, ab2 = 0.0f, aw2 = 0.0f, aa3 = 0.0f, ab3 = 0.0f, aw3 = 0.0f;
+    // closed-form point weights at |ca|, |cb| and l1
+    float wi0 = 0.0f, wi1 = 0.0f, wi2 = 0.0f;
     // quadrature intervals
-    R qa0 = R(0), qb0 = R(0), qa1 = R(0), qb1 = R(0);
+    float qa0 = 0.0f, qb0 = 0.0f, qa1 = 0.0f, qb1 = 0.0f;
     bool q0 = false, q1 = false;
-    R l2 = R(0), c = R(1), l1 = R(0), ca = la, cb = lb;
-    if (!(c2 < R(4))) {
+    float l2 = 0.0f, c = 1.0f, l1 = 0.0f, ca = la, cb = lb;
+    if (!(c2 < 4.0f)) {
         aw0 = -Ht;  // the whole edge lies beyond the support
     } else {
         wk.eterms++;
-        l2 = f_sqrt(R(4) - c2);
-        c = f_sqrt(c2);
+        l2 = sqrt_f32(4.0f - c2);
+        c = sqrt_f32(c2);
         ca = fmin(fmax(la, -l2), l2);
         cb = fmin(fmax(lb, -l2), l2);
         if (la < -l2) {
@@ -237,85 +197,205 @@ __device__ __forceinline__ R edge_term(R r0, R R0, R la, R lb, R Ht, R dH, Work 
             ab1 = lb;
             aw1 = -Ht;
         }
-        if (c2 >= R(1)) {
+        if (c2 >= 1.0f) {
             if (cb > ca) {
-                if (kQuad) {
-                    q0 = true;
-                    qa0 = ca;
-                    qb0 = cb;
-                } else {
-                    ws1 += sgnr(cb);
-                    ws0 -= sgnr(ca);
-                }
+                q0 = true;
+                qa0 = ca;
+                qb0 = cb;
                 aa2 = ca;
                 ab2 = cb;
                 aw2 = dH;
             }
         } else {
-            l1 = f_sqrt(R(1) - c2);
+            l1 = sqrt_f32(1.0f - c2);
             // left shell part [max(ca, -l2), min(cb, -l1)]
             if (ca < -l1) {
-                const R B = fmin(cb, -l1);
-                if (kQuad) {
-                    q0 = true;
-                    qa0 = ca;
-                    qb0 = B;
-                } else {
-                    ws0 -= sgnr(ca);
-                    if (B == cb) ws1 += sgnr(cb);
-                    else ws2 -= R(1);  // B = -l1
-                }
+                q0 = true;
+                qa0 = ca;
+                qb0 = fmin(cb, -l1);
                 aa2 = ca;
-                ab2 = B;
+                ab2 = qb0;
                 aw2 = dH;
             }
             // right shell part [max(ca, l1), min(cb, l2)]
             if (cb > l1) {
-                const R Aq = fmax(ca, l1);
-                if (kQuad) {
-                    q1 = true;
-                    qa1 = Aq;
-                    qb1 = cb;
-                } else {
-                    ws1 += sgnr(cb);
-                    if (Aq == ca) ws0 -= sgnr(ca);
-                    else ws2 -= R(1);  // A = +l1
-                }
-                aa3 = Aq;
+                q1 = true;
+                qa1 = fmax(ca, l1);
+                qb1 = cb;
+                aa3 = qa1;
                 ab3 = cb;
                 aw3 = dH;
             }
             // inner part [max(ca, -l1), min(cb, l1)]
-            const R Ai = fmax(ca, -l1), Bi = fmin(cb, l1);
+            const float Ai = fmax(ca, -l1), Bi = fmin(cb, l1);
             if (Bi > Ai) {
                 if (Bi == cb) wi1 += sgnr(cb);
-                else wi2 += R(1);  // B = +l1
+                else wi2 += 1.0f;  // B = +l1
                 if (Ai == ca) wi0 -= sgnr(ca);
-                else wi2 += R(1);  // A = -l1: -sgn(A) core(l1) = +core(l1)
+                else wi2 += 1.0f;  // A = -l1: -sgn(A) core(l1) = +core(l1)
             }
         }
     }
-    R tot = R(0);
-    if (aw0 != R(0)) tot += aw0 * seg_angle<R>(R0, aa0, ab0, wk);
-    if (aw1 != R(0)) tot += aw1 * seg_angle<R>(R0, aa1, ab1, wk);
-    if (aw2 != R(0)) tot += aw2 * seg_angle<R>(R0, aa2, ab2, wk);
-    if (aw3 != R(0)) tot += aw3 * seg_angle<R>(R0, aa3, ab3, wk);
-    const R x0 = fabs(ca), x1 = fabs(cb);
-    if ((wi0 != R(0) || ws0 != R(0)) && x0 > R(0)) {
-        const Trans<R> t = trans<R>(r0, R0, c2, c, x0, x0 == l2 ? R(2) : f_sqrt(c2 + x0 * x0), wk);
-        tot += wi0 * core_inner<R>(t, r0, R0, A, c2) + ws0 * core_shell<R>(t, r0, R0, A, c2);
+    float tot = 0.0f;
+    if (aw0 != 0.0f) tot += aw0 * seg_angle(R0, aa0, ab0, wk);
+    if (aw1 != 0.0f) tot += aw1 * seg_angle(R0, aa1, ab1, wk);
+    if (aw2 != 0.0f) tot += aw2 * seg_angle(R0, aa2, ab2, wk);
+    if (aw3 != 0.0f) tot += aw3 * seg_angle(R0, aa3, ab3, wk);
+    const float x0 = fabsf(ca), x1 = fabsf(cb);
+    if (wi0 != 0.0f && x0 > 0.0f) {
+        const Trans t = trans(r0, R0, c2, c, x0, x0 == l2 ? 2.0f : sqrt_f32(c2 + x0 * x0), wk);
+        tot += wi0 * core_inner(t, r0, R0, A, c2);
     }
-    if ((wi1 != R(0) || ws1 != R(0)) && x1 > R(0)) {
-        const Trans<R> t = trans<R>(r0, R0, c2, c, x1, x1 == l2 ? R(2) : f_sqrt(c2 + x1 * x1), wk);
-        tot += wi1 * core_inner<R>(t, r0, R0, A, c2) + ws1 * core_shell<R>(t, r0, R0, A, c2);
+    if (wi1 != 0.0f && x1 > 0.0f) {
+        const Trans t = trans(r0, R0, c2, c, x1, x1 == l2 ? 2.0f : sqrt_f32(c2 + x1 * x1), wk);
+        tot += wi1 * core_inner(t, r0, R0, A, c2);
     }
-    if (wi2 != R(0) || ws2 != R(0)) {
-        const Trans<R> t = trans<R>(r0, R0, c2, c, l1, R(1), wk);
-        tot += wi2 * core_inner<R>(t, r0, R0, A, c2) + ws2 * core_shell<R>(t, r0, R0, A, c2);
+    if (wi2 != 0.0f) {
+        const Trans t = trans(r0, R0, c2, c, l1, 1.0f, wk);
+        tot += wi2 * core_inner(t, r0, R0, A, c2);
     }
-    if (kQuad) {
-        if (q0) tot += shell_quad_t(r0, R0, c2, c2 >= R(1) ? c : R(1), qa0, qb0, wk);
-        if (q1) tot += shell_quad_t(r0, R0, c2, R(1), qa1, qb1, wk);
+    if (q0) tot += shell_quad(r0, R0, c2, c2 >= 1.0f ? c : 1.0f, qa0, qb0, wk);
+    if (q1) tot += shell_quad(r0, R0, c2, 1.0f, qa1, qb1, wk);
+    return tot;
+}
+
+// ---------------------------------------------------------------- FP64 edge terms
+// The parts of an edge [la, lb]: beyond the support [la, ca] + [cb, lb], shell
+// [ca, ia] + [ib, cb], inner [ia, ib], every part oriented and possibly empty.
+// Far edges (c >= 2) are all beyond (l2 = 0).
+struct EdgeParts {
+    double ca, cb, ia, ib;
+    bool near, inner;
+};
+
+__device__ __forceinline__ EdgeParts edge_parts(bool live, double r0, double R0, double la, double lb)
+{
+    EdgeParts P;
+    const double c2 = fma(R0, R0, r0 * r0);
+    P.near = live && c2 < 4.0;
+    P.inner = P.near && c2 < 1.0;
+    const double l2 = P.near ? sqrt_f64(4.0 - c2) : 0.0;
+    // min(max(x, lo), hi) of la <= lb: the median of three also when lo > hi
+    P.ca = fmin(fmax(la, -l2), lb);
+    P.cb = fmax(P.ca, fmin(l2, lb));
+    P.ia = P.cb;
+    P.ib = P.cb;
+    if (P.inner) {
+        const double l1 = sqrt_f64(1.0 - c2);
+        P.ia = fmin(fmax(P.ca, -l1), P.cb);
+        P.ib = fmax(P.ia, fmin(l1, P.cb));
+    }
+    return P;
+}
+
+// Length of the part [x, y]: the edge length from the edge record when the
+// part is the whole edge (the difference of its ends would lose digits of a
+// short edge far from the foot point), else the difference (a clipped end sits
+// on a kernel sphere, where an end shift changes the integral only to second
+// order).
+__device__ __forceinline__ double part_len(double x, double y, double la, double lb, double Le)
+{
+    return (x == la && y == lb) ? Le : y - x;
+}
+
+// The angle of two parts [a1, b1], [a2, b2] at the foot point as the argument
+// of the product of their complex numbers (R0^2 + a b) + i R0 (b - a) (the sum
+// stays below pi).
+__device__ __forceinline__ void angle_product(double R0, double a1, double b1, double a2, double b2, double &y,
+                                              double &x)
+{
+    const double R02 = R0 * R0;
+    const double x1 = fma(a1, b1, R02), y1 = R0 * (b1 - a1), x2 = fma(a2, b2, R02), y2 = R0 * (b2 - a2);
+    x = fma(x1, x2, -(y1 * y2));
+    y = fma(x1, y2, x2 * y1);
+}
+
+// Closed form of one piece over one edge part [a, a + L]: the integral along it
+// of pi r0 [G_p(S) - G_p(r0)] dalpha for the piece polynomial pi G_p = g_-1/s +
+// g_0 + g_2 s^2 + g_3 s^3 + g_4 s^4 + g_5 s^5, that is the difference between
+// the part's ends of the antiderivative
+//   -beta H_odd + r0 R0 T,  H_odd = g_-1 + g_3 r0^4 + g_5 r0^6,
+//   T = g_2 x + g_3 P3' + g_4 (2 r0^2 x + R0^2 x + x^3/3)
+//       + g_5 (x (S^3/4 + 3 c^2 S/8) + 3 c^4 a/8 + r0^2 P3'),
+//   P3' = (x S + c^2 a)/2 + r0^2 a,  a = asinh(x/c),
+//   beta = atan(x/R0) - atan(r0 x/(R0 S)),
+// with every difference formed by a factor L instead of subtracting end values:
+//   beta_b - beta_a = 2 atan2(R0 L, S_a S_b + a b + c^2 + r0 (S_a + S_b)),
+//     numerator and denominator scaled by S_a S_b - a b where the sum S_a S_b +
+//     a b would cancel ((S_a S_b)^2 - (a b)^2 = c^2 (a^2 + b^2 + c^2));
+//   asinh(b/c) - asinh(a/c) = log(1 + L (1 + (a + b)/(S_a + S_b)) / (a + S_a)),
+//     with a + S_a = c^2 / (S_a - a) for a < 0;
+//   b S_b - a S_a = L (S_b + t),  t = a (a + b) / (S_a + S_b),
+//   b S_b^3 - a S_a^3 = L (S_b^3 + t (S_a^2 + S_a S_b + S_b^2)),
+//   b^3 - a^3 = L (a^2 + a b + b^2).
+// The integrand is even in l, so a part with a + b < 0 is mirrored first.  One
+// arctangent and one logarithm per part, where the ends taken apart cost two
+// of each and every wall crossing a point of its own.
+__device__ __forceinline__ double part_term(double r0, double R0, double a0, double L, bool shell)
+{
+    const double b0 = a0 + L;
+    const bool mirror = a0 + b0 < 0.0;
+    const double a = mirror ? -b0 : a0, b = mirror ? -a0 : b0;
+    const double A = r0 * r0, R02 = R0 * R0;
+    const double c2 = fmax(A + R02, 1e-290);
+    const double Sa = sqrt_f64(fma(a, a, c2)), Sb = sqrt_f64(fma(b, b, c2));
+    const double ab = a * b, SS = Sa * Sb, Ssum = Sa + Sb;
+    const double rs = div_f64(1.0, Ssum);
+    const bool neg = ab < 0.0;
+    const double k = SS - ab, dx = fma(r0, Ssum, c2);
+    const double yb = R0 * L * (neg ? k : 1.0);
+    const double xb = neg ? fma(dx, k, c2 * (fma(a, a, fma(b, b, c2)))) : SS + ab + dx;
+    const double Dbeta = 2.0 * atan2_f64(yb, xb);
+    const double u = L * fma(a + b, rs, 1.0);
+    const bool an = a < 0.0;
+    const double Da = log1p_ratio_f64(an ? u * (Sa - a) : u, an ? c2 : a + Sa);
+    const double t = a * (a + b) * rs;
+    const double DxS = L * (Sb + t);
+    const double DxS3 = L * fma(t, fma(Sa, Sa, fma(Sb, Sb, SS)), Sb * Sb * Sb);
+    const double D3 = L * (fma(a, a, ab) + b * b);
+    // the piece's coefficients (inner, or inner plus the step to the shell)
+    const double sh = shell ? 1.0 : 0.0;
+    const double gm1 = fma(sh, -1.0 / 60.0, -0.25), g2 = fma(sh, -1.0 / 6.0, -1.0 / 6.0), g3 = 0.25 * sh;
+    const double g4 = fma(sh, -0.15, 0.075), g5 = fma(sh, 1.0 / 30.0, -0.025);
+    const double Hodd = fma(A * A, fma(g5, A, g3), gm1);
+    const double cD = fma(c2, Da, DxS);
+    const double DP3 = fma(0.5, cD, A * Da);
+    const double T5 = fma(0.25, DxS3, fma(0.375 * c2, cD, A * DP3));
+    const double T4 = fma(fma(2.0, A, R02), L, D3 * (1.0 / 3.0));
+    const double DT = fma(g2, L, fma(g3, DP3, fma(g4, T4, g5 * T5)));
+    return fma(-Dbeta, Hodd, r0 * R0 * DT);
+}
+
+// The FP64 form of the edge's terms, one edge at a time (per-pair
+// distributions, fixups, recomputed cells, table nodes); the task batches
+// (k_integrate_queued64) spread the same terms over a wavefront.
+__device__ __forceinline__ double edge_term(double r0, double R0, double la, double lb, double Le, double Ht,
+                                            double dH, Work &wk)
+{
+    const EdgeParts P = edge_parts(true, r0, R0, la, lb);
+    double tot = 0.0;
+    if (la < P.ca || P.cb < lb) {
+        double y, x;
+        angle_product(R0, la, P.ca, P.cb, lb, y, x);
+        tot -= Ht * atan2_f64(y, x);
+        wk.angles++;
+    }
+    if (P.near) {
+        wk.eterms++;
+        if (dH != 0.0 && (P.ca < P.ia || P.ib < P.cb)) {
+            double y, x;
+            angle_product(R0, P.ca, P.ia, P.ib, P.cb, y, x);
+            tot += dH * atan2_f64(y, x);
+            wk.angles++;
+        }
+#pragma unroll 1
+        for (int q = 0; q < 3; q++) {  // shell, inner, shell
+            const double x = q == 0 ? P.ca : (q == 1 ? P.ia : P.ib), y = q == 0 ? P.ia : (q == 1 ? P.ib : P.cb);
+            if (y > x) {
+                tot += part_term(r0, R0, x, part_len(x, y, la, lb, Le), q != 1);
+                wk.moments++;
+            }
+        }
     }
     return tot;
 }
@@ -393,14 +473,14 @@ __device__ __forceinline__ double pair_fraction(double px, double py, double pz,
             wk.edges++;
             if (rho == 0.0) continue;
             const double la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
-            const double lb = la + E.L * invh;
+            const double Le = E.L * invh, lb = la + Le;
             const double R0d = fabs(rho) * invh;
             if (PREC == MAP_MIXED && needs_fp64(r0d, R0d, r0d * r0d + R0d * R0d)) {
                 const unsigned slot = atomicAdd(fix_count, 1u);
                 if (slot < fix_cap) fix_items[slot] = (pair_k << 32) | (uint64_t)(uint32_t)s;
                 continue;
             }
-            const R t = edge_term<R>(r0, (R)R0d, (R)la, (R)lb, Ht, dH, wk);
+            const R t = edge_term(r0, (R)R0d, (R)la, (R)lb, (R)Le, Ht, dH, wk);
             face += (rho > 0.0) ? (double)t : -(double)t;
             if (PREC == MAP_MIXED) ev = fmaf((float)t, (float)t, ev);
         }
@@ -423,8 +503,8 @@ __device__ double edge_contribution_fp64(double px, double py, double pz, double
     const double rho = E.mx * wx + E.my * wy + E.mz * wz;
     if (rho == 0.0) return 0.0;
     const double la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
-    const double lb = la + E.L * invh;
-    const double t = edge_term<double>(r0, fabs(rho) * invh, la, lb, pi_H<double>(r0), pi_dH<double>(r0), wk);
+    const double Le = E.L * invh;
+    const double t = edge_term(r0, fabs(rho) * invh, la, la + Le, Le, pi_H<double>(r0), pi_dH<double>(r0), wk);
     const double face = (rho > 0.0) ? t : -t;
     return -(d >= 0.0 ? face : -face) * kInvPi;
 }
@@ -975,28 +1055,31 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
     if (cur >= 0) flush_work(wk, MULTI ? A.table[cur].counters : A.one.counters);
 }
 
-// FP64 form of the task batches: no quadrature (the shell piece keeps its
-// closed form), so two task kinds: angles and closed-form points carrying
-// both piece weights.
+// FP64 form of the task batches: the beyond parts' angle (or the shell parts',
+// in a lane without the former) is taken in place, a lane with both pushes the
+// shell angle; every shell and inner part is one closed-form task (part_term),
+// both pieces on one stack, since only their coefficients differ.
+constexpr int kQP = 192;  // part stack capacity: below 64 pending before a step, run above 128 before its last push
 struct WaveStacks64 {
-    double ang[4][kQ];  // R0, a, b, weight
-    double pnt[8][kQ];  // r0, R0, c2, c, x, S, inner weight, shell weight
+    double ang[3][kQA];  // atan2 arguments of the angle (imaginary, real part), weight
+    double pnt[4][kQP];  // parts: r0, signed R0 (sign = the term's sign), start a, length L
     double acc[64];
-    uint8_t ang_o[kQ], pnt_o[kQ];  // owner lanes
+    uint8_t ang_o[kQA], pnt_o[kQP];  // owner lanes (pnt_o: plus kShellPart for a shell part)
 };
+constexpr int kShellPart = 64;
 
 template <int KIND>
 __device__ __forceinline__ void run_one64(WaveStacks64 &W, int i, Work &wk)
 {
     if (KIND == 0) {
-        const double R0 = W.ang[0][i], a = W.ang[1][i], b = W.ang[2][i], w = W.ang[3][i];
-        atomicAdd(&W.acc[W.ang_o[i]], w * seg_angle<double>(R0, a, b, wk));
+        wk.angles++;
+        atomicAdd(&W.acc[W.ang_o[i]], W.ang[2][i] * atan2_f64(W.ang[0][i], W.ang[1][i]));
     } else {
-        const double r0 = W.pnt[0][i], R0 = W.pnt[1][i], c2 = W.pnt[2][i], c = W.pnt[3][i];
-        const double x = W.pnt[4][i], S = W.pnt[5][i], wi = W.pnt[6][i], wsh = W.pnt[7][i];
-        const Trans<double> t = trans<double>(r0, R0, c2, c, x, S, wk);
-        const double A = r0 * r0;
-        atomicAdd(&W.acc[W.pnt_o[i]], wi * core_inner<double>(t, r0, R0, A, c2) + wsh * core_shell<double>(t, r0, R0, A, c2));
+        wk.moments++;
+        const double sR0 = W.pnt[1][i];
+        const int o = W.pnt_o[i];
+        const double v = part_term(W.pnt[0][i], fabs(sR0), W.pnt[2][i], W.pnt[3][i], (o & kShellPart) != 0);
+        atomicAdd(&W.acc[o & 63], sR0 < 0.0 ? -v : v);
     }
 }
 
@@ -1017,9 +1100,12 @@ __device__ __forceinline__ void run_stack64(WaveStacks64 &W, int &count, int lan
     }
 }
 
-// WPE: resident wavefronts per SIMD the register budget is cut for (2: no
-// spills; 3: the LDS stacks of three workgroups fit a compute unit, at the
-// price of a few spilled registers)
+// Bound by FP64 VALU issue: 0.20 vector instructions per SIMD and clock (a
+// dense FMA stream reaches 0.235), 81 % of the lanes active; 10.2e6 pairs of a
+// clumpy cloud take 10.2 ms, and took 20.2 ms with two closed-form points per
+// part, an angle task per part and the library's double functions.  WPE:
+// resident wavefronts per SIMD the register budget is cut for (3: 167 VGPRs;
+// 2 waves 12.2 ms; a budget for 4 spills 60 to 100 registers, 27.7 ms).
 template <int WPE, bool MULTI>
 __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsigned *tile_ctr)
 {
@@ -1044,7 +1130,7 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
         const int64_t k = (t - JOB(tile_base)) * 64 + lane;
         const bool active = k < JOB(np);
         double px = 0.0, py = 0.0, pz = 0.0, invh = 1.0;
-        int64_t s = 0, s_end = 0, j = 0;
+        int32_t s = 0, s_end = 0, j = 0;
         if (active) {
             const int64_t a = JOB(pair_p)[k];
             const int64_t c = JOB(pair_c)[k];
@@ -1053,23 +1139,24 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
             pz = JOB(xyz)[3 * a + 2];
             invh = 1.0 / JOB(h)[a];
             const int64_t *__restrict__ cfo = JOB(cfo);
-            j = cfo[c] - 1;
-            s = fvo[cfo[c]];
-            s_end = fvo[cfo[c + 1]];
+            j = (int32_t)cfo[c] - 1;
+            s = (int32_t)fvo[cfo[c]];
+            s_end = (int32_t)fvo[cfo[c + 1]];
         }
         W.acc[lane] = 0.0;
-        int64_t face_end = s;
+        int32_t face_end = s;
         const int n_steps = wave_max((int)(s_end - s));
         int nA = 0, nP = 0;
         bool inside = true;
         int n_on = 0;  // walls whose plane holds the particle
         bool face_ok = false;
         double r0 = 0.0, Ht = 0.0, dH = 0.0, fsign = 1.0;
+        double acc_in = 0.0;  // this lane's angle terms taken in place
         for (int it = 0; it < n_steps; it++, s++) {
             const bool valid = s < s_end;
             if (valid && s == face_end) {
                 j++;
-                face_end = fvo[j + 1];
+                face_end = (int32_t)fvo[j + 1];
                 const double d = plane[4 * j + 3] - (plane[4 * j] * px + plane[4 * j + 1] * py + plane[4 * j + 2] * pz);
                 wk.faces++;
                 const bool in_j = d >= 0.0;
@@ -1082,7 +1169,7 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
                 dH = pi_dH<double>(r0);
             }
             bool live = valid && face_ok;
-            double R0 = 0.0, la = 0.0, lb = 0.0, sg = 0.0;
+            double R0 = 0.0, la = 0.0, lb = 0.0, Le = 0.0, sg = 0.0;
             if (live) {
                 const EdgeRec E = edges[s];
                 const double wx = px - E.vx, wy = py - E.vy, wz = pz - E.vz;
@@ -1092,113 +1179,64 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
                     live = false;
                 } else {
                     la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
-                    lb = la + E.L * invh;
+                    Le = E.L * invh;
+                    lb = la + Le;
                     R0 = fabs(rho) * invh;
                     sg = (rho > 0.0 ? 1.0 : -1.0) * fsign;
                 }
             }
-            // classification (the FP64 form of edge_term)
-            const double A = r0 * r0;
-            const double c2 = A + R0 * R0;
-            double aa[4] = {la, 0.0, 0.0, 0.0}, ab[4] = {lb, 0.0, 0.0, 0.0}, aw[4] = {0.0, 0.0, 0.0, 0.0};
-            double wi[3] = {0.0, 0.0, 0.0}, wsh[3] = {0.0, 0.0, 0.0};
-            double l2 = 0.0, c = 1.0, l1 = 0.0, ca = la, cb = lb;
-            if (live) {
-                if (!(c2 < 4.0)) {
-                    aw[0] = -Ht;
-                } else {
-                    wk.eterms++;
-                    l2 = sqrt(4.0 - c2);
-                    c = sqrt(c2);
-                    ca = fmin(fmax(la, -l2), l2);
-                    cb = fmin(fmax(lb, -l2), l2);
-                    if (la < -l2) {
-                        aw[0] = -Ht;
-                        ab[0] = fmin(lb, -l2);
-                    }
-                    if (lb > l2) {
-                        aa[1] = fmax(la, l2);
-                        ab[1] = lb;
-                        aw[1] = -Ht;
-                    }
-                    if (c2 >= 1.0) {
-                        if (cb > ca) {
-                            wsh[1] += sgnr(cb);
-                            wsh[0] -= sgnr(ca);
-                            aa[2] = ca;
-                            ab[2] = cb;
-                            aw[2] = dH;
-                        }
-                    } else {
-                        l1 = sqrt(1.0 - c2);
-                        if (ca < -l1) {
-                            const double B = fmin(cb, -l1);
-                            wsh[0] -= sgnr(ca);
-                            if (B == cb) wsh[1] += sgnr(cb);
-                            else wsh[2] -= 1.0;
-                            aa[2] = ca;
-                            ab[2] = B;
-                            aw[2] = dH;
-                        }
-                        if (cb > l1) {
-                            const double Aq = fmax(ca, l1);
-                            wsh[1] += sgnr(cb);
-                            if (Aq == ca) wsh[0] -= sgnr(ca);
-                            else wsh[2] -= 1.0;
-                            aa[3] = Aq;
-                            ab[3] = cb;
-                            aw[3] = dH;
-                        }
-                        const double Ai = fmax(ca, -l1), Bi = fmin(cb, l1);
-                        if (Bi > Ai) {
-                            if (Bi == cb) wi[1] += sgnr(cb);
-                            else wi[2] += 1.0;
-                            if (Ai == ca) wi[0] -= sgnr(ca);
-                            else wi[2] += 1.0;
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const bool want = live && aw[q] != 0.0;
-                const int slot = wave_push(want, nA);
-                if (want) {
-                    W.ang[0][slot] = R0;
-                    W.ang[1][slot] = aa[q];
-                    W.ang[2][slot] = ab[q];
-                    W.ang[3][slot] = sg * aw[q];
-                    W.ang_o[slot] = (uint8_t)lane;
-                }
-                run_stack64<0>(W, nA, lane, false, wk);
-            }
+            const EdgeParts P = edge_parts(live, r0, R0, la, lb);
+            if (P.near) wk.eterms++;
+            const bool has_b = live && (la < P.ca || P.cb < lb);
+            const bool has_s = P.near && dH != 0.0 && (P.ca < P.ia || P.ib < P.cb);
             {
-                const double xs[3] = {fabs(ca), fabs(cb), l1};
-#pragma unroll
-                for (int q = 0; q < 3; q++) {
-                    const double x = xs[q];
-                    const bool want = live && (wi[q] != 0.0 || wsh[q] != 0.0) && (q == 2 || x > 0.0);
-                    const int slot = wave_push(want, nP);
+                const double a1 = has_b ? la : P.ca, b1 = has_b ? P.ca : P.ia;
+                const double a2 = has_b ? P.cb : P.ib, b2 = has_b ? lb : P.cb;
+                double y, x;
+                angle_product(R0, a1, b1, a2, b2, y, x);
+                const double w = has_b ? -Ht : (has_s ? dH : 0.0);
+                acc_in = fma(w * sg, atan2_f64(y, x), acc_in);
+            }
+            wk.angles += (has_b || has_s) ? 1u : 0u;
+            {
+                const bool want = has_b && has_s;
+                const unsigned long long m = __ballot(want);
+                if (m != 0) {
+                    if (nA + __popcll(m) > kQA) run_stack64<0>(W, nA, lane, true, wk);
+                    const int slot = wave_push(want, nA);
                     if (want) {
-                        W.pnt[0][slot] = r0;
-                        W.pnt[1][slot] = R0;
-                        W.pnt[2][slot] = c2;
-                        W.pnt[3][slot] = c;
-                        W.pnt[4][slot] = x;
-                        W.pnt[5][slot] = q == 2 ? 1.0 : (x == l2 ? 2.0 : sqrt(c2 + x * x));
-                        W.pnt[6][slot] = sg * wi[q];
-                        W.pnt[7][slot] = sg * wsh[q];
-                        W.pnt_o[slot] = (uint8_t)lane;
+                        double y, x;
+                        angle_product(R0, P.ca, P.ia, P.ib, P.cb, y, x);
+                        W.ang[0][slot] = y;
+                        W.ang[1][slot] = x;
+                        W.ang[2][slot] = sg * dH;
+                        W.ang_o[slot] = (uint8_t)lane;
                     }
-                    run_stack64<1>(W, nP, lane, false, wk);
                 }
             }
+            auto push_part = [&](double x, double y, int kind) {
+                const bool want = P.near && y > x;
+                if (__ballot(want) == 0) return;
+                const int slot = wave_push(want, nP);
+                if (want) {
+                    W.pnt[0][slot] = r0;
+                    W.pnt[1][slot] = sg < 0.0 ? -R0 : R0;
+                    W.pnt[2][slot] = x;
+                    W.pnt[3][slot] = part_len(x, y, la, lb, Le);
+                    W.pnt_o[slot] = (uint8_t)(lane + kind);
+                }
+            };
+            push_part(P.ca, P.ia, kShellPart);
+            push_part(P.ia, P.ib, 0);
+            if (nP > kQP - 64) run_stack64<1>(W, nP, lane, false, wk);
+            push_part(P.ib, P.cb, kShellPart);
+            while (nP >= 64) run_stack64<1>(W, nP, lane, false, wk);
         }
         run_stack64<0>(W, nA, lane, true, wk);
         run_stack64<1>(W, nP, lane, true, wk);
         lds_sync_wave();
         if (active) {
-            JOB(f)[k] = (inside ? 1.0 : 0.0) - W.acc[lane] * kInvPi;
+            JOB(f)[k] = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
             if (inside && n_on >= 2) push_fix(FixList{JOB(fix_count), JOB(fix_items), JOB(fix_cap), nullptr}, k, kWindingSlot);
         }
         lds_sync_wave();
@@ -1286,14 +1324,14 @@ __global__ void __launch_bounds__(256) k_integrate_tiles(int64_t n_tiles, const 
                     wk.edges++;
                     if (rho == 0.0) continue;
                     const double la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
-                    const double lb = la + E.L * invh;
+                    const double Le = E.L * invh, lb = la + Le;
                     const double R0d = fabs(rho) * invh;
                     if (PREC == MAP_MIXED && needs_fp64(r0d, R0d, r0d * r0d + R0d * R0d)) {
                         const unsigned slot = atomicAdd(fx.count, 1u);
                         if (slot < fx.cap) fx.items[slot] = ((uint64_t)k << 32) | (uint64_t)(uint32_t)s;
                         continue;
                     }
-                    const R tv = edge_term<R>(r0, (R)R0d, (R)la, (R)lb, Ht, dH, wk);
+                    const R tv = edge_term(r0, (R)R0d, (R)la, (R)lb, (R)Le, Ht, dH, wk);
                     face += (rho > 0.0) ? (double)tv : -(double)tv;
                     if (PREC == MAP_MIXED) ev = fmaf((float)tv, (float)tv, ev);
                 }
@@ -1374,7 +1412,7 @@ __global__ void k_table_build(int n0, int n1, int n2, double *__restrict__ tab64
         const double S = sqrt(r0 * r0 + R0 * R0 + l * l);
         const double om = atan2(l * R0 * (R0 * R0 + l * l), (S + r0) * (R0 * R0 * S + r0 * l * l));
         Work wk;
-        const double e = edge_term<double>(r0, R0, 0.0, l, pi_H<double>(r0), pi_dH<double>(r0), wk);
+        const double e = edge_term(r0, R0, 0.0, l, l, pi_H<double>(r0), pi_dH<double>(r0), wk);
         I = om * (0.25 * kInvPi) - e * kInvPi;
     }
     tab64[q] = I;
@@ -1445,8 +1483,8 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
                         const double rho = E.mx * wx + E.my * wy + E.mz * wz;
                         if (rho == 0.0) continue;
                         const double la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
-                        const double lb = la + E.L * invh;
-                        const double t = edge_term<double>(r0d, fabs(rho) * invh, la, lb, Ht, dH, wk);
+                        const double Le = E.L * invh;
+                        const double t = edge_term(r0d, fabs(rho) * invh, la, la + Le, Le, Ht, dH, wk);
                         face += (rho > 0.0) ? t : -t;
                     }
                 }

@@ -20,14 +20,15 @@ namespace em {
 
 // Untuned shape: task batches (distribution 3) for both precisions, with the
 // register budgets and workgroup counts measured fastest on MI355X for the
-// 262,144-particle clumpy workload (FP64: 3 waves per SIMD, 4 workgroups per
-// CU; mixed: 6 and 6).
+// 262,144-particle clumpy workload (FP64: 3 waves per SIMD and 3 workgroups per
+// CU, mixed: 6 and 6: as many workgroups as are resident at once, so that none
+// starts when the others' tiles have run out).
 IntegrateTune default_tune(int precision)
 {
     IntegrateTune t;
     t.persistent = 3;
     t.tile_waves = 1;
-    t.grid_per_cu = precision == MAP_FP64 ? 4 : 6;
+    t.grid_per_cu = precision == MAP_FP64 ? 3 : 6;
     t.waves = precision == MAP_FP64 ? 3 : 6;
     return t;
 }
@@ -131,7 +132,7 @@ extern "C" int map_autotune(map_ctx *h, const map_particles_in *p, const map_cel
         const int wv64[] = {2, 3};
         const int wvmx[] = {3, 6};
         const int tws[] = {1, 2};
-        const int grids[] = {4, 8};
+        const int grids[] = {3, 6};
         const int dists[] = {1, 2, 3};
         IntegrateTune best = default_tune(precision);
         float best_t = 1e30f;
