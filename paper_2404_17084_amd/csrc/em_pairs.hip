@@ -2,10 +2,10 @@
 // than 2 h_a, ordered by cell and then particle.
 //
 // The particles, in storage order, are grouped 8 per leaf of an implicit
-// complete binary tree of the boxes their supports can reach.  Each cell
-// walks the tree without a stack (heap indices) and lists the particles whose
-// support comes within its bounding box (candidates), already in cell-major
-// order with particles ascending.  Cheap ball and box tests settle most
+// complete binary tree of the boxes their supports can reach.  Wavefronts walk
+// the tree for a few cells each and list the particles whose support comes
+// within a cell's bounding box (candidates), already in cell-major order with
+// particles ascending.  Cheap ball and box tests settle most
 // candidates, the rest take the exact distance test below (FP32 screening
 // with a rounding bound, then the exact IEEE arithmetic near the threshold),
 // and a wavefront per cell compacts the pairs.
@@ -186,14 +186,15 @@ __device__ __forceinline__ double box_dist2(const double *bb, double px, double 
 // a relative 1e-9 on its square) comes within the cell's bounding box.  The
 // particles form an implicit complete binary tree (heap indices: children 2i,
 // 2i+1) over leaves of 8 consecutive particles, each node holding the box of
-// its particles' reach boxes.  A wavefront of 64 consecutive cells walks it as
-// one packet: it descends into a node when the node's box meets any lane's
-// cell box, and at a leaf each lane whose box meets the leaf box tests the
-// leaf's particles.  Leaves are visited left to right, so each cell lists its
-// particles in ascending order: the candidate list comes out cell-major with
-// particles ascending, with no sort.  Particles stored in a spatially coherent
-// order (Morton, Hilbert, as SPH codes keep them) give tight boxes; any order
-// gives the same candidates.
+// its particles' reach boxes.  A wavefront walks it for kCells consecutive
+// cells: pending nodes lie on a stack in LDS, leftmost on top, and each step
+// takes the top 16 and tests their 64 grandchildren, one per lane, against the
+// cells' boxes; the nodes met go back in order.  Once 8 leaves are on top, the
+// lanes take their 64 particles and test them against each cell.  Nodes are
+// expanded left to right, so each cell lists its particles in ascending order:
+// the candidate list comes out cell-major with particles ascending, with no
+// sort.  Particles stored in a spatially coherent order (Morton, Hilbert, as
+// SPH codes keep them) give tight boxes; any order gives the same candidates.
 // The walk also settles what it can without the exact test: accepted when
 // the cell's whole bounding box lies within (1 - 1e-6) 2h of the particle, or
 // when the ball about the cell's interior point g (radius rin) comes closer
@@ -205,110 +206,145 @@ __device__ __forceinline__ double box_dist2(const double *bb, double px, double 
 // stores the first K of them in buf (particle index, bit 31 = marked); MODE 1
 // writes the candidates past the first K of the cells that have more, at
 // their final places, with their marks and exact-test list entries.
+//
+// Bound by the dependent loads of a walk (about 25 per wavefront) and, on full
+// chips, by the FP64 tests.  One lane per cell over a packet of 64 cells (the
+// lanes walking together, one node at a time) was a chain of several hundred
+// loads on 1/64 of the wavefronts: 0.57 -> 0.038 ms for 4,096 uniform particles,
+// 1.38 -> 0.26 ms for 65,537 and 2.18 -> 0.82 ms for 262,144 clumpy ones.
+// kCells = 4: more cells share a walk but test more particles that only the
+// others need.
+constexpr int kCells = 4;
+// Stack entries: from the top down the pending nodes' levels never increase (6,
+// 8, ..., the leaves' level, at most 28 for 2^31 particles), and a step takes
+// the nodes of a level only when it takes all deeper inner ones too, so a level
+// holds at most the 64 nodes that one step put there (the leaves' level 15
+// more that waited).
+constexpr int kCandStack = 13 * 64 + 16;
+
 template <int MODE>
-__global__ void k_candidates(int64_t n_cells, const double *__restrict__ aabb, const double *__restrict__ centre,
-                             const double *__restrict__ radii, int64_t n, const double *__restrict__ xyz,
-                             const double *__restrict__ h, const double *__restrict__ nodes, int64_t NL,
-                             int64_t *__restrict__ ccount, int64_t *__restrict__ ncount, int64_t *__restrict__ qcount,
-                             const int64_t *__restrict__ coffs, const int64_t *__restrict__ noffs,
-                             uint32_t *__restrict__ buf, int K, uint32_t *__restrict__ cand_c,
-                             uint32_t *__restrict__ cand_p, uint8_t *__restrict__ flag, uint32_t *__restrict__ list,
-                             unsigned *__restrict__ max_count)
+__global__ void __launch_bounds__(256) k_candidates(
+    int64_t n_cells, const double *__restrict__ aabb, const double *__restrict__ centre,
+    const double *__restrict__ radii, int64_t n, const double *__restrict__ xyz, const double *__restrict__ h,
+    const double *__restrict__ nodes, int64_t NL, int64_t *__restrict__ ccount, int64_t *__restrict__ ncount,
+    int64_t *__restrict__ qcount, const int64_t *__restrict__ coffs, const int64_t *__restrict__ noffs,
+    uint32_t *__restrict__ buf, int K, uint32_t *__restrict__ cand_c, uint32_t *__restrict__ cand_p,
+    uint8_t *__restrict__ flag, uint32_t *__restrict__ list, unsigned *__restrict__ max_count)
 {
-    const int64_t c = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    bool active = c < n_cells;
-    if (MODE == 1 && active) active = ccount[c] > K;
-    if (MODE == 1 && __ballot(active) == 0) return;
-    double lo0 = INFINITY, lo1 = INFINITY, lo2 = INFINITY, hi0 = -INFINITY, hi1 = -INFINITY, hi2 = -INFINITY;
-    double gx = 0.0, gy = 0.0, gz = 0.0, rin = 0.0, rc = 0.0;
-    if (active) {
-        lo0 = aabb[6 * c];
-        lo1 = aabb[6 * c + 1];
-        lo2 = aabb[6 * c + 2];
-        hi0 = aabb[6 * c + 3];
-        hi1 = aabb[6 * c + 4];
-        hi2 = aabb[6 * c + 5];
-        gx = centre[3 * c];
-        gy = centre[3 * c + 1];
-        gz = centre[3 * c + 2];
-        rin = radii[2 * c];
-        rc = radii[2 * c + 1];
-    }
-    const double cb[6] = {lo0, lo1, lo2, hi0, hi1, hi2};
-    int64_t count = 0, nmark = 0, nacc = 0;
-    const int64_t out = (MODE == 1 && active) ? coffs[c] : 0;
-    const int64_t nout = (MODE == 1 && active) ? noffs[c] : 0;
-    uint32_t *mine = buf + (MODE == 0 ? c * (int64_t)K : 0);
-    // The walk is a chain of dependent loads of node boxes (wave-uniform).  A
-    // descent loads both children's boxes at once (adjacent in the heap), so
-    // that a left child that is a leaf or not entered hands over to its right
-    // sibling without a load.
-    int64_t i = 1;
-    double b[6], sib[6];
-    bool have_sib = false;
-    for (int d = 0; d < 6; d++) b[d] = nodes[6 + d];
-    for (;;) {
-        const bool hit = active && b[0] <= hi0 && lo0 <= b[3] && b[1] <= hi1 && lo1 <= b[4] && b[2] <= hi2 &&
-                         lo2 <= b[5];
-        const bool any = __ballot(hit) != 0;
-        if (any && i < NL) {
-            i = 2 * i;
-            const double *nb = nodes + 6 * i;
-            for (int d = 0; d < 6; d++) {
-                b[d] = nb[d];
-                sib[d] = nb[6 + d];
-            }
-            have_sib = true;
-            continue;
-        }
-        if (hit) {
-            const int64_t t0 = kLeaf * (i - NL);
-            for (int64_t t = t0; t < t0 + kLeaf && t < n; t++) {
-                const double px = xyz[3 * t], py = xyz[3 * t + 1], pz = xyz[3 * t + 2];
-                const double r = 2.0 * h[t];
-                const double r2 = r * r;
-                if (box_dist2(cb, px, py, pz) > r2 * (1.0 + 1e-9)) continue;
-                const double fx = fmax(fabs(lo0 - px), fabs(hi0 - px));
-                const double fy = fmax(fabs(lo1 - py), fabs(hi1 - py));
-                const double fz = fmax(fabs(lo2 - pz), fabs(hi2 - pz));
-                const double dx = gx - px, dy = gy - py, dz = gz - pz;
-                const double dg = sqrt(dx * dx + dy * dy + dz * dz);
-                const bool ok = fx * fx + fy * fy + fz * fz < r2 * 0.999998 || dg - rin < r * (1.0 - 1e-9);
-                if (!ok && dg - rc >= r * (1.0 + 1e-9)) continue;
-                if (MODE == 0 && count < K) mine[count] = (uint32_t)t | (ok ? 0u : 0x80000000u);
-                if (MODE == 1 && count >= K) {
-                    cand_c[out + count] = (uint32_t)c;
-                    cand_p[out + count] = (uint32_t)t;
-                    flag[out + count] = ok ? 1 : 0;
-                    if (!ok) list[nout + nmark] = (uint32_t)(out + count);
-                }
-                nmark += ok ? 0 : 1;
-                nacc += ok ? 1 : 0;
-                count++;
-            }
-        }
-        if ((i & 1) == 0 && have_sib) {  // the right sibling, loaded with this node
-            i += 1;
-            for (int d = 0; d < 6; d++) b[d] = sib[d];
-            have_sib = false;
-            continue;
-        }
-        while (i & 1) i >>= 1;
-        if (i == 0) break;
-        i += 1;
-        for (int d = 0; d < 6; d++) b[d] = nodes[6 * i + d];
-        have_sib = false;
-    }
-    if (MODE == 0) {
-        if (active) {
-            ccount[c] = count;
-            ncount[c] = nmark;
-            qcount[c] = nacc;
-        }
-        unsigned m = (unsigned)(count < 0xffffffffLL ? count : 0xffffffffLL);
+    __shared__ int stacks[4][kCandStack];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int *S = stacks[wave];
+    const int64_t c0 = ((int64_t)xcd_block(blockIdx.x, gridDim.x) * 4 + wave) * kCells;
+    if (c0 >= n_cells) return;  // whole wavefronts
+    const int ng = n_cells - c0 < kCells ? (int)(n_cells - c0) : kCells;
+    bool use[kCells];
+    double lo[kCells][3], hi[kCells][3];
+    bool any_cell = false;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o, 64));
-        if ((threadIdx.x & 63) == 0 && m > 0) atomicMax(max_count, m);
+    for (int g = 0; g < kCells; g++) {
+        use[g] = g < ng && (MODE == 0 || ccount[c0 + (g < ng ? g : 0)] > K);
+        any_cell = any_cell || use[g];
+        for (int d = 0; d < 3; d++) {  // an unused cell's inverted box meets nothing
+            lo[g][d] = use[g] ? aabb[6 * (c0 + g) + d] : INFINITY;
+            hi[g][d] = use[g] ? aabb[6 * (c0 + g) + 3 + d] : -INFINITY;
+        }
+    }
+    if (!any_cell) return;
+    int count[kCells], nmark[kCells];
+#pragma unroll
+    for (int g = 0; g < kCells; g++) count[g] = nmark[g] = 0;
+    auto meets = [&](int64_t node) {
+        const double *b = nodes + 6 * node;
+        const double b0 = b[0], b1 = b[1], b2 = b[2], b3 = b[3], b4 = b[4], b5 = b[5];
+        bool m = false;
+#pragma unroll
+        for (int g = 0; g < kCells; g++)
+            m = m || (b0 <= hi[g][0] && lo[g][0] <= b3 && b1 <= hi[g][1] && lo[g][1] <= b4 && b2 <= hi[g][2] &&
+                      lo[g][2] <= b5);
+        return m;
+    };
+    auto below = [&](unsigned long long m) {
+        return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    };
+    // level 6 of the tree (or the leaves of a smaller one)
+    int sp;
+    {
+        const int64_t first = NL < 64 ? NL : 64;
+        const bool v = lane < first && meets(first + lane);
+        const unsigned long long m = __ballot(v);
+        sp = __popcll(m);
+        if (v) S[sp - 1 - below(m)] = (int)(first + lane);
+    }
+    lds_sync_wave();
+    while (sp > 0) {
+        const int k = sp < 16 ? sp : 16;
+        const int e = lane >> 2, q = lane & 3;
+        const int64_t node = e < k ? S[sp - 1 - e] : 0;
+        const bool inner = e < k && node < NL;
+        const unsigned long long im = __ballot(inner);
+        const int lead = im ? __builtin_ctzll(im) >> 2 : k;  // leaves on top of the stack
+        if (lead >= 8 || lead == k) {
+            const int kk = lead < 8 ? lead : 8;
+            const int64_t t = (lane >> 3) < kk ? kLeaf * ((int64_t)S[sp - 1 - (lane >> 3)] - NL) + (lane & 7) : n;
+            sp -= kk;
+            const bool valid = t < n;
+            const int64_t a = valid ? t : 0;
+            const double px = xyz[3 * a], py = xyz[3 * a + 1], pz = xyz[3 * a + 2], r = 2.0 * h[a], r2 = r * r;
+#pragma unroll
+            for (int g = 0; g < kCells; g++) {
+                if (!use[g]) continue;
+                const double cb[6] = {lo[g][0], lo[g][1], lo[g][2], hi[g][0], hi[g][1], hi[g][2]};
+                const bool in_reach = valid && !(box_dist2(cb, px, py, pz) > r2 * (1.0 + 1e-9));
+                if (__ballot(in_reach) == 0) continue;
+                const int64_t c = c0 + g;
+                const double fx = fmax(fabs(cb[0] - px), fabs(cb[3] - px));
+                const double fy = fmax(fabs(cb[1] - py), fabs(cb[4] - py));
+                const double fz = fmax(fabs(cb[2] - pz), fabs(cb[5] - pz));
+                const double dx = centre[3 * c] - px, dy = centre[3 * c + 1] - py, dz = centre[3 * c + 2] - pz;
+                const double dg2 = dx * dx + dy * dy + dz * dz;
+                const double ri = r * (1.0 - 1e-9) + radii[2 * c], ro = r * (1.0 + 1e-9) + radii[2 * c + 1];
+                const bool ok = fx * fx + fy * fy + fz * fz < r2 * 0.999998 || dg2 < ri * ri;
+                const bool cand = in_reach && (ok || dg2 < ro * ro);
+                const unsigned long long mc = __ballot(cand), mm = __ballot(cand && !ok);
+                const int at = count[g] + below(mc);
+                if (MODE == 0) {
+                    if (cand && at < K) buf[c * (int64_t)K + at] = (uint32_t)t | (ok ? 0u : 0x80000000u);
+                } else if (cand && at >= K) {
+                    const int64_t o = coffs[c] + at;
+                    cand_c[o] = (uint32_t)c;
+                    cand_p[o] = (uint32_t)t;
+                    flag[o] = ok ? 1 : 0;
+                    if (!ok) list[noffs[c] + nmark[g] + below(mm)] = (uint32_t)o;
+                }
+                count[g] += __popcll(mc);
+                nmark[g] += __popcll(mm);
+            }
+            lds_sync_wave();  // the leaves are read before their places are written again
+            continue;
+        }
+        // grandchildren (children above the leaves); a leaf below an inner node stays
+        const bool two = 2 * node < NL;
+        const int64_t child = inner ? (two ? 4 * node + q : 2 * node + q) : node;
+        const bool exists = inner ? (two || q < 2) : (e < k && q == 0);
+        const bool v = exists && (!inner || meets(child));
+        const unsigned long long m = __ballot(v);
+        sp += __popcll(m) - k;
+        lds_sync_wave();  // every lane has its node before the places are written
+        if (v) S[sp - 1 - below(m)] = (int)child;
+        lds_sync_wave();
+    }
+    if (MODE == 0 && lane == 0) {
+        int most = 0;
+#pragma unroll
+        for (int g = 0; g < kCells; g++)
+            if (g < ng) {
+                ccount[c0 + g] = count[g];
+                ncount[c0 + g] = nmark[g];
+                qcount[c0 + g] = count[g] - nmark[g];
+                most = most > count[g] ? most : count[g];
+            }
+        if (most > 0) atomicMax(max_count, (unsigned)most);
     }
 }
 
@@ -577,8 +613,8 @@ PairSet build_pairs(Workspace &ws, const DevInputs &in, const double *aabb, cons
     unsigned *cmax = ws.get<unsigned>(S_CAND_MAX, 64);
     fill_zero_bytes(cmax, sizeof(unsigned), s);
     const double *centre = aabb + 6 * nc, *radii = aabb + 9 * nc;
-    const unsigned pb = 128;
-    const unsigned pg = (unsigned)((nc + pb - 1) / pb);
+    const unsigned pb = 256;
+    const unsigned pg = (unsigned)((nc + 4 * kCells - 1) / (4 * kCells));
     hipLaunchKernelGGL(k_candidates<0>, dim3(pg), dim3(pb), 0, s, nc, aabb, centre, radii, n, in.xyz, in.h,
                        (const double *)nodes, NL, ccount, ncount, qcount, (const int64_t *)nullptr,
                        (const int64_t *)nullptr, cbuf, K, (uint32_t *)nullptr, (uint32_t *)nullptr, (uint8_t *)nullptr,
