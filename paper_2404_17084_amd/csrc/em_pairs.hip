@@ -6,9 +6,9 @@
 // the tree for a few cells each and list the particles whose support comes
 // within a cell's bounding box (candidates), already in cell-major order with
 // particles ascending.  Cheap ball and box tests settle most
-// candidates, the rest take the exact distance test below (FP32 screening
-// with a rounding bound, then the exact IEEE arithmetic near the threshold),
-// and a wavefront per cell compacts the pairs.
+// candidates, the rest take the exact distance test below, one wavefront per
+// cell (FP32 screening with a rounding bound, then the exact IEEE arithmetic
+// near the threshold), and a wavefront per cell compacts the pairs.
 #include <cmath>
 
 #include "em_internal.h"
@@ -102,15 +102,21 @@ struct CellGlobal {
 // One cell staged in LDS by a wavefront for the screened distance test:
 // wall planes in FP64 (the exact test's plane pass) and, per slot, the edge
 // start vertex relative to the cell centre g, the unit direction, the unit
-// in-wall normal (pointing into the wall polygon) and the length, in FP32.
+// in-wall normal (pointing into the wall polygon) and the length, in FP32; the
+// candidates that wait for the test, and the walls that undecided ones still
+// have to look at.
 constexpr int kExactMaxFaces = 40, kExactMaxSlots = 160;
+constexpr int kExactQueue = 128;  // below 64 waiting before a push of at most 64
 struct CellFast {
     double pl_[kExactMaxFaces][4];
+    float p_[64][3];            // the tested particles, about g
     float4 a_[kExactMaxSlots];  // vertex - g (x, y, z), length
     float4 b_[kExactMaxSlots];  // e (x, y, z), m.x
     float2 c_[kExactMaxSlots];  // m.y, m.z
+    unsigned dmin_[64];         // least squared distance of each tested particle (bits of a float >= 0)
+    uint32_t wait_[kExactQueue], part_[kExactQueue];  // places in the candidate list, particles
+    uint16_t task_[kExactQueue];                      // lane << 8 | wall
     int so_[kExactMaxFaces + 1];
-    int nf;
 };
 
 __device__ __noinline__ bool cell_meets(double px, double py, double pz, double r2, int64_t cell,
@@ -202,10 +208,9 @@ __device__ __forceinline__ double box_dist2(const double *bb, double px, double 
 // (radius rc) stays (1 + 1e-9) 2h or more away.  The margins exceed the
 // rounding of every distance involved, so these decisions are the exact
 // test's.  The rest are marked for the exact test.
-// MODE 0 counts every cell's kept candidates (kept, marked, accepted) and
-// stores the first K of them in buf (particle index, bit 31 = marked); MODE 1
-// writes the candidates past the first K of the cells that have more, at
-// their final places, with their marks and exact-test list entries.
+// A cell has room for K candidates (particle index, bit 31 = marked), from c K
+// on.  A cell with more has all of them in the overflow list, from ovf_off[c]
+// on, which a second walk of those cells writes (SECOND).
 //
 // Bound by the dependent loads of a walk (about 25 per wavefront) and, on full
 // chips, by the FP64 tests.  One lane per cell over a packet of 64 cells (the
@@ -222,14 +227,12 @@ constexpr int kCells = 4;
 // more that waited).
 constexpr int kCandStack = 13 * 64 + 16;
 
-template <int MODE>
+template <bool SECOND>
 __global__ void __launch_bounds__(256) k_candidates(
     int64_t n_cells, const double *__restrict__ aabb, const double *__restrict__ centre,
     const double *__restrict__ radii, int64_t n, const double *__restrict__ xyz, const double *__restrict__ h,
-    const double *__restrict__ nodes, int64_t NL, int64_t *__restrict__ ccount, int64_t *__restrict__ ncount,
-    int64_t *__restrict__ qcount, const int64_t *__restrict__ coffs, const int64_t *__restrict__ noffs,
-    uint32_t *__restrict__ buf, int K, uint32_t *__restrict__ cand_c, uint32_t *__restrict__ cand_p,
-    uint8_t *__restrict__ flag, uint32_t *__restrict__ list, unsigned *__restrict__ max_count)
+    const double *__restrict__ nodes, int64_t NL, int64_t *__restrict__ ccount, uint32_t *__restrict__ buf, int K,
+    const int64_t *__restrict__ ovf_off, unsigned *__restrict__ max_count)
 {
     __shared__ int stacks[4][kCandStack];
     const int lane = threadIdx.x & 63;
@@ -238,22 +241,22 @@ __global__ void __launch_bounds__(256) k_candidates(
     const int64_t c0 = ((int64_t)xcd_block(blockIdx.x, gridDim.x) * 4 + wave) * kCells;
     if (c0 >= n_cells) return;  // whole wavefronts
     const int ng = n_cells - c0 < kCells ? (int)(n_cells - c0) : kCells;
-    bool use[kCells];
     double lo[kCells][3], hi[kCells][3];
-    bool any_cell = false;
+    bool use[kCells], any_cell = false;
 #pragma unroll
     for (int g = 0; g < kCells; g++) {
-        use[g] = g < ng && (MODE == 0 || ccount[c0 + (g < ng ? g : 0)] > K);
+        const int64_t c = c0 + (g < ng ? g : 0);
+        use[g] = g < ng && (!SECOND || ccount[c] > K);
         any_cell = any_cell || use[g];
         for (int d = 0; d < 3; d++) {  // an unused cell's inverted box meets nothing
-            lo[g][d] = use[g] ? aabb[6 * (c0 + g) + d] : INFINITY;
-            hi[g][d] = use[g] ? aabb[6 * (c0 + g) + 3 + d] : -INFINITY;
+            lo[g][d] = use[g] ? aabb[6 * c + d] : INFINITY;
+            hi[g][d] = use[g] ? aabb[6 * c + 3 + d] : -INFINITY;
         }
     }
     if (!any_cell) return;
-    int count[kCells], nmark[kCells];
+    int count[kCells];
 #pragma unroll
-    for (int g = 0; g < kCells; g++) count[g] = nmark[g] = 0;
+    for (int g = 0; g < kCells; g++) count[g] = 0;
     auto meets = [&](int64_t node) {
         const double *b = nodes + 6 * node;
         const double b0 = b[0], b1 = b[1], b2 = b[2], b3 = b[3], b4 = b[4], b5 = b[5];
@@ -293,8 +296,8 @@ __global__ void __launch_bounds__(256) k_candidates(
             const double px = xyz[3 * a], py = xyz[3 * a + 1], pz = xyz[3 * a + 2], r = 2.0 * h[a], r2 = r * r;
 #pragma unroll
             for (int g = 0; g < kCells; g++) {
-                if (!use[g]) continue;
                 const double cb[6] = {lo[g][0], lo[g][1], lo[g][2], hi[g][0], hi[g][1], hi[g][2]};
+                if (!use[g]) continue;
                 const bool in_reach = valid && !(box_dist2(cb, px, py, pz) > r2 * (1.0 + 1e-9));
                 if (__ballot(in_reach) == 0) continue;
                 const int64_t c = c0 + g;
@@ -306,19 +309,11 @@ __global__ void __launch_bounds__(256) k_candidates(
                 const double ri = r * (1.0 - 1e-9) + radii[2 * c], ro = r * (1.0 + 1e-9) + radii[2 * c + 1];
                 const bool ok = fx * fx + fy * fy + fz * fz < r2 * 0.999998 || dg2 < ri * ri;
                 const bool cand = in_reach && (ok || dg2 < ro * ro);
-                const unsigned long long mc = __ballot(cand), mm = __ballot(cand && !ok);
+                const unsigned long long mc = __ballot(cand);
                 const int at = count[g] + below(mc);
-                if (MODE == 0) {
-                    if (cand && at < K) buf[c * (int64_t)K + at] = (uint32_t)t | (ok ? 0u : 0x80000000u);
-                } else if (cand && at >= K) {
-                    const int64_t o = coffs[c] + at;
-                    cand_c[o] = (uint32_t)c;
-                    cand_p[o] = (uint32_t)t;
-                    flag[o] = ok ? 1 : 0;
-                    if (!ok) list[noffs[c] + nmark[g] + below(mm)] = (uint32_t)o;
-                }
+                if (cand && (SECOND || at < K))
+                    buf[(SECOND ? ovf_off[c] : c * (int64_t)K) + at] = (uint32_t)t | (ok ? 0u : 0x80000000u);
                 count[g] += __popcll(mc);
-                nmark[g] += __popcll(mm);
             }
             lds_sync_wave();  // the leaves are read before their places are written again
             continue;
@@ -334,206 +329,253 @@ __global__ void __launch_bounds__(256) k_candidates(
         if (v) S[sp - 1 - below(m)] = (int)child;
         lds_sync_wave();
     }
-    if (MODE == 0 && lane == 0) {
+    if (!SECOND && lane == 0) {
         int most = 0;
 #pragma unroll
         for (int g = 0; g < kCells; g++)
             if (g < ng) {
                 ccount[c0 + g] = count[g];
-                ncount[c0 + g] = nmark[g];
-                qcount[c0 + g] = count[g] - nmark[g];
                 most = most > count[g] ? most : count[g];
             }
         if (most > 0) atomicMax(max_count, (unsigned)most);
     }
 }
 
-// The first K candidates of every cell from buf to their places in the
-// cell-major candidate list, with their marks and exact-test list entries (in
-// candidate order), one wavefront per cell.
-__global__ void k_cand_gather(int64_t n_cells, int K, const int64_t *__restrict__ ccount,
-                              const int64_t *__restrict__ coffs, const int64_t *__restrict__ noffs,
-                              const uint32_t *__restrict__ buf, uint32_t *__restrict__ cand_c,
-                              uint32_t *__restrict__ cand_p, uint8_t *__restrict__ flag, uint32_t *__restrict__ list)
+// The tested and accepted candidates of each cell, one wavefront per cell: the
+// marked ones are collected 64 at a time and take the exact test, the rejected
+// ones are struck from the list (kNoCand), and the cell's pairs are counted.
+// The wavefront stages its cell in LDS.  Each lane then, for its particle, (1)
+// runs the exact test's plane pass (inside: accept; a wall plane beyond the
+// radius by the relative margin: reject), (2) takes the squared distance D to
+// the wall polygon that is farthest beneath the particle, in FP32 about the
+// cell centre: the wall's own distance when the foot point lies inside the
+// polygon, which is then the distance to the cell, else the least distance to
+// the wall's edge segments, an upper bound of it; accepted when below r^2; (3)
+// the rest, whose nearest point may lie on another wall seen from outside,
+// become tasks (lane, wall) that the lanes share, and D is the least of all.
+// D decides when |D - r^2| exceeds a bound on its rounding, tol = 1e-6 (r + 2
+// rc)^2 (every vector involved is shorter than r + 2 rc, FP32 rounding of D is
+// below 10 u (r + 2 rc)^2); (4) D within tol of r^2, and cells too large for the
+// staging area, run the exact test from the global tables.
+//
+// Bound by latency: 70 % of the wavefronts' time is waits (the cell's records,
+// gathers from LDS), vector instructions at 0.09 per SIMD and clock with half
+// of the lanes active.  With 64 list entries per wavefront (two or three cells
+// each, staged one after the other, a third of the lanes each), every lane
+// looping over all walls it sees, and the candidates gathered into lists of
+// their own first, 262,144 clumpy particles took 2.22 ms here and 0.37 ms around
+// it; 1.84 and 0.13 ms now.
+constexpr uint32_t kNoCand = 0xffffffffu;
+
+// squared FP32 distance from q (about the cell centre) to wall j of the staged cell: d^2 (its plane's distance) when
+// q's foot point lies inside the polygon
+__device__ __forceinline__ float wall_dist2(const CellFast &L, int j, float qx, float qy, float qz, float d2,
+                                            bool &in_poly)
 {
-    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (c >= n_cells) return;
-    const int64_t cnt = ccount[c] < K ? ccount[c] : K;
-    const int64_t o = coffs[c];
-    int64_t nl = noffs[c];
-    for (int64_t k0 = 0; k0 < cnt; k0 += 64) {
-        const int64_t k = k0 + lane;
-        const bool valid = k < cnt;
-        const uint32_t e = valid ? buf[c * K + k] : 0u;
-        const bool marked = valid && (e >> 31) != 0;
-        const unsigned long long m = __ballot(marked);
-        if (valid) {
-            cand_c[o + k] = (uint32_t)c;
-            cand_p[o + k] = e & 0x7fffffffu;
-            flag[o + k] = marked ? 0 : 1;
-        }
-        if (marked) {
-            const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-            list[nl + below] = (uint32_t)(o + k);
-        }
-        nl += __popcll(m);
+    in_poly = true;
+    float D = INFINITY;
+    for (int k = L.so_[j]; k < L.so_[j + 1]; k++) {
+        const float4 A = L.a_[k], B = L.b_[k];
+        const float2 C = L.c_[k];
+        const float wx = qx - A.x, wy = qy - A.y, wz = qz - A.z;
+        in_poly = in_poly && fmaf(B.w, wx, fmaf(C.x, wy, C.y * wz)) >= 0.0f;
+        const float sp = fmaf(B.x, wx, fmaf(B.y, wy, B.z * wz));
+        const float tt = fminf(fmaxf(sp, 0.0f), A.w);
+        const float ux = fmaf(-tt, B.x, wx), uy = fmaf(-tt, B.y, wy), uz = fmaf(-tt, B.z, wz);
+        D = fminf(D, fmaf(ux, ux, fmaf(uy, uy, uz * uz)));
     }
+    return in_poly ? d2 : D;
 }
 
-// Pairs per cell: accepted by the walk's tests plus accepted by the exact test.
-__global__ void k_pair_counts(int64_t n_cells, const int64_t *__restrict__ qcount, const unsigned *__restrict__ ecount,
-                              int64_t *__restrict__ pcount)
-{
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < n_cells) pcount[c] = qcount[c] + (int64_t)ecount[c];
-}
+constexpr int kExactWaves = 2;  // cells per workgroup: 20 KB of LDS, 4 wavefronts per SIMD
 
-// Accepted candidates of each cell to the cell-major pair list (candidate
-// order kept), one wavefront per cell.
-__global__ void k_compact(int64_t n_cells, const int64_t *__restrict__ coffs, const int64_t *__restrict__ coff,
-                          const uint32_t *__restrict__ cand_p, const uint8_t *__restrict__ flag,
-                          uint32_t *__restrict__ pair_c, uint32_t *__restrict__ pair_p)
-{
-    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63;
-    if (c >= n_cells) return;
-    const int64_t b = coffs[c], e = coffs[c + 1];
-    int64_t o = coff[c];
-    for (int64_t k0 = b; k0 < e; k0 += 64) {
-        const int64_t k = k0 + lane;
-        const bool take = k < e && flag[k] != 0;
-        const unsigned long long m = __ballot(take);
-        if (take) {
-            const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-            pair_c[o + below] = (uint32_t)c;
-            pair_p[o + below] = cand_p[k];
-        }
-        o += __popcll(m);
-    }
-}
-
-
-__global__ void k_set_u64(unsigned long long *p, unsigned long long v)
-{
-    if (threadIdx.x == 0) *p = v;
-}
-
-
-// Exact test of the listed candidates, one wavefront per 64 consecutive list
-// entries (the list is in cell order).  The wavefront stages each distinct
-// cell of its entries in LDS; each lane then (1) runs the exact test's plane
-// pass (inside: accept; a wall plane beyond the radius by the relative margin:
-// reject), (2) computes the squared distance D to the cell in FP32 about the
-// cell centre (least over the walls seen from outside of d^2 when the foot
-// point is inside the wall polygon, else of the squared distances to the
-// wall's edge segments) and decides when |D - r^2| exceeds a bound on its
-// rounding, tol = 1e-6 (r + 2 rc)^2 (every vector involved is shorter than
-// r + 2 rc, FP32 rounding of D is below 10 u (r + 2 rc)^2), and (3) runs the
-// exact test from the global tables for the rest (D within tol of r^2) and
-// for cells too large for the staging area.
-__global__ void __launch_bounds__(256) k_exact(int64_t n_need, const uint32_t *__restrict__ list,
-                                               const uint32_t *__restrict__ cand_c, const uint32_t *__restrict__ cand_p,
-                                               const double *__restrict__ xyz, const double *__restrict__ h,
-                                               const int64_t *__restrict__ cfo, const int64_t *__restrict__ fvo,
-                                               const EdgeRec *__restrict__ edges, const double *__restrict__ plane,
-                                               const double *__restrict__ centre, const double *__restrict__ radii,
-                                               uint8_t *__restrict__ flag, unsigned *__restrict__ ecount)
+template <bool SECOND>
+__global__ void __launch_bounds__(64 * kExactWaves) k_exact(
+    int64_t n_cells, const int64_t *__restrict__ ccount, uint32_t *__restrict__ buf, int K,
+    const int64_t *__restrict__ ovf_off, const double *__restrict__ xyz, const double *__restrict__ h,
+    const int64_t *__restrict__ cfo, const int64_t *__restrict__ fvo, const EdgeRec *__restrict__ edges,
+    const double *__restrict__ plane, const double *__restrict__ centre, const double *__restrict__ radii,
+    int64_t *__restrict__ pcount, unsigned long long *__restrict__ n_tested)
 {
 #pragma clang fp contract(off)
-    __shared__ CellFast stage[4];
-    CellFast &L = stage[threadIdx.x >> 6];
+    __shared__ CellFast stage[kExactWaves];
+    __shared__ unsigned tested[kExactWaves];
     const int lane = threadIdx.x & 63;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = t < n_need;
-    int64_t i = 0, c = -1, a = 0;
-    double px = 0.0, py = 0.0, pz = 0.0, r2 = 0.0, r = 0.0;
-    if (valid) {
-        i = list[t];
-        c = cand_c[i];
-        a = cand_p[i];
-        px = xyz[3 * a];
-        py = xyz[3 * a + 1];
-        pz = xyz[3 * a + 2];
-        r = 2.0 * h[a];
-        r2 = r * r;
-    }
-    bool hit = false;
-    unsigned long long todo = __ballot(valid);
-    while (todo != 0) {
-        const int leader = __builtin_ctzll(todo);
-        const int64_t cc = (int64_t)__shfl((long long)c, leader, 64);
-        const bool mine = valid && c == cc;
-        todo &= ~__ballot(mine);
-        const int64_t j0 = cfo[cc], nf = cfo[cc + 1] - j0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    CellFast &L = stage[wave];
+    const int64_t c = (int64_t)blockIdx.x * kExactWaves + wave;
+    unsigned n_test = 0;
+    const int64_t cnt = c < n_cells ? ccount[c] : 0;
+    if (c < n_cells && (cnt > K) == SECOND) {
+        uint32_t *mine = buf + (SECOND ? ovf_off[c] : c * (int64_t)K);
+        const int64_t j0 = cfo[c], nf = cfo[c + 1] - j0;
         const int64_t s0 = fvo[j0], ns = fvo[j0 + nf] - s0;
-        const double gx = centre[3 * cc], gy = centre[3 * cc + 1], gz = centre[3 * cc + 2];
-        bool exact = mine;
-        if (nf <= kExactMaxFaces && ns <= kExactMaxSlots) {
-            lds_sync_wave();
-            for (int q = lane; q < 4 * nf; q += 64) L.pl_[q >> 2][q & 3] = plane[4 * j0 + q];
-            for (int q = lane; q <= nf; q += 64) L.so_[q] = (int)(fvo[j0 + q] - s0);
-            for (int q = lane; q < ns; q += 64) {
-                const EdgeRec &E = edges[s0 + q];
-                L.a_[q] = make_float4((float)(E.vx - gx), (float)(E.vy - gy), (float)(E.vz - gz), (float)E.L);
-                L.b_[q] = make_float4((float)E.ex, (float)E.ey, (float)E.ez, (float)E.mx);
-                L.c_[q] = make_float2((float)E.my, (float)E.mz);
+        const bool fits = nf <= kExactMaxFaces && ns <= kExactMaxSlots;
+        const double gx = centre[3 * c], gy = centre[3 * c + 1], gz = centre[3 * c + 2], rc2 = 2.0 * radii[2 * c + 1];
+        int64_t pairs = 0;
+        bool staged = false;
+        int waiting = 0;
+        auto test = [&](int n) {  // the first n (<= 64) of the waiting candidates
+            if (fits && !staged) {
+                for (int q = lane; q < 4 * (int)nf; q += 64) L.pl_[q >> 2][q & 3] = plane[4 * j0 + q];
+                for (int q = lane; q <= (int)nf; q += 64) L.so_[q] = (int)(fvo[j0 + q] - s0);
+                for (int q = lane; q < (int)ns; q += 64) {
+                    const EdgeRec &E = edges[s0 + q];
+                    L.a_[q] = make_float4((float)(E.vx - gx), (float)(E.vy - gy), (float)(E.vz - gz), (float)E.L);
+                    L.b_[q] = make_float4((float)E.ex, (float)E.ey, (float)E.ez, (float)E.mx);
+                    L.c_[q] = make_float2((float)E.my, (float)E.mz);
+                }
+                staged = true;
             }
-            if (lane == 0) L.nf = (int)nf;
             lds_sync_wave();
-            if (mine) {
-                exact = false;
-                // (1) the exact test's plane pass, same arithmetic
-                double far = 0.0;
+            const bool valid = lane < n;
+            const int64_t a = valid ? L.part_[lane] : 0;
+            const double px = xyz[3 * a], py = xyz[3 * a + 1], pz = xyz[3 * a + 2], r = 2.0 * h[a], r2 = r * r;
+            bool hit = false, exact = valid && !fits;
+            if (fits) {
                 bool inside = true;
+                double far = 0.0;
+                int jf = 0;
                 unsigned long long seen = 0;  // walls seen from outside
-                for (int j = 0; j < nf; j++) {
+                for (int j = 0; j < (int)nf; j++) {
                     const double d = L.pl_[j][3] - (L.pl_[j][0] * px + L.pl_[j][1] * py + L.pl_[j][2] * pz);
                     if (d < 0.0) {
                         inside = false;
                         seen |= 1ull << j;
-                        if (-d > far) far = -d;
+                        if (-d > far) {
+                            far = -d;
+                            jf = j;
+                        }
                     }
                 }
-                if (inside) {
-                    hit = true;
-                } else if (!(far * far > r2 * (1.0 + 1e-9))) {
-                    // (2) screened distance in FP32 about g
-                    const float qx = (float)(px - gx), qy = (float)(py - gy), qz = (float)(pz - gz);
-                    float D = INFINITY;
-                    for (unsigned long long sm = seen; sm != 0; sm &= sm - 1) {
-                        const int j = __builtin_ctzll(sm);
-                        const double d = L.pl_[j][3] - (L.pl_[j][0] * px + L.pl_[j][1] * py + L.pl_[j][2] * pz);
-                        bool in_poly = true;
-                        float Dj = INFINITY;
-                        for (int k = L.so_[j]; k < L.so_[j + 1]; k++) {
-                            const float4 A = L.a_[k], B = L.b_[k];
-                            const float2 C = L.c_[k];
-                            const float wx = qx - A.x, wy = qy - A.y, wz = qz - A.z;
-                            in_poly = in_poly && fmaf(B.w, wx, fmaf(C.x, wy, C.y * wz)) >= 0.0f;
-                            const float sp = fmaf(B.x, wx, fmaf(B.y, wy, B.z * wz));
-                            const float tt = fminf(fmaxf(sp, 0.0f), A.w);
-                            const float ux = fmaf(-tt, B.x, wx), uy = fmaf(-tt, B.y, wy), uz = fmaf(-tt, B.z, wz);
-                            Dj = fminf(Dj, fmaf(ux, ux, fmaf(uy, uy, uz * uz)));
-                        }
-                        D = fminf(D, in_poly ? (float)(d * d) : Dj);
+                hit = valid && inside;
+                bool open = valid && !inside && !(far * far > r2 * (1.0 + 1e-9));
+                const double rr = r + rc2, tol = 1e-6 * rr * rr;
+                const float qx = (float)(px - gx), qy = (float)(py - gy), qz = (float)(pz - gz);
+                float D = INFINITY;
+                if (open) {
+                    bool in_poly;
+                    D = wall_dist2(L, jf, qx, qy, qz, (float)(far * far), in_poly);
+                    seen &= in_poly ? 0ull : ~(1ull << jf);
+                    if ((double)D < r2 - tol) {
+                        hit = true;
+                        open = false;
                     }
-                    const double rr = r + 2.0 * radii[2 * cc + 1];
-                    const double tol = 1e-6 * rr * rr;
+                }
+                unsigned long long sm = open ? seen : 0ull;
+                if (__ballot(sm != 0) != 0) {
+                    L.p_[lane][0] = qx;
+                    L.p_[lane][1] = qy;
+                    L.p_[lane][2] = qz;
+                    L.dmin_[lane] = __float_as_uint(D);
+                    int nt = 0;
+                    auto run = [&](int at, int m) {
+                        lds_sync_wave();
+                        if (lane < m) {
+                            const int o = L.task_[at + lane] >> 8, j = L.task_[at + lane] & 255;
+                            const float x = L.p_[o][0], y = L.p_[o][1], z = L.p_[o][2];
+                            const double d = L.pl_[j][3] - (L.pl_[j][0] * (gx + x) + L.pl_[j][1] * (gy + y) +
+                                                            L.pl_[j][2] * (gz + z));
+                            bool in_poly;
+                            const float Dj = wall_dist2(L, j, x, y, z, (float)(d * d), in_poly);
+                            atomicMin(&L.dmin_[o], __float_as_uint(Dj));
+                        }
+                        lds_sync_wave();
+                    };
+                    while (__ballot(sm != 0) != 0) {
+                        const bool want = sm != 0;
+                        const int at = wave_push(want, nt);
+                        if (want) L.task_[at] = (uint16_t)(lane << 8 | __builtin_ctzll(sm));
+                        sm &= sm - 1;
+                        if (nt >= 64) {
+                            run(nt - 64, 64);
+                            nt -= 64;
+                        }
+                    }
+                    run(0, nt);
+                    D = __uint_as_float(L.dmin_[lane]);
+                }
+                if (open) {
                     if ((double)D < r2 - tol) hit = true;
                     else if (!((double)D > r2 + tol)) exact = true;
                 }
             }
+            if (exact) hit = cell_meets(px, py, pz, r2, c, cfo, fvo, edges, plane);
+            if (valid) mine[L.wait_[lane]] = hit ? (uint32_t)a : kNoCand;
+            pairs += __popcll(__ballot(hit));
+            n_test += (unsigned)n;
+            // the others move up
+            lds_sync_wave();
+            const int left = waiting - n;
+            const uint32_t w = lane < left ? L.wait_[n + lane] : 0u, q = lane < left ? L.part_[n + lane] : 0u;
+            lds_sync_wave();
+            if (lane < left) {
+                L.wait_[lane] = w;
+                L.part_[lane] = q;
+            }
+            waiting = left;
+        };
+        for (int64_t k0 = 0; k0 < cnt || waiting > 0;) {
+            if (k0 < cnt && waiting < 64) {
+                const int64_t k = k0 + lane;
+                const uint32_t e = k < cnt ? mine[k] : 0u;
+                const bool marked = k < cnt && (e >> 31) != 0;
+                pairs += __popcll(__ballot(k < cnt && !marked));
+                const int at = wave_push(marked, waiting);
+                if (marked) {
+                    L.wait_[at] = (uint32_t)k;
+                    L.part_[at] = e & 0x7fffffffu;
+                }
+                k0 += 64;
+            }
+            if (waiting >= 64 || (k0 >= cnt && waiting > 0)) test(waiting < 64 ? waiting : 64);
         }
-        // (3) the exact test from the global tables
-        if (exact) hit = cell_meets(px, py, pz, r2, cc, cfo, fvo, edges, plane);
+        if (lane == 0) pcount[c] = pairs;
+    } else if (!SECOND && c < n_cells && lane == 0) {
+        pcount[c] = 0;  // counted by the second pass
     }
-    if (valid) {
-        flag[i] = hit ? 1 : 0;
-        if (hit) atomicAdd(&ecount[c], 1u);
+    if (lane == 0) tested[wave] = n_test;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned all = 0;
+        for (int w = 0; w < kExactWaves; w++) all += tested[w];
+        if (all > 0) atomicAdd(n_tested, (unsigned long long)all);
     }
 }
 
+// Sizes of the overflow lists.
+__global__ void k_overflow_sizes(int64_t n_cells, const int64_t *__restrict__ ccount, int K, int64_t *__restrict__ size)
+{
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c < n_cells) size[c] = ccount[c] > K ? ccount[c] : 0;
+}
+
+// The candidates left of each cell to the cell-major pair list (candidate
+// order kept), one wavefront per cell.
+__global__ void k_compact(int64_t n_cells, const int64_t *__restrict__ ccount, const uint32_t *__restrict__ buf, int K,
+                          const uint32_t *__restrict__ ovf, const int64_t *__restrict__ ovf_off,
+                          const int64_t *__restrict__ coff, uint32_t *__restrict__ pair_c,
+                          uint32_t *__restrict__ pair_p)
+{
+    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63;
+    if (c >= n_cells) return;
+    const int64_t cnt = ccount[c];
+    const uint32_t *mine = cnt > K ? ovf + ovf_off[c] : buf + c * (int64_t)K;
+    int64_t o = coff[c];
+    for (int64_t k0 = 0; k0 < cnt; k0 += 64) {
+        const int64_t k = k0 + lane;
+        const uint32_t e = k < cnt ? mine[k] : kNoCand;
+        const bool take = e != kNoCand;
+        const unsigned long long m = __ballot(take);
+        if (take) {
+            const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            pair_c[o + below] = (uint32_t)c;
+            pair_p[o + below] = e;
+        }
+        o += __popcll(m);
+    }
+}
 
 // Segment offsets of sorted keys: off[v] = first i with keys[i] >= v, v = 0..n_seg.
 __global__ void k_seg_offsets(int64_t n_items, const uint32_t *__restrict__ keys, int64_t n_seg,
@@ -596,83 +638,65 @@ PairSet build_pairs(Workspace &ws, const DevInputs &in, const double *aabb, cons
         EM_HIP(hipGetLastError());
     }
 
-    // candidates per cell (tree walk with the cheap tests), cell-major with
-    // particles ascending: one walk keeps the first K of each cell's
-    // candidates; cells with more walk again
+    // candidates per cell (tree walk with the cheap tests, particles ascending),
+    // the exact test of the marked ones, and the pairs per cell.  Each cell has
+    // room for K candidates: at most 2^30 in all (4 GiB; 128 per cell at 8.4
+    // million cells), and in arena mode at most a quarter of the free scratch.
     int64_t *ccount = ws.get<int64_t>(S_PCNT, (size_t)nc);
-    int64_t *coffs = ws.get<int64_t>(S_CCNT64, (size_t)(nc + 1));
-    int64_t *ncount = ws.get<int64_t>(S_NCNT, (size_t)nc);
-    int64_t *noffs = ws.get<int64_t>(S_NOFF, (size_t)(nc + 1));
-    int64_t *qcount = ws.get<int64_t>(S_QCNT, (size_t)nc);
-    // candidate slots per cell: at most 2^30 in all (4 GiB; 128 per cell at
-    // 8.4 million cells), and in arena mode at most a quarter of the free
-    // scratch (cells with more candidates walk again)
+    int64_t *pcount = ws.get<int64_t>(S_PCNT2, (size_t)nc);
     const int64_t slot_cap = std::min<int64_t>(int64_t(1) << 30, (int64_t)std::min<size_t>(ws.arena_free() / 16, size_t(1) << 40));
     const int K = (int)std::max<int64_t>(32, std::min<int64_t>(512, slot_cap / nc));
-    uint32_t *cbuf = ws.get<uint32_t>(S_CAND_BUF, (size_t)(nc * K));
+    uint32_t *buf = ws.get<uint32_t>(S_CAND_BUF, (size_t)(nc * K)), *ovf = nullptr;
+    int64_t *ovf_off = nullptr;
     unsigned *cmax = ws.get<unsigned>(S_CAND_MAX, 64);
     fill_zero_bytes(cmax, sizeof(unsigned), s);
     const double *centre = aabb + 6 * nc, *radii = aabb + 9 * nc;
-    const unsigned pb = 256;
-    const unsigned pg = (unsigned)((nc + 4 * kCells - 1) / (4 * kCells));
-    hipLaunchKernelGGL(k_candidates<0>, dim3(pg), dim3(pb), 0, s, nc, aabb, centre, radii, n, in.xyz, in.h,
-                       (const double *)nodes, NL, ccount, ncount, qcount, (const int64_t *)nullptr,
-                       (const int64_t *)nullptr, cbuf, K, (uint32_t *)nullptr, (uint32_t *)nullptr, (uint8_t *)nullptr,
-                       (uint32_t *)nullptr, cmax);
+    unsigned long long *tested = reinterpret_cast<unsigned long long *>(counters + C_CANDIDATES);
+    const dim3 wg((unsigned)((nc + 4 * kCells - 1) / (4 * kCells))), eg((unsigned)((nc + kExactWaves - 1) / kExactWaves));
+    hipLaunchKernelGGL(k_candidates<false>, wg, dim3(256), 0, s, nc, aabb, centre, radii, n, in.xyz, in.h,
+                       (const double *)nodes, NL, ccount, buf, K, (const int64_t *)nullptr, cmax);
     EM_HIP(hipGetLastError());
-    scan_counts(ws, ccount, coffs, nc, s);
-    scan_counts(ws, ncount, noffs, nc, s);
-    int64_t ncand = 0, n_need = 0;
-    unsigned max_cand = 0;
-    EM_HIP(hipMemcpyAsync(&ncand, coffs + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&n_need, noffs + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&max_cand, cmax, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    stream_sync(s);
-    EM_CHECK(ncand < (int64_t)UINT32_MAX, MAP_ENOMEM, "candidate count exceeds 2^32-1");
-    uint32_t *cand_c = ws.get<uint32_t>(S_KEY2, (size_t)(ncand > 0 ? ncand : 1));
-    uint32_t *cand_p = ws.get<uint32_t>(S_IOTA, (size_t)(ncand > 0 ? ncand : 1));
-    uint8_t *flag = reinterpret_cast<uint8_t *>(ws.get<uint32_t>(S_F_PM, (size_t)(ncand / 4 + 1)));
-    uint32_t *list = ws.get<uint32_t>(S_BINLIST, (size_t)(n_need > 0 ? n_need : 1));
-    unsigned *ecount = ws.get<unsigned>(S_ECNT, (size_t)nc);
-    fill_zero_bytes(ecount, sizeof(unsigned) * nc, s);
-    if (ncand > 0) {
-        hipLaunchKernelGGL(k_cand_gather, dim3((unsigned)((nc + 3) / 4)), dim3(256), 0, s, nc, K,
-                           (const int64_t *)ccount, (const int64_t *)coffs, (const int64_t *)noffs,
-                           (const uint32_t *)cbuf, cand_c, cand_p, flag, list);
-        EM_HIP(hipGetLastError());
-    }
-    if ((int64_t)max_cand > K) {
-        hipLaunchKernelGGL(k_candidates<1>, dim3(pg), dim3(pb), 0, s, nc, aabb, centre, radii, n, in.xyz, in.h,
-                           (const double *)nodes, NL, ccount, ncount, qcount, (const int64_t *)coffs,
-                           (const int64_t *)noffs, cbuf, K, cand_c, cand_p, flag, list, cmax);
-        EM_HIP(hipGetLastError());
-    }
-    // the exact test of the marked candidates (listed in candidate order)
-    if (n_need > 0) {
-        hipLaunchKernelGGL(k_exact, dim3((unsigned)((n_need + 255) / 256)), dim3(256), 0, s, n_need,
-                           (const uint32_t *)list, (const uint32_t *)cand_c, (const uint32_t *)cand_p, in.xyz, in.h,
-                           in.cfo, in.fvo, edges, in.plane, centre, radii, flag, ecount);
-        EM_HIP(hipGetLastError());
-    }
-    unsigned long long *cand = reinterpret_cast<unsigned long long *>(counters + C_CANDIDATES);
-    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, cand, (unsigned long long)n_need);
-    EM_HIP(hipGetLastError());
-    // pairs per cell, their offsets, and the cell-major pair list
-    int64_t *pcount = ws.get<int64_t>(S_PCNT2, (size_t)nc);
-    hipLaunchKernelGGL(k_pair_counts, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, nc,
-                       (const int64_t *)qcount, (const unsigned *)ecount, pcount);
+    hipLaunchKernelGGL(k_exact<false>, eg, dim3(64 * kExactWaves), 0, s, nc, (const int64_t *)ccount, buf, K,
+                       (const int64_t *)nullptr, in.xyz, in.h, in.cfo, in.fvo, edges, in.plane, centre, radii, pcount,
+                       tested);
     EM_HIP(hipGetLastError());
     scan_counts(ws, pcount, coff, nc, s);
     int64_t np = 0;
+    unsigned max_cand = 0;
     EM_HIP(hipMemcpyAsync(&np, coff + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    EM_HIP(hipMemcpyAsync(&max_cand, cmax, sizeof(unsigned), hipMemcpyDeviceToHost, s));
     stream_sync(s);
+    if ((int64_t)max_cand > K) {
+        // the cells with more candidates: their lists' places, the walk and the test again for them
+        int64_t *size = ws.get<int64_t>(S_NCNT, (size_t)nc);
+        ovf_off = ws.get<int64_t>(S_CCNT64, (size_t)(nc + 1));
+        hipLaunchKernelGGL(k_overflow_sizes, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, nc,
+                           (const int64_t *)ccount, K, size);
+        EM_HIP(hipGetLastError());
+        scan_counts(ws, size, ovf_off, nc, s);
+        int64_t n_ovf = 0;
+        EM_HIP(hipMemcpyAsync(&n_ovf, ovf_off + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        stream_sync(s);
+        ovf = ws.get<uint32_t>(S_BINLIST, (size_t)n_ovf);
+        hipLaunchKernelGGL(k_candidates<true>, wg, dim3(256), 0, s, nc, aabb, centre, radii, n, in.xyz, in.h,
+                           (const double *)nodes, NL, ccount, ovf, K, (const int64_t *)ovf_off, cmax);
+        EM_HIP(hipGetLastError());
+        hipLaunchKernelGGL(k_exact<true>, eg, dim3(64 * kExactWaves), 0, s, nc, (const int64_t *)ccount, ovf, K,
+                           (const int64_t *)ovf_off, in.xyz, in.h, in.cfo, in.fvo, edges, in.plane, centre, radii,
+                           pcount, tested);
+        EM_HIP(hipGetLastError());
+        scan_counts(ws, pcount, coff, nc, s);
+        EM_HIP(hipMemcpyAsync(&np, coff + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        stream_sync(s);
+    }
     EM_CHECK(np < (int64_t)UINT32_MAX, MAP_ENOMEM, "pair count exceeds 2^32-1");
     ps.n_pairs = np;
     if (np == 0) return ps;
     uint32_t *pair_c = ws.get<uint32_t>(S_PAIR_C, (size_t)np);
     uint32_t *pair_p = ws.get<uint32_t>(S_PAIR_P, (size_t)np);
-    hipLaunchKernelGGL(k_compact, dim3((unsigned)((nc + 3) / 4)), dim3(256), 0, s, nc, (const int64_t *)coffs,
-                       (const int64_t *)coff, (const uint32_t *)cand_p, (const uint8_t *)flag, pair_c, pair_p);
+    hipLaunchKernelGGL(k_compact, dim3((unsigned)((nc + 3) / 4)), dim3(256), 0, s, nc, (const int64_t *)ccount,
+                       (const uint32_t *)buf, K, (const uint32_t *)ovf, (const int64_t *)ovf_off,
+                       (const int64_t *)coff, pair_c, pair_p);
     EM_HIP(hipGetLastError());
     ps.pair_c = pair_c;
     ps.pair_p = pair_p;
