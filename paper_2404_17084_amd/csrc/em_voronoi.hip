@@ -116,27 +116,36 @@ __global__ void k_vor_parent_boxes(int64_t first, double *__restrict__ bx)
 // so the reverse of a removed triangle's edge is kept exactly when it is in
 // no removed triangle), and compacts kept and new triangles with prefix
 // counts.  The candidate sites of a pass come from a walk of the site tree by
-// the whole wavefront (a node stack in LDS, 64 nodes at a time).  A cell built
-// by one lane in private memory instead reads its arrays with a different
-// index on every lane, so that each access fetches a cache line per lane.
-constexpr int kWCand = 192;   // candidates of one pass (wavefront walk); the serial walk uses the first 64
-constexpr int kWStack = 384;  // tree nodes pending in the wavefront walk (with kWCand: 9.7 kB of LDS per cell, 4 cells per SIMD)
-static_assert(kWCand >= vor::kMaxCand, "the serial walk's candidate heap lives in the same arrays");
+// the whole wavefront (pending nodes in LDS, 64 tests at a time) and are held
+// by the lanes.  A cell built by one lane in private memory instead reads its
+// arrays with a different index on every lane, so that each access fetches a
+// cache line per lane.
+//
+// Bound by vector issue and latency together (10,200 vector instructions per
+// cell, 0.17 per SIMD and clock at 4 wavefronts per SIMD): 6.4 ms for 262,144
+// clumpy sites.  It was 18.7 ms with 26,300 instructions per cell: each leaf's 8
+// sites by one lane, the candidate list sorted and every candidate's plane
+// taken in turn, the reductions of every cut through the LDS crossbar, the
+// new vertices of a cut by the lanes that lost one.
+constexpr int kWCand = 192;   // candidates of one pass (wavefront walk), three per lane; the serial walk uses the first 64
+constexpr int kWStack = 384;  // tree nodes pending in the wavefront walk
+static_assert(kWCand >= vor::kMaxCand && kWCand <= 192, "the serial walk's candidates live in the same array");
 
 struct WCell {
     vor::Plane pl[vor::kMaxPlanes];
     double vx[vor::kMaxTris], vy[vor::kMaxTris], vz[vor::kMaxTris];
     uint32_t tri[vor::kMaxTris];
     int32_t src[vor::kMaxPlanes];
-    double cd2[kWCand];
     int32_t cand[kWCand];
     union {  // (never live at the same time)
-        int32_t nodes[kWStack];                                 // the wavefront walk's pending nodes
-        int64_t stack[64];                                      // the serial walk's stack
+        int32_t nodes[kWStack];  // the wavefront walk's pending nodes: inner ones from the front, leaves from the back
+        struct {                 // the serial walk's stack and keys
+            int64_t stack[64];
+            double cd2[vor::kMaxCand];
+        };
         uint32_t bits[vor::kMaxPlanes * vor::kMaxPlanes / 32];  // a cut's directed edges (x, y) of kept triangles: bit 64 x + y
     };
-    int32_t np, nt, status, cnt;
-    int32_t more, pad[3];
+    int32_t status, cnt, more, pad;
 };
 
 __device__ __forceinline__ double wave_max_d(double v)
@@ -153,79 +162,117 @@ __device__ __forceinline__ double wave_min_d(double v)
     return v;
 }
 
+// Largest of the lanes' values, wave-uniform, by data-parallel primitives (one
+// vector instruction a step; a step through the LDS crossbar takes a
+// hundred clocks and the reductions are on the path of every cut).
+__device__ __forceinline__ unsigned wave_umax(unsigned v)
+{
+#define EM_DPP_MAX(ctrl, rows)                                                                              \
+    {                                                                                                       \
+        const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, true);          \
+        v = v > o ? v : o;                                                                                  \
+    }
+    EM_DPP_MAX(0xB1, 0xf)   // quad_perm 1,0,3,2
+    EM_DPP_MAX(0x4E, 0xf)   // quad_perm 2,3,0,1
+    EM_DPP_MAX(0x141, 0xf)  // row_half_mirror
+    EM_DPP_MAX(0x140, 0xf)  // row_mirror: every row of 16 has its largest value
+    EM_DPP_MAX(0x142, 0xa)  // row_bcast15 into rows 1 and 3
+    EM_DPP_MAX(0x143, 0xc)  // row_bcast31 into rows 2 and 3
+#undef EM_DPP_MAX
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // Set lanes of mask m below this lane.
 __device__ __forceinline__ int lanes_below(uint64_t m)
 {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
-// The farthest vertex's squared distance and the vertices' bounding box
-// (site-centred) of the wavefront's cell.
-__device__ double wbounds(const WCell &W, int nt, int lane, double *blo, double *bhi)
+__device__ __forceinline__ double lane_value(double v, int l)
 {
-    double m = 0.0, lx = INFINITY, ly = INFINITY, lz = INFINITY, hx = -INFINITY, hy = -INFINITY, hz = -INFINITY;
-    for (int t = lane; t < nt; t += 64) {
-        const double x = W.vx[t], y = W.vy[t], z = W.vz[t];
-        m = fmax(m, x * x + y * y + z * z);
-        lx = fmin(lx, x), hx = fmax(hx, x);
-        ly = fmin(ly, y), hy = fmax(hy, y);
-        lz = fmin(lz, z), hz = fmax(hz, z);
-    }
-    blo[0] = wave_min_d(lx), blo[1] = wave_min_d(ly), blo[2] = wave_min_d(lz);
-    bhi[0] = wave_max_d(hx), bhi[1] = wave_max_d(hy), bhi[2] = wave_max_d(hz);
-    return wave_max_d(m);
+    const uint64_t b = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
 }
 
-// Sorts the first cnt (<= kWCand) candidates by key (squared distance, then
-// index) in LDS: each lane holds up to 4 of them and counts the keys below
-// each (keys are distinct: the index breaks ties), reading the list with
-// broadcast loads; then writes each at its rank.
-__device__ void sort_cands(WCell &W, int cnt, int lane)
+// This lane's triangles (lane, lane + 64) of the wavefront's cell, held in
+// registers between cuts.
+struct MyTris {
+    uint32_t q[2];
+    double x[2], y[2], z[2];
+};
+
+__device__ __forceinline__ void load_tris(const WCell &W, int nt, int lane, MyTris &T)
 {
-    if (cnt <= 1) return;
-    static_assert(kWCand <= 256, "four candidates per lane");
-    double d[4];
-    int32_t q[4];
-    int rk[4];
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
-        const int i = lane + 64 * u;
-        d[u] = i < cnt ? W.cd2[i] : INFINITY;
-        q[u] = i < cnt ? W.cand[i] : 0x7fffffff;
-        rk[u] = 0;
-    }
-    const int per = (cnt + 63) >> 6;  // wave-uniform
-    for (int j = 0; j < cnt; j++) {
-        const double e = W.cd2[j];
-        const int32_t eq = W.cand[j];
-        rk[0] += vor::key_less(e, eq, d[0], q[0]) ? 1 : 0;
-        if (per > 1) rk[1] += vor::key_less(e, eq, d[1], q[1]) ? 1 : 0;
-        if (per > 2) rk[2] += vor::key_less(e, eq, d[2], q[2]) ? 1 : 0;
-        if (per > 3) rk[3] += vor::key_less(e, eq, d[3], q[3]) ? 1 : 0;
-    }
-    lds_sync_wave();  // every read done before the list is rewritten
-#pragma unroll
-    for (int u = 0; u < 4; u++)
-        if (lane + 64 * u < cnt) {
-            W.cd2[rk[u]] = d[u];
-            W.cand[rk[u]] = q[u];
+    for (int u = 0; u < 2; u++) {
+        const int t = lane + 64 * u;
+        if (t < nt) {
+            T.q[u] = W.tri[t];
+            T.x[u] = W.vx[t];
+            T.y[u] = W.vy[t];
+            T.z[u] = W.vz[t];
         }
-    lds_sync_wave();
+    }
 }
 
-// The candidate sites of one pass with the whole wavefront: pending tree
-// nodes sit on a stack in LDS, and each step takes the top 64 (one per lane):
-// an internal node pushes those of its children that pass the visit test, a
-// leaf tests its sites, with the tests of the serial walk (vor::collect).  The
-// walk starts from the (at most 64) nodes of the tree's level 6.  The list of
-// candidates holds kWCand: when it fills up, it is sorted and cut to the
-// sites nearer than its (kWCand / 2)th, whose distance becomes the walk's radius (as the
-// serial walk's heap prunes with its farthest entry), and *more is set.  So
-// the result is the nearest sites of the ball whose key follows (lo2, lo_q)
-// and whose bisector can reach the box [blo, bhi], sorted by key (squared
-// distance, then index), all of them unless *more.  Returns the count, or -1
-// when the node stack would overflow or a cut list keeps nothing (the caller
-// then takes the serial walk).
+// Upper bounds of the cell about its site, wave-uniform: how far it reaches
+// along the six axis directions and the squared distance of its farthest
+// vertex, rounded up to FP32.  (The site lies in its cell, so all are >= 0.)
+// They only decide which sites need no cut, so a bound that is a little too
+// large changes nothing.
+struct Bounds {
+    float lo[3], hi[3];  // reach along -x, -y, -z and +x, +y, +z
+    double m2;
+};
+
+__device__ __forceinline__ float round_up(double v)  // v >= 0
+{
+    return (float)v * 1.0000002f;
+}
+
+__device__ __forceinline__ void bounds_of(const MyTris &T, int nt, int lane, Bounds &B)
+{
+    float l[3] = {0.0f, 0.0f, 0.0f}, h[3] = {0.0f, 0.0f, 0.0f}, m = 0.0f;
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+        if (lane + 64 * u < nt) {
+            const double x = T.x[u], y = T.y[u], z = T.z[u];
+            const float f[3] = {(float)x, (float)y, (float)z};
+            for (int d = 0; d < 3; d++) {
+                l[d] = fmaxf(l[d], -f[d]);
+                h[d] = fmaxf(h[d], f[d]);
+            }
+            m = fmaxf(m, (float)(x * x + y * y + z * z));
+        }
+    for (int d = 0; d < 3; d++) {
+        B.lo[d] = __uint_as_float(wave_umax(__float_as_uint(l[d] + 0.0f))) * 1.0000002f;
+        B.hi[d] = __uint_as_float(wave_umax(__float_as_uint(h[d] + 0.0f))) * 1.0000002f;
+    }
+    B.m2 = (double)(__uint_as_float(wave_umax(__float_as_uint(m))) * 1.0000002f);
+}
+
+// A site at offset w reaches the cell only if some vertex v has w.v > |w|^2 /
+// 2; w.v is at most the box's reach along w (all of whose terms are >= 0).
+// FP32, with a margin above its rounding.
+__device__ __forceinline__ bool may_cut(const Bounds &B, float dx, float dy, float dz, float d2)
+{
+    const float r = fmaxf(-dx * B.lo[0], dx * B.hi[0]) + fmaxf(-dy * B.lo[1], dy * B.hi[1]) +
+                    fmaxf(-dz * B.lo[2], dz * B.hi[2]);
+    return 0.5f * d2 < r * 1.000002f;
+}
+
+// The candidate sites of one pass with the whole wavefront: each step takes 16
+// pending inner nodes of the site tree and tests their 64 grandchildren, one
+// per lane, or the 64 sites of 8 pending leaves, with the tests of the serial
+// walk (vor::collect).  The walk starts from the (at most 64) nodes of the
+// tree's level 6.  The list of candidates holds kWCand: when it fills up, it
+// is cut to its nearer half, and the distance of the nearest one dropped
+// becomes the walk's radius, and *more is set.  So the result is the sites of
+// the ball whose key follows (lo2, lo_q) and whose bisector can reach the
+// cell's box, all of them unless *more.  Returns the count, or -1 when the
+// pending nodes do not fit or a cut list keeps nothing (the caller then takes
+// the serial walk).
 __device__ int collect_wave(WCell &W, const double *__restrict__ ps, int64_t n, const double *__restrict__ bx,
                             int64_t NL, int64_t self, double sx, double sy, double sz, double lo2, int64_t lo_q,
                             double hi2, const double *blo, const double *bhi, int lane, bool *more)
@@ -235,106 +282,119 @@ __device__ int collect_wave(WCell &W, const double *__restrict__ ps, int64_t n, 
     auto visit = [&](int64_t node) {
         const double *b = bx + 6 * node;
         const double g2 = vor::box_gap2(b, sx, sy, sz);
-        if (!(g2 < h2)) return false;
         const double ax = b[0] - sx, bxx = b[3] - sx, ay = b[1] - sy, by = b[4] - sy, az = b[2] - sz, bz = b[5] - sz;
         const double gm = fmax(fmax(ax * blo[0], ax * bhi[0]), fmax(bxx * blo[0], bxx * bhi[0])) +
                           fmax(fmax(ay * blo[1], ay * bhi[1]), fmax(by * blo[1], by * bhi[1])) +
                           fmax(fmax(az * blo[2], az * bhi[2]), fmax(bz * blo[2], bz * bhi[2]));
-        return 0.5 * g2 < gm;
+        return g2 < h2 && 0.5 * g2 < gm;
     };
-    // level 6 of the tree (or the leaves, for a tree of fewer than 64): nodes
-    // first .. 2 first - 1; NL is a power of two
-    const int64_t first = NL < 64 ? NL : 64;
-    int sp = 0, cnt = 0;
-    bool cut = false;  // h2 was lowered: popped nodes are tested again
+    // the site's squared distance
+    auto dist2 = [&](int64_t q, double &dx, double &dy, double &dz) {
+        dx = ps[3 * q] - sx;
+        dy = ps[3 * q + 1] - sy;
+        dz = ps[3 * q + 2] - sz;
+        return dx * dx + dy * dy + dz * dz;
+    };
+    int sp = 0, nl = 0, cnt = 0;  // inner nodes, leaves, candidates
+    auto push = [&](bool v, int64_t node) {  // false: no room
+        const uint64_t leaf = __ballot(v && node >= NL), inner = __ballot(v && node < NL);
+        if (sp + nl + __popcll(leaf) + __popcll(inner) > kWStack) return false;
+        if (v) W.nodes[node < NL ? sp + lanes_below(inner) : kWStack - 1 - (nl + lanes_below(leaf))] = (int32_t)node;
+        sp += __popcll(inner);
+        nl += __popcll(leaf);
+        return true;
+    };
     {
-        const bool v = lane < first && visit(first + lane);
-        const int c = wave_push(v, sp);
-        if (v) W.nodes[c] = (int32_t)(first + lane);
+        const int64_t first = NL < 64 ? NL : 64;  // NL is a power of two
+        push(lane < first && visit(first + lane), first + lane);
     }
     lds_sync_wave();
-    while (sp > 0) {
-        const int k = sp < 64 ? sp : 64;
-        sp -= k;
-        const int64_t node = lane < k ? (int64_t)W.nodes[sp + lane] : 0;
-        lds_sync_wave();  // read before the pushes below overwrite these slots
-        const bool act = lane < k && (!cut || visit(node));
-        const bool internal = act && node < NL, leaf = act && node >= NL;
-        const bool v1 = internal && visit(2 * node), v2 = internal && visit(2 * node + 1);
-        const int c1 = wave_push(v1, sp);
-        const int c2 = wave_push(v2, sp);
-        if (v1 && c1 < kWStack) W.nodes[c1] = (int32_t)(2 * node);
-        if (v2 && c2 < kWStack) W.nodes[c2] = (int32_t)(2 * node + 1);
-        // a leaf's sites, all loaded before any is pushed
-        const int64_t j = leaf ? node - NL : 0;
-        double d2[vor::kLeaf];
-        bool take[vor::kLeaf];
-#pragma unroll
-        for (int t = 0; t < vor::kLeaf; t++) {
-            const int64_t q = vor::kLeaf * j + t;
-            const bool ok = leaf && q < n && q != self;
-            const int64_t qq = ok ? q : 0;
-            const double dx = ps[3 * qq] - sx, dy = ps[3 * qq + 1] - sy, dz = ps[3 * qq + 2] - sz;
-            d2[t] = dx * dx + dy * dy + dz * dz;
-            take[t] = ok && vor::key_less(lo2, lo_q, d2[t], q) && 0.5 * d2[t] < vor::reach(blo, bhi, dx, dy, dz);
-        }
-#pragma unroll
-        for (int t = 0; t < vor::kLeaf; t++) {
+    while (sp > 0 || nl > 0) {
+        if (nl >= 8 || sp == 0) {
             if (cnt > kWCand - 64) {
-                // full: keep the sites nearer than the (kWCand / 2)th
-                lds_sync_wave();
-                sort_cands(W, cnt, lane);
-                h2 = W.cd2[kWCand / 2 - 1];
-                int keep = 0;
-                for (int u = lane; u < cnt; u += 64) keep += W.cd2[u] < h2 ? 1 : 0;
+                // full: keep the nearer half
+                double d[3], dx, dy, dz;
+                int32_t q[3];
+                uint32_t key[3];
 #pragma unroll
-                for (int o = 32; o > 0; o >>= 1) keep += __shfl_xor(keep, o, 64);
-                cnt = keep;
+                for (int u = 0; u < 3; u++) {
+                    const bool in = lane + 64 * u < cnt;
+                    q[u] = in ? W.cand[lane + 64 * u] : 0;
+                    d[u] = in ? dist2(q[u], dx, dy, dz) : INFINITY;
+                    key[u] = __float_as_uint((float)d[u]);
+                }
+                auto upto = [&](uint32_t k) {
+                    return __popcll(__ballot(key[0] <= k)) + __popcll(__ballot(key[1] <= k)) +
+                           __popcll(__ballot(key[2] <= k));
+                };
+                uint32_t ka = 0, kb = __float_as_uint(INFINITY);  // at most half are <= ka, more than half <= kb
+                while (kb - ka > 1) {
+                    const uint32_t km = ka + (kb - ka) / 2;
+                    if (upto(km) <= kWCand / 2) ka = km;
+                    else kb = km;
+                }
+                double first_out = INFINITY;
+#pragma unroll
+                for (int u = 0; u < 3; u++)
+                    if (key[u] > ka) first_out = fmin(first_out, d[u]);
+                h2 = wave_min_d(first_out);
+                lds_sync_wave();  // every entry read before the list is rewritten
+                cnt = 0;
+#pragma unroll
+                for (int u = 0; u < 3; u++) {
+                    const bool keep = key[u] <= ka;
+                    const int at = wave_push(keep, cnt);
+                    if (keep) W.cand[at] = q[u];
+                }
                 *more = true;
-                cut = true;
                 if (cnt == 0) return -1;  // ties: the serial walk orders them by index
                 lds_sync_wave();
             }
-            const bool tk = take[t] && d2[t] < h2;
-            const int c = wave_push(tk, cnt);
-            if (tk) {
-                W.cd2[c] = d2[t];
-                W.cand[c] = (int32_t)(vor::kLeaf * j + t);
-            }
+            const int k = nl < 8 ? nl : 8;
+            const bool act = (lane >> 3) < k;
+            const int64_t j = act ? (int64_t)W.nodes[kWStack - nl + (lane >> 3)] - NL : 0;
+            nl -= k;
+            const int64_t q = vor::kLeaf * j + (lane & 7);
+            const bool ok = act && q < n && q != self;
+            double dx, dy, dz;
+            const double d2 = dist2(ok ? q : 0, dx, dy, dz);
+            const bool take = ok && d2 < h2 && vor::key_less(lo2, lo_q, d2, q) && 0.5 * d2 < vor::reach(blo, bhi, dx, dy, dz);
+            const int at = wave_push(take, cnt);
+            if (take) W.cand[at] = (int32_t)q;
+            lds_sync_wave();
+            continue;
         }
+        const int k = sp < 16 ? sp : 16;
+        const bool act = (lane >> 2) < k;
+        const int64_t node = act ? (int64_t)W.nodes[sp - k + (lane >> 2)] : 1;
+        sp -= k;
+        const bool two = 2 * node < NL;  // the grandchildren, or the children above the leaves
+        const int64_t child = two ? 4 * node + (lane & 3) : 2 * node + (lane & 1);
+        const bool v = act && (two || (lane & 3) < 2) && visit(child);
+        lds_sync_wave();  // every node read before the pushes overwrite them
+        if (!push(v, child)) return -1;
         lds_sync_wave();
-        if (sp > kWStack) return -1;
     }
-    sort_cands(W, cnt, lane);
     return cnt;
 }
 
 // Cut by P (n.x <= d) in wave-uniform control flow; np, nt, status are
-// wave-uniform copies of the cell's counts.  Returns true when P removed a vertex.
-__device__ bool wclip(WCell &W, int &np, int &nt, int &status, const vor::Plane &P, int32_t src, int lane)
+// wave-uniform copies of the cell's counts, T this lane's triangles (reloaded
+// after a cut).  Returns true when P removed a vertex.
+__device__ bool wclip(WCell &W, int &np, int &nt, int &status, const vor::Plane &P, int32_t src, int lane, MyTris &T)
 {
     const double nn = sqrt(P.nx * P.nx + P.ny * P.ny + P.nz * P.nz);
     const double tol = vor::kEps * nn;
-    const int t0 = lane, t1 = lane + 64;
-    const bool h0 = t0 < nt, h1 = t1 < nt;
-    uint32_t q0 = 0, q1 = 0;
-    double x0 = 0.0, y0 = 0.0, z0 = 0.0, x1 = 0.0, y1 = 0.0, z1 = 0.0;
-    if (h0) {
-        q0 = W.tri[t0];
-        x0 = W.vx[t0];
-        y0 = W.vy[t0];
-        z0 = W.vz[t0];
+    const bool two = nt > 64;  // some lanes own a second triangle
+    bool h[2] = {lane < nt, lane + 64 < nt}, o[2] = {false, false};
+    uint64_t out[2] = {0, 0};
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        if (u == 1 && !two) break;
+        o[u] = h[u] && P.nx * T.x[u] + P.ny * T.y[u] + P.nz * T.z[u] - P.d > tol;
+        out[u] = __ballot(o[u]);
     }
-    if (h1) {
-        q1 = W.tri[t1];
-        x1 = W.vx[t1];
-        y1 = W.vy[t1];
-        z1 = W.vz[t1];
-    }
-    const bool o0 = h0 && P.nx * x0 + P.ny * y0 + P.nz * z0 - P.d > tol;
-    const bool o1 = h1 && P.nx * x1 + P.ny * y1 + P.nz * z1 - P.d > tol;
-    const uint64_t m0 = __ballot(o0), m1 = __ballot(o1);
-    if ((m0 | m1) == 0) return false;
+    if ((out[0] | out[1]) == 0) return false;
     if (np >= vor::kMaxPlanes) {
         status = vor::ST_PLANES;
         return false;
@@ -349,75 +409,82 @@ __device__ bool wclip(WCell &W, int &np, int &nt, int &status, const vor::Plane 
     W.bits[lane] = 0u;
     W.bits[lane + 64] = 0u;
     lds_sync_wave();
-    auto mark = [&](uint32_t q) {
-        const int a = vor::tri_a(q), b = vor::tri_b(q), c = vor::tri_c(q);
-        const int e0 = 64 * a + b, e1 = 64 * b + c, e2 = 64 * c + a;
-        atomicOr(&W.bits[e0 >> 5], 1u << (e0 & 31));
-        atomicOr(&W.bits[e1 >> 5], 1u << (e1 & 31));
-        atomicOr(&W.bits[e2 >> 5], 1u << (e2 & 31));
-    };
-    if (h0 && !o0) mark(q0);
-    if (h1 && !o1) mark(q1);
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        if (u == 1 && !two) break;
+        if (h[u] && !o[u]) {
+            const int a = vor::tri_a(T.q[u]), b = vor::tri_b(T.q[u]), c = vor::tri_c(T.q[u]);
+            const int e0 = 64 * a + b, e1 = 64 * b + c, e2 = 64 * c + a;
+            atomicOr(&W.bits[e0 >> 5], 1u << (e0 & 31));
+            atomicOr(&W.bits[e1 >> 5], 1u << (e1 & 31));
+            atomicOr(&W.bits[e2 >> 5], 1u << (e2 & 31));
+        }
+    }
     lds_sync_wave();
     // new triangles (x, y, p) on the boundary edges (x, y) of the removed
     // ones, in the serial order: by removed triangle, then edge
-    uint32_t n0[3], n1[3];
-    int c0 = 0, c1 = 0;
-    auto boundary = [&](uint32_t q, uint32_t *out, int &c) {
-        const int v[3] = {vor::tri_a(q), vor::tri_b(q), vor::tri_c(q)};
-        for (int e = 0; e < 3; e++) {
-            const int x = v[e], y = v[(e + 1) % 3];
-            const int r = 64 * y + x;
-            if ((W.bits[r >> 5] >> (r & 31)) & 1u) out[c++] = vor::tri_pack(x, y, p);
+    bool on[2][3] = {{false, false, false}, {false, false, false}};  // edge e of triangle u is on the boundary
+    int before[2] = {0, 0}, total[2] = {0, 0}, kept = 0, kept_below[2] = {0, 0};
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        if (u == 1 && !two) break;
+        if (o[u]) {
+            const int v[3] = {vor::tri_a(T.q[u]), vor::tri_b(T.q[u]), vor::tri_c(T.q[u])};
+#pragma unroll
+            for (int e = 0; e < 3; e++) {
+                const int r = 64 * v[(e + 1) % 3] + v[e];
+                on[u][e] = ((W.bits[r >> 5] >> (r & 31)) & 1u) != 0;
+            }
         }
-    };
-    if (o0) boundary(q0, n0, c0);
-    if (o1) boundary(q1, n1, c1);
-    const uint64_t a0 = __ballot(c0 & 1), b0 = __ballot(c0 & 2), a1 = __ballot(c1 & 1), b1 = __ballot(c1 & 2);
-    const int s0 = lanes_below(a0) + 2 * lanes_below(b0), s1 = lanes_below(a1) + 2 * lanes_below(b1);
-    const int tot0 = __popcll(a0) + 2 * __popcll(b0), tot1 = __popcll(a1) + 2 * __popcll(b1);
-    const uint64_t k0 = __ballot(h0 && !o0), k1 = __ballot(h1 && !o1);
-    const int kept = __popcll(k0) + __popcll(k1);
-    if (kept + tot0 + tot1 > vor::kMaxTris) {
+#pragma unroll
+        for (int e = 0; e < 3; e++) {
+            const uint64_t m = __ballot(on[u][e]);
+            before[u] += lanes_below(m);
+            total[u] += __popcll(m);
+        }
+        const uint64_t k = __ballot(h[u] && !o[u]);
+        kept_below[u] = kept + lanes_below(k);
+        kept += __popcll(k);
+    }
+    const int n_new = total[0] + total[1];
+    if (kept + n_new > vor::kMaxTris) {
         status = vor::ST_TRIS;
         return false;
     }
-    // every lane holds its triangles in registers: compact in place
-    if (h0 && !o0) {
-        const int k = lanes_below(k0);
-        W.tri[k] = q0;
-        W.vx[k] = x0;
-        W.vy[k] = y0;
-        W.vz[k] = z0;
+    // every lane holds its triangles in registers: compact in place, the new ones after the kept ones
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        if (u == 1 && !two) break;
+        if (h[u] && !o[u]) {
+            const int k = kept_below[u];
+            W.tri[k] = T.q[u];
+            W.vx[k] = T.x[u];
+            W.vy[k] = T.y[u];
+            W.vz[k] = T.z[u];
+        }
+        if (o[u]) {
+            const int v[3] = {vor::tri_a(T.q[u]), vor::tri_b(T.q[u]), vor::tri_c(T.q[u])};
+            int k = kept + (u == 1 ? total[0] : 0) + before[u];
+#pragma unroll
+            for (int e = 0; e < 3; e++)
+                if (on[u][e]) W.tri[k++] = vor::tri_pack(v[e], v[(e + 1) % 3], p);
+        }
     }
-    if (h1 && !o1) {
-        const int k = __popcll(k0) + lanes_below(k1);
-        W.tri[k] = q1;
-        W.vx[k] = x1;
-        W.vy[k] = y1;
-        W.vz[k] = z1;
-    }
-    for (int i = 0; i < c0; i++) {
-        const int k = kept + s0 + i;
-        const uint32_t q = n0[i];
-        W.tri[k] = q;
-        vor::meet(W.pl[vor::tri_a(q)], W.pl[vor::tri_b(q)], W.pl[vor::tri_c(q)], W.vx[k], W.vy[k], W.vz[k]);
-    }
-    for (int i = 0; i < c1; i++) {
-        const int k = kept + tot0 + s1 + i;
-        const uint32_t q = n1[i];
-        W.tri[k] = q;
-        vor::meet(W.pl[vor::tri_a(q)], W.pl[vor::tri_b(q)], W.pl[vor::tri_c(q)], W.vx[k], W.vy[k], W.vz[k]);
-    }
-    nt = kept + tot0 + tot1;
+    nt = kept + n_new;
     lds_sync_wave();
+    for (int k = kept + lane; k < nt; k += 64) {  // the new vertices, one per lane
+        const uint32_t q = W.tri[k];
+        vor::meet(W.pl[vor::tri_a(q)], W.pl[vor::tri_b(q)], W.pl[vor::tri_c(q)], W.vx[k], W.vy[k], W.vz[k]);
+    }
+    lds_sync_wave();
+    load_tris(W, nt, lane, T);
     return true;
 }
 
 // One wavefront per sorted site: its cell, the cell's record and its face,
 // face-vertex slot and vertex counts (stored at the site's input index); flags
 // bit 2: a cell needed more planes, vertices or passes than its record holds.
-__global__ void __launch_bounds__(128) k_vor_build_wave(int64_t n, const double *__restrict__ ps,
+__global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const double *__restrict__ ps,
                                                         const int32_t *__restrict__ orig,
                                                         const double *__restrict__ bx, int64_t NL, VBox B,
                                                         vor::Cell *__restrict__ cells, int64_t *__restrict__ nfc,
@@ -431,12 +498,32 @@ __global__ void __launch_bounds__(128) k_vor_build_wave(int64_t n, const double 
     if (r >= n) return;  // whole wavefronts
     const double box[6] = {B.lo[0], B.lo[1], B.lo[2], B.hi[0], B.hi[1], B.hi[2]};
     const double sx = ps[3 * r], sy = ps[3 * r + 1], sz = ps[3 * r + 2];
-    if (lane == 0) {
-        vor::init_box(W, box, sx, sy, sz);
-        W.status = vor::ST_OK;
+    // the box: planes 0..5 = x-, x+, y-, y+, z-, z+ and its 8 corners (one lane each)
+    if (lane < 6) {
+        const int ax = lane >> 1, side = lane & 1;
+        const double sg = side ? 1.0 : -1.0, sa = ax == 0 ? sx : (ax == 1 ? sy : sz);
+        vor::Plane P;
+        P.nx = ax == 0 ? sg : 0.0;
+        P.ny = ax == 1 ? sg : 0.0;
+        P.nz = ax == 2 ? sg : 0.0;
+        const double lo = ax == 0 ? box[0] : (ax == 1 ? box[1] : box[2]), hi = ax == 0 ? box[3] : (ax == 1 ? box[4] : box[5]);
+        P.d = side ? hi - sa : sa - lo;
+        W.pl[lane] = P;
+        W.src[lane] = -1 - lane;
+    }
+    if (lane < 8) {
+        const int cx = lane & 1, cy = (lane >> 1) & 1, cz = (lane >> 2) & 1;
+        const int a = cx, b = 2 + cy, c = 4 + cz;
+        const bool pos = ((cx + cy + cz) & 1) != 0;  // det(n_a, n_b, n_c), the product of the three signs
+        W.tri[lane] = pos ? vor::tri_pack(a, b, c) : vor::tri_pack(a, c, b);
+        W.vx[lane] = cx ? box[3] - sx : -(sx - box[0]);
+        W.vy[lane] = cy ? box[4] - sy : -(sy - box[1]);
+        W.vz[lane] = cz ? box[5] - sz : -(sz - box[2]);
     }
     lds_sync_wave();
     int np = 6, nt = 8, status = vor::ST_OK;
+    MyTris T = {};
+    load_tris(W, nt, lane, T);
     // The first pass only looks within 0.87 times the diagonal of the site's
     // leaf box (about 110 sites when the leaf's 8 sites fill it: most cells
     // end within it), at least an eighth of the mean spacing (for a leaf of
@@ -450,23 +537,32 @@ __global__ void __launch_bounds__(128) k_vor_build_wave(int64_t n, const double 
     if (hi2 < mean * mean / 64.0) hi2 = mean * mean / 64.0;
     double lo2 = -1.0;
     int64_t lo_q = -1;
-    double blo[3], bhi[3];
-    double m2 = wbounds(W, nt, lane, blo, bhi);
+    Bounds bd;
+    bounds_of(T, nt, lane, bd);
     // Passes: the ball first, then everything that can still reach the cell;
-    // each pass lists the nearest sites whose key follows the last one taken.
-    // The sites are cut in key order, skipping those whose bisector cannot
-    // reach the vertices' current bounding box (a pass's own reach filter used
-    // the box at its start, which contains the current one), until one is at
-    // least twice as far as the farthest vertex: the sequence of cuts, and so
-    // the cell, is the same however the passes split it.
+    // each pass lists the sites whose key (squared distance, then index)
+    // follows the last pass's.  The sites are cut in key order, skipping those
+    // whose bisector cannot reach the vertices' current bounding box, until
+    // one is at least twice as far as the farthest vertex: the sequence of
+    // cuts, and so the cell, is the same however the passes split it.  The
+    // lanes hold the candidates; the next one is the least key among those
+    // that may still cut, so the list is not sorted and a site that cannot cut
+    // costs nothing.
     bool done = false;
     int pass = 0;
     for (; pass < 4096 && !done && status == vor::ST_OK; pass++) {
         bool more = false;
+        double blo[3], bhi[3];
+        for (int d = 0; d < 3; d++) {
+            blo[d] = -(double)bd.lo[d];
+            bhi[d] = (double)bd.hi[d];
+        }
         int cnt = collect_wave(W, ps, n, bx, NL, r, sx, sy, sz, lo2, lo_q, hi2, blo, bhi, lane, &more);
         if (cnt < 0) {  // the serial walk, 64 at a time
+            lds_sync_wave();
             if (lane == 0) {
                 bool m = false;
+                W.status = vor::ST_OK;
                 W.cnt = vor::collect(W, ps, n, bx, NL, r, sx, sy, sz, lo2, lo_q, hi2, blo, bhi, &m, W.stack);
                 W.more = m ? 1 : 0;
             }
@@ -478,26 +574,99 @@ __global__ void __launch_bounds__(128) k_vor_build_wave(int64_t n, const double 
                 break;
             }
         }
-        for (int it = 0; it < cnt; it++) {
-            const double bd = W.cd2[it];
-            const int64_t q = W.cand[it];
-            if (bd >= 4.0 * m2) {  // this site and every farther one miss the cell
-                done = true;
-                break;
-            }
-            lo2 = bd;
-            lo_q = q;
-            vor::Plane P;
-            P.nx = ps[3 * q] - sx;
-            P.ny = ps[3 * q + 1] - sy;
-            P.nz = ps[3 * q + 2] - sz;
-            P.d = 0.5 * (P.nx * P.nx + P.ny * P.ny + P.nz * P.nz);
-            if (P.d == 0.0) continue;
-            if (!(P.d < vor::reach(blo, bhi, P.nx, P.ny, P.nz))) continue;
-            if (wclip(W, np, nt, status, P, orig[q], lane)) m2 = wbounds(W, nt, lane, blo, bhi);
-            if (status != vor::ST_OK) break;
+        // candidates lane, lane + 64, lane + 128: offsets, squared distances (bits of the FP32 value as the coarse key)
+        double cx[3], cy[3], cz[3], cd[3];
+        int32_t cq[3];
+        bool left[3];
+#pragma unroll
+        for (int u = 0; u < 3; u++) {
+            left[u] = lane + 64 * u < cnt;
+            cq[u] = left[u] ? W.cand[lane + 64 * u] : 0;
+            cx[u] = ps[3 * (int64_t)cq[u]] - sx;
+            cy[u] = ps[3 * (int64_t)cq[u] + 1] - sy;
+            cz[u] = ps[3 * (int64_t)cq[u] + 2] - sz;
+            cd[u] = cx[u] * cx[u] + cy[u] * cy[u] + cz[u] * cz[u];
         }
-        if (done || status != vor::ST_OK) break;
+        bool fresh = true;  // the bounds have changed
+        uint32_t key[3] = {~0u, ~0u, ~0u};
+        while (status == vor::ST_OK) {
+            if (fresh) {
+#pragma unroll
+                for (int u = 0; u < 3; u++) {
+                    const float d2 = (float)cd[u];
+                    const bool cuts = left[u] && cd[u] < 4.0 * bd.m2 && cd[u] > 0.0 &&
+                                      may_cut(bd, (float)cx[u], (float)cy[u], (float)cz[u], d2);
+                    key[u] = cuts ? __float_as_uint(d2) : ~0u;
+                }
+                fresh = false;
+            }
+            const uint32_t mine = min(key[0], min(key[1], key[2]));
+            const uint32_t least = ~wave_umax(~mine);
+            if (least == ~0u) break;
+            uint64_t at[3];
+#pragma unroll
+            for (int u = 0; u < 3; u++) at[u] = __ballot(key[u] == least);
+            int bu = -1, bl = 0;
+            double bd2 = 0.0;
+            int32_t bq = 0;
+            const bool tie = __popcll(at[0]) + __popcll(at[1]) + __popcll(at[2]) > 1;
+#pragma unroll
+            for (int u = 0; u < 3; u++)
+                for (uint64_t m = at[u]; m != 0; m &= m - 1) {  // (one, but for equal FP32 distances)
+                    const int l = __builtin_ctzll(m);
+                    if (tie) {
+                        const double d = lane_value(cd[u], l);
+                        const int32_t q = __builtin_amdgcn_readlane(cq[u], l);
+                        if (bu >= 0 && !vor::key_less(d, q, bd2, bq)) continue;
+                        bd2 = d;
+                        bq = q;
+                    }
+                    bu = u;
+                    bl = l;
+                }
+            vor::Plane P;
+            int64_t q;
+            auto take = [&](int u) {
+                P.nx = lane_value(cx[u], bl);
+                P.ny = lane_value(cy[u], bl);
+                P.nz = lane_value(cz[u], bl);
+                q = __builtin_amdgcn_readlane(cq[u], bl);
+                if (lane == bl) {
+                    left[u] = false;
+                    key[u] = ~0u;
+                }
+            };
+            if (bu == 0) take(0);
+            else if (bu == 1) take(1);
+            else take(2);
+            P.d = 0.5 * (P.nx * P.nx + P.ny * P.ny + P.nz * P.nz);
+            if (wclip(W, np, nt, status, P, orig[q], lane, T)) {
+                bounds_of(T, nt, lane, bd);
+                fresh = true;
+            }
+        }
+        if (status != vor::ST_OK) break;
+        // a listed site at least twice as far as the farthest vertex: it and every farther one miss the cell
+        bool beyond = false;
+#pragma unroll
+        for (int u = 0; u < 3; u++) beyond = beyond || (lane + 64 * u < cnt && cd[u] >= 4.0 * bd.m2);
+        if (__ballot(beyond) != 0) {
+            done = true;
+            break;
+        }
+        if (cnt > 0) {  // the next pass's keys follow the last of this one's
+            double d = -1.0;
+#pragma unroll
+            for (int u = 0; u < 3; u++)
+                if (lane + 64 * u < cnt) d = fmax(d, cd[u]);
+            lo2 = wave_max_d(d);
+            int32_t q = -1;
+#pragma unroll
+            for (int u = 0; u < 3; u++)
+                if (lane + 64 * u < cnt && cd[u] == lo2) q = max(q, cq[u]);
+            for (int o = 32; o > 0; o >>= 1) q = max(q, __shfl_xor(q, o, 64));
+            lo_q = q;
+        }
         if (!more) {
             if (hi2 == INFINITY) {
                 done = true;

@@ -68,43 +68,6 @@ __host__ __device__ inline void meet(const Plane &A, const Plane &B, const Plane
     z = (A.d * bcz + B.d * caz + C.d * abz) / det;
 }
 
-template <class CellT>
-__host__ __device__ inline void set_vertex(CellT &C, int t)
-{
-    const uint32_t q = C.tri[t];
-    meet(C.pl[tri_a(q)], C.pl[tri_b(q)], C.pl[tri_c(q)], C.vx[t], C.vy[t], C.vz[t]);
-}
-
-// the box [lo, hi] around site s: planes 0..5 = x-, x+, y-, y+, z-, z+
-template <class CellT>
-__host__ __device__ inline void init_box(CellT &C, const double *box, double sx, double sy, double sz)
-{
-    const double s[3] = {sx, sy, sz};
-    for (int ax = 0; ax < 3; ax++)
-        for (int side = 0; side < 2; side++) {
-            Plane &P = C.pl[2 * ax + side];
-            P.nx = P.ny = P.nz = 0.0;
-            const double sg = side ? 1.0 : -1.0;
-            if (ax == 0) P.nx = sg;
-            if (ax == 1) P.ny = sg;
-            if (ax == 2) P.nz = sg;
-            P.d = side ? box[3 + ax] - s[ax] : s[ax] - box[ax];
-            C.src[2 * ax + side] = -1 - (2 * ax + side);
-        }
-    C.np = 6;
-    C.nt = 0;
-    for (int k = 0; k < 8; k++) {
-        const int px = k & 1, py = (k >> 1) & 1, pz = (k >> 2) & 1;
-        const int a = px, b = 2 + py, c = 4 + pz;
-        // det(n_a, n_b, n_c) = product of the three signs
-        const int sgn = (px ? 1 : -1) * (py ? 1 : -1) * (pz ? 1 : -1);
-        C.tri[C.nt] = sgn > 0 ? tri_pack(a, b, c) : tri_pack(a, c, b);
-        set_vertex(C, C.nt);
-        C.nt++;
-    }
-    C.status = ST_OK;
-}
-
 __host__ __device__ inline double box_gap2(const double *bb, double px, double py, double pz)
 {
     const double dx = fmax(fmax(bb[0] - px, px - bb[3]), 0.0);

@@ -205,3 +205,33 @@ def test_merging_and_site_cells():
         assert np.array_equal(N.site_cell, np.arange(2000))
         with pytest.raises(em.MapError):
             mp.voronoi(s, BOX, merge_dist=-1.0)
+
+
+@pytest.mark.parametrize("n", [5, 9, 63, 65, 511, 513, 1025])
+def test_voronoi_tree_sizes(n):
+    """Trees about the walk's edges: fewer leaves than its 64 starting nodes, an odd and an even number of levels
+    below them, and a last leaf that is not full."""
+    say(f"case: voronoi uniform {n}, tree sizes")
+    s = np.random.default_rng(900 + n).random((n, 3))
+    with em.Mapper(device=0) as mp:
+        G = mp.voronoi(s, BOX)
+    O = oracle.voronoi(s, BOX)
+    assert (np.abs(G.cell_volume - O["cell_volume"]) / O["cell_volume"]).max() < 1e-12
+    assert _nb_sets(G, range(n)) == _nb_sets(O, range(n))
+
+
+@pytest.mark.parametrize("centred", [False, True])
+def test_voronoi_equal_distances(centred):
+    """Lattices: every candidate's distance is shared by others (ties by index), lists that fill up are cut between
+    equal distances, and every cut passes through vertices."""
+    say(f"case: voronoi lattice, centred {centred}")
+    k = (np.arange(9) + 0.5) / 9
+    s = np.stack(np.meshgrid(k, k, k, indexing="ij"), -1).reshape(-1, 3)
+    if centred:
+        c = np.arange(1, 9) / 9
+        s = np.concatenate([s, np.stack(np.meshgrid(c, c, c, indexing="ij"), -1).reshape(-1, 3)])
+    with em.Mapper(device=0) as mp:
+        G = mp.voronoi(s, BOX)
+    O = oracle.voronoi(s, BOX)
+    assert (np.abs(G.cell_volume - O["cell_volume"]) / O["cell_volume"]).max() < 1e-12
+    assert G.cell_volume.sum() == pytest.approx(1.0, rel=1e-12)
