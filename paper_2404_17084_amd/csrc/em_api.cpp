@@ -560,8 +560,13 @@ int map_voronoi(map_ctx *h, int64_t n, const double *sites, int mem_kind, const 
         EM_HIP(hipEventSynchronize(C->ev[1]));
         float ms = 0.f;
         EM_HIP(hipEventElapsedTime(&ms, C->ev[0], C->ev[1]));
-        // the per-cell records of the build (about 5.9 kB per cell) are not kept
-        C->ws.drop(S_VOR8);
+        // the per-cell records of the build (2.4 kB per cell) stay for the next call up to 1 GiB in all (a
+        // program rebuilds its grid every step, and allocating them anew cost more than the build); those of
+        // larger grids are given back
+        if (C->ws.held(S_VOR8) + C->ws.held(S_VOR15) > (size_t(1) << 30)) {
+            C->ws.drop(S_VOR8);
+            C->ws.drop(S_VOR15);
+        }
         for (int d = 0; d < 6; d++) C->vor_box[d] = box[d];
         out->n_cells = m;
         out->n_faces = V.n_faces;

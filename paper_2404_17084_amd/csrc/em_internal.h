@@ -55,6 +55,8 @@ public:
     void release();
     // frees one slot's buffer (not in arena mode, where it stays reserved)
     void drop(int slot);
+    // bytes of one slot's buffer
+    size_t held(int slot) const { return bufs_[slot].cap; }
     void use_arena(void *base, size_t bytes);
     // Stream-ordered mode: buffers come from the device's memory pool with
     // hipMallocAsync / hipFreeAsync on stream s (no device-wide
@@ -95,7 +97,7 @@ enum Slot : int {
     S_PSEUDO8, S_PSEUDO9, S_PSEUDO10, S_PSEUDO11, S_PSEUDO12, S_PSEUDO13, S_PSEUDO14, S_PSEUDO15,
     S_ADAPT0, S_ADAPT1, S_ADAPT2, S_ADAPT3, S_ADAPT4, S_ADAPT5, S_ADAPT6, S_ADAPT7,
     S_VOR0, S_VOR1, S_VOR2, S_VOR3, S_VOR4, S_VOR5, S_VOR6, S_VOR7, S_VOR8, S_VOR9, S_VOR10, S_VOR11, S_VOR12,
-    S_VOR13, S_VOR14,
+    S_VOR13, S_VOR14, S_VOR15,
     S_ERR, S_CHECK,
     S_NUM_SLOTS
 };

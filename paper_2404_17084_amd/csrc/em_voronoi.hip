@@ -487,9 +487,10 @@ __device__ bool wclip(WCell &W, int &np, int &nt, int &status, const vor::Plane 
 __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const double *__restrict__ ps,
                                                         const int32_t *__restrict__ orig,
                                                         const double *__restrict__ bx, int64_t NL, VBox B,
-                                                        vor::Cell *__restrict__ cells, int64_t *__restrict__ nfc,
-                                                        int64_t *__restrict__ nsc, int64_t *__restrict__ nvc,
-                                                        unsigned *flags)
+                                                        char *__restrict__ recs, char *__restrict__ bigs,
+                                                        unsigned n_big, unsigned *__restrict__ big_used,
+                                                        int64_t *__restrict__ nfc, int64_t *__restrict__ nsc,
+                                                        int64_t *__restrict__ nvc, unsigned *flags)
 {
     __shared__ WCell cellbuf[2];
     const int lane = threadIdx.x & 63;
@@ -677,26 +678,11 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
         lds_sync_wave();  // the candidate list is rewritten by the next pass
     }
     if (!done && status == vor::ST_OK) status = vor::ST_PASSES;
-    // the record for the extraction pass, and the counts
-    vor::Cell &G = cells[r];
-    if (lane == 0) {
-        G.np = np;
-        G.nt = nt;
-        G.status = status;
-    }
-    if (lane < np) {
-        G.pl[lane] = W.pl[lane];
-        G.src[lane] = W.src[lane];
-    }
-    for (int t = lane; t < nt; t += 64) {
-        G.tri[t] = W.tri[t];
-        G.vx[t] = W.vx[t];
-        G.vy[t] = W.vy[t];
-        G.vz[t] = W.vz[t];
-    }
+    // the counts, and the record for the extraction pass: the planes that are left (a plane cut away by later ones
+    // has no vertex), in order, and the triangles in terms of them
     int64_t f = 0, sl = 0;
+    int c = 0;
     if (status == vor::ST_OK) {
-        int c = 0;
         if (lane < np)
             for (int t = 0; t < nt; t++) {
                 const uint32_t q = W.tri[t];
@@ -710,6 +696,31 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
         sl = cs;
     } else if (lane == 0) {
         atomicOr(flags, 4u);
+    }
+    const uint64_t used = __ballot(c > 0);
+    const int nu = __popcll(used);
+    char *base = recs + r * (int64_t)vor::kRecBytes;
+    int big = -1;
+    if (status == vor::ST_OK && vor::rec_bytes(nu, nt) > vor::kRecBytes) {
+        if (lane == 0) big = (int)atomicAdd(big_used, 1u);
+        big = __builtin_amdgcn_readfirstlane(big);
+    }
+    if (lane == 0) *reinterpret_cast<vor::RecHead *>(base) = vor::RecHead{nu, nt, status, big};
+    if (status == vor::ST_OK && (big < 0 || (unsigned)big < n_big)) {  // (too many big cells: the host builds again)
+        const vor::Rec G = vor::rec_at(big < 0 ? base : bigs + big * (int64_t)vor::kBigRecBytes, nu, nt);
+        if (c > 0) {
+            const int k = lanes_below(used);
+            G.pl[k] = W.pl[lane];
+            G.src[k] = W.src[lane];
+        }
+        auto now = [&](int p) { return __popcll(used & ((uint64_t(1) << p) - 1)); };
+        for (int t = lane; t < nt; t += 64) {
+            const uint32_t q = W.tri[t];
+            G.tri[t] = vor::tri_pack(now(vor::tri_a(q)), now(vor::tri_b(q)), now(vor::tri_c(q)));
+            G.vx[t] = W.vx[t];
+            G.vy[t] = W.vy[t];
+            G.vz[t] = W.vz[t];
+        }
     }
     if (lane == 0) {
         const int64_t i = orig[r];
@@ -748,7 +759,7 @@ static_assert(vor::kMaxTris < 255 && vor::kMaxPlanes <= 64, "triangle ids in byt
 
 __global__ void __launch_bounds__(128) k_vor_extract(int64_t n, const double *__restrict__ s,
                                                      const int64_t *__restrict__ rank,
-                                                     const vor::Cell *__restrict__ cells,
+                                                     char *__restrict__ recs, char *__restrict__ bigs,
                                                      const int64_t *__restrict__ foff, const int64_t *__restrict__ soff,
                                                      const int64_t *__restrict__ voff, VorOut O, unsigned *flags)
 {
@@ -757,13 +768,15 @@ __global__ void __launch_bounds__(128) k_vor_extract(int64_t n, const double *__
     XCell &X = xbuf[threadIdx.x >> 6];
     const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     if (i >= n) return;  // whole wavefronts
-    const vor::Cell &C = cells[rank[i]];
+    char *base = recs + rank[i] * (int64_t)vor::kRecBytes;
+    const vor::RecHead H = *reinterpret_cast<const vor::RecHead *>(base);
     if (lane == 0) {
         O.cfo[i] = foff[i];
         if (i == n - 1) O.cfo[n] = foff[n];
     }
-    if (C.status != vor::ST_OK) return;
-    const int np = C.np, nt = C.nt;
+    if (H.status != vor::ST_OK) return;
+    const int np = H.np, nt = H.nt;
+    const vor::Rec C = vor::rec_at(H.big < 0 ? base : bigs + H.big * (int64_t)vor::kBigRecBytes, np, nt);
     const double sx = s[3 * i], sy = s[3 * i + 1], sz = s[3 * i + 2];
     const int64_t vbase = voff[i], fbase = foff[i], sbase = soff[i];
     uint32_t *et32 = reinterpret_cast<uint32_t *>(X.et);
@@ -1116,25 +1129,38 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
     const int64_t NL = T.NL;
     unsigned *flags = ws.get<unsigned>(S_FLAGS, 4);
     unsigned hf = 0;
-    vor::Cell *cells = reinterpret_cast<vor::Cell *>(ws.get(S_VOR8, sizeof(vor::Cell) * (size_t)n));
     int64_t *nfc = ws.get<int64_t>(S_VOR9, (size_t)n + 1);
     int64_t *nsc = ws.get<int64_t>(S_VOR10, (size_t)n + 1);
     int64_t *nvc = ws.get<int64_t>(S_VOR11, (size_t)n + 1);
-    hipLaunchKernelGGL(k_vor_build_wave, dim3(vgrid(64 * n, 128)), dim3(128), 0, s, n, (const double *)ps,
-                       (const int32_t *)orig, (const double *)bx, NL, B, cells, nfc, nsc, nvc, flags);
-    EM_HIP(hipGetLastError());
     int64_t *foff = ws.get<int64_t>(S_VOR12, (size_t)n + 1);
     int64_t *soff = ws.get<int64_t>(S_VOR13, (size_t)n + 1);
     int64_t *voff = ws.get<int64_t>(S_VOR14, (size_t)n + 1);
-    scan_counts(ws, nfc, foff, n, s);
-    scan_counts(ws, nsc, soff, n, s);
-    scan_counts(ws, nvc, voff, n, s);
+    unsigned *big_used = flags + 1;
+    // the cells' records, and big ones for one cell in 16; a grid with more big cells is built again with as
+    // many as it asked for
+    char *recs = static_cast<char *>(ws.get(S_VOR8, vor::kRecBytes * (size_t)n)), *bigs = nullptr;
+    unsigned n_big = (unsigned)(n / 16 + 16);
     int64_t tot[3] = {0, 0, 0};
-    EM_HIP(hipMemcpyAsync(&tot[0], foff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&tot[1], soff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&tot[2], voff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&hf, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    for (;;) {
+        bigs = static_cast<char *>(ws.get(S_VOR15, vor::kBigRecBytes * (size_t)n_big));
+        hipLaunchKernelGGL(k_vor_build_wave, dim3(vgrid(64 * n, 128)), dim3(128), 0, s, n, (const double *)ps,
+                           (const int32_t *)orig, (const double *)bx, NL, B, recs, bigs, n_big, big_used, nfc, nsc,
+                           nvc, flags);
+        EM_HIP(hipGetLastError());
+        scan_counts(ws, nfc, foff, n, s);
+        scan_counts(ws, nsc, soff, n, s);
+        scan_counts(ws, nvc, voff, n, s);
+        unsigned h2[2] = {0, 0};
+        EM_HIP(hipMemcpyAsync(&tot[0], foff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        EM_HIP(hipMemcpyAsync(&tot[1], soff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        EM_HIP(hipMemcpyAsync(&tot[2], voff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        EM_HIP(hipMemcpyAsync(h2, flags, sizeof(h2), hipMemcpyDeviceToHost, s));
+        EM_HIP(hipStreamSynchronize(s));
+        hf = h2[0];
+        if (h2[1] <= n_big) break;
+        n_big = h2[1];
+        fill_zero_bytes(flags, sizeof(unsigned) * 4, s);
+    }
     EM_CHECK(!(hf & 4u), MAP_EDEVICE,
              "a Voronoi cell needs more than 64 faces or 128 vertices (or its neighbour search did not settle)");
     EM_CHECK(tot[2] < (int64_t)INT32_MAX, MAP_EINVAL, "too many Voronoi vertices for 32-bit vertex ids");
@@ -1151,7 +1177,7 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
     O.fv = dev_alloc(V.fv, V.cap_fv, (size_t)tot[1]);
     O.verts = dev_alloc(V.verts, V.cap_verts, (size_t)(3 * tot[2]));
     hipLaunchKernelGGL(k_vor_extract, dim3(vgrid(64 * n, 128)), dim3(128), 0, s, n, sites, (const int64_t *)rank,
-                       (const vor::Cell *)cells,
+                       recs, bigs,
                        (const int64_t *)foff, (const int64_t *)soff, (const int64_t *)voff, O, flags);
     EM_HIP(hipGetLastError());
     EM_HIP(hipMemcpyAsync(&hf, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));

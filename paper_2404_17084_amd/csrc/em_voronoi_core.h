@@ -39,14 +39,39 @@ struct Plane {
     double nx, ny, nz, d;
 };
 
-// A built cell as the extraction pass reads it (device memory, one per site).
-struct Cell {
-    Plane pl[kMaxPlanes];
-    int32_t src[kMaxPlanes];  // site (input index) across the plane, or -1 - wall
-    uint32_t tri[kMaxTris];   // a | b << 8 | c << 16
-    double vx[kMaxTris], vy[kMaxTris], vz[kMaxTris];
-    int32_t np, nt, status, pad;
+// A built cell as the extraction pass reads it (device memory): a header, np
+// planes, nt vertices (x, then y, then z), the np sites across the planes (input
+// index, or -1 - wall) and the nt triangles (a | b << 8 | c << 16).  Every cell
+// has kRecBytes (16 planes and 27 vertices, the usual cell, take 1,350 bytes; 23
+// and 42 fit); larger ones have a full-size record among the big ones.
+struct RecHead {
+    int32_t np, nt, status, big;  // big: index among the big records, or -1 (only np, nt and status count then)
 };
+constexpr size_t kRecBytes = 2048;
+__host__ __device__ constexpr size_t rec_bytes(int np, int nt)
+{
+    return sizeof(RecHead) + (size_t)np * (sizeof(Plane) + 4) + (size_t)nt * (3 * sizeof(double) + 4);
+}
+constexpr size_t kBigRecBytes = (rec_bytes(kMaxPlanes, kMaxTris) + 255) / 256 * 256;
+
+struct Rec {
+    Plane *pl;
+    double *vx, *vy, *vz;
+    int32_t *src;
+    uint32_t *tri;
+};
+
+__host__ __device__ inline Rec rec_at(char *base, int np, int nt)
+{
+    Rec R;
+    R.pl = reinterpret_cast<Plane *>(base + sizeof(RecHead));
+    R.vx = reinterpret_cast<double *>(R.pl + np);
+    R.vy = R.vx + nt;
+    R.vz = R.vy + nt;
+    R.src = reinterpret_cast<int32_t *>(R.vz + nt);
+    R.tri = reinterpret_cast<uint32_t *>(R.src + np);
+    return R;
+}
 
 __host__ __device__ inline uint32_t tri_pack(int a, int b, int c)
 {

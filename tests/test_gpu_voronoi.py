@@ -235,3 +235,20 @@ def test_voronoi_equal_distances(centred):
     O = oracle.voronoi(s, BOX)
     assert (np.abs(G.cell_volume - O["cell_volume"]) / O["cell_volume"]).max() < 1e-12
     assert G.cell_volume.sum() == pytest.approx(1.0, rel=1e-12)
+
+
+@pytest.mark.parametrize("per_line", [8, 30])
+def test_voronoi_many_faced_cells(per_line):
+    """Sites on two skew lines: every cell of one line meets every cell of the other (35 faces at 30 per line), more
+    than a usual cell's record holds and than the first build has large records for."""
+    say(f"case: voronoi two skew lines of {per_line}")
+    t = np.linspace(0.3, 0.7, per_line)
+    a = np.stack([t, np.full_like(t, 0.5), np.full_like(t, 0.4)], 1)
+    b = np.stack([np.full_like(t, 0.5), t, np.full_like(t, 0.6)], 1)
+    s = np.concatenate([a, b]) + 1e-5 * np.random.default_rng(1).standard_normal((2 * per_line, 3))
+    O = oracle.voronoi(s, BOX)
+    with em.Mapper(device=0) as mp:
+        for _ in range(2):  # the second call finds the first one's buffers
+            G = mp.voronoi(s, BOX)
+            assert (np.abs(G.cell_volume - O["cell_volume"]) / O["cell_volume"]).max() < 1e-10
+            assert _nb_sets(G, range(2 * per_line)) == _nb_sets(O, range(2 * per_line))
