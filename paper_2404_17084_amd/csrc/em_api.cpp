@@ -44,7 +44,7 @@ Ctx::~Ctx()
     ws.release();
     free_voronoi(vor);
     if (table.d64) (void)hipFree(table.d64);
-    if (table.d32) (void)hipFree(table.d32);
+    if (table.d4) (void)hipFree(table.d4);
     for (auto &e : ev)
         if (e) (void)hipEventDestroy(e);
     if (stream) (void)hipStreamDestroy(stream);
@@ -325,12 +325,12 @@ void ensure_table(Ctx &C, hipStream_t s)
     if (C.table.built) return;
     const size_t nodes = (size_t)C.table.n[0] * C.table.n[1] * C.table.n[2];
     if (C.table.d64) EM_HIP(hipFree(C.table.d64));
-    if (C.table.d32) EM_HIP(hipFree(C.table.d32));
+    if (C.table.d4) EM_HIP(hipFree(C.table.d4));
     C.table.d64 = nullptr;
-    C.table.d32 = nullptr;
+    C.table.d4 = nullptr;
     EM_HIP(hipMalloc(&C.table.d64, sizeof(double) * nodes));
-    EM_HIP(hipMalloc(&C.table.d32, sizeof(float) * nodes));
-    launch_table_build(C.table.n[0], C.table.n[1], C.table.n[2], C.table.d64, C.table.d32, s);
+    EM_HIP(hipMalloc(&C.table.d4, sizeof(float4) * nodes));
+    launch_table_build(C.table.n[0], C.table.n[1], C.table.n[2], C.table.d64, C.table.d4, s);
     EM_HIP(hipStreamSynchronize(s));
     C.table.built = true;
 }
@@ -348,7 +348,7 @@ void run_mapping(Ctx &C, Workspace &ws, const map_particles_in *p, const map_cel
     if (precision == MAP_TABLE) {
         ensure_table(C, s);
         if (timed) EM_HIP(hipEventRecord(C.ev[2], s));
-        launch_integrate_table(js.in, js.edges, js.ps, C.table.d32, C.table.n[0], C.table.n[1], C.table.n[2], js.f,
+        launch_integrate_table(js.in, js.edges, js.ps, C.table.d4, C.table.n[0], C.table.n[1], C.table.n[2], js.f,
                                js.counters, s);
     } else {
         const IntegrateTune tune = pick_tune(C, precision, js.ps.n_pairs);

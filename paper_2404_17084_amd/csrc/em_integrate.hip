@@ -1395,7 +1395,7 @@ __global__ void k_fixup_apply(int64_t n_fix, const uint64_t *__restrict__ keys, 
 // pi/2 - 1e-12), from the FP64 closed form above:
 //     I = Omega / (4 pi) - (1/pi) [pi (Q - phi H)](0 .. l),   l = R0 tan(phi),
 // with the triangle's solid angle Omega = atan2(l R0 (R0^2 + l^2), (S + r0)(R0^2 S + r0 l^2)).
-__global__ void k_table_build(int n0, int n1, int n2, double *__restrict__ tab64, float *__restrict__ tab32)
+__global__ void k_table_build(int n0, int n1, int n2, double *__restrict__ tab64)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t total = (int64_t)n0 * n1 * n2;
@@ -1416,7 +1416,18 @@ __global__ void k_table_build(int n0, int n1, int n2, double *__restrict__ tab64
         I = om * (0.25 * kInvPi) - e * kInvPi;
     }
     tab64[q] = I;
-    tab32[q] = (float)I;
+}
+
+// The node values as the reads take them (em_table.hip).
+__global__ void k_table_pack(int n0, int n1, int n2, const double *__restrict__ tab64, float4 *__restrict__ tab4)
+{
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t dj = n2, di = (int64_t)n1 * n2;
+    if (q >= (int64_t)n0 * di) return;
+    const int j = (int)((q / n2) % n1), i = (int)(q / di);
+    const bool in = i + 1 < n0 && j + 1 < n1;
+    tab4[q] = in ? make_float4((float)tab64[q], (float)tab64[q + dj], (float)tab64[q + di], (float)tab64[q + di + dj])
+                 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
 }  // namespace
@@ -1513,11 +1524,13 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
     if (threadIdx.x == 0 && blockIdx.y == 0) atomicAdd(counters + C_FP64_PAIRS, (unsigned long long)np);
 }
 
-void launch_table_build(int n0, int n1, int n2, double *tab64, float *tab32, hipStream_t s)
+void launch_table_build(int n0, int n1, int n2, double *tab64, float4 *tab4, hipStream_t s)
 {
     const int64_t total = (int64_t)n0 * n1 * n2;
-    hipLaunchKernelGGL(k_table_build, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, n0, n1, n2, tab64,
-                       tab32);
+    const dim3 g((unsigned)((total + 255) / 256));
+    hipLaunchKernelGGL(k_table_build, g, dim3(256), 0, s, n0, n1, n2, tab64);
+    EM_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_table_pack, g, dim3(256), 0, s, n0, n1, n2, (const double *)tab64, tab4);
     EM_HIP(hipGetLastError());
 }
 

@@ -116,7 +116,7 @@ struct CellFast {
     unsigned dmin_[64];         // least squared distance of each tested particle (bits of a float >= 0)
     uint32_t wait_[kExactQueue], part_[kExactQueue];  // places in the candidate list, particles
     uint16_t task_[kExactQueue];                      // lane << 8 | wall
-    int so_[kExactMaxFaces + 1];
+    uint16_t so_[66];
 };
 
 __device__ __noinline__ bool cell_meets(double px, double py, double pz, double r2, int64_t cell,
@@ -355,8 +355,9 @@ __global__ void __launch_bounds__(256) k_candidates(
 // become tasks (lane, wall) that the lanes share, and D is the least of all.
 // D decides when |D - r^2| exceeds a bound on its rounding, tol = 1e-6 (r + 2
 // rc)^2 (every vector involved is shorter than r + 2 rc, FP32 rounding of D is
-// below 10 u (r + 2 rc)^2); (4) D within tol of r^2, and cells too large for the
-// staging area, run the exact test from the global tables.
+// below 10 u (r + 2 rc)^2); (4) D within tol of r^2, and cells of more than 64
+// walls, run the exact test.  Cells too large for the staging area are read
+// from the global tables throughout.
 //
 // Bound by latency: 70 % of the wavefronts' time is waits (the cell's records,
 // gathers from LDS), vector instructions at 0.09 per SIMD and clock with half
@@ -364,24 +365,37 @@ __global__ void __launch_bounds__(256) k_candidates(
 // each, staged one after the other, a third of the lanes each), every lane
 // looping over all walls it sees, and the candidates gathered into lists of
 // their own first, 262,144 clumpy particles took 2.22 ms here and 0.37 ms around
-// it; 1.84 and 0.13 ms now.
+// it; 1.73 and 0.13 ms now.
 constexpr uint32_t kNoCand = 0xffffffffu;
 
-// squared FP32 distance from q (about the cell centre) to wall j of the staged cell: d^2 (its plane's distance) when
-// q's foot point lies inside the polygon
-__device__ __forceinline__ float wall_dist2(const CellFast &L, int j, float qx, float qy, float qz, float d2,
+// One slot of the tested cell as the screened test takes it: edge start (about
+// the cell centre) and length, edge direction, in-wall normal.  From the staged
+// cell, or for a cell too large for it from its records.
+struct SlotF {
+    float ax, ay, az, len, ex, ey, ez, mx, my, mz;
+};
+
+__device__ __forceinline__ SlotF slot_of(const EdgeRec &E, double gx, double gy, double gz)
+{
+    return SlotF{(float)(E.vx - gx), (float)(E.vy - gy), (float)(E.vz - gz), (float)E.L, (float)E.ex, (float)E.ey,
+                 (float)E.ez, (float)E.mx, (float)E.my, (float)E.mz};
+}
+
+// squared FP32 distance from q (about the cell centre) to wall j of the cell: d2 (its plane's distance) when q's foot
+// point lies inside the polygon
+template <class Slots>
+__device__ __forceinline__ float wall_dist2(const Slots &slot, int k0, int k1, float qx, float qy, float qz, float d2,
                                             bool &in_poly)
 {
     in_poly = true;
     float D = INFINITY;
-    for (int k = L.so_[j]; k < L.so_[j + 1]; k++) {
-        const float4 A = L.a_[k], B = L.b_[k];
-        const float2 C = L.c_[k];
-        const float wx = qx - A.x, wy = qy - A.y, wz = qz - A.z;
-        in_poly = in_poly && fmaf(B.w, wx, fmaf(C.x, wy, C.y * wz)) >= 0.0f;
-        const float sp = fmaf(B.x, wx, fmaf(B.y, wy, B.z * wz));
-        const float tt = fminf(fmaxf(sp, 0.0f), A.w);
-        const float ux = fmaf(-tt, B.x, wx), uy = fmaf(-tt, B.y, wy), uz = fmaf(-tt, B.z, wz);
+    for (int k = k0; k < k1; k++) {
+        const SlotF E = slot(k);
+        const float wx = qx - E.ax, wy = qy - E.ay, wz = qz - E.az;
+        in_poly = in_poly && fmaf(E.mx, wx, fmaf(E.my, wy, E.mz * wz)) >= 0.0f;
+        const float sp = fmaf(E.ex, wx, fmaf(E.ey, wy, E.ez * wz));
+        const float tt = fminf(fmaxf(sp, 0.0f), E.len);
+        const float ux = fmaf(-tt, E.ex, wx), uy = fmaf(-tt, E.ey, wy), uz = fmaf(-tt, E.ez, wz);
         D = fminf(D, fmaf(ux, ux, fmaf(uy, uy, uz * uz)));
     }
     return in_poly ? d2 : D;
@@ -410,35 +424,50 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
         uint32_t *mine = buf + (SECOND ? ovf_off[c] : c * (int64_t)K);
         const int64_t j0 = cfo[c], nf = cfo[c + 1] - j0;
         const int64_t s0 = fvo[j0], ns = fvo[j0 + nf] - s0;
+        const bool screen = nf <= 64 && ns < 65536;  // (a bit per wall, 16-bit slot offsets)
         const bool fits = nf <= kExactMaxFaces && ns <= kExactMaxSlots;
         const double gx = centre[3 * c], gy = centre[3 * c + 1], gz = centre[3 * c + 2], rc2 = 2.0 * radii[2 * c + 1];
         int64_t pairs = 0;
         bool staged = false;
         int waiting = 0;
         auto test = [&](int n) {  // the first n (<= 64) of the waiting candidates
-            if (fits && !staged) {
-                for (int q = lane; q < 4 * (int)nf; q += 64) L.pl_[q >> 2][q & 3] = plane[4 * j0 + q];
-                for (int q = lane; q <= (int)nf; q += 64) L.so_[q] = (int)(fvo[j0 + q] - s0);
-                for (int q = lane; q < (int)ns; q += 64) {
-                    const EdgeRec &E = edges[s0 + q];
-                    L.a_[q] = make_float4((float)(E.vx - gx), (float)(E.vy - gy), (float)(E.vz - gz), (float)E.L);
-                    L.b_[q] = make_float4((float)E.ex, (float)E.ey, (float)E.ez, (float)E.mx);
-                    L.c_[q] = make_float2((float)E.my, (float)E.mz);
+            if (screen && !staged) {
+                for (int q = lane; q <= (int)nf; q += 64) L.so_[q] = (uint16_t)(fvo[j0 + q] - s0);
+                if (fits) {
+                    for (int q = lane; q < 4 * (int)nf; q += 64) L.pl_[q >> 2][q & 3] = plane[4 * j0 + q];
+                    for (int q = lane; q < (int)ns; q += 64) {
+                        const SlotF E = slot_of(edges[s0 + q], gx, gy, gz);
+                        L.a_[q] = make_float4(E.ax, E.ay, E.az, E.len);
+                        L.b_[q] = make_float4(E.ex, E.ey, E.ez, E.mx);
+                        L.c_[q] = make_float2(E.my, E.mz);
+                    }
                 }
                 staged = true;
             }
+            auto pl = [&](int j, int d) { return fits ? L.pl_[j][d] : plane[4 * (j0 + j) + d]; };
+            auto wall = [&](int j, float qx, float qy, float qz, float d2, bool &in_poly) {
+                auto lds = [&](int k) {
+                    const float4 A = L.a_[k], B = L.b_[k];
+                    const float2 C = L.c_[k];
+                    return SlotF{A.x, A.y, A.z, A.w, B.x, B.y, B.z, B.w, C.x, C.y};
+                };
+                auto rec = [&](int k) { return slot_of(edges[s0 + k], gx, gy, gz); };
+                const int k0 = L.so_[j], k1 = L.so_[j + 1];
+                return fits ? wall_dist2(lds, k0, k1, qx, qy, qz, d2, in_poly)
+                            : wall_dist2(rec, k0, k1, qx, qy, qz, d2, in_poly);
+            };
             lds_sync_wave();
             const bool valid = lane < n;
             const int64_t a = valid ? L.part_[lane] : 0;
             const double px = xyz[3 * a], py = xyz[3 * a + 1], pz = xyz[3 * a + 2], r = 2.0 * h[a], r2 = r * r;
-            bool hit = false, exact = valid && !fits;
-            if (fits) {
+            bool hit = false, exact = valid && !screen;
+            if (screen) {
                 bool inside = true;
                 double far = 0.0;
                 int jf = 0;
                 unsigned long long seen = 0;  // walls seen from outside
                 for (int j = 0; j < (int)nf; j++) {
-                    const double d = L.pl_[j][3] - (L.pl_[j][0] * px + L.pl_[j][1] * py + L.pl_[j][2] * pz);
+                    const double d = pl(j, 3) - (pl(j, 0) * px + pl(j, 1) * py + pl(j, 2) * pz);
                     if (d < 0.0) {
                         inside = false;
                         seen |= 1ull << j;
@@ -455,7 +484,7 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
                 float D = INFINITY;
                 if (open) {
                     bool in_poly;
-                    D = wall_dist2(L, jf, qx, qy, qz, (float)(far * far), in_poly);
+                    D = wall(jf, qx, qy, qz, (float)(far * far), in_poly);
                     seen &= in_poly ? 0ull : ~(1ull << jf);
                     if ((double)D < r2 - tol) {
                         hit = true;
@@ -474,10 +503,9 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
                         if (lane < m) {
                             const int o = L.task_[at + lane] >> 8, j = L.task_[at + lane] & 255;
                             const float x = L.p_[o][0], y = L.p_[o][1], z = L.p_[o][2];
-                            const double d = L.pl_[j][3] - (L.pl_[j][0] * (gx + x) + L.pl_[j][1] * (gy + y) +
-                                                            L.pl_[j][2] * (gz + z));
+                            const double d = pl(j, 3) - (pl(j, 0) * (gx + x) + pl(j, 1) * (gy + y) + pl(j, 2) * (gz + z));
                             bool in_poly;
-                            const float Dj = wall_dist2(L, j, x, y, z, (float)(d * d), in_poly);
+                            const float Dj = wall(j, x, y, z, (float)(d * d), in_poly);
                             atomicMin(&L.dmin_[o], __float_as_uint(Dj));
                         }
                         lds_sync_wave();

@@ -15,21 +15,28 @@
 // is one solid angle (FP32, one atan2) less a trilinear read of the table;
 // geometry is FP64, sums are FP64.
 //
-// One thread per pair, cell-major pair order (neighbouring threads share a
-// cell, so wall and edge records are read once per wavefront from cache); the
-// table stays in L2 (1 MiB at 64^3).
+// One lane per pair, cell-major pair order (neighbouring lanes share a cell, so
+// wall and edge records are read once per wavefront from cache); the table
+// stays in L2.  The lanes of a wavefront walk their cells' wall
+// slots with one counter, so that an edge's two table reads run once for all
+// lanes that have an edge.  Bound by the gathers: a read with its eight nodes in
+// four places fetched four cache lines per lane, 40 TB/s from L2 on 2.8e6
+// pairs, and took 6.5 ms however few instructions went with it; with the nodes
+// of a read in 32 neighbouring bytes (a table of four times the size, 4 MiB at
+// 64^3) it is 2.3 ms.
 #include <cmath>
 
 #include "em_boundary.h"
 #include "em_internal.h"
 #include "em_fmath.h"
+#include "em_wave.h"
 
 namespace em {
 
 namespace {
 
 struct TableView {
-    const float *__restrict__ t;
+    const float4 *__restrict__ t;  // per node (i, j, k), i < n0 - 1, j < n1 - 1: the values at (i, j), (i, j + 1), (i + 1, j), (i + 1, j + 1)
     int n0, n1, n2;
     float s0, s1, s2;  // grid coordinates per unit of r0, R0, phi
 };
@@ -49,36 +56,29 @@ __device__ __forceinline__ float table_I(const TableView &T, float r0, float R0,
     grid_cell(r0 * T.s0, T.n0, i, a);
     grid_cell(R0 * T.s1, T.n1, j, b);
     grid_cell(phi * T.s2, T.n2, k, c);
-    const float *p = T.t + ((int64_t)i * T.n1 + j) * T.n2 + k;
-    const int64_t dj = T.n2, di = (int64_t)T.n1 * T.n2;
-    const float v00 = p[0] + c * (p[1] - p[0]);
-    const float v01 = p[dj] + c * (p[dj + 1] - p[dj]);
-    const float v10 = p[di] + c * (p[di + 1] - p[di]);
-    const float v11 = p[di + dj] + c * (p[di + dj + 1] - p[di + dj]);
+    const float4 *p = T.t + ((int64_t)i * T.n1 + j) * T.n2 + k;
+    const float4 A = p[0], B = p[1];
+    const float v00 = A.x + c * (B.x - A.x);
+    const float v01 = A.y + c * (B.y - A.y);
+    const float v10 = A.z + c * (B.z - A.z);
+    const float v11 = A.w + c * (B.w - A.w);
     const float v0 = v00 + b * (v01 - v00);
     const float v1 = v10 + b * (v11 - v10);
     return v0 + a * (v1 - v0);
 }
 
-// D of the right triangle [0, l] (l >= 0) at wall distance r0 < 2
-__device__ __forceinline__ float table_D(const TableView &T, float r0, float R0, float l)
+// D of the right triangle [0, |l|] at wall distance r0 < 2, odd in l
+__device__ __forceinline__ float table_Dt(const TableView &T, float r0, float R0, float ls)
 {
-    if (!(l > 0.0f)) return 0.0f;
+    const float l = fabsf(ls);
     const float phi = atan2_f32(l, R0);
-    float Rc = R0, lc = l;
-    if (R0 > 2.0f) {  // same angle at R0 = 2
-        Rc = 2.0f;
-        lc = l * (2.0f * rcp_f32(R0));
-    }
+    const bool far = R0 > 2.0f;  // same angle at R0 = 2
+    const float Rc = far ? 2.0f : R0, lc = far ? l * (2.0f * rcp_f32(R0)) : l;
     const float R2 = Rc * Rc, l2 = lc * lc;
-    const float S = sqrt_f32(r0 * r0 + R2 + l2);
-    const float om = atan2_f32(lc * Rc * (R2 + l2), (S + r0) * (R2 * S + r0 * l2));
-    return om * 0.0795774715459477f - table_I(T, r0, Rc, phi);
-}
-
-__device__ __forceinline__ float table_Dt(const TableView &T, float r0, float R0, float l)
-{
-    return l < 0.0f ? -table_D(T, r0, R0, -l) : table_D(T, r0, R0, l);
+    const float S = sqrt_f32(fmaf(lc, lc, fmaf(Rc, Rc, r0 * r0)));
+    const float om = atan2_f32(lc * Rc * fmaf(Rc, Rc, l2), (S + r0) * fmaf(l2, r0, R2 * S));
+    const float D = fmaf(om, 0.0795774715459477f, -table_I(T, r0, Rc, phi));
+    return l > 0.0f ? (ls < 0.0f ? -D : D) : 0.0f;
 }
 
 __global__ void __launch_bounds__(256) k_integrate_table(int64_t np, const uint32_t *__restrict__ pair_p,
@@ -90,32 +90,55 @@ __global__ void __launch_bounds__(256) k_integrate_table(int64_t np, const uint3
                                                          const EdgeRec *__restrict__ edges, TableView T,
                                                          double *__restrict__ f, unsigned long long *counters)
 {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long n_faces = 0, n_edges = 0, n_terms = 0;
-    if (q < np) {
-        const int64_t a = pair_p[q], cell = pair_c[q];
-        const double px = xyz[3 * a], py = xyz[3 * a + 1], pz = xyz[3 * a + 2];
-        const double invh = 1.0 / h[a];
-        bool inside = true;
-        int n_on = 0;
-        double acc = 0.0;
-        for (int64_t j = cfo[cell]; j < cfo[cell + 1]; j++) {
-            const double nx = plane[4 * j], ny = plane[4 * j + 1], nz = plane[4 * j + 2], cj = plane[4 * j + 3];
+    const int64_t q = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    const bool active = q < np;
+    unsigned n_faces = 0, n_edges = 0, n_terms = 0;
+    double px = 0.0, py = 0.0, pz = 0.0, invh = 1.0;
+    int64_t cell = 0;
+    int32_t j = 0, s = 0, s_end = 0;
+    if (active) {
+        const int64_t a = pair_p[q];
+        cell = pair_c[q];
+        px = xyz[3 * a];
+        py = xyz[3 * a + 1];
+        pz = xyz[3 * a + 2];
+        invh = 1.0 / h[a];
+        j = (int32_t)cfo[cell] - 1;
+        s = (int32_t)fvo[cfo[cell]];
+        s_end = (int32_t)fvo[cfo[cell + 1]];
+    }
+    int32_t face_end = s;  // first slot past the current wall: the first step opens the cell's first wall
+    int n_steps = s_end - s;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n_steps = max(n_steps, __shfl_xor(n_steps, o, 64));
+    bool inside = true, in_j = true, face_ok = false;
+    int n_on = 0;
+    double acc = 0.0, face = 0.0;
+    float r0 = 0.0f;
+    for (int it = 0; it < n_steps; it++, s++) {
+        const bool valid = s < s_end;
+        if (valid && s == face_end) {  // the next wall
+            acc += in_j ? face : -face;
+            face = 0.0;
+            j++;
+            face_end = (int32_t)fvo[j + 1];
+            const double nx = plane[4 * (int64_t)j], ny = plane[4 * (int64_t)j + 1], nz = plane[4 * (int64_t)j + 2],
+                         cj = plane[4 * (int64_t)j + 3];
             const double d = cj - (nx * px + ny * py + nz * pz);
             n_faces++;
-            const bool in_j = d >= 0.0;
+            in_j = d >= 0.0;
             inside = inside && in_j;
             n_on += d == 0.0 ? 1 : 0;
             const double r0d = fabs(d) * invh;
-            if (!(r0d < 2.0)) continue;
-            const float r0 = (float)r0d;
-            double face = 0.0;
-            for (int64_t s = fvo[j]; s < fvo[j + 1]; s++) {
-                const EdgeRec E = edges[s];
-                const double wx = px - E.vx, wy = py - E.vy, wz = pz - E.vz;
-                const double rho = E.mx * wx + E.my * wy + E.mz * wz;
-                n_edges++;
-                if (rho == 0.0) continue;
+            face_ok = r0d < 2.0;
+            r0 = (float)r0d;
+        }
+        if (valid && face_ok) {
+            const EdgeRec E = edges[s];
+            const double wx = px - E.vx, wy = py - E.vy, wz = pz - E.vz;
+            const double rho = E.mx * wx + E.my * wy + E.mz * wz;
+            n_edges++;
+            if (rho != 0.0) {
                 const double la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
                 const double lb = la + E.L * invh;
                 const float R0 = (float)(fabs(rho) * invh);
@@ -123,25 +146,25 @@ __global__ void __launch_bounds__(256) k_integrate_table(int64_t np, const uint3
                 n_terms += 2;
                 face += rho > 0.0 ? (double)t : -(double)t;
             }
-            acc += in_j ? face : -face;
         }
+    }
+    if (active) {
+        acc += in_j ? face : -face;
         f[q] = winding_term(inside, n_on, px, py, pz, cell, cfo, fvo, plane, edges) - acc;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        n_faces += __shfl_xor(n_faces, o, 64);
-        n_edges += __shfl_xor(n_edges, o, 64);
-        n_terms += __shfl_xor(n_terms, o, 64);
-    }
+    unsigned long long v[3] = {n_faces, n_edges, n_terms};
+    for (int u = 0; u < 3; u++)
+        for (int o = 32; o > 0; o >>= 1) v[u] += __shfl_xor(v[u], o, 64);
     if ((threadIdx.x & 63) == 0) {
-        atomicAdd(counters + C_FACES, n_faces);
-        atomicAdd(counters + C_EDGES, n_edges);
-        atomicAdd(counters + C_EDGE_TERMS, n_terms);
+        atomicAdd(counters + C_FACES, v[0]);
+        atomicAdd(counters + C_EDGES, v[1]);
+        atomicAdd(counters + C_EDGE_TERMS, v[2]);
     }
 }
 
 }  // namespace
 
-void launch_integrate_table(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const float *tab, int n0,
+void launch_integrate_table(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const float4 *tab, int n0,
                             int n1, int n2, double *f, int64_t *counters, hipStream_t s)
 {
     const int64_t np = ps.n_pairs;
