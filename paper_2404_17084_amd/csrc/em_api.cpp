@@ -235,14 +235,13 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
         }
         if (js.precision == MAP_FP64 && n_fix != np) n_fix = 0;  // FP64: no edge terms are recomputed
         if (n_items > 0) {
-            uint32_t *iv = ws.get<uint32_t>(S_FIX_VAL2, (size_t)n_items);
             uint64_t *k2 = ws.get<uint64_t>(S_FIX_KEY2, (size_t)n_items);
-            uint32_t *v2 = reinterpret_cast<uint32_t *>(ws.get<uint64_t>(S_FIX_VALS, (size_t)n_items * 2));
-            fill_iota_u32(iv, n_items, s);
-            radix_sort_u64(ws, js.fix_items, iv, k2, v2, n_items, 64, s);
-            double *fv = reinterpret_cast<double *>(k2);
-            launch_fixup(in, js.edges, ps, js.fix_items, n_items, fv, js.counters, s);
-            launch_fixup_apply(js.fix_items, fv, n_items, f, s);
+            double *fv = ws.get<double>(S_FIX_VALS, (size_t)n_items);
+            int bits = 33;  // keys are pair << 32 | slot
+            while (bits < 64 && ((uint64_t)(np - 1) >> (bits - 32)) != 0) bits++;
+            const uint64_t *items = sort_keys_u64(ws, js.fix_items, k2, n_items, bits, s);
+            launch_fixup(in, js.edges, ps, items, n_items, fv, js.counters, s);
+            launch_fixup_apply(items, fv, n_items, f, s);
         }
     }
     if (js.ev_fix) EM_HIP(hipEventRecord(js.ev_fix, s));

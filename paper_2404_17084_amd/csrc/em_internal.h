@@ -183,6 +183,8 @@ void radix_sort_u32(Workspace &ws, uint32_t *keys, uint32_t *vals, uint32_t *key
 // The same for 64-bit keys.
 void radix_sort_u64(Workspace &ws, uint64_t *keys, uint32_t *vals, uint64_t *keys2, uint32_t *vals2, int64_t n,
                     int bits, hipStream_t s);
+// Sorts distinct 64-bit keys below 2^bits; returns where the result is (keys or keys2).
+const uint64_t *sort_keys_u64(Workspace &ws, uint64_t *keys, uint64_t *keys2, int64_t n, int bits, hipStream_t s);
 void fill_iota_u32(uint32_t *p, int64_t n, hipStream_t s);
 void fill_iota_i64(int64_t *p, int64_t n, hipStream_t s);
 // Waits until the work queued on stream s has finished.  On a thread that set
