@@ -640,7 +640,7 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
             if (bu == 0) take(0);
             else if (bu == 1) take(1);
             else take(2);
-            P.d = 0.5 * (P.nx * P.nx + P.ny * P.ny + P.nz * P.nz);
+            P.d = 0.5 * fma(P.nz, P.nz, fma(P.nx, P.nx, P.ny * P.ny));
             if (wclip(W, np, nt, status, P, orig[q], lane, T)) {
                 bounds_of(T, nt, lane, bd);
                 fresh = true;
@@ -705,7 +705,7 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
         if (lane == 0) big = (int)atomicAdd(big_used, 1u);
         big = __builtin_amdgcn_readfirstlane(big);
     }
-    if (lane == 0) *reinterpret_cast<vor::RecHead *>(base) = vor::RecHead{nu, nt, status, big};
+    if (lane == 0) *reinterpret_cast<vor::RecHead *>(base) = vor::RecHead{nu, nt, status, big, used};
     if (status == vor::ST_OK && (big < 0 || (unsigned)big < n_big)) {  // (too many big cells: the host builds again)
         const vor::Rec G = vor::rec_at(big < 0 ? base : bigs + big * (int64_t)vor::kBigRecBytes, nu, nt);
         if (c > 0) {
@@ -880,6 +880,14 @@ __global__ void __launch_bounds__(128) k_vor_extract(int64_t n, const double *__
         }
     }
     if (lane == 0) O.fvo[fbase + nf] = sbase + total;
+    // summed as plane by plane in the order of the cuts: the rounding does not depend on which planes were dropped
+    const int from = lanes_below(H.used);
+    const bool left = (H.used >> lane) & 1;
+    auto spread = [&](double v) {
+        const double w = __shfl(v, from, 64);
+        return left ? w : 0.0;
+    };
+    V = spread(V), M0 = spread(M0), M1 = spread(M1), M2 = spread(M2);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         V += __shfl_xor(V, o, 64);

@@ -45,7 +45,8 @@ struct Plane {
 // has kRecBytes (16 planes and 27 vertices, the usual cell, take 1,350 bytes; 23
 // and 42 fit); larger ones have a full-size record among the big ones.
 struct RecHead {
-    int32_t np, nt, status, big;  // big: index among the big records, or -1 (only np, nt and status count then)
+    int32_t np, nt, status, big;  // big: index among the big records, or -1 (the other fields hold all the same)
+    uint64_t used;                // the planes that are left, by the order in which they were cut
 };
 constexpr size_t kRecBytes = 2048;
 __host__ __device__ constexpr size_t rec_bytes(int np, int nt)
