@@ -25,6 +25,35 @@ __device__ __forceinline__ void lds_sync_wave()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Reduction of a double over the wavefront by data-parallel primitives (three
+// vector instructions a step, against two trips through the LDS crossbar),
+// wave-uniform; `identity` stands in for lanes without a partner.
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, double identity, Op op)
+{
+    const uint64_t id = (uint64_t)__double_as_longlong(identity);
+#define EM_DPP_STEP(ctrl, rows)                                                                               \
+    {                                                                                                         \
+        const uint64_t b = (uint64_t)__double_as_longlong(v);                                                 \
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)id, (int)(uint32_t)b, ctrl,   \
+                                                                  rows, 0xf, false);                          \
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(id >> 32), (int)(b >> 32), ctrl, rows, \
+                                                                  0xf, false);                                \
+        v = op(v, __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo)));                                \
+    }
+    EM_DPP_STEP(0xB1, 0xf)   // quad_perm 1,0,3,2
+    EM_DPP_STEP(0x4E, 0xf)   // quad_perm 2,3,0,1
+    EM_DPP_STEP(0x141, 0xf)  // row_half_mirror
+    EM_DPP_STEP(0x140, 0xf)  // row_mirror: every row of 16 has its result
+    EM_DPP_STEP(0x142, 0xa)  // row_bcast15 into rows 1 and 3
+    EM_DPP_STEP(0x143, 0xc)  // row_bcast31 into rows 2 and 3
+#undef EM_DPP_STEP
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+
 // Logical index of this workgroup in an XCD-aware order.  Workgroups are
 // dispatched round-robin over the 8 XCDs (workgroup b to XCD b mod 8); this
 // gives XCD x a contiguous run of logical indices (x * per + min(x, rem) ...,
