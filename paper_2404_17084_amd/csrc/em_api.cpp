@@ -182,6 +182,8 @@ void stage_pairs(Ctx &C, Workspace &ws, const map_particles_in *p, const map_cel
     const int64_t np = js.ps.n_pairs;
     js.f = ws.get<double>(S_F, (size_t)(np > 0 ? np : 1));
     js.err = precision == MAP_MIXED ? ws.get<float>(S_ERR, (size_t)(np > 0 ? np : 1)) : nullptr;
+    js.S = ws.get<double>(S_S, (size_t)(js.in.n > 0 ? js.in.n : 1));
+    fill_zero_bytes(js.S, sizeof(double) * js.in.n, s);
     js.tile_ctr = ws.get<uint32_t>(S_TILE_CTR, 64);
     js.fix_cap = C.config.fixup_cap > 0 ? C.config.fixup_cap : np / 8 + 65536;
     js.fix_items = ws.get<uint64_t>(S_FIX_ITEMS, (size_t)js.fix_cap);
@@ -215,7 +217,8 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
             if (js.precision == MAP_MIXED) {
                 // too many flagged edges for the list: every pair again in FP64
                 // (whose list then holds winding items only)
-                launch_integrate(in, js.edges, ps, MAP_FP64, t64, f, nullptr, js.counters, js.tile_ctr,
+                fill_zero_bytes(js.S, sizeof(double) * in.n, s);
+                launch_integrate(in, js.edges, ps, MAP_FP64, t64, f, nullptr, js.S, js.counters, js.tile_ctr,
                                  js.fix_items, js.fix_cap, s);
                 n_items = read_count();
                 n_fix = np;
@@ -225,7 +228,8 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
                 // more winding items than the list holds: a list that fits them, and the FP64 pass again
                 js.fix_cap = n_items;
                 js.fix_items = ws.get<uint64_t>(S_FIX_ITEMS, (size_t)n_items);
-                launch_integrate(in, js.edges, ps, MAP_FP64, t64, f, nullptr, js.counters, js.tile_ctr,
+                fill_zero_bytes(js.S, sizeof(double) * in.n, s);
+                launch_integrate(in, js.edges, ps, MAP_FP64, t64, f, nullptr, js.S, js.counters, js.tile_ctr,
                                  js.fix_items, js.fix_cap, s);
                 n_items = read_count();
                 js.err = nullptr;
@@ -241,7 +245,7 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
             while (bits < 64 && ((uint64_t)(np - 1) >> (bits - 32)) != 0) bits++;
             const uint64_t *items = sort_keys_u64(ws, js.fix_items, k2, n_items, bits, s);
             launch_fixup(in, js.edges, ps, items, n_items, fv, js.counters, s);
-            launch_fixup_apply(items, fv, n_items, f, s);
+            launch_fixup_apply(items, fv, n_items, ps.pair_p, f, js.S, s);
         }
     }
     if (js.ev_fix) EM_HIP(hipEventRecord(js.ev_fix, s));
@@ -256,9 +260,9 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
         EM_HIP(hipMemcpyAsync(&hc, cnt, sizeof(unsigned), hipMemcpyDeviceToHost, s));
         stream_sync(s);
         n_cells_fp64 = hc;
-        if (hc > 0) launch_recompute_cells(in, js.edges, ps, list, (int64_t)hc, f, js.counters, s);
+        if (hc > 0) launch_recompute_cells(in, js.edges, ps, list, (int64_t)hc, f, js.S, js.counters, s);
     }
-    double *S = ws.get<double>(S_S, (size_t)(in.n > 0 ? in.n : 1));
+    double *S = js.S;
     double *M = ws.get<double>(S_MCELL, (size_t)(in.n_cells > 0 ? in.n_cells : 1));
     double *rho = ws.get<double>(S_RHO, (size_t)(in.n_cells > 0 ? in.n_cells : 1));
     double *red = ws.get<double>(S_RED, 16 + 4 * 256);
@@ -349,12 +353,13 @@ void run_mapping(Ctx &C, Workspace &ws, const map_particles_in *p, const map_cel
         if (timed) EM_HIP(hipEventRecord(C.ev[2], s));
         launch_integrate_table(js.in, js.edges, js.ps, C.table.d4, C.table.n[0], C.table.n[1], C.table.n[2], js.f,
                                js.counters, s);
+        launch_particle_sum(js.ps, js.f, js.S, s);
     } else {
         const IntegrateTune tune = pick_tune(C, precision, js.ps.n_pairs);
         if (tune.persistent == 2) build_tiles(ws, js.in, js.ps, s);
         if (timed) EM_HIP(hipEventRecord(C.ev[2], s));
-        launch_integrate(js.in, js.edges, js.ps, precision, tune, js.f, js.err, js.counters, js.tile_ctr, js.fix_items,
-                         js.fix_cap, s);
+        launch_integrate(js.in, js.edges, js.ps, precision, tune, js.f, js.err, js.S, js.counters, js.tile_ctr,
+                         js.fix_items, js.fix_cap, s);
     }
     if (timed) {
         EM_HIP(hipEventRecord(C.ev[3], s));

@@ -1045,7 +1045,9 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
         run_stack<2>(W, nQ, lane, true, wk);
         lds_sync_wave();
         if (active) {
-            JOB(f)[k] = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
+            const double v = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
+            JOB(f)[k] = v;
+            if (JOB(S)) atomicAdd(JOB(S) + JOB(pair_p)[k], fixed52(v));
             float *const err = JOB(err);  // null when no estimate is wanted (the autotuner's timing runs)
             if (err) err[k] = kTermErr * kInvPiF * sqrt_f32(ev_in + W.ev[lane]);
             if (inside && n_on >= 2) push_fix(fx, k, kWindingSlot);
@@ -1236,7 +1238,9 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
         run_stack64<1>(W, nP, lane, true, wk);
         lds_sync_wave();
         if (active) {
-            JOB(f)[k] = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
+            const double v = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
+            JOB(f)[k] = v;
+            if (JOB(S)) atomicAdd(JOB(S) + JOB(pair_p)[k], fixed52(v));
             if (inside && n_on >= 2) push_fix(FixList{JOB(fix_count), JOB(fix_items), JOB(fix_cap), nullptr}, k, kWindingSlot);
         }
         lds_sync_wave();
@@ -1378,7 +1382,8 @@ __global__ void k_fixup_values(int64_t n_fix, const uint64_t *__restrict__ keys,
 
 // Adds the (key-sorted) fixup values of each pair, in key order, to f.
 __global__ void k_fixup_apply(int64_t n_fix, const uint64_t *__restrict__ keys, const double *__restrict__ vals,
-                              double *__restrict__ f)
+                              const uint32_t *__restrict__ pair_p, double *__restrict__ f,
+                              unsigned long long *__restrict__ S)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_fix) return;
@@ -1386,7 +1391,9 @@ __global__ void k_fixup_apply(int64_t n_fix, const uint64_t *__restrict__ keys, 
     if (i > 0 && (keys[i - 1] >> 32) == k) return;
     double sum = 0.0;
     for (int64_t j = i; j < n_fix && (keys[j] >> 32) == k; j++) sum += vals[j];
-    f[k] += sum;
+    const double old = f[k];
+    f[k] = old + sum;
+    atomicAdd(S + pair_p[k], fixed52(old + sum) - fixed52(old));
 }
 
 // Node values of the tabulated pyramid integral I(r0, R0, phi) (the variant of
@@ -1450,6 +1457,7 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
                                                          const int64_t *__restrict__ fvo,
                                                          const double *__restrict__ plane,
                                                          const EdgeRec *__restrict__ edges, double *__restrict__ f,
+                                                         unsigned long long *__restrict__ S,
                                                          unsigned long long *counters)
 {
     static_assert(kRecPairs * kRecWalls <= 2048, "one chunk's terms in LDS");
@@ -1466,8 +1474,10 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
             const int64_t a = pair_p[k];
             Work wk;
             float ev = 0.0f;
-            f[k] = pair_fraction<MAP_FP64>(xyz[3 * a], xyz[3 * a + 1], xyz[3 * a + 2], h[a], c, cfo, fvo, plane,
-                                           edges, wk, (uint64_t)k, nullptr, nullptr, 0u, ev);
+            const double v = pair_fraction<MAP_FP64>(xyz[3 * a], xyz[3 * a + 1], xyz[3 * a + 2], h[a], c, cfo, fvo,
+                                                     plane, edges, wk, (uint64_t)k, nullptr, nullptr, 0u, ev);
+            atomicAdd(S + a, fixed52(v) - fixed52(f[k]));
+            f[k] = v;
         }
     } else {
         const int W = (int)nw;
@@ -1515,9 +1525,11 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
                     const double face = term[p * W + w];
                     acc += in_j ? face : -face;
                 }
-                f[k] = winding_term(inside, n_on, xyz[3 * a], xyz[3 * a + 1], xyz[3 * a + 2], c, cfo, fvo, plane,
-                                    edges) -
-                       acc * kInvPi;
+                const double v = winding_term(inside, n_on, xyz[3 * a], xyz[3 * a + 1], xyz[3 * a + 2], c, cfo, fvo,
+                                              plane, edges) -
+                                 acc * kInvPi;
+                atomicAdd(S + a, fixed52(v) - fixed52(f[k]));
+                f[k] = v;
             }
         }
     }
@@ -1604,11 +1616,16 @@ static void launch_queued(const IntJob *h_jobs, const IntJob *d_jobs, int n_jobs
 }
 
 void launch_integrate(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, int precision,
-                      const IntegrateTune &tune, double *f, float *err, int64_t *counters, uint32_t *tile_ctr,
-                      uint64_t *fix_items, int64_t fix_cap, hipStream_t s)
+                      const IntegrateTune &tune, double *f, float *err, double *S, int64_t *counters,
+                      uint32_t *tile_ctr, uint64_t *fix_items, int64_t fix_cap, hipStream_t s)
 {
     const int64_t np = ps.n_pairs;
     if (np == 0) return;
+    if (tune.persistent != 3 && S) {  // the other distributions leave the sums to a pass of their own
+        launch_integrate(in, edges, ps, precision, tune, f, err, nullptr, counters, tile_ctr, fix_items, fix_cap, s);
+        launch_particle_sum(ps, f, S, s);
+        return;
+    }
     unsigned long long *cnt = reinterpret_cast<unsigned long long *>(counters);
     FixList fx;
     fx.count = tile_ctr + 1;
@@ -1643,6 +1660,7 @@ void launch_integrate(const DevInputs &in, const EdgeRec *edges, const PairSet &
         J.edges = edges;
         J.f = f;
         J.err = fx.err;
+        J.S = reinterpret_cast<unsigned long long *>(S);
         J.counters = cnt;
         J.fix_count = fx.count;
         J.fix_items = fx.items;
@@ -1696,12 +1714,12 @@ void launch_integrate_jobs(const IntJob *h_jobs, const IntJob *d_jobs, int n_job
 }
 
 void launch_recompute_cells(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const uint32_t *cells,
-                            int64_t n_cells, double *f, int64_t *counters, hipStream_t s)
+                            int64_t n_cells, double *f, double *S, int64_t *counters, hipStream_t s)
 {
     if (n_cells <= 0) return;
     hipLaunchKernelGGL(k_recompute_cells, dim3((unsigned)n_cells, kRecBlocks), dim3(256), 0, s, n_cells,
                        cells, ps.coff, ps.pair_p, in.xyz, in.h, in.cfo, in.fvo, in.plane, edges, f,
-                       reinterpret_cast<unsigned long long *>(counters));
+                       reinterpret_cast<unsigned long long *>(S), reinterpret_cast<unsigned long long *>(counters));
     EM_HIP(hipGetLastError());
 }
 
@@ -1715,10 +1733,12 @@ void launch_fixup(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, 
     EM_HIP(hipGetLastError());
 }
 
-void launch_fixup_apply(const uint64_t *keys, const double *vals, int64_t n_fix, double *f, hipStream_t s)
+void launch_fixup_apply(const uint64_t *keys, const double *vals, int64_t n_fix, const uint32_t *pair_p, double *f,
+                        double *S, hipStream_t s)
 {
     if (n_fix <= 0) return;
-    hipLaunchKernelGGL(k_fixup_apply, dim3((unsigned)((n_fix + 255) / 256)), dim3(256), 0, s, n_fix, keys, vals, f);
+    hipLaunchKernelGGL(k_fixup_apply, dim3((unsigned)((n_fix + 255) / 256)), dim3(256), 0, s, n_fix, keys, vals,
+                       pair_p, f, reinterpret_cast<unsigned long long *>(S));
     EM_HIP(hipGetLastError());
 }
 

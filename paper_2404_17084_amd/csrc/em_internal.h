@@ -261,6 +261,7 @@ struct IntJob {
     const EdgeRec *edges = nullptr;
     double *f = nullptr;
     float *err = nullptr;  // mixed path: FP32 error estimate per pair (units of f)
+    unsigned long long *S = nullptr;  // fixed-point sums of f per particle (em_wave.h), or null
     unsigned long long *counters = nullptr;
     unsigned *fix_count = nullptr;
     uint64_t *fix_items = nullptr;
@@ -284,21 +285,24 @@ void launch_integrate_jobs(const IntJob *h_jobs, const IntJob *d_jobs, int n_job
 // em_integrate.hip: raw f per pair (cell-major order).
 void build_tiles(Workspace &ws, const DevInputs &in, PairSet &ps, hipStream_t s);
 // err: MAP_MIXED: per-pair FP32 error estimates (units of f) are written there
-// (may be null; ignored for MAP_FP64).
+// (may be null; ignored for MAP_FP64).  S (or null): the fixed-point sums of f
+// per particle (em_wave.h), zeroed by the caller, which every pair's f is added to.
 void launch_integrate(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, int precision,
-                      const IntegrateTune &tune, double *f, float *err, int64_t *counters, uint32_t *tile_ctr,
-                      uint64_t *fix_items, int64_t fix_cap, hipStream_t s);
+                      const IntegrateTune &tune, double *f, float *err, double *S, int64_t *counters,
+                      uint32_t *tile_ctr, uint64_t *fix_items, int64_t fix_cap, hipStream_t s);
 // FP64 recomputation (the whole pair, winding weight included) of every pair
-// of the n_cells listed cells, written over f; counters[C_FP64_PAIRS] counts them.
+// of the n_cells listed cells, written over f, and S brought along;
+// counters[C_FP64_PAIRS] counts them.
 void launch_recompute_cells(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const uint32_t *cells,
-                            int64_t n_cells, double *f, int64_t *counters, hipStream_t s);
+                            int64_t n_cells, double *f, double *S, int64_t *counters, hipStream_t s);
 // FP64 values of the fixup items: flagged edge terms, and the winding
 // correction of pairs whose particle lies on two or more wall planes of the
 // cell (counted in counters[C_WINDING]).
 void launch_fixup(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const uint64_t *fix_items,
                   int64_t n_fix, double *fix_vals, int64_t *counters, hipStream_t s);
-// adds sorted fixup values into f
-void launch_fixup_apply(const uint64_t *keys, const double *vals, int64_t n_fix, double *f, hipStream_t s);
+// adds sorted fixup values into f, and brings S along
+void launch_fixup_apply(const uint64_t *keys, const double *vals, int64_t n_fix, const uint32_t *pair_p, double *f,
+                        double *S, hipStream_t s);
 
 // em_integrate.hip: node values of the tabulated pyramid integral: FP64, and FP32 as the reads take them (per node
 // (i, j, k) the four values at i, i + 1 and j, j + 1; zeros where there is no i + 1 or j + 1)
@@ -330,6 +334,9 @@ void site_cells(Workspace &ws, const VorGrid &V, int64_t n_in, const double *in,
 void free_voronoi(VorGrid &V);
 
 // em_reduce.hip
+// adds every pair's f to the fixed-point sums S (after a kernel that does not)
+void launch_particle_sum(const PairSet &ps, const double *f, double *S, hipStream_t s);
+// S: fixed-point sums on entry, S_a on return
 void launch_reduce(const DevInputs &in, const PairSet &ps, const double *f, double *S, double *M,
                    double *rho, double *red, unsigned *flags, hipStream_t s);
 // Mixed path, before the reduction: lists the cells whose estimated FP32

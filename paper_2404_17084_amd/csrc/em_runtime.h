@@ -72,6 +72,7 @@ struct JobState {
     PairSet ps;
     double *f = nullptr;
     float *err = nullptr;  // mixed path: per-pair FP32 error estimates
+    double *S = nullptr;   // per particle: fixed-point sums of f (em_wave.h), S_a once reduced
     uint32_t *tile_ctr = nullptr;
     uint64_t *fix_items = nullptr;
     int64_t fix_cap = 0;

@@ -328,6 +328,7 @@ static bool launch_batch(Server &S)
                     e.edges = js.edges;
                     e.f = js.f;
                     e.err = js.err;
+                    e.S = reinterpret_cast<unsigned long long *>(js.S);
                     e.counters = reinterpret_cast<unsigned long long *>(js.counters);
                     e.fix_count = js.tile_ctr + 1;
                     e.fix_items = js.fix_items;

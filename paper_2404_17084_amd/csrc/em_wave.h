@@ -54,6 +54,14 @@ __device__ __forceinline__ double wave_reduce(double v, double identity, Op op)
     return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
 }
 
+// S_a is summed in 2^-52 fixed point with 64-bit integer atomics (each term
+// rounded by at most 2^-53, the sum exact, so it does not depend on the order
+// of the additions, and a pair's term can be replaced by adding the difference).
+__device__ __forceinline__ unsigned long long fixed52(double f)
+{
+    return (unsigned long long)__double2ll_rn(f * 4503599627370496.0);
+}
+
 // Logical index of this workgroup in an XCD-aware order.  Workgroups are
 // dispatched round-robin over the 8 XCDs (workgroup b to XCD b mod 8); this
 // gives XCD x a contiguous run of logical indices (x * per + min(x, rem) ...,
