@@ -426,15 +426,6 @@ __device__ __forceinline__ bool needs_fp64(double r0, double R0, double c2)
            (fabs(c2 - 1.0) < e) || (fabs(c2 - 4.0) < 4.0 * e);
 }
 
-// The same test on the FP32 values the terms use (r0, R0 rounded from FP64;
-// the FP32 rounding of c^2 is 2^-24 relative, far inside the 2^-20 margins).
-__device__ __forceinline__ bool needs_fp64_f32(float r0, float R0, float c2)
-{
-    const float e = 9.5367431640625e-07f;  // 2^-20
-    return (R0 * R0 < 9.094947017729282e-13f * c2) || (c2 < 8.673617379884035e-19f) || (fabsf(r0 - 1.0f) < e) ||
-           (fabsf(c2 - 1.0f) < e) || (fabsf(c2 - 4.0f) < 4.0f * e);
-}
-
 // Raw f for one pair.  PREC = MAP_FP64 or MAP_MIXED.  Wall distance, foot
 // point and edge projections are always FP64; in the mixed path the edge
 // terms are FP32 (accumulated in FP64) unless the conditioning test sends the
@@ -651,17 +642,27 @@ struct WaveStacks {
     float ang[3][kQA];  // atan2 arguments of the angle (imaginary, real part), weight
     float pnt[4][kQ];   // inner parts: r0, signed R0 (sign = the term's sign), start a, length L
     float qd[4][kQ];    // shell sub-intervals: r0, signed R0, mid, half-length
-    uint8_t ang_o[kQA], pnt_o[kQ], qd_o[kQ];  // owner lanes
+    uint32_t qd_o[kQ];                // owner lanes (a word each: the sub-intervals are the most frequent tasks)
+    uint8_t ang_o[kQA], pnt_o[kQ];
     double acc[64];
-    float ev[64];  // sums of the squared FP32 task values per owner (error estimate)
+    double ev[64];  // sums of the squared FP32 task values per owner (error estimate)
 };
 
-__device__ __forceinline__ void run_angle(WaveStacks &W, int i, Work &wk)
+// A task's value to its owner.  Both sums take the LDS double atomic, which
+// issues in 8 clocks per wavefront (20 where owners repeat in pairs); the float
+// one takes 193 (measured, all lanes on addresses of their own).
+__device__ __forceinline__ void add_task(WaveStacks &W, int o, float v)
 {
-    wk.angles++;
+    const double d = (double)v;
+    atomicAdd(&W.acc[o], d);
+    atomicAdd(&W.ev[o], d * d);
+}
+
+__device__ __forceinline__ void run_angle(WaveStacks &W, int i)
+{
+    const int o = W.ang_o[i];
     const float v = W.ang[2][i] * atan2_f32(W.ang[0][i], W.ang[1][i]);
-    atomicAdd(&W.acc[W.ang_o[i]], (double)v);
-    atomicAdd(&W.ev[W.ang_o[i]], v * v);
+    add_task(W, o, v);
 }
 
 // Closed form of the inner piece (s <= 1) over one edge part [a, a + L],
@@ -681,9 +682,9 @@ __device__ __forceinline__ void run_angle(WaveStacks &W, int i, Work &wk)
 // S_a S_b +- a b is formed from (S_a S_b)^2 - (a b)^2 = c^2 (a^2 + b^2 + c^2)
 // on the side where it would cancel.  L comes from the FP64 edge length when
 // the part is the whole edge.
-__device__ __forceinline__ void run_seg(WaveStacks &W, int i, Work &wk)
+__device__ __forceinline__ void run_seg(WaveStacks &W, int i)
 {
-    wk.moments++;
+    const int o = W.pnt_o[i];
     const float r0 = W.pnt[0][i], sR0 = W.pnt[1][i], a = W.pnt[2][i], L = W.pnt[3][i];
     const float R0 = fabsf(sR0), w = sR0 < 0.0f ? -1.0f : 1.0f;
     const float b = a + L;
@@ -713,8 +714,7 @@ __device__ __forceinline__ void run_seg(WaveStacks &W, int i, Work &wk)
     const float DT = (-1.0f / 6.0f) * L + 0.075f * fmaf(2.0f * A + R02, L, D3 * (1.0f / 3.0f)) -
                      0.025f * (0.25f * DxS3 + 0.375f * c2 * fmaf(c2, Da, DxS) + A * DP3r);
     const float v = w * fmaf(-Dbeta, Hodd, r0 * R0 * DT);
-    atomicAdd(&W.acc[W.pnt_o[i]], (double)v);
-    atomicAdd(&W.ev[W.pnt_o[i]], v * v);
+    add_task(W, o, v);
 }
 
 // 4-point Gauss-Legendre nodes and weights on [-1, 1] (nodes in pairs +-x)
@@ -728,8 +728,9 @@ __constant__ float kGL4w[2] = {0.6521451548625461f, 0.3478548451374538f};
 // 5 + sqrt(26) of every sub-interval; the Gauss-Legendre error theorem for
 // analytic integrands then bounds the truncation by 1e-8 of the pair fraction
 // per sub-interval over the whole (r0, c) range (measured: below 3e-10).
-__device__ __forceinline__ void run_quad(WaveStacks &W, int i, Work &wk)
+__device__ __forceinline__ void run_quad(WaveStacks &W, int i)
 {
+    const int o = (int)W.qd_o[i];
     const float r0 = W.qd[0][i], sR0 = W.qd[1][i], mid = W.qd[2][i], hl = W.qd[3][i];
     const float c2 = fmaf(sR0, sR0, r0 * r0), w = sR0 * hl * (1.0f / 120.0f);
     // the numerator (r0+1)(r0 Sigma + V^5) - r0 U^5 as a polynomial in U with
@@ -748,34 +749,31 @@ __device__ __forceinline__ void run_quad(WaveStacks &W, int i, Work &wk)
         const float num = fmaf(fmaf(fmaf(fmaf(fmaf(-r0, U, t), U, a3), U, a2), U, a1), U, a0);
         acc = fmaf(kGL4w[q >> 1], num * rcp_f32(S * (S + r0)), acc);
     }
-    wk.quads++;
-    wk.qpoints += 4;
     const float v = w * acc;
-    atomicAdd(&W.acc[W.qd_o[i]], (double)v);
-    atomicAdd(&W.ev[W.qd_o[i]], v * v);
+    add_task(W, o, v);
 }
 
 template <int KIND>
-__device__ __forceinline__ void run_one(WaveStacks &W, int i, Work &wk)
+__device__ __forceinline__ void run_one(WaveStacks &W, int i)
 {
-    if (KIND == 0) run_angle(W, i, wk);
-    else if (KIND == 1) run_seg(W, i, wk);
-    else run_quad(W, i, wk);
+    if (KIND == 0) run_angle(W, i);
+    else if (KIND == 1) run_seg(W, i);
+    else run_quad(W, i);
 }
 
 // run the top 64 entries when 64 are pending (all = false), or all pending ones
 template <int KIND>
-__device__ __forceinline__ void run_stack(WaveStacks &W, int &count, int lane, bool all, Work &wk)
+__device__ __forceinline__ void run_stack(WaveStacks &W, int &count, int lane, bool all)
 {
     if (count >= 64) {
         lds_sync_wave();
-        run_one<KIND>(W, count - 64 + lane, wk);
+        run_one<KIND>(W, count - 64 + lane);
         count -= 64;
         lds_sync_wave();
     }
     if (all && count > 0) {
         lds_sync_wave();
-        if (lane < count) run_one<KIND>(W, lane, wk);
+        if (lane < count) run_one<KIND>(W, lane);
         count = 0;
         lds_sync_wave();
     }
@@ -795,155 +793,192 @@ __device__ __forceinline__ int wave_max(int v)
     return v;
 }
 
-// One step of the mixed task batches: this lane's edge (slot s of the current
-// wall; live = the lane has a wall within the support and an edge at this
-// step) is projected in FP64, classified in FP32 and its tasks are pushed;
-// full stacks run as they fill.  Wave-uniform control flow; r0d, r0, Ht, dH
-// and fsign describe the lane's current wall.
-__device__ __forceinline__ void mixed_edge_step(WaveStacks &W, int lane, Work &wk, int &nA, int &nP, int &nQ, bool live,
-                                                const EdgeRec *__restrict__ edges, int32_t s, double px, double py,
-                                                double pz, double invh, double r0d, float r0, float Ht, float dH,
-                                                float fsign, int64_t k, FixList fx, double &acc_in, float &ev_in)
+// A lane's current wall in the mixed task batches.
+struct MixedWall {
+    float r0 = 0.0f, nHt = 0.0f, dH = 0.0f;  // distance, -pi H, pi dH
+    uint32_t sbit = 0;    // sign bit of the wall's terms (set: the particle is on its outer side)
+    float c2_min = 0.0f;  // edges with a smaller c^2 go to the FP64 fixup pass (NaN: all of them, r0 asks for it)
+    float r_len = 0.0f;   // reciprocal of the longest sub-interval of a shell part next to the inner piece; 0: the
+                          // wall lies beyond the support, or the lane has none
+};
+
+// Work counters of a wavefront (scalars: the masks are there anyway).
+struct WaveWork {
+    unsigned eterms = 0, moments = 0, quads = 0, angles = 0;
+};
+
+// Lane masks: one bit per lane in a scalar register pair, so that logic on them is scalar.
+__device__ __forceinline__ uint64_t mask_of(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// x with the sign bit flipped where sbit is set
+__device__ __forceinline__ float flip_sign(float x, uint32_t sbit)
 {
-    float R0 = 0.0f, la = 0.0f, lb = 0.0f, Le = 0.0f, sg = 0.0f;
-    if (live) {
-        const EdgeRec E = edges[s];
-        const double wx = px - E.vx, wy = py - E.vy, wz = pz - E.vz;
-        const double rho = E.mx * wx + E.my * wy + E.mz * wz;
-        wk.edges++;
-        if (rho == 0.0) {
-            live = false;
-        } else {
-            const double lad = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
-            const double Ld = E.L * invh;
-            const float R0f = (float)(fabs(rho) * invh);
-            if (needs_fp64_f32(r0, R0f, fmaf(r0, r0, R0f * R0f))) {
-                const unsigned slot = atomicAdd(fx.count, 1u);
-                if (slot < fx.cap) fx.items[slot] = ((uint64_t)k << 32) | (uint64_t)(uint32_t)s;
-                live = false;
-            } else {
-                R0 = R0f;
-                la = (float)lad;
-                lb = (float)(lad + Ld);
-                Le = (float)Ld;  // the edge's length from FP64: parts spanning the whole edge keep their digits
-                sg = (rho > 0.0 ? 1.0f : -1.0f) * fsign;
-            }
+    return __uint_as_float(__float_as_uint(x) ^ sbit);
+}
+
+// One step of the mixed task batches: this lane's edge E (record s of the edge
+// table; live = the lane has a wall within the support and an edge at this
+// step) is projected in FP64, classified in FP32 and its tasks are pushed;
+// full stacks run as they fill.  Wave-uniform control flow; a lane that is not
+// live goes through the same operations on undefined values and contributes
+// nothing.
+//
+// Bound by vector issue.  On this chip an FP32 add, multiply or fused
+// multiply-add and a 32-bit add or logical operation on registers or literals
+// take 2 clocks per wavefront, comparisons, selects, minima, conversions, shifts,
+// bit counts and all FP64 take 4, and reciprocals and square roots 8 (measured,
+// single instructions in a loop).  So lane masks live in scalar registers, signs
+// are bits, counts are floats, what depends on the wall alone is kept with the
+// wall, and one coarse test stands before the exact conditioning test: 258 vector
+// instructions a step where a form with lane predicates, counters in vector
+// registers and float atomics took 290.  34.7e6 pairs of a clumpy cloud: 21.0 ->
+// 16.9 ms, of which 2.4 ms are the atomics (add_task).
+__device__ __forceinline__ void mixed_edge_step(WaveStacks &W, int lane, WaveWork &ww, int &nA, int &nP, int &nQ,
+                                                uint64_t live, const EdgeRec &E, int32_t s, double px, double py,
+                                                double pz, double invh, const MixedWall &wall, int64_t k,
+                                                const FixList &fx, double &acc_in, float &ev_in)
+{
+    const float r0 = wall.r0;
+    const double wx = px - E.vx, wy = py - E.vy, wz = pz - E.vz;
+    const double rho = E.mx * wx + E.my * wy + E.mz * wz;
+    const double lad = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
+    const double Ld = E.L * invh;
+    const float R0 = (float)(fabs(rho) * invh);
+    const float la = (float)lad, lb = (float)(lad + Ld);
+    const float Le = (float)Ld;  // the edge's length from FP64: parts spanning the whole edge keep their digits
+    const uint32_t sbit = ((uint32_t)__double2hiint(rho) ^ wall.sbit) & 0x80000000u;  // of the edge's terms
+    const float R02 = R0 * R0, c2 = fmaf(r0, r0, R02);
+    // The conditioning test (needs_fp64, here on FP32 values: the rounding of c^2
+    // is 2^-24 relative, far inside the 2^-20 margins) and rho = 0, seldom true, behind a
+    // coarse test that holds wherever they do: c^2 >= R0^2, so c^2 < c2_min or
+    // R0^2 < 2^-40 c^2 gives R0^2 < c2_min + 2^-40 c^2; |c^2 - 1| < e or
+    // |c^2 - 4| < 4 e gives |(c^2 - 1) (c^2 - 4)| < 13 e; rho = 0 gives R0 = 0
+    // and c2_min > 0.
+    constexpr float e = 9.5367431640625e-07f;  // 2^-20
+    const uint64_t near_bad = live & (mask_of(!(R02 >= fmaf(c2, 9.094947017729282e-13f, wall.c2_min))) |
+                                      mask_of(fabsf(fmaf(c2, c2 - 5.0f, 4.0f)) < 16.0f * e));
+    if (near_bad != 0) {
+        const bool bad = R02 < 9.094947017729282e-13f * c2 || c2 < wall.c2_min || wall.c2_min != wall.c2_min ||
+                         fabsf(c2 - 1.0f) < e || fabsf(c2 - 4.0f) < 4.0f * e;
+        if (lane_in(near_bad) && bad && rho != 0.0) {
+            const unsigned slot = atomicAdd(fx.count, 1u);
+            if (slot < fx.cap) fx.items[slot] = ((uint64_t)k << 32) | (uint64_t)(uint32_t)s;
         }
+        live &= ~(near_bad & mask_of(bad || rho == 0.0));
     }
-    // length of the part [x, y] of the edge: the FP64-derived length when it
-    // is the whole edge, else the FP32 difference (a clipped end sits on a
-    // kernel sphere, where an end shift changes the integral only to second order)
-    auto part_len = [&](float x, float y) { return (x == la && y == lb) ? Le : y - x; };
     // classification (the mixed form of edge_term).  The edge [la, lb] splits
     // into the parts beyond the support (|l| > l2), the shell parts and the
     // inner part (|l| < l1, when c < 1): [la, ca] + [cb, lb] beyond,
     // [ca, ia] + [ib, cb] shell, [ia, ib] inner, every part oriented and
     // possibly empty.  Far edges (c >= 2) are all beyond (l2 = 0).
-    const float A = r0 * r0;
-    const float c2 = A + R0 * R0;
-    const bool near = live && c2 < 4.0f;
-    const bool has_inner = near && c2 < 1.0f;
-    const float l2 = near ? sqrt_f32(4.0f - c2) : 0.0f;
-    const float l1 = has_inner ? sqrt_f32(1.0f - c2) : 0.0f;
-    const float c = near && !has_inner ? sqrt_f32(c2) : 1.0f;
+    const uint64_t near = live & mask_of(c2 < 4.0f), inner = near & mask_of(c2 < 1.0f);
+    const float l2 = lane_in(near) ? sqrt_f32(4.0f - c2) : 0.0f;
+    const float l1 = lane_in(inner) ? sqrt_f32(1.0f - c2) : 0.0f;
     // clamps as medians of three (la <= lb, so min(max(x, lo), hi) is the
     // median of x, lo and hi also when lo > hi: one instruction each)
     const float ca = __builtin_amdgcn_fmed3f(la, -l2, lb);
     const float cb = __builtin_amdgcn_fmed3f(ca, l2, lb);
-    const float ia = has_inner ? __builtin_amdgcn_fmed3f(ca, -l1, cb) : cb;
-    const float ib = has_inner ? __builtin_amdgcn_fmed3f(ia, l1, cb) : cb;
-    if (near) wk.eterms++;
+    const float ia = lane_in(inner) ? __builtin_amdgcn_fmed3f(ca, -l1, cb) : cb;
+    const float ib = lane_in(inner) ? __builtin_amdgcn_fmed3f(ia, l1, cb) : cb;
+    const uint64_t cut_a = mask_of(la < ca), cut_b = mask_of(cb < lb);      // (else ca = la, cb = lb)
+    const uint64_t shell_a = near & mask_of(ca < ia), shell_b = near & mask_of(ib < cb);
+    // Length of a part: the FP64-derived length when it is the whole edge, else
+    // the FP32 difference (a clipped end sits on a kernel sphere, where an end
+    // shift changes the integral only to second order)
+    auto part_len = [&](bool whole, float x, float y) { return whole ? Le : y - x; };
+    const float len_a = part_len(lane_in(~cut_a & mask_of(ia == lb)), ca, ia);  // shell parts [ca, ia] and [ib, cb]
+    const float len_b = part_len(lane_in(~cut_b & mask_of(ib == la)), ib, cb);
     // angle terms: -H times the beyond parts' angle, dH times the shell
     // parts' angle.  The angle of two parts is the argument of the product of
     // their complex numbers (R0^2 + a b) + i R0 (b - a) (sum below pi).  One
     // angle per lane is taken here; a lane that has both pushes the shell
     // angle as a task.
-    const bool has_b = live && (la < ca || cb < lb);
-    const bool has_s = near && dH != 0.0f && (ca < ia || ib < cb);
-    float zx, zy;
+    const uint64_t has_b = live & (cut_a | cut_b);
+    const uint64_t has_s = (shell_a | shell_b) & mask_of(wall.dH != 0.0f);
     {
-        const float R02 = R0 * R0;
-        const bool b = has_b;
-        const float a1 = b ? la : ca, b1 = b ? ca : ia, a2 = b ? cb : ib, b2 = b ? lb : cb;
-        const float x1 = R02 + a1 * b1, y1 = R0 * part_len(a1, b1), x2 = R02 + a2 * b2, y2 = R0 * part_len(a2, b2);
-        zx = x1 * x2 - y1 * y2;
-        zy = x1 * y2 + x2 * y1;
-    }
-    const float w_in = has_b ? -Ht * sg : (has_s ? dH * sg : 0.0f);
-    {
-        const float v = w_in * atan2_f32(zy, zx);
+        // the parts [la, b1] and [a2, lb] (a lane without beyond parts has ca = la and cb = lb)
+        const float b1 = lane_in(has_b) ? ca : ia, a2 = lane_in(has_b) ? cb : ib;
+        const float x1 = fmaf(la, b1, R02), y1 = R0 * part_len(b1 == lb, la, b1);
+        const float x2 = fmaf(lb, a2, R02), y2 = R0 * part_len(a2 == la, a2, lb);
+        const float zx = fmaf(x1, x2, -(y1 * y2)), zy = fmaf(x2, y1, x1 * y2);
+        const float w_in = flip_sign(lane_in(has_b) ? wall.nHt : (lane_in(has_s) ? wall.dH : 0.0f), sbit);
+        const float v = lane_in(live) ? w_in * atan2_f32(zy, zx) : 0.0f;
         acc_in += (double)v;
         ev_in = fmaf(v, v, ev_in);
     }
-    wk.angles += (has_b || has_s) ? 1u : 0u;
+    ww.eterms += __popcll(near);
+    ww.angles += __popcll(has_b) + __popcll(has_s);
     {
-        const bool want = has_b && has_s;
-        const unsigned long long m = __ballot(want);
+        const uint64_t m = has_b & has_s;
         if (m != 0) {
-            if (nA + __popcll(m) > kQA) run_stack<0>(W, nA, lane, true, wk);
-            const int slot = wave_push(want, nA);
-            if (want) {
-                const float R02 = R0 * R0;
-                const float x1 = R02 + ca * ia, y1 = R0 * part_len(ca, ia), x2 = R02 + ib * cb, y2 = R0 * part_len(ib, cb);
-                W.ang[0][slot] = x1 * y2 + x2 * y1;
-                W.ang[1][slot] = x1 * x2 - y1 * y2;
-                W.ang[2][slot] = dH * sg;
+            if (nA + __popcll(m) > kQA) run_stack<0>(W, nA, lane, true);
+            const int slot = wave_push(m, nA);
+            if (lane_in(m)) {
+                const float x1 = fmaf(ca, ia, R02), y1 = R0 * len_a;
+                const float x2 = fmaf(cb, ib, R02), y2 = R0 * len_b;
+                W.ang[0][slot] = fmaf(x2, y1, x1 * y2);
+                W.ang[1][slot] = fmaf(x1, x2, -(y1 * y2));
+                W.ang[2][slot] = flip_sign(wall.dH, sbit);
                 W.ang_o[slot] = (uint8_t)lane;
             }
-            run_stack<0>(W, nA, lane, false, wk);
+            run_stack<0>(W, nA, lane, false);
         }
     }
+    const float sR0 = flip_sign(R0, sbit);
     // inner part [ia, ib]: one closed-form task over the part (run_seg)
     {
-        const bool want = has_inner && ib > ia;
-        if (__ballot(want) != 0) {
-            const int slot = wave_push(want, nP);
-            if (want) {
+        const uint64_t m = inner & mask_of(ib > ia);
+        if (m != 0) {
+            const int slot = wave_push(m, nP);
+            ww.moments += __popcll(m);
+            if (lane_in(m)) {
                 W.pnt[0][slot] = r0;
-                W.pnt[1][slot] = sg < 0.0f ? -R0 : R0;
+                W.pnt[1][slot] = sR0;
                 W.pnt[2][slot] = ia;
-                W.pnt[3][slot] = part_len(ia, ib);
+                W.pnt[3][slot] = part_len(ia == la && ib == lb, ia, ib);
                 W.pnt_o[slot] = (uint8_t)lane;
             }
-            run_stack<1>(W, nP, lane, false, wk);
+            run_stack<1>(W, nP, lane, false);
         }
     }
-    // shell parts by quadrature: [ca, ia] and [ib, cb]
-    const bool q0 = near && ia > ca, q1 = near && cb > ib;
-    const float qa0 = ca, qb0 = ia, qa1 = ib, qb1 = cb, qd0 = has_inner ? 1.0f : c;
-    // both shell parts' sub-intervals in one uniform loop
-    int n0 = 0, n1 = 0;
-    float hl0 = 0.0f, hl1 = 0.0f;
+    // shell parts by quadrature: [ca, ia] and [ib, cb], each cut into 1 to 32
     // sub-intervals no longer than 0.4 times the distance to the branch points
-    // l = +-ic of the integrand, nor than V = 2 - r0: the shell integrand is of
-    // order V^4 on the edge, and a sub-interval longer than V would let the
-    // polynomial in U = 2 - S grow far beyond that inside the ellipse of
-    // analyticity that bounds the Gauss-Legendre error
-    const float Vs = 2.0f - r0;
-    if (q0) {
-        const float len = part_len(qa0, qb0);
-        n0 = min(max((int)ceilf(len * rcp_f32(fminf(0.4f * qd0, Vs))), 1), 32);
-        hl0 = 0.5f * len * rcp_f32((float)n0);
+    // l = +-ic of the integrand (c < 1: to the inner piece's sphere), nor than
+    // V = 2 - r0: the shell integrand is of order V^4 on the edge, and a
+    // sub-interval longer than V would let the polynomial in U = 2 - S grow far
+    // beyond that inside the ellipse of analyticity that bounds the
+    // Gauss-Legendre error
+    float hl0 = 0.0f, hl1 = 0.0f, end0 = 0.0f, end1 = 0.0f;  // half-lengths, twice the numbers of sub-intervals
+    if (lane_in(shell_a)) {
+        const float r_len = lane_in(inner) ? wall.r_len : rcp_f32(fminf(0.4f * sqrt_f32(c2), 2.0f - r0));
+        const float n = __builtin_amdgcn_fmed3f(ceilf(len_a * r_len), 1.0f, 32.0f);
+        hl0 = 0.5f * len_a * rcp_f32(n);
+        end0 = n + n;
     }
-    if (q1) {
-        const float len = part_len(qa1, qb1);
-        n1 = min(max((int)ceilf(len * rcp_f32(fminf(0.4f, Vs))), 1), 32);
-        hl1 = 0.5f * len * rcp_f32((float)n1);
+    if (lane_in(shell_b)) {
+        const float n = __builtin_amdgcn_fmed3f(ceilf(len_b * wall.r_len), 1.0f, 32.0f);
+        hl1 = 0.5f * len_b * rcp_f32(n);
+        end1 = n + n;
     }
-    const int nq = n0 + n1;
-    for (int kk = 0; __ballot(kk < nq) != 0; kk++) {
-        const bool want = kk < nq;
-        const int slot = wave_push(want, nQ);
-        if (want) {
-            const bool first = kk < n0;
-            const float hl = first ? hl0 : hl1;
+    // both parts' sub-intervals in one uniform loop: midpoints from + at hl, at = 1, 3, 5, ... below the part's end
+    const float end = end0 + end1;
+    for (float step = 1.0f;; step += 2.0f) {
+        const uint64_t m = mask_of(step < end);
+        if (m == 0) break;
+        const int slot = wave_push(m, nQ);
+        ww.quads += __popcll(m);
+        if (lane_in(m)) {
+            const float past = step - end0;
+            const bool second = past > 0.0f;
+            const float hl = second ? hl1 : hl0;
             W.qd[0][slot] = r0;
-            W.qd[1][slot] = sg < 0.0f ? -R0 : R0;
-            W.qd[2][slot] = first ? qa0 + (2.0f * (float)kk + 1.0f) * hl0 : qa1 + (2.0f * (float)(kk - n0) + 1.0f) * hl1;
+            W.qd[1][slot] = sR0;
+            W.qd[2][slot] = fmaf(hl, second ? past : step, second ? ib : ca);
             W.qd[3][slot] = hl;
-            W.qd_o[slot] = (uint8_t)lane;
+            W.qd_o[slot] = (uint32_t)lane;
         }
-        run_stack<2>(W, nQ, lane, false, wk);
+        run_stack<2>(W, nQ, lane, false);
     }
 }
 
@@ -978,14 +1013,26 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
     WaveStacks &W = stacks[threadIdx.x >> 6];
     int probe = 0;
     int cur = MULTI ? -1 : 0;
-    Work wk;
+    Work wk;      // walls and edges, per lane
+    WaveWork ww;  // the rest
+    auto flush = [&](unsigned long long *counters) {
+        if (lane == 0) {
+            wk.eterms = ww.eterms;
+            wk.moments = ww.moments;
+            wk.quads = ww.quads;
+            wk.qpoints = 4 * ww.quads;
+            wk.angles = ww.angles;
+        }
+        flush_work(wk, counters);
+        wk = Work();
+        ww = WaveWork();
+    };
     for (;;) {
         const int64_t t = next_tile_xcd(tile_ctr + 16, A.n_tiles, probe, lane);
         if (t < 0) break;
         const int jj = MULTI ? job_of_tile(A, t) : 0;
         if (MULTI && jj != cur) {
-            if (cur >= 0) flush_work(wk, A.table[cur].counters);
-            wk = Work();
+            if (cur >= 0) flush(A.table[cur].counters);
             cur = jj;
         }
         const FixList fx = {JOB(fix_count), JOB(fix_items), JOB(fix_cap), nullptr};
@@ -1009,52 +1056,69 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
             s_end = (int32_t)fvo[cfo[c + 1]];
         }
         W.acc[lane] = 0.0;
-        W.ev[lane] = 0.0f;
+        W.ev[lane] = 0.0;
         int32_t face_end = s;  // first slot past the current wall: the first step opens the cell's first wall
-        const int n_steps = wave_max((int)(s_end - s));
+        const int n_steps = __builtin_amdgcn_readfirstlane(wave_max((int)(s_end - s)));
+        const EdgeRec *ep = edges + s;
         int nA = 0, nP = 0, nQ = 0;
         double acc_in = 0.0;  // this lane's terms taken in place (not as tasks)
         float ev_in = 0.0f;   // the sum of their squares
-        bool inside = true;
-        int n_on = 0;  // walls whose plane holds the particle
-        bool face_ok = false;
-        double r0d = 0.0;
-        float r0 = 0.0f, Ht = 0.0f, dH = 0.0f, fsign = 1.0f;
-        for (int it = 0; it < n_steps; it++, s++) {
-            const bool valid = s < s_end;
-            if (valid && s == face_end) {
-                j++;
-                face_end = (int32_t)fvo[j + 1];
-                const double d = plane[4 * j + 3] - (plane[4 * j] * px + plane[4 * j + 1] * py + plane[4 * j + 2] * pz);
-                wk.faces++;
-                const bool in_j = d >= 0.0;
-                inside = inside && in_j;
-                n_on += d == 0.0 ? 1 : 0;
-                fsign = in_j ? 1.0f : -1.0f;
-                r0d = fabs(d) * invh;
-                face_ok = r0d < 2.0;
-                r0 = (float)r0d;
-                Ht = pi_H<float>(r0);
-                dH = pi_dH<float>(r0);
+        unsigned at_walls = 0;  // walls whose plane holds the particle; top bit: it is outside of a wall
+        MixedWall wall;
+        for (int it = 0; it < n_steps; it++, s++, ep++) {
+            if (s == face_end) {
+                wall.r_len = 0.0f;
+                face_end = -1;
+                if (s < s_end) {
+                    j++;
+                    face_end = (int32_t)fvo[j + 1];
+                    const double d =
+                        plane[4 * j + 3] - (plane[4 * j] * px + plane[4 * j + 1] * py + plane[4 * j + 2] * pz);
+                    wk.faces++;
+                    const bool in_j = d >= 0.0;
+                    at_walls = (at_walls + (d == 0.0)) | (in_j ? 0u : 0x80000000u);
+                    const double r0d = fabs(d) * invh;
+                    const float r0 = (float)r0d;
+                    wall.sbit = in_j ? 0u : 0x80000000u;
+                    wall.r0 = r0;
+                    wall.nHt = -pi_H<float>(r0);
+                    wall.dH = pi_dH<float>(r0);
+                    wall.c2_min = fabsf(r0 - 1.0f) < 9.5367431640625e-07f ? NAN : 8.673617379884035e-19f;
+                    if (r0d < 2.0) {
+                        wall.r_len = rcp_f32(fminf(0.4f, 2.0f - r0));
+                        wk.edges += face_end - s;
+                    }
+                }
             }
-            mixed_edge_step(W, lane, wk, nA, nP, nQ, valid && face_ok, edges, s, px, py, pz, invh, r0d, r0, Ht, dH,
-                            fsign, k, fx, acc_in, ev_in);
+            const uint64_t live = mask_of(wall.r_len != 0.0f);
+            double E[10];  // the edge record; some value or other in a lane without one
+#pragma unroll
+            for (int q = 0; q < 10; q++) asm volatile("" : "=v"(E[q]));
+            if (lane_in(live)) {
+                const double *from = reinterpret_cast<const double *>(ep);
+#pragma unroll
+                for (int q = 0; q < 10; q++) E[q] = from[q];
+            }
+            mixed_edge_step(W, lane, ww, nA, nP, nQ, live,
+                            EdgeRec{E[0], E[1], E[2], E[3], E[4], E[5], E[6], E[7], E[8], E[9]}, s, px, py, pz, invh,
+                            wall, k, fx, acc_in, ev_in);
         }
-        run_stack<0>(W, nA, lane, true, wk);
-        run_stack<1>(W, nP, lane, true, wk);
-        run_stack<2>(W, nQ, lane, true, wk);
+        const bool inside = at_walls < 0x80000000u;
+        run_stack<0>(W, nA, lane, true);
+        run_stack<1>(W, nP, lane, true);
+        run_stack<2>(W, nQ, lane, true);
         lds_sync_wave();
         if (active) {
             const double v = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
             JOB(f)[k] = v;
             if (JOB(S)) atomicAdd(JOB(S) + JOB(pair_p)[k], fixed52(v));
             float *const err = JOB(err);  // null when no estimate is wanted (the autotuner's timing runs)
-            if (err) err[k] = kTermErr * kInvPiF * sqrt_f32(ev_in + W.ev[lane]);
-            if (inside && n_on >= 2) push_fix(fx, k, kWindingSlot);
+            if (err) err[k] = kTermErr * kInvPiF * sqrt_f32(ev_in + (float)W.ev[lane]);
+            if (inside && at_walls >= 2) push_fix(fx, k, kWindingSlot);
         }
         lds_sync_wave();
     }
-    if (cur >= 0) flush_work(wk, MULTI ? A.table[cur].counters : A.one.counters);
+    if (cur >= 0) flush(MULTI ? A.table[cur].counters : A.one.counters);
 }
 
 // FP64 form of the task batches: the beyond parts' angle (or the shell parts',

@@ -5,16 +5,18 @@
 
 namespace em {
 
-// Slot of this lane in a wave-wide push (lanes with want = true, in lane
-// order); count (wave-uniform) grows by the number of pushing lanes.  Call in
+// Slot of this lane in a wave-wide push (lanes in the mask, or with want = true,
+// in lane order); count (wave-uniform) grows by the number of pushing lanes.  Call in
 // wave-uniform control flow.
-__device__ __forceinline__ int wave_push(bool want, int &count)
+__device__ __forceinline__ int wave_push(uint64_t m, int &count)
 {
-    const unsigned long long m = __ballot(want);
-    const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-    const int slot = count + below;
+    const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)count));
     count += __popcll(m);
     return slot;
+}
+__device__ __forceinline__ int wave_push(bool want, int &count)
+{
+    return wave_push(__builtin_amdgcn_ballot_w64(want), count);
 }
 
 // Orders LDS writes of one wavefront before its later reads by other lanes.
