@@ -807,6 +807,20 @@ struct WaveWork {
     unsigned eterms = 0, moments = 0, quads = 0, angles = 0;
 };
 
+__device__ __forceinline__ void flush_wave_work(Work &wk, WaveWork &ww, int lane, unsigned long long *counters)
+{
+    if (lane == 0) {
+        wk.eterms = ww.eterms;
+        wk.moments = ww.moments;
+        wk.quads = ww.quads;
+        wk.qpoints = 4 * ww.quads;
+        wk.angles = ww.angles;
+    }
+    flush_work(wk, counters);
+    wk = Work();
+    ww = WaveWork();
+}
+
 // Lane masks: one bit per lane in a scalar register pair, so that logic on them is scalar.
 __device__ __forceinline__ uint64_t mask_of(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
@@ -815,6 +829,10 @@ __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_in
 __device__ __forceinline__ float flip_sign(float x, uint32_t sbit)
 {
     return __uint_as_float(__float_as_uint(x) ^ sbit);
+}
+__device__ __forceinline__ double flip_sign(double x, uint32_t sbit)
+{
+    return __hiloint2double((int)((uint32_t)__double2hiint(x) ^ sbit), __double2loint(x));
 }
 
 // One step of the mixed task batches: this lane's edge E (record s of the edge
@@ -1015,18 +1033,7 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
     int cur = MULTI ? -1 : 0;
     Work wk;      // walls and edges, per lane
     WaveWork ww;  // the rest
-    auto flush = [&](unsigned long long *counters) {
-        if (lane == 0) {
-            wk.eterms = ww.eterms;
-            wk.moments = ww.moments;
-            wk.quads = ww.quads;
-            wk.qpoints = 4 * ww.quads;
-            wk.angles = ww.angles;
-        }
-        flush_work(wk, counters);
-        wk = Work();
-        ww = WaveWork();
-    };
+    auto flush = [&](unsigned long long *counters) { flush_wave_work(wk, ww, lane, counters); };
     for (;;) {
         const int64_t t = next_tile_xcd(tile_ctr + 16, A.n_tiles, probe, lane);
         if (t < 0) break;
@@ -1135,13 +1142,11 @@ struct WaveStacks64 {
 constexpr int kShellPart = 64;
 
 template <int KIND>
-__device__ __forceinline__ void run_one64(WaveStacks64 &W, int i, Work &wk)
+__device__ __forceinline__ void run_one64(WaveStacks64 &W, int i)
 {
     if (KIND == 0) {
-        wk.angles++;
         atomicAdd(&W.acc[W.ang_o[i]], W.ang[2][i] * atan2_f64(W.ang[0][i], W.ang[1][i]));
     } else {
-        wk.moments++;
         const double sR0 = W.pnt[1][i];
         const int o = W.pnt_o[i];
         const double v = part_term(W.pnt[0][i], fabs(sR0), W.pnt[2][i], W.pnt[3][i], (o & kShellPart) != 0);
@@ -1150,17 +1155,17 @@ __device__ __forceinline__ void run_one64(WaveStacks64 &W, int i, Work &wk)
 }
 
 template <int KIND>
-__device__ __forceinline__ void run_stack64(WaveStacks64 &W, int &count, int lane, bool all, Work &wk)
+__device__ __forceinline__ void run_stack64(WaveStacks64 &W, int &count, int lane, bool all)
 {
     if (count >= 64) {
         lds_sync_wave();
-        run_one64<KIND>(W, count - 64 + lane, wk);
+        run_one64<KIND>(W, count - 64 + lane);
         count -= 64;
         lds_sync_wave();
     }
     if (all && count > 0) {
         lds_sync_wave();
-        if (lane < count) run_one64<KIND>(W, lane, wk);
+        if (lane < count) run_one64<KIND>(W, lane);
         count = 0;
         lds_sync_wave();
     }
@@ -1168,8 +1173,9 @@ __device__ __forceinline__ void run_stack64(WaveStacks64 &W, int &count, int lan
 
 // Bound by FP64 VALU issue: 0.20 vector instructions per SIMD and clock (a
 // dense FMA stream reaches 0.235), 81 % of the lanes active; 10.2e6 pairs of a
-// clumpy cloud take 10.2 ms, and took 20.2 ms with two closed-form points per
-// part, an angle task per part and the library's double functions.  WPE:
+// clumpy cloud take 9.8 ms (10.1 with lane predicates instead of masks), and took
+// 20.2 ms with two closed-form points per part, an angle task per part and the
+// library's double functions.  WPE:
 // resident wavefronts per SIMD the register budget is cut for (3: 167 VGPRs;
 // 2 waves 12.2 ms; a budget for 4 spills 60 to 100 registers, 27.7 ms).
 template <int WPE, bool MULTI>
@@ -1180,14 +1186,15 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
     WaveStacks64 &W = stacks[threadIdx.x >> 6];
     int probe = 0;
     int cur = MULTI ? -1 : 0;
-    Work wk;
+    Work wk;      // walls and edges, per lane
+    WaveWork ww;  // the rest
+    auto flush = [&](unsigned long long *counters) { flush_wave_work(wk, ww, lane, counters); };
     for (;;) {
         const int64_t t = next_tile_xcd(tile_ctr + 16, A.n_tiles, probe, lane);
         if (t < 0) break;
         const int jj = MULTI ? job_of_tile(A, t) : 0;
         if (MULTI && jj != cur) {
-            if (cur >= 0) flush_work(wk, A.table[cur].counters);
-            wk = Work();
+            if (cur >= 0) flush(A.table[cur].counters);
             cur = jj;
         }
         const EdgeRec *__restrict__ edges = JOB(edges);
@@ -1211,105 +1218,114 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
         }
         W.acc[lane] = 0.0;
         int32_t face_end = s;
-        const int n_steps = wave_max((int)(s_end - s));
+        const int n_steps = __builtin_amdgcn_readfirstlane(wave_max((int)(s_end - s)));
+        const EdgeRec *ep = edges + s;
         int nA = 0, nP = 0;
-        bool inside = true;
-        int n_on = 0;  // walls whose plane holds the particle
+        unsigned at_walls = 0;  // walls whose plane holds the particle; top bit: it is outside of a wall
         bool face_ok = false;
-        double r0 = 0.0, Ht = 0.0, dH = 0.0, fsign = 1.0;
+        uint32_t wall_sign = 0;
+        double r0 = 0.0, nHt = 0.0, dH = 0.0;
         double acc_in = 0.0;  // this lane's angle terms taken in place
-        for (int it = 0; it < n_steps; it++, s++) {
-            const bool valid = s < s_end;
-            if (valid && s == face_end) {
-                j++;
-                face_end = (int32_t)fvo[j + 1];
-                const double d = plane[4 * j + 3] - (plane[4 * j] * px + plane[4 * j + 1] * py + plane[4 * j + 2] * pz);
-                wk.faces++;
-                const bool in_j = d >= 0.0;
-                inside = inside && in_j;
-                n_on += d == 0.0 ? 1 : 0;
-                fsign = in_j ? 1.0 : -1.0;
-                r0 = fabs(d) * invh;
-                face_ok = r0 < 2.0;
-                Ht = pi_H<double>(r0);
-                dH = pi_dH<double>(r0);
-            }
-            bool live = valid && face_ok;
-            double R0 = 0.0, la = 0.0, lb = 0.0, Le = 0.0, sg = 0.0;
-            if (live) {
-                const EdgeRec E = edges[s];
-                const double wx = px - E.vx, wy = py - E.vy, wz = pz - E.vz;
-                const double rho = E.mx * wx + E.my * wy + E.mz * wz;
-                wk.edges++;
-                if (rho == 0.0) {
-                    live = false;
-                } else {
-                    la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
-                    Le = E.L * invh;
-                    lb = la + Le;
-                    R0 = fabs(rho) * invh;
-                    sg = (rho > 0.0 ? 1.0 : -1.0) * fsign;
+        for (int it = 0; it < n_steps; it++, s++, ep++) {
+            if (s == face_end) {
+                face_ok = false;
+                face_end = -1;
+                if (s < s_end) {
+                    j++;
+                    face_end = (int32_t)fvo[j + 1];
+                    const double d =
+                        plane[4 * j + 3] - (plane[4 * j] * px + plane[4 * j + 1] * py + plane[4 * j + 2] * pz);
+                    wk.faces++;
+                    const bool in_j = d >= 0.0;
+                    at_walls = (at_walls + (d == 0.0)) | (in_j ? 0u : 0x80000000u);
+                    wall_sign = in_j ? 0u : 0x80000000u;
+                    r0 = fabs(d) * invh;
+                    face_ok = r0 < 2.0;
+                    if (face_ok) wk.edges += face_end - s;
+                    nHt = -pi_H<double>(r0);
+                    dH = pi_dH<double>(r0);
                 }
             }
-            const EdgeParts P = edge_parts(live, r0, R0, la, lb);
-            if (P.near) wk.eterms++;
-            const bool has_b = live && (la < P.ca || P.cb < lb);
-            const bool has_s = P.near && dH != 0.0 && (P.ca < P.ia || P.ib < P.cb);
-            {
-                const double a1 = has_b ? la : P.ca, b1 = has_b ? P.ca : P.ia;
-                const double a2 = has_b ? P.cb : P.ib, b2 = has_b ? lb : P.cb;
-                double y, x;
-                angle_product(R0, a1, b1, a2, b2, y, x);
-                const double w = has_b ? -Ht : (has_s ? dH : 0.0);
-                acc_in = fma(w * sg, atan2_f64(y, x), acc_in);
+            uint64_t live = mask_of(face_ok);
+            double E[10];  // the edge record (EdgeRec's order); some value or other in a lane without one
+#pragma unroll
+            for (int q = 0; q < 10; q++) asm volatile("" : "=v"(E[q]));
+            if (lane_in(live)) {
+                const double *from = reinterpret_cast<const double *>(ep);
+#pragma unroll
+                for (int q = 0; q < 10; q++) E[q] = from[q];
             }
-            wk.angles += (has_b || has_s) ? 1u : 0u;
+            const double wx = px - E[0], wy = py - E[1], wz = pz - E[2];
+            const double rho = E[7] * wx + E[8] * wy + E[9] * wz;
+            live &= mask_of(rho != 0.0);
+            const double la = -(E[4] * wx + E[5] * wy + E[6] * wz) * invh;
+            const double Le = E[3] * invh, lb = la + Le;
+            const double R0 = fabs(rho) * invh;
+            const uint32_t sbit = ((uint32_t)__double2hiint(rho) ^ wall_sign) & 0x80000000u;  // of the edge's terms
+            const EdgeParts P = edge_parts(lane_in(live), r0, R0, la, lb);
+            const uint64_t near = mask_of(P.near);
+            const uint64_t cut_a = mask_of(la < P.ca), cut_b = mask_of(P.cb < lb);  // (else ca = la, cb = lb)
+            const uint64_t shell_a = near & mask_of(P.ca < P.ia), shell_b = near & mask_of(P.ib < P.cb);
+            const uint64_t has_b = live & (cut_a | cut_b);
+            const uint64_t has_s = (shell_a | shell_b) & mask_of(dH != 0.0);
+            ww.eterms += __popcll(near);
+            ww.angles += __popcll(has_b) + __popcll(has_s);
             {
-                const bool want = has_b && has_s;
-                const unsigned long long m = __ballot(want);
+                // the parts [la, b1] and [a2, lb] (a lane without beyond parts has ca = la and cb = lb)
+                const double b1 = lane_in(has_b) ? P.ca : P.ia, a2 = lane_in(has_b) ? P.cb : P.ib;
+                double y, x;
+                angle_product(R0, la, b1, a2, lb, y, x);
+                const double w = lane_in(has_b) ? nHt : (lane_in(has_s) ? dH : 0.0);
+                const double v = flip_sign(w, sbit) * atan2_f64(y, x);
+                acc_in += lane_in(live) ? v : 0.0;
+            }
+            {
+                const uint64_t m = has_b & has_s;
                 if (m != 0) {
-                    if (nA + __popcll(m) > kQA) run_stack64<0>(W, nA, lane, true, wk);
-                    const int slot = wave_push(want, nA);
-                    if (want) {
+                    if (nA + __popcll(m) > kQA) run_stack64<0>(W, nA, lane, true);
+                    const int slot = wave_push(m, nA);
+                    if (lane_in(m)) {
                         double y, x;
                         angle_product(R0, P.ca, P.ia, P.ib, P.cb, y, x);
                         W.ang[0][slot] = y;
                         W.ang[1][slot] = x;
-                        W.ang[2][slot] = sg * dH;
+                        W.ang[2][slot] = flip_sign(dH, sbit);
                         W.ang_o[slot] = (uint8_t)lane;
                     }
                 }
             }
-            auto push_part = [&](double x, double y, int kind) {
-                const bool want = P.near && y > x;
-                if (__ballot(want) == 0) return;
-                const int slot = wave_push(want, nP);
-                if (want) {
+            auto push_part = [&](uint64_t m, double x, double len, int kind) {
+                if (m == 0) return;
+                const int slot = wave_push(m, nP);
+                ww.moments += __popcll(m);
+                if (lane_in(m)) {
                     W.pnt[0][slot] = r0;
-                    W.pnt[1][slot] = sg < 0.0 ? -R0 : R0;
+                    W.pnt[1][slot] = flip_sign(R0, sbit);
                     W.pnt[2][slot] = x;
-                    W.pnt[3][slot] = part_len(x, y, la, lb, Le);
+                    W.pnt[3][slot] = len;
                     W.pnt_o[slot] = (uint8_t)(lane + kind);
                 }
             };
-            push_part(P.ca, P.ia, kShellPart);
-            push_part(P.ia, P.ib, 0);
-            if (nP > kQP - 64) run_stack64<1>(W, nP, lane, false, wk);
-            push_part(P.ib, P.cb, kShellPart);
-            while (nP >= 64) run_stack64<1>(W, nP, lane, false, wk);
+            const uint64_t ia_end = mask_of(P.ia == lb), ib_start = mask_of(P.ib == la);
+            push_part(shell_a, P.ca, lane_in(~cut_a & ia_end) ? Le : P.ia - P.ca, kShellPart);
+            push_part(near & mask_of(P.ia < P.ib), P.ia, part_len(P.ia, P.ib, la, lb, Le), 0);
+            if (nP > kQP - 64) run_stack64<1>(W, nP, lane, false);
+            push_part(shell_b, P.ib, lane_in(~cut_b & ib_start) ? Le : P.cb - P.ib, kShellPart);
+            while (nP >= 64) run_stack64<1>(W, nP, lane, false);
         }
-        run_stack64<0>(W, nA, lane, true, wk);
-        run_stack64<1>(W, nP, lane, true, wk);
+        const bool inside = at_walls < 0x80000000u;
+        run_stack64<0>(W, nA, lane, true);
+        run_stack64<1>(W, nP, lane, true);
         lds_sync_wave();
         if (active) {
             const double v = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
             JOB(f)[k] = v;
             if (JOB(S)) atomicAdd(JOB(S) + JOB(pair_p)[k], fixed52(v));
-            if (inside && n_on >= 2) push_fix(FixList{JOB(fix_count), JOB(fix_items), JOB(fix_cap), nullptr}, k, kWindingSlot);
+            if (inside && at_walls >= 2) push_fix(FixList{JOB(fix_count), JOB(fix_items), JOB(fix_cap), nullptr}, k, kWindingSlot);
         }
         lds_sync_wave();
     }
-    if (cur >= 0) flush_work(wk, MULTI ? A.table[cur].counters : A.one.counters);
+    if (cur >= 0) flush(MULTI ? A.table[cur].counters : A.one.counters);
 }
 #undef JOB
 
