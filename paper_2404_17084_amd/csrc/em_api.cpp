@@ -134,9 +134,9 @@ void prepare(Ctx &C, Workspace &ws, const map_particles_in *p, const map_cells_i
     in.vol = c->cell_volume ? stage(ws, S_VOL, c->cell_volume, c->n_cells, c->mem_kind, s) : nullptr;
 
     flags = ws.get<unsigned>(S_FLAGS, 4);
-    counters = ws.get<int64_t>(S_COUNTERS, C_NUM);
+    counters = ws.get<int64_t>(S_COUNTERS, kCounterCopies * kCounterStride);
     fill_zero_bytes(flags, sizeof(unsigned) * 4, s);
-    fill_zero_bytes(counters, sizeof(int64_t) * C_NUM, s);
+    fill_zero_bytes(counters, sizeof(int64_t) * kCounterCopies * kCounterStride, s);
     launch_validate(in, flags, s);
     unsigned hf = 0;
     EM_HIP(hipMemcpyAsync(&hf, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
@@ -184,7 +184,7 @@ void stage_pairs(Ctx &C, Workspace &ws, const map_particles_in *p, const map_cel
     js.err = precision == MAP_MIXED ? ws.get<float>(S_ERR, (size_t)(np > 0 ? np : 1)) : nullptr;
     js.S = ws.get<double>(S_S, (size_t)(js.in.n > 0 ? js.in.n : 1));
     fill_zero_bytes(js.S, sizeof(double) * js.in.n, s);
-    js.tile_ctr = ws.get<uint32_t>(S_TILE_CTR, 64);
+    js.tile_ctr = ws.get<uint32_t>(S_TILE_CTR, kLaunchCtrs);
     js.fix_cap = C.config.fixup_cap > 0 ? C.config.fixup_cap : np / 8 + 65536;
     js.fix_items = ws.get<uint64_t>(S_FIX_ITEMS, (size_t)js.fix_cap);
     fill_zero_bytes(js.tile_ctr, 2 * sizeof(unsigned), s);
@@ -293,12 +293,14 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
         }
     }
     double hred[4] = {0, 0, 0, 0};
-    int64_t hcnt[C_NUM];
+    int64_t hcopies[kCounterCopies][kCounterStride], hcnt[C_NUM] = {};
     unsigned hf = 0;
     EM_HIP(hipMemcpyAsync(hred, red, sizeof(hred), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(hcnt, js.counters, sizeof(hcnt), hipMemcpyDeviceToHost, s));
+    EM_HIP(hipMemcpyAsync(hcopies, js.counters, sizeof(hcopies), hipMemcpyDeviceToHost, s));
     EM_HIP(hipMemcpyAsync(&hf, js.flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
     stream_sync(s);
+    for (const auto &copy : hcopies)
+        for (int q = 0; q < C_NUM; q++) hcnt[q] += copy[q];
     EM_CHECK(hf == 0, flag_code(hf), flag_text(hf));
     if (st) {
         std::memset(st, 0, sizeof(*st));

@@ -151,6 +151,13 @@ enum : int {
     C_FP64_PAIRS = 10,  // mixed path: pairs recomputed in FP64 because their cell's error estimate was too large
     C_NUM = 11
 };
+// The counters are kept in copies, a cache line each, that the host adds up:
+// additions from all over the chip to one line are done one after the other
+// (about 10 ns each).  Kernels take the copy of their workgroup (counter_copy).
+constexpr int kCounterCopies = 16, kCounterStride = 16;
+// Counters of a persistent launch: [0] tiles, [1] fixups, and from [32] on the
+// tiles of each XCD's eighth, a cache line each.
+constexpr int kXcdCtr = 32, kXcdCtrStride = 32, kLaunchCtrs = kXcdCtr + 8 * kXcdCtrStride;
 
 // Device-resident view of one job's inputs.
 struct DevInputs {
@@ -277,7 +284,7 @@ struct JobsArg {
 // One persistent launch of the task-batch kernel (distribution 3) of
 // `precision` over n_jobs jobs: h_jobs is the host table (checked: tile bases
 // are the running tile counts), d_jobs its device copy (needed when
-// n_jobs > 1, read by the kernel).  tile_ctr: 24 counters of the launch,
+// n_jobs > 1, read by the kernel).  tile_ctr: kLaunchCtrs counters of the launch,
 // zeroed here.  A pair's result does not depend on the other jobs.
 void launch_integrate_jobs(const IntJob *h_jobs, const IntJob *d_jobs, int n_jobs, int precision,
                            const IntegrateTune &tune, unsigned *tile_ctr, hipStream_t s);

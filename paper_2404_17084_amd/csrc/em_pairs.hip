@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(256) k_candidates(
                 ccount[c0 + g] = count[g];
                 most = most > count[g] ? most : count[g];
             }
-        if (most > 0) atomicMax(max_count, (unsigned)most);
+        if (most > K) atomicMax(max_count, (unsigned)most);  // (asked for only where it is more than K)
     }
 }
 
@@ -567,7 +567,7 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
     if (threadIdx.x == 0) {
         unsigned all = 0;
         for (int w = 0; w < kExactWaves; w++) all += tested[w];
-        if (all > 0) atomicAdd(n_tested, (unsigned long long)all);
+        if (all > 0) atomicAdd(counter_copy(n_tested), (unsigned long long)all);
     }
 }
 

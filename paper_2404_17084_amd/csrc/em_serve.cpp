@@ -103,7 +103,7 @@ struct Server {
     hipEvent_t bevent = nullptr;
     IntJob *d_table = nullptr;  // device job tables, one region of max_jobs entries per precision
     IntJob *h_table = nullptr;  // pinned host copies (rewritten only while no launch is in flight)
-    unsigned *d_ctr = nullptr;  // launch counters, 32 per precision
+    unsigned *d_ctr = nullptr;  // launch counters, kLaunchCtrs per precision
     int table_cap = 0;
     std::vector<Job *> batch;   // jobs of the launch in flight
     Clock::time_point batch_t0;
@@ -339,7 +339,7 @@ static bool launch_batch(Server &S)
                 if (n == 0) continue;
                 IntJob *dt = S.d_table + (size_t)prec * S.table_cap;
                 EM_HIP(hipMemcpyAsync(dt, ht, sizeof(IntJob) * (size_t)n, hipMemcpyHostToDevice, S.bstream));
-                launch_integrate_jobs(ht, dt, n, prec, S.tune[prec], S.d_ctr + 32 * prec, S.bstream);
+                launch_integrate_jobs(ht, dt, n, prec, S.tune[prec], S.d_ctr + kLaunchCtrs * prec, S.bstream);
                 launched.insert(launched.end(), members.begin(), members.end());
             }
             if (!launched.empty()) EM_HIP(hipEventRecord(S.bevent, S.bstream));
@@ -476,7 +476,7 @@ static Server &server_of(Ctx &C)
     EM_HIP(hipEventCreateWithFlags(&S->bevent, hipEventDisableTiming));
     EM_HIP(hipMalloc(&S->d_table, 2 * sizeof(IntJob) * (size_t)S->table_cap));
     EM_HIP(hipHostMalloc(&S->h_table, 2 * sizeof(IntJob) * (size_t)S->table_cap, hipHostMallocDefault));
-    EM_HIP(hipMalloc(&S->d_ctr, 64 * sizeof(unsigned)));
+    EM_HIP(hipMalloc(&S->d_ctr, 2 * kLaunchCtrs * sizeof(unsigned)));
     for (int i = 0; i < n_slots; i++) {
         S->slots.push_back(std::make_unique<ServeSlot>(C.device));
         S->slots.back()->ws.use_stream(S->sstream);

@@ -155,11 +155,11 @@ __global__ void __launch_bounds__(256) k_integrate_table(int64_t np, const uint3
     unsigned long long v[3] = {n_faces, n_edges, n_terms};
     for (int u = 0; u < 3; u++)
         for (int o = 32; o > 0; o >>= 1) v[u] += __shfl_xor(v[u], o, 64);
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(counters + C_FACES, v[0]);
-        atomicAdd(counters + C_EDGES, v[1]);
-        atomicAdd(counters + C_EDGE_TERMS, v[2]);
-    }
+    // lane q brings the q-th (one atomic instruction on one cache line)
+    const int lane = threadIdx.x & 63;
+    if (lane < 3)
+        atomicAdd(counter_copy(counters) + (lane == 0 ? C_FACES : (lane == 1 ? C_EDGES : C_EDGE_TERMS)),
+                  lane == 0 ? v[0] : (lane == 1 ? v[1] : v[2]));
 }
 
 }  // namespace

@@ -126,7 +126,7 @@ extern "C" int map_autotune(map_ctx *h, const map_particles_in *p, const map_cel
         const int64_t np = ps.n_pairs;
         EM_CHECK(np > 0, MAP_EINVAL, "no pairs to tune on");
         double *f = ws.get<double>(S_F, (size_t)np);
-        uint32_t *tile_ctr = ws.get<uint32_t>(S_TILE_CTR, 64);
+        uint32_t *tile_ctr = ws.get<uint32_t>(S_TILE_CTR, kLaunchCtrs);
         const int64_t fix_cap = np / 8 + 65536;
         uint64_t *fix_items = ws.get<uint64_t>(S_FIX_ITEMS, (size_t)fix_cap);
         const int wv64[] = {2, 3};

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "em_internal.h"
+
 namespace em {
 
 // Slot of this lane in a wave-wide push (lanes in the mask, or with want = true,
@@ -62,6 +64,12 @@ __device__ __forceinline__ double wave_reduce(double v, double identity, Op op)
 __device__ __forceinline__ unsigned long long fixed52(double f)
 {
     return (unsigned long long)__double2ll_rn(f * 4503599627370496.0);
+}
+
+// This workgroup's copy of the counters (em_internal.h).
+__device__ __forceinline__ unsigned long long *counter_copy(unsigned long long *counters)
+{
+    return counters + (blockIdx.x % (unsigned)kCounterCopies) * (unsigned)kCounterStride;
 }
 
 // Logical index of this workgroup in an XCD-aware order.  Workgroups are
