@@ -1047,6 +1047,13 @@ __device__ __forceinline__ int job_of_tile(const JobsArg &A, int64_t t)
 // of the cell; see em_boundary.h).
 constexpr uint32_t kWindingSlot = 0xffffffffu;
 
+// The states of two lanes that walked different walls of one pair: counts of
+// walls whose plane holds the particle, and the top bit (outside of a wall).
+__device__ __forceinline__ unsigned join_walls(unsigned a, unsigned b)
+{
+    return ((a & 0x7fffffffu) + (b & 0x7fffffffu)) | ((a | b) & 0x80000000u);
+}
+
 template <int WPE, bool MULTI>
 __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsigned *tile_ctr)
 {
@@ -1070,7 +1077,8 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
         const EdgeRec *__restrict__ edges = JOB(edges);
         const double *__restrict__ plane = JOB(plane);
         const int64_t *__restrict__ fvo = JOB(fvo);
-        const int64_t k = (t - JOB(tile_base)) * 64 + lane;
+        const int sh = JOB(split), part = lane & ((1 << sh) - 1);  // 2^sh neighbouring lanes share a pair
+        const int64_t k = (t - JOB(tile_base)) * (64 >> sh) + (lane >> sh);
         const bool active = k < JOB(np);
         double px = 0.0, py = 0.0, pz = 0.0, invh = 1.0;
         int32_t s = 0, s_end = 0, j = 0;
@@ -1082,9 +1090,10 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
             pz = JOB(xyz)[3 * a + 2];
             invh = 1.0 / JOB(h)[a];
             const int64_t *__restrict__ cfo = JOB(cfo);
-            j = (int32_t)cfo[c] - 1;
-            s = (int32_t)fvo[cfo[c]];
-            s_end = (int32_t)fvo[cfo[c + 1]];
+            const int64_t f0 = cfo[c], walls = cfo[c + 1] - f0, from = f0 + ((walls * part) >> sh);
+            j = (int32_t)from - 1;
+            s = (int32_t)fvo[from];
+            s_end = (int32_t)fvo[f0 + ((walls * (part + 1)) >> sh)];
         }
         W.acc[lane] = 0.0;
         W.ev[lane] = 0.0;
@@ -1134,17 +1143,24 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
                             EdgeRec{E[0], E[1], E[2], E[3], E[4], E[5], E[6], E[7], E[8], E[9]}, s, px, py, pz, invh,
                             wall, k, fx, acc_in, ev_in);
         }
-        const bool inside = at_walls < 0x80000000u;
         run_stack<0>(W, nA, lane, true);
         run_stack<1>(W, nP, lane, true);
         run_stack<2>(W, nQ, lane, true);
         lds_sync_wave();
-        if (active) {
-            const double v = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
+        double sum = W.acc[lane] + acc_in;
+        float ev = ev_in + (float)W.ev[lane];
+        for (int o = 1; o < 1 << sh; o <<= 1) {
+            sum += __shfl_xor(sum, o, 64);
+            ev += __shfl_xor(ev, o, 64);
+            at_walls = join_walls(at_walls, __shfl_xor(at_walls, o, 64));
+        }
+        const bool inside = at_walls < 0x80000000u;
+        if (active && part == 0) {
+            const double v = (inside ? 1.0 : 0.0) - sum * kInvPi;
             JOB(f)[k] = v;
             if (JOB(S)) atomicAdd(JOB(S) + JOB(pair_p)[k], fixed52(v));
             float *const err = JOB(err);  // null when no estimate is wanted (the autotuner's timing runs)
-            if (err) err[k] = kTermErr * kInvPiF * sqrt_f32(ev_in + (float)W.ev[lane]);
+            if (err) err[k] = kTermErr * kInvPiF * sqrt_f32(ev);
             if (inside && at_walls >= 2) push_fix(fx, k, kWindingSlot);
         }
         lds_sync_wave();
@@ -1224,7 +1240,8 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
         const EdgeRec *__restrict__ edges = JOB(edges);
         const double *__restrict__ plane = JOB(plane);
         const int64_t *__restrict__ fvo = JOB(fvo);
-        const int64_t k = (t - JOB(tile_base)) * 64 + lane;
+        const int sh = JOB(split), part = lane & ((1 << sh) - 1);  // 2^sh neighbouring lanes share a pair
+        const int64_t k = (t - JOB(tile_base)) * (64 >> sh) + (lane >> sh);
         const bool active = k < JOB(np);
         double px = 0.0, py = 0.0, pz = 0.0, invh = 1.0;
         int32_t s = 0, s_end = 0, j = 0;
@@ -1236,9 +1253,10 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
             pz = JOB(xyz)[3 * a + 2];
             invh = 1.0 / JOB(h)[a];
             const int64_t *__restrict__ cfo = JOB(cfo);
-            j = (int32_t)cfo[c] - 1;
-            s = (int32_t)fvo[cfo[c]];
-            s_end = (int32_t)fvo[cfo[c + 1]];
+            const int64_t f0 = cfo[c], walls = cfo[c + 1] - f0, from = f0 + ((walls * part) >> sh);
+            j = (int32_t)from - 1;
+            s = (int32_t)fvo[from];
+            s_end = (int32_t)fvo[f0 + ((walls * (part + 1)) >> sh)];
         }
         W.acc[lane] = 0.0;
         int32_t face_end = s;
@@ -1337,12 +1355,17 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
             push_part(shell_b, P.ib, lane_in(~cut_b & ib_start) ? Le : P.cb - P.ib, kShellPart);
             while (nP >= 64) run_stack64<1>(W, nP, lane, false);
         }
-        const bool inside = at_walls < 0x80000000u;
         run_stack64<0>(W, nA, lane, true);
         run_stack64<1>(W, nP, lane, true);
         lds_sync_wave();
-        if (active) {
-            const double v = (inside ? 1.0 : 0.0) - (W.acc[lane] + acc_in) * kInvPi;
+        double sum = W.acc[lane] + acc_in;
+        for (int o = 1; o < 1 << sh; o <<= 1) {
+            sum += __shfl_xor(sum, o, 64);
+            at_walls = join_walls(at_walls, __shfl_xor(at_walls, o, 64));
+        }
+        const bool inside = at_walls < 0x80000000u;
+        if (active && part == 0) {
+            const double v = (inside ? 1.0 : 0.0) - sum * kInvPi;
             JOB(f)[k] = v;
             if (JOB(S)) atomicAdd(JOB(S) + JOB(pair_p)[k], fixed52(v));
             if (inside && at_walls >= 2) push_fix(FixList{JOB(fix_count), JOB(fix_items), JOB(fix_cap), nullptr}, k, kWindingSlot);
@@ -1673,7 +1696,7 @@ void build_tiles(Workspace &ws, const DevInputs &in, PairSet &ps, hipStream_t s)
 
 // The task-batch kernels (distribution 3) over one job (its entry passed by
 // value) or several (the table in device memory, h_jobs its host copy): the
-// tile space of a launch is the concatenation of the jobs' tiles of 64 pairs.
+// tile space of a launch is the concatenation of the jobs' tiles.
 static void launch_queued(const IntJob *h_jobs, const IntJob *d_jobs, int n_jobs, int precision,
                           const IntegrateTune &tune, unsigned *tile_ctr, bool zero_ctr, hipStream_t s)
 {
@@ -1683,7 +1706,9 @@ static void launch_queued(const IntJob *h_jobs, const IntJob *d_jobs, int n_jobs
     for (int i = 0; i < n_jobs; i++) {
         EM_CHECK(h_jobs[i].tile_base == tiles && h_jobs[i].np > 0, MAP_EINVAL,
                  "integration job table: tile bases are not the running tile count");
-        tiles += (h_jobs[i].np + 63) / 64;
+        EM_CHECK(h_jobs[i].split == job_split(h_jobs[i].np, precision), MAP_EINVAL,
+                 "integration job table: a job's split is not the one of its size");
+        tiles += job_tiles(h_jobs[i]);
     }
     JobsArg A;
     A.table = d_jobs;
@@ -1751,6 +1776,7 @@ void launch_integrate(const DevInputs &in, const EdgeRec *edges, const PairSet &
     if (tune.persistent == 3) {
         IntJob J;
         J.np = np;
+        J.split = job_split(np, precision);
         J.tile_base = 0;
         J.pair_p = ps.pair_p;
         J.pair_c = ps.pair_c;

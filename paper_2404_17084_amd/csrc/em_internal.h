@@ -256,11 +256,12 @@ int64_t run_pseudo_adaptive(Workspace &ws, const DevParticles &p, const double b
 
 // One job of an integration launch of the task-batch kernels: its pairs
 // (cell-major), inputs, geometry tables and outputs.  tile_base is the job's
-// first tile (64 pairs each) in the launch's tile space, the running sum of
-// the tiles of the jobs before it.
+// first tile (a wavefront's pairs) in the launch's tile space, the running sum
+// of the tiles of the jobs before it.
 struct IntJob {
     int64_t np = 0;
     int64_t tile_base = 0;
+    int split = 0;  // 2^split lanes share a pair, each with its part of the cell's walls (job_split)
     const uint32_t *pair_p = nullptr, *pair_c = nullptr;
     const double *xyz = nullptr, *h = nullptr;
     const int64_t *cfo = nullptr, *fvo = nullptr;
@@ -274,6 +275,17 @@ struct IntJob {
     uint64_t *fix_items = nullptr;
     unsigned fix_cap = 0;
 };
+// How many lanes share a pair, as a power of two.  A wavefront alone on its SIMD
+// is bound by the latency of its ~80 steps (0.18 ms), so where few pairs leave
+// most wavefront slots empty, four lanes take a quarter of a cell's walls each.
+// Calls, whole -> split: mixed, 39,356 pairs 598 -> 486 us, 89,788 587 -> 502,
+// 191,374 649 -> 619, 327,588 767 -> 793, 4.5e6 3.09 -> 4.32 ms; FP64, 39,356 pairs
+// 513 -> 419 us, 191,374 636 -> 603, 412,133 875 -> 843, 696,406 1,154 -> 1,192.  The
+// lines are drawn where the gain is still 15 % and 5 %, since among other jobs
+// the split costs what it costs large ones.  It depends on the job's size alone,
+// so that a pair's result does not depend on the launch.
+inline int job_split(int64_t np, int precision) { return np <= (precision == MAP_FP64 ? 196608 : 98304) ? 2 : 0; }
+inline int64_t job_tiles(const IntJob &j) { return (j.np + (64 >> j.split) - 1) / (64 >> j.split); }
 // Kernel argument: one job by value (n = 1) or a device table of n jobs.
 struct JobsArg {
     const IntJob *table;

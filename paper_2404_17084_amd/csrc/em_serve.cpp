@@ -317,6 +317,7 @@ static bool launch_batch(Server &S)
                     IntJob &e = ht[n++];
                     e = IntJob();
                     e.np = js.ps.n_pairs;
+                    e.split = job_split(e.np, prec);
                     e.tile_base = tiles;
                     e.pair_p = js.ps.pair_p;
                     e.pair_c = js.ps.pair_c;
@@ -333,7 +334,7 @@ static bool launch_batch(Server &S)
                     e.fix_count = js.tile_ctr + 1;
                     e.fix_items = js.fix_items;
                     e.fix_cap = (unsigned)std::min<int64_t>(js.fix_cap, 0xffffffffLL);
-                    tiles += (e.np + 63) / 64;
+                    tiles += job_tiles(e);
                     members.push_back(j);
                 }
                 if (n == 0) continue;
