@@ -4,10 +4,13 @@
 // Tree (Sec. III-A).  An octree over 63-bit Morton keys (21 bits per axis,
 // octal digits (x, y, z) from the most significant).  Particles are sorted by
 // key; dlev[i] is the first level at which particles i-1 and i sit in
-// different nodes, so a level-L node is a maximal run of particles of one
-// internal level-(L-1) node with no dlev <= L inside.  Levels are built one at
-// a time from segment flags and a scan; a node is a leaf when it holds at most
-// leaf_size particles or L = 21.  Masses and mass-weighted positions are summed
+// different nodes.  A level-L cell holds more than leaf_size particles exactly if
+// some two of its sorted particles leaf_size apart agree on L digits, so the
+// level of the leaf that holds particle i is one more than the most digits that
+// such a pair around i shares (21 at most): a node of level L starts at particle
+// i if dlev[i] <= L <= that level.  All levels are built at once: the starts of
+// each run of 256 particles are counted per level, one scan over (level, run)
+// numbers the nodes level by level, and a second pass writes them.  Masses and mass-weighted positions are summed
 // bottom-up (leaves over their particles, internal nodes over their children,
 // each in Morton order); the size s (distance from the centre of mass to the
 // furthest member) is a max over the node's particles, by one thread for
@@ -95,21 +98,25 @@ __global__ void k_keys(int64_t n, const double *__restrict__ xyz, BoxIn B, uint6
     idx[i] = (uint32_t)i;
 }
 
-// sorted particles: (x, y, z, m); dlev = first level where i-1 and i differ
-__global__ void k_sorted(int64_t n, const uint32_t *__restrict__ perm, const uint64_t *__restrict__ key,
+// first level at which two keys differ, kMaxLevel + 1 for equal ones
+__device__ __forceinline__ int split_level(uint64_t a, uint64_t b)
+{
+    const uint64_t x = a ^ b;
+    return x ? (__clzll((long long)x) - 1) / 3 + 1 : kMaxLevel + 1;
+}
+
+// sorted particles: (x, y, z, m); dlev = first level where i-1 and i differ;
+// deep = first level where i and i + leaf_size differ (0: no such particle)
+__global__ void k_sorted(int64_t n, int leaf_size, const uint32_t *__restrict__ perm, const uint64_t *__restrict__ key,
                          const double *__restrict__ xyz, const double *__restrict__ m, double4 *__restrict__ pos,
-                         uint8_t *__restrict__ dlev)
+                         uint8_t *__restrict__ dlev, uint8_t *__restrict__ deep)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int64_t a = perm[i];
     pos[i] = make_double4(xyz[3 * a], xyz[3 * a + 1], xyz[3 * a + 2], m[a]);
-    int d = 0;
-    if (i > 0) {
-        const uint64_t x = key[i - 1] ^ key[i];
-        d = x ? (__clzll((long long)x) - 1) / 3 + 1 : kMaxLevel + 1;
-    }
-    dlev[i] = (uint8_t)d;
+    dlev[i] = (uint8_t)(i > 0 ? split_level(key[i - 1], key[i]) : 0);
+    deep[i] = (uint8_t)(i + leaf_size < n ? min(split_level(key[i], key[i + leaf_size]), kMaxLevel) : 0);
 }
 
 // Node table (structure of arrays, capacity `cap`).
@@ -122,113 +129,99 @@ struct Nodes {
     uint64_t *d2;      // bits of the largest squared member distance
 };
 
-__global__ void k_root(int64_t n, int leaf_size, Nodes T, int32_t *__restrict__ cur, int32_t *__restrict__ leaf_of)
+// Sorted particles per wavefront of the two tree passes.  Both are bound by the
+// ballots of some ten levels per 64 particles: 14 and 22 us for 2,097,152
+// particles, where a build level by level (seven kernels, a scan over the
+// particles and a host read each) took 0.69 ms and ten waits.
+constexpr int kRun = 256;
+
+// The level of each particle's leaf (the largest `deep` among the leaf_size
+// particles before it and itself) and, per run of kRun particles and level, the
+// nodes that start there.
+__global__ void __launch_bounds__(256) k_tree_count(int64_t n, int64_t n_runs, int leaf_size,
+                                                    const uint8_t *__restrict__ dlev,
+                                                    const uint8_t *__restrict__ deep, uint8_t *__restrict__ leaf_level,
+                                                    int64_t *__restrict__ count)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool leaf = n <= leaf_size;
-    if (i == 0) {
-        T.start[0] = 0;
-        T.end[0] = (int32_t)n;
-        T.parent[0] = -1;
-        T.level[0] = 0;
-        T.leaf[0] = leaf;
-        T.label[0] = 1;
+    const int lane = threadIdx.x & 63;
+    const int64_t run = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (run >= n_runs) return;  // whole wavefronts
+    int mine = 0;               // lane L: the nodes of level L
+    for (int g = 0; g < kRun / 64; g++) {
+        const int64_t i = run * kRun + 64 * g + lane;
+        int t = 0, d = 255;
+        if (i < n) {
+            for (int64_t j = i - leaf_size < 0 ? 0 : i - leaf_size; j <= i; j++) t = max(t, (int)deep[j]);
+            leaf_level[i] = (uint8_t)t;
+            d = dlev[i];
+        }
+        for (int L = 1; L <= kMaxLevel; L++) {
+            if (__ballot(L <= t) == 0) break;
+            const int k = __popcll(__ballot(d <= L && L <= t));
+            mine += lane == L ? k : 0;
+        }
     }
-    if (i < n) {
-        cur[i] = leaf ? -1 : 0;
-        leaf_of[i] = leaf ? 0 : -1;
+    if (lane >= 1 && lane <= kMaxLevel) count[(lane - 1) * n_runs + run] = mine;
+}
+
+// lv[L] = first node of level L (L = 1 .. kMaxLevel), lv[kMaxLevel + 1] = number of nodes
+__global__ void k_tree_levels(int64_t n_runs, const int64_t *__restrict__ off, unsigned *__restrict__ lv)
+{
+    const int L = threadIdx.x;
+    if (L >= 1 && L <= kMaxLevel + 1) lv[L] = (unsigned)(1 + off[(L - 1) * n_runs]);
+}
+
+// The nodes and the particles' leaves.  Lane L holds the number of the next
+// node of level L; a particle's node of level L is the last one that started at
+// it or before.
+__global__ void __launch_bounds__(256) k_tree_nodes(int64_t n, int64_t n_runs, const uint8_t *__restrict__ dlev,
+                                                    const uint8_t *__restrict__ leaf_level,
+                                                    const uint64_t *__restrict__ key, const int64_t *__restrict__ off,
+                                                    Nodes T, int32_t *__restrict__ leaf_of)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t run = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (run >= n_runs) return;  // whole wavefronts
+    int next = lane >= 1 && lane <= kMaxLevel ? (int)(1 + off[(lane - 1) * n_runs + run]) : 0;
+    for (int g = 0; g < kRun / 64; g++) {
+        const int64_t i = run * kRun + 64 * g + lane;
+        const bool active = i < n, last = i + 1 == n;
+        const int t = active ? leaf_level[i] : 0, d = active ? dlev[i] : 255;
+        const int d_next = active && !last ? dlev[i + 1] : (active ? 0 : 255);
+        const uint64_t k = active ? key[i] : 0;
+        if (i == 0) {
+            T.start[0] = 0;
+            T.end[0] = (int32_t)n;
+            T.parent[0] = -1;
+            T.level[0] = 0;
+            T.leaf[0] = t == 0;
+            T.label[0] = 1;
+        }
+        int32_t node = 0;  // the particle's node of the level before
+        for (int L = 1; L <= kMaxLevel; L++) {
+            const bool in = L <= t, start = in && d <= L;
+            if (__ballot(in) == 0) break;
+            const uint64_t m = __ballot(start);
+            const int32_t id = __builtin_amdgcn_readlane(next, L) + lanes_below(m) + (start ? 1 : 0) - 1;
+            next += lane == L ? __popcll(m) : 0;
+            if (in) {
+                if (start) {
+                    T.start[id] = (int32_t)i;
+                    T.parent[id] = node;
+                    T.level[id] = (uint8_t)L;
+                    T.leaf[id] = L == t;
+                    T.label[id] = (1ULL << (3 * L)) | (k >> (63 - 3 * L));
+                    if (L == 1 ? i == 0 : d <= L - 1) T.cb[node] = id;  // the first child of its parent
+                }
+                if (d_next <= L) {
+                    T.end[id] = (int32_t)(i + 1);
+                    if (L == 1 ? last : d_next <= L - 1) T.ce[node] = id + 1;  // the last one
+                }
+                node = id;
+            }
+        }
+        if (active) leaf_of[i] = node;
     }
-}
-
-__global__ void k_lv_flags(int64_t n, int L, const int32_t *__restrict__ cur, const uint8_t *__restrict__ dlev,
-                           int64_t *__restrict__ flag)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t c = cur[i];
-    flag[i] = (c >= 0 && (i == 0 || cur[i - 1] != c || dlev[i] <= L)) ? 1 : 0;
-}
-
-// Level state on the device (so a level needs one host read, at its end):
-// lv[0] internal nodes of the level, lv[1] nodes of the level, lv[2] set when
-// the node table would overflow (the level's kernels then write nothing),
-// lv[3] index of the level's first node.
-__global__ void k_lv_init(unsigned *lv)
-{
-    lv[0] = 0u;
-    lv[1] = 0u;
-    lv[2] = 0u;
-    lv[3] = 1u;
-}
-
-__global__ void k_lv_count(int64_t n, const int64_t *__restrict__ off, int32_t cap, unsigned *lv)
-{
-    const int64_t cnt = off[n];
-    lv[0] = 0u;
-    lv[1] = (unsigned)cnt;
-    if ((int64_t)lv[3] + cnt > (int64_t)cap) lv[2] = 1u;
-}
-
-__global__ void k_lv_advance(unsigned *lv)
-{
-    if (!lv[2]) lv[3] += lv[1];
-}
-
-__global__ void k_lv_nodes(int64_t n, int L, const unsigned *__restrict__ lv, const int32_t *__restrict__ cur,
-                           const int64_t *__restrict__ flag, const int64_t *__restrict__ off,
-                           const uint64_t *__restrict__ key, Nodes T)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || lv[2]) return;
-    const int32_t c = cur[i];
-    if (c < 0) return;
-    const int32_t nid = (int32_t)lv[3] + (int32_t)(off[i] + flag[i] - 1);
-    if (flag[i]) {
-        T.start[nid] = (int32_t)i;
-        T.parent[nid] = c;
-        T.level[nid] = (uint8_t)L;
-        T.label[nid] = (1ULL << (3 * L)) | (key[i] >> (63 - 3 * L));
-    }
-    if (i + 1 == n || cur[i + 1] != c || flag[i + 1]) T.end[nid] = (int32_t)(i + 1);
-}
-
-__global__ void k_lv_leaf(int L, int leaf_size, Nodes T, unsigned *lv)
-{
-    const int32_t t = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    bool inner = false;
-    if (!lv[2] && t < (int32_t)lv[1]) {
-        const int32_t i = (int32_t)lv[3] + t;
-        const bool leaf = (T.end[i] - T.start[i] <= leaf_size) || L == kMaxLevel;
-        T.leaf[i] = leaf;
-        inner = !leaf;
-    }
-    const unsigned long long b = __ballot(inner);
-    if ((threadIdx.x & 63) == 0 && b) atomicAdd(lv, (unsigned)__popcll(b));
-}
-
-__global__ void k_lv_cur(int64_t n, const unsigned *__restrict__ lv, const int64_t *__restrict__ flag,
-                         const int64_t *__restrict__ off, const uint8_t *__restrict__ leaf, int32_t *__restrict__ cur,
-                         int32_t *__restrict__ leaf_of)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || lv[2] || cur[i] < 0) return;
-    const int32_t nid = (int32_t)lv[3] + (int32_t)(off[i] + flag[i] - 1);
-    if (leaf[nid]) {
-        leaf_of[i] = nid;
-        cur[i] = -1;
-    } else {
-        cur[i] = nid;
-    }
-}
-
-// children of a node are consecutive in the next level
-__global__ void k_children(int32_t n_nodes, Nodes T)
-{
-    const int32_t c = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (c < 1 || c >= n_nodes) return;
-    const int32_t p = T.parent[c];
-    if (T.parent[c - 1] != p) T.cb[p] = c;
-    if (c + 1 == n_nodes || T.parent[c + 1] != p) T.ce[p] = c + 1;
 }
 
 // masses and mass-weighted positions of the nodes of one level
@@ -292,11 +285,19 @@ __global__ void k_size_small(int32_t n_nodes, const double4 *__restrict__ pos, N
     T.d2[i] = __double_as_longlong(best);
 }
 
-__global__ void k_size_items(int32_t n_nodes, const int64_t *__restrict__ ioff, uint64_t *__restrict__ item)
+// One thread per item finds its node (the root alone has thousands of items).
+__global__ void k_size_items(int64_t n_items, int32_t n_nodes, const int64_t *__restrict__ ioff,
+                             uint64_t *__restrict__ item)
 {
-    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= n_nodes) return;
-    for (int64_t j = ioff[i]; j < ioff[i + 1]; j++) item[j] = ((uint64_t)i << 32) | (uint64_t)(j - ioff[i]);
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= n_items) return;
+    int32_t lo = 0, hi = n_nodes;  // the last node with ioff <= j; ioff[n_nodes] = n_items > j
+    while (hi - lo > 1) {
+        const int32_t mid = lo + (hi - lo) / 2;
+        if (ioff[mid] <= j) lo = mid;
+        else hi = mid;
+    }
+    item[j] = ((uint64_t)lo << 32) | (uint64_t)(j - ioff[lo]);
 }
 
 // one wavefront per item: max squared distance over a chunk, then an atomic max
@@ -418,27 +419,34 @@ __global__ void k_mark(int32_t n_nodes, Nodes T, int64_t *__restrict__ omark, in
     }
 }
 
-// leaves, accepted nodes, substitute leaves and extracted particles
-__global__ void k_walk_stats(int32_t n_nodes, Nodes T, unsigned long long *__restrict__ cnt)
+// leaves, accepted nodes, substitute leaves and extracted particles: summed per
+// workgroup first, since atomics on one cache line are done one after the other
+// (one per wavefront and count took 167 us for the tree of 2,097,152 particles, now 8)
+__global__ void __launch_bounds__(256) k_walk_stats(int32_t n_nodes, Nodes T, unsigned long long *__restrict__ cnt)
 {
-    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    __shared__ unsigned long long part[4][4];
     unsigned long long v[4] = {0, 0, 0, 0};
-    if (i < n_nodes) {
-        v[0] = T.leaf[i];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_nodes; i += (int64_t)gridDim.x * blockDim.x) {
+        v[0] += T.leaf[i];
         if (T.vis[i]) {
-            v[1] = !(T.open[i] & 1);
+            v[1] += !(T.open[i] & 1);
             if (T.open[i] & 2) {
-                v[2] = 1;
-                v[3] = (unsigned long long)(T.end[i] - T.start[i]);
+                v[2] += 1;
+                v[3] += (unsigned long long)(T.end[i] - T.start[i]);
             }
         }
     }
 #pragma unroll
-    for (int q = 0; q < 4; q++)
+    for (int q = 0; q < 4; q++) {
         for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
-    if ((threadIdx.x & 63) == 0)
-        for (int q = 0; q < 4; q++)
-            if (v[q]) atomicAdd(cnt + q, v[q]);
+        if ((threadIdx.x & 63) == 0) part[q][threadIdx.x >> 6] = v[q];
+    }
+    __syncthreads();
+    const int q = threadIdx.x;
+    if (q < 4) {
+        const unsigned long long sum = part[q][0] + part[q][1] + part[q][2] + part[q][3];
+        if (sum) atomicAdd(cnt + q, sum);
+    }
 }
 
 struct PseudoOut {
@@ -989,8 +997,9 @@ void build_tree(Workspace &ws, const DevParticles &P, const double box[6], int l
     radix_sort_u64(ws, key, perm, key2, perm2, n, 63, s);
     double4 *pos = ws.get<double4>(S_PSEUDO4, (size_t)n);
     uint8_t *dlev = ws.get<uint8_t>(S_PSEUDO5, (size_t)n);
-    hipLaunchKernelGGL(k_sorted, dim3(grid_of(n)), dim3(256), 0, s, n, (const uint32_t *)perm,
-                       (const uint64_t *)key, P.xyz, P.m, pos, dlev);
+    uint8_t *deep = reinterpret_cast<uint8_t *>(key2), *leaf_level = deep + n;  // (the sort's scratch is free again)
+    hipLaunchKernelGGL(k_sorted, dim3(grid_of(n)), dim3(256), 0, s, n, ls, (const uint32_t *)perm,
+                       (const uint64_t *)key, P.xyz, P.m, pos, dlev, deep);
     EM_HIP(hipGetLastError());
 
     // node table in one allocation
@@ -1016,50 +1025,29 @@ void build_tree(Workspace &ws, const DevParticles &P, const double box[6], int l
 
     int32_t *cur = ws.get<int32_t>(S_PSEUDO7, (size_t)n);
     int32_t *leaf_of = ws.get<int32_t>(S_PSEUDO8, (size_t)n);
-    int64_t *flag = ws.get<int64_t>(S_PSEUDO9, (size_t)n + 1);
-    int64_t *off = ws.get<int64_t>(S_PSEUDO10, (size_t)n + 1);
-    unsigned *small = ws.get<unsigned>(S_PSEUDO11, 64);  // [0..3] level state, see k_lv_init
-    hipLaunchKernelGGL(k_root, dim3(grid_of(n)), dim3(256), 0, s, n, ls, T, cur, leaf_of);
+    const int64_t n_runs = (n + kRun - 1) / kRun, n_cnt = kMaxLevel * n_runs;
+    int64_t *flag = ws.get<int64_t>(S_PSEUDO9, (size_t)std::max(n, n_cnt) + 1);
+    int64_t *off = ws.get<int64_t>(S_PSEUDO10, (size_t)std::max(n, n_cnt) + 1);
+    unsigned *small = ws.get<unsigned>(S_PSEUDO11, 64);
+    hipLaunchKernelGGL(k_tree_count, dim3(grid_of(64 * n_runs)), dim3(256), 0, s, n, n_runs, ls, (const uint8_t *)dlev,
+                       (const uint8_t *)deep, leaf_level, flag);
     EM_HIP(hipGetLastError());
-
+    scan_counts(ws, flag, off, n_cnt, s);
+    hipLaunchKernelGGL(k_tree_levels, dim3(1), dim3(64), 0, s, n_runs, (const int64_t *)off, small);
+    EM_HIP(hipGetLastError());
+    unsigned lv[kMaxLevel + 2];
+    EM_HIP(hipMemcpyAsync(lv, small, sizeof(lv), hipMemcpyDeviceToHost, s));
+    EM_HIP(hipStreamSynchronize(s));
+    EM_CHECK((int64_t)lv[kMaxLevel + 1] <= cap64, MAP_EDEVICE, "octree node table overflow");
+    hipLaunchKernelGGL(k_tree_nodes, dim3(grid_of(64 * n_runs)), dim3(256), 0, s, n, n_runs, (const uint8_t *)dlev,
+                       (const uint8_t *)leaf_level, (const uint64_t *)key, (const int64_t *)off, T, leaf_of);
+    EM_HIP(hipGetLastError());
+    const int32_t n_nodes = (int32_t)lv[kMaxLevel + 1];
     int32_t lvl_off[kMaxLevel + 2];
     lvl_off[0] = 0;
-    lvl_off[1] = 1;
-    int32_t base = 1;
     int max_level = 0;
-    bool inner = n > ls;
-    hipLaunchKernelGGL(k_lv_init, dim3(1), dim3(1), 0, s, small);
-    EM_HIP(hipGetLastError());
-    for (int L = 1; L <= kMaxLevel && inner; L++) {
-        hipLaunchKernelGGL(k_lv_flags, dim3(grid_of(n)), dim3(256), 0, s, n, L, (const int32_t *)cur,
-                           (const uint8_t *)dlev, flag);
-        EM_HIP(hipGetLastError());
-        scan_counts(ws, flag, off, n, s);
-        hipLaunchKernelGGL(k_lv_count, dim3(1), dim3(1), 0, s, n, (const int64_t *)off, cap, small);
-        EM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_lv_nodes, dim3(grid_of(n)), dim3(256), 0, s, n, L, (const unsigned *)small,
-                           (const int32_t *)cur, (const int64_t *)flag, (const int64_t *)off, (const uint64_t *)key, T);
-        EM_HIP(hipGetLastError());
-        // a level has at most n nodes
-        hipLaunchKernelGGL(k_lv_leaf, dim3(grid_of(n)), dim3(256), 0, s, L, ls, T, small);
-        EM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_lv_cur, dim3(grid_of(n)), dim3(256), 0, s, n, (const unsigned *)small,
-                           (const int64_t *)flag, (const int64_t *)off, (const uint8_t *)T.leaf, cur, leaf_of);
-        EM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_lv_advance, dim3(1), dim3(1), 0, s, small);
-        EM_HIP(hipGetLastError());
-        unsigned lv[4] = {0u, 0u, 0u, 0u};
-        EM_HIP(hipMemcpyAsync(lv, small, sizeof(lv), hipMemcpyDeviceToHost, s));
-        EM_HIP(hipStreamSynchronize(s));
-        EM_CHECK(lv[2] == 0u, MAP_EDEVICE, "octree node table overflow");
-        base = (int32_t)lv[3];
-        lvl_off[L + 1] = base;
-        max_level = L;
-        inner = lv[0] > 0u;
-    }
-    const int32_t n_nodes = base;
-    hipLaunchKernelGGL(k_children, dim3(grid_of(n_nodes)), dim3(256), 0, s, n_nodes, T);
-    EM_HIP(hipGetLastError());
+    for (int L = 1; L <= kMaxLevel + 1; L++) lvl_off[L] = (int32_t)lv[L];
+    while (max_level < kMaxLevel && lvl_off[max_level + 2] > lvl_off[max_level + 1]) max_level++;
     for (int L = max_level; L >= 0; L--) {
         const int32_t lo = lvl_off[L], hi = lvl_off[L + 1];
         hipLaunchKernelGGL(k_moments, dim3(grid_of(hi - lo)), dim3(256), 0, s, lo, hi, (const double4 *)pos, T);
@@ -1077,8 +1065,8 @@ void build_tree(Workspace &ws, const DevParticles &P, const double box[6], int l
     EM_HIP(hipStreamSynchronize(s));
     if (n_items > 0) {
         uint64_t *items = ws.get<uint64_t>(S_PSEUDO14, (size_t)n_items);
-        hipLaunchKernelGGL(k_size_items, dim3(grid_of(n_nodes)), dim3(256), 0, s, n_nodes, (const int64_t *)ioff,
-                           items);
+        hipLaunchKernelGGL(k_size_items, dim3(grid_of(n_items)), dim3(256), 0, s, n_items, n_nodes,
+                           (const int64_t *)ioff, items);
         EM_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_size_big, dim3(grid_of(64 * n_items)), dim3(256), 0, s, n_items,
                            (const uint64_t *)items, (const double4 *)pos, T);
@@ -1130,7 +1118,7 @@ int64_t walk_tree(Workspace &ws, const TreeState &TS, const DevParticles &P, con
     EM_HIP(hipGetLastError());
     unsigned long long *wc = reinterpret_cast<unsigned long long *>(small + 32);
     fill_zero_bytes(wc, 4 * sizeof(unsigned long long), s);
-    hipLaunchKernelGGL(k_walk_stats, dim3(grid_of(n_nodes)), dim3(256), 0, s, n_nodes, T, wc);
+    hipLaunchKernelGGL(k_walk_stats, dim3(std::min(grid_of(n_nodes), 256u)), dim3(256), 0, s, n_nodes, T, wc);
     EM_HIP(hipGetLastError());
     // marks and their scans (reuse the level buffers)
     int64_t *omark = flag;

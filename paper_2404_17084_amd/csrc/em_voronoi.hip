@@ -182,12 +182,6 @@ __device__ __forceinline__ unsigned wave_umax(unsigned v)
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Set lanes of mask m below this lane.
-__device__ __forceinline__ int lanes_below(uint64_t m)
-{
-    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-}
-
 __device__ __forceinline__ double lane_value(double v, int l)
 {
     const uint64_t b = __double_as_longlong(v);

@@ -21,6 +21,12 @@ __device__ __forceinline__ int wave_push(bool want, int &count)
     return wave_push(__builtin_amdgcn_ballot_w64(want), count);
 }
 
+// Set lanes of mask m below this lane.
+__device__ __forceinline__ int lanes_below(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
 // Orders LDS writes of one wavefront before its later reads by other lanes.
 __device__ __forceinline__ void lds_sync_wave()
 {
