@@ -5,6 +5,7 @@
 #include <thread>
 
 #include "em_internal.h"
+#include "em_wave.h"
 
 namespace em {
 
@@ -359,60 +360,100 @@ __global__ void k_rs_hist(const K *keys, int64_t n, int shift, int rb, int64_t n
     for (int t = threadIdx.x; t < nb; t += RS_BLOCK) hist[(int64_t)t * nblocks + blockIdx.x] = cnt[t];
 }
 
-// Stable scatter: items of a tile are taken in order, 256 at a time; the rank of
-// an item among equal digits is (items of earlier chunks and blocks) + (equal
-// digits in earlier waves of the chunk) + (equal digits in lower lanes).
+// Stable scatter: each wavefront ranks its own consecutive part of the tile, 64
+// items at a time, against its own digit counts (the rank of an item among equal
+// digits is the count so far plus the equal digits in lower lanes), with no
+// barrier; the counts of the wavefronts become places in the tile, the tile is put
+// in order in LDS, and neighbouring threads write neighbouring items.  The items
+// stay in registers, so a thread's loads are all in flight together.  Bound by the
+// scattered stores, runs of 8 items on average at 512 digits: a pass over
+// 2,097,152 64-bit keys takes 25 us (46 with 256 items at a time, three barriers
+// each, and stores item by item; 49 with the barriers gone alone), one over 14.5e6
+// 32-bit keys 95 us (198).
 template <typename K, int ITEMS>
-__global__ void k_rs_scatter(const K *keys, const uint32_t *vals, K *keys_out, uint32_t *vals_out, int64_t n,
-                             int shift, int rb, int64_t nblocks, const int64_t *offsets)
+__global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const K *__restrict__ keys, const uint32_t *__restrict__ vals,
+                                                         K *__restrict__ keys_out, uint32_t *__restrict__ vals_out,
+                                                         int64_t n, int shift, int rb, int64_t nblocks,
+                                                         const int64_t *__restrict__ offsets)
 {
-    __shared__ int64_t run[RS_MAX_BUCKETS];
+    constexpr int TILE = RS_BLOCK * ITEMS, PER = RS_MAX_BUCKETS / RS_BLOCK;
     __shared__ unsigned wcnt[RS_WAVES][RS_MAX_BUCKETS];
+    __shared__ unsigned to[RS_MAX_BUCKETS];  // where a digit's items go, less their place in the tile
+    __shared__ unsigned wsum[RS_WAVES];
+    __shared__ K item[TILE];
+    __shared__ uint32_t carried[TILE];
     const int t = threadIdx.x;
     const int lane = t & 63;
-    const int wave = t >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int nb = 1 << rb;
     const unsigned mask = (unsigned)nb - 1u;
-    for (int q = t; q < nb; q += RS_BLOCK) {
-        run[q] = offsets[(int64_t)q * nblocks + blockIdx.x];
-        for (int w = 0; w < RS_WAVES; w++) wcnt[w][q] = 0;
+    for (int q = lane; q < nb; q += 64) wcnt[wave][q] = 0;
+    const int64_t tile = (int64_t)blockIdx.x * TILE, base = tile + (int64_t)wave * (64 * ITEMS) + lane;
+    K key[ITEMS];
+    uint32_t val[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        const int64_t i = base + 64 * k;
+        key[k] = i < n ? keys[i] : K(0);
+        val[k] = i < n ? vals[i] : 0u;
+    }
+    lds_sync_wave();
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        const bool valid = base + 64 * k < n;
+        const unsigned d = (unsigned)(key[k] >> shift) & mask;
+        uint64_t peers = __ballot(valid);
+        for (int b = 0; b < rb; b++) {
+            const bool one = (d >> b) & 1u;
+            const uint64_t bb = __ballot(one);
+            peers &= one ? bb : ~bb;
+        }
+        const unsigned below = (unsigned)lanes_below(peers), before = valid ? wcnt[wave][d] : 0u;
+        rank[k] = before + below;
+        lds_sync_wave();
+        if (valid && below == 0) wcnt[wave][d] = before + (unsigned)__popcll(peers);
+        lds_sync_wave();
     }
     __syncthreads();
-    const unsigned long long lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-    int64_t base = (int64_t)blockIdx.x * (RS_BLOCK * ITEMS);
-    for (int k = 0; k < ITEMS; k++) {
-        int64_t i = base + (int64_t)k * RS_BLOCK + t;
-        bool valid = i < n;
-        K key = valid ? keys[i] : K(0);
-        uint32_t val = valid ? vals[i] : 0u;
-        unsigned d = (unsigned)(key >> shift) & mask;
-        unsigned long long peers = __ballot(valid);
+    // thread t: digits PER t ..., their items and the items of the digits before (a scan over the threads)
+    unsigned sum = 0;
+    for (int u = 0; u < PER; u++)
+        for (int w = 0; w < RS_WAVES; w++) sum += PER * t + u < nb ? wcnt[w][PER * t + u] : 0u;
+    unsigned incl = sum;
 #pragma unroll
-        for (int b = 0; b < RS_MAX_BITS; b++) {
-            if (b < rb) {
-                unsigned long long bb = __ballot((d >> b) & 1u);
-                peers &= ((d >> b) & 1u) ? bb : ~bb;
-            }
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    unsigned at = incl - sum;
+    for (int w = 0; w < wave; w++) at += wsum[w];
+    for (int u = 0; u < PER; u++) {
+        const int q = PER * t + u;
+        if (q >= nb) break;
+        to[q] = (unsigned)offsets[(int64_t)q * nblocks + blockIdx.x] - at;  // (fewer than 2^32 items)
+        for (int w = 0; w < RS_WAVES; w++) {
+            const unsigned c = wcnt[w][q];
+            wcnt[w][q] = at;
+            at += c;
         }
-        unsigned rank_in_wave = (unsigned)__popcll(peers & lt);
-        if (valid && rank_in_wave == 0) wcnt[wave][d] = (unsigned)__popcll(peers);
-        __syncthreads();
-        if (valid) {
-            int64_t dest = run[d] + rank_in_wave;
-            for (int w = 0; w < wave; w++) dest += wcnt[w][d];
-            keys_out[dest] = key;
-            vals_out[dest] = val;
-        }
-        __syncthreads();
-        for (int q = t; q < nb; q += RS_BLOCK) {
-            unsigned add = 0;
-            for (int w = 0; w < RS_WAVES; w++) {
-                add += wcnt[w][q];
-                wcnt[w][q] = 0;
-            }
-            run[q] += add;
-        }
-        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; k++) {
+        if (base + 64 * k >= n) continue;
+        const unsigned p = wcnt[wave][(unsigned)(key[k] >> shift) & mask] + rank[k];
+        item[p] = key[k];
+        carried[p] = val[k];
+    }
+    __syncthreads();
+    const int m = (int)(n - tile < TILE ? n - tile : TILE);
+    for (int p = t; p < m; p += RS_BLOCK) {
+        const K x = item[p];
+        const unsigned dest = to[(unsigned)(x >> shift) & mask] + (unsigned)p;
+        keys_out[dest] = x;
+        vals_out[dest] = carried[p];
     }
 }
 
@@ -512,8 +553,9 @@ static void radix_sort(Workspace &ws, K *keys, uint32_t *vals, K *keys2, uint32_
         EM_HIP(hipGetLastError());
         return;
     }
-    // items per thread: enough workgroups to fill the chip, as a workgroup takes its items one after the other
-    // (262,144 keys: a scatter pass 21 us with 16 items, 10.5 with 4; 2,097,152: 46 us with 16, 50 with 8)
+    // items per thread: enough workgroups to fill the chip, and more items per digit for the stores where there are
+    // (a scatter pass with 4, 8 and 16 items: 262,144 keys 9.9, 11.7 and 15.3 us, 700,000 15.7, 14.7 and 16.7,
+    // 2,097,152 40, 31 and 26)
     if (n <= (int64_t(1) << 19)) radix_passes<K, 4>(ws, keys, vals, keys2, vals2, n, bits, s);
     else if (n <= (int64_t(1) << 20)) radix_passes<K, 8>(ws, keys, vals, keys2, vals2, n, bits, s);
     else radix_passes<K, 16>(ws, keys, vals, keys2, vals2, n, bits, s);
