@@ -139,8 +139,7 @@ void prepare(Ctx &C, Workspace &ws, const map_particles_in *p, const map_cells_i
     fill_zero_bytes(counters, sizeof(int64_t) * kCounterCopies * kCounterStride, s);
     launch_validate(in, flags, s);
     unsigned hf = 0;
-    EM_HIP(hipMemcpyAsync(&hf, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    stream_sync(s);
+    read_back(ws, {{&hf, flags, sizeof(unsigned)}}, s);
     EM_CHECK(hf == 0, flag_code(hf), flag_text(hf));
 
     edges = ws.get<EdgeRec>(S_EDGE, (size_t)(c->n_face_verts > 0 ? c->n_face_verts : 1));
@@ -206,8 +205,7 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
         // wall planes (winding weight), both precisions
         auto read_count = [&]() -> int64_t {
             unsigned hfix = 0;
-            EM_HIP(hipMemcpyAsync(&hfix, js.tile_ctr + 1, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-            stream_sync(s);
+            read_back(ws, {{&hfix, js.tile_ctr + 1, sizeof(unsigned)}}, s);
             return (int64_t)hfix;
         };
         int64_t n_items = read_count();
@@ -257,8 +255,7 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
         uint32_t *list = reinterpret_cast<uint32_t *>(cnt) + 64;
         launch_cell_check(in, ps, js.err, f, tol, cnt, list, in.n_cells, s);
         unsigned hc = 0;
-        EM_HIP(hipMemcpyAsync(&hc, cnt, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-        stream_sync(s);
+        read_back(ws, {{&hc, cnt, sizeof(unsigned)}}, s);
         n_cells_fp64 = hc;
         if (hc > 0) launch_recompute_cells(in, js.edges, ps, list, (int64_t)hc, f, js.S, js.counters, s);
     }
@@ -266,7 +263,6 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
     double *M = ws.get<double>(S_MCELL, (size_t)(in.n_cells > 0 ? in.n_cells : 1));
     double *rho = ws.get<double>(S_RHO, (size_t)(in.n_cells > 0 ? in.n_cells : 1));
     double *red = ws.get<double>(S_RED, 16 + 4 * 256);
-    EM_HIP(hipMemcpyAsync(red + 4, in.box, sizeof(double) * 6, hipMemcpyHostToDevice, s));
     launch_reduce(in, ps, f, S, M, rho, red, js.flags, s);
     if (js.ev_reduce) EM_HIP(hipEventRecord(js.ev_reduce, s));
 
@@ -295,10 +291,7 @@ int64_t stage_finish(Ctx &C, Workspace &ws, JobState &js, const map_out *out, hi
     double hred[4] = {0, 0, 0, 0};
     int64_t hcopies[kCounterCopies][kCounterStride], hcnt[C_NUM] = {};
     unsigned hf = 0;
-    EM_HIP(hipMemcpyAsync(hred, red, sizeof(hred), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(hcopies, js.counters, sizeof(hcopies), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&hf, js.flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    stream_sync(s);
+    read_back(ws, {{hred, red, sizeof(hred)}, {hcopies, js.counters, sizeof(hcopies)}, {&hf, js.flags, sizeof(unsigned)}}, s);
     for (const auto &copy : hcopies)
         for (int q = 0; q < C_NUM; q++) hcnt[q] += copy[q];
     EM_CHECK(hf == 0, flag_code(hf), flag_text(hf));

@@ -1684,8 +1684,7 @@ void build_tiles(Workspace &ws, const DevInputs &in, PairSet &ps, hipStream_t s)
     EM_HIP(hipGetLastError());
     scan_counts(ws, tcnt, toff, nc, s);
     int64_t nt = 0;
-    EM_HIP(hipMemcpyAsync(&nt, toff + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    stream_sync(s);
+    read_back(ws, {{&nt, toff + nc, sizeof(int64_t)}}, s);
     uint64_t *tiles = ws.get<uint64_t>(S_TILES, (size_t)(nt > 0 ? nt : 1));
     hipLaunchKernelGGL(k_tile_fill, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, nc, (const int64_t *)toff,
                        tiles);

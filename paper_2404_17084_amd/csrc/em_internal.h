@@ -1,6 +1,7 @@
 // Internal declarations shared by the library's translation units.
 #pragma once
 
+#include <initializer_list>
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -63,6 +64,9 @@ public:
     // synchronisation when a buffer is replaced or released).
     void use_stream(hipStream_t s) { stream_ = s; }
     bool is_arena() const { return arena_base_ != nullptr; }
+    // Pinned host memory (kMailboxBytes) that kernels write results to, allocated on
+    // first use; null in arena mode, which allocates nothing.
+    void *mailbox();
     // bytes still free in arena mode (SIZE_MAX otherwise)
     size_t arena_free() const;
     size_t arena_used() const { return arena_used_; }
@@ -78,7 +82,18 @@ private:
     char *arena_base_ = nullptr;
     size_t arena_cap_ = 0, arena_used_ = 0;
     hipStream_t stream_ = nullptr;
+    void *mailbox_ = nullptr;
 };
+constexpr size_t kMailboxBytes = 4096;
+
+// Small results to the host: the items (up to 6, multiples of 4 bytes, at most
+// kMailboxBytes in all), then a wait for the stream.
+struct ReadItem {
+    void *to;
+    const void *from;  // device memory
+    size_t bytes;
+};
+void read_back(Workspace &ws, std::initializer_list<ReadItem> items, hipStream_t s);
 
 // Buffer slots of one mapping job.
 enum Slot : int {

@@ -691,9 +691,7 @@ PairSet build_pairs(Workspace &ws, const DevInputs &in, const double *aabb, cons
     scan_counts(ws, pcount, coff, nc, s);
     int64_t np = 0;
     unsigned max_cand = 0;
-    EM_HIP(hipMemcpyAsync(&np, coff + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&max_cand, cmax, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    stream_sync(s);
+    read_back(ws, {{&np, coff + nc, sizeof(int64_t)}, {&max_cand, cmax, sizeof(unsigned)}}, s);
     if ((int64_t)max_cand > K) {
         // the cells with more candidates: their lists' places, the walk and the test again for them
         int64_t *size = ws.get<int64_t>(S_NCNT, (size_t)nc);
@@ -703,8 +701,7 @@ PairSet build_pairs(Workspace &ws, const DevInputs &in, const double *aabb, cons
         EM_HIP(hipGetLastError());
         scan_counts(ws, size, ovf_off, nc, s);
         int64_t n_ovf = 0;
-        EM_HIP(hipMemcpyAsync(&n_ovf, ovf_off + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        stream_sync(s);
+        read_back(ws, {{&n_ovf, ovf_off + nc, sizeof(int64_t)}}, s);
         ovf = ws.get<uint32_t>(S_BINLIST, (size_t)n_ovf);
         hipLaunchKernelGGL(k_candidates<true>, wg, dim3(256), 0, s, nc, aabb, centre, radii, n, in.xyz, in.h,
                            (const double *)nodes, NL, ccount, ovf, K, (const int64_t *)ovf_off, cmax);
@@ -714,8 +711,7 @@ PairSet build_pairs(Workspace &ws, const DevInputs &in, const double *aabb, cons
                            pcount, tested);
         EM_HIP(hipGetLastError());
         scan_counts(ws, pcount, coff, nc, s);
-        EM_HIP(hipMemcpyAsync(&np, coff + nc, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        stream_sync(s);
+        read_back(ws, {{&np, coff + nc, sizeof(int64_t)}}, s);
     }
     EM_CHECK(np < (int64_t)UINT32_MAX, MAP_ENOMEM, "pair count exceeds 2^32-1");
     ps.n_pairs = np;

@@ -2,6 +2,7 @@
 // stable LSD radix sort (keys with 32-bit values), all written for wave64.
 #include <algorithm>
 #include <chrono>
+#include <cstring>
 #include <thread>
 
 #include "em_internal.h"
@@ -12,7 +13,17 @@ namespace em {
 // ---------------------------------------------------------------- workspace
 Workspace::Workspace(int device) : device_(device), bufs_(S_NUM_SLOTS) {}
 
-Workspace::~Workspace() { release(); }
+Workspace::~Workspace()
+{
+    release();
+    if (mailbox_) (void)hipHostFree(mailbox_);
+}
+
+void *Workspace::mailbox()
+{
+    if (!mailbox_ && !arena_base_) EM_HIP(hipHostMalloc(&mailbox_, kMailboxBytes, hipHostMallocDefault));
+    return arena_base_ ? nullptr : mailbox_;
+}
 
 void Workspace::use_arena(void *base, size_t bytes)
 {
@@ -124,6 +135,58 @@ void stream_sync(hipStream_t s)
         if (spin < 200) std::this_thread::yield();
         else std::this_thread::sleep_for(std::chrono::microseconds(20));
     }
+}
+
+namespace {
+
+constexpr int kReadItems = 6;
+struct ReadArgs {
+    const uint32_t *from[kReadItems];
+    int words[kReadItems], at[kReadItems], n;
+};
+
+__global__ void k_read_back(ReadArgs A, uint32_t *mail)
+{
+    for (int q = 0; q < A.n; q++)
+        for (int i = threadIdx.x; i < A.words[q]; i += blockDim.x) mail[A.at[q] + i] = A.from[q][i];
+}
+
+}  // namespace
+
+// A copy to pageable memory is a kernel into a staging buffer and a wait of the
+// host for each; one kernel that writes all items to pinned memory and one wait
+// bring a call on 512 particles (12 copies, now five of these) from 500 to 349 us,
+// with the box as a kernel argument and k_stats_final.  Where waits have a limit (the
+// server's threads) the stream is polled with sleeps between, and the copies stay:
+// twelve served jobs 24.4 ms without them, 23.0 with.
+void read_back(Workspace &ws, std::initializer_list<ReadItem> items, hipStream_t s)
+{
+    uint32_t *mail = t_wait_limit_ms > 0.0 ? nullptr : static_cast<uint32_t *>(ws.mailbox());
+    ReadArgs A{};
+    size_t at = 0;
+    for (const ReadItem &r : items) {
+        if (!mail) {
+            EM_HIP(hipMemcpyAsync(r.to, r.from, r.bytes, hipMemcpyDeviceToHost, s));
+            continue;
+        }
+        EM_CHECK(A.n < kReadItems && r.bytes % 4 == 0 && at + r.bytes <= kMailboxBytes, MAP_EINVAL,
+                 "results do not fit the mailbox");
+        A.from[A.n] = static_cast<const uint32_t *>(r.from);
+        A.words[A.n] = (int)(r.bytes / 4);
+        A.at[A.n++] = (int)(at / 4);
+        at += r.bytes;
+    }
+    if (mail) {
+        hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, s, A, mail);
+        EM_HIP(hipGetLastError());
+    }
+    stream_sync(s);
+    at = 0;
+    if (mail)
+        for (const ReadItem &r : items) {
+            std::memcpy(r.to, reinterpret_cast<const char *>(mail) + at, r.bytes);
+            at += r.bytes;
+        }
 }
 
 int device_cu_count()

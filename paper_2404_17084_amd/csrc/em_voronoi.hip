@@ -1095,8 +1095,7 @@ SiteTree site_tree(Workspace &ws, int64_t n, const double *sites, const VBox &B,
                        rank, flags);
     EM_HIP(hipGetLastError());
     unsigned hf = 0;
-    EM_HIP(hipMemcpyAsync(&hf, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{&hf, flags, sizeof(unsigned)}}, s);
     EM_CHECK(!(hf & 1u), MAP_EINVAL, "a site is not finite or lies outside the box");
     EM_CHECK(!distinct || !(hf & 2u), MAP_EINVAL, "two sites coincide (merge them first)");
 
@@ -1153,11 +1152,8 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
         scan_counts(ws, nsc, soff, n, s);
         scan_counts(ws, nvc, voff, n, s);
         unsigned h2[2] = {0, 0};
-        EM_HIP(hipMemcpyAsync(&tot[0], foff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        EM_HIP(hipMemcpyAsync(&tot[1], soff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        EM_HIP(hipMemcpyAsync(&tot[2], voff + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        EM_HIP(hipMemcpyAsync(h2, flags, sizeof(h2), hipMemcpyDeviceToHost, s));
-        EM_HIP(hipStreamSynchronize(s));
+        read_back(ws, {{&tot[0], foff + n, sizeof(int64_t)}, {&tot[1], soff + n, sizeof(int64_t)},
+                       {&tot[2], voff + n, sizeof(int64_t)}, {h2, flags, sizeof(h2)}}, s);
         hf = h2[0];
         if (h2[1] <= n_big) break;
         n_big = h2[1];
@@ -1182,8 +1178,7 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
                        recs, bigs,
                        (const int64_t *)foff, (const int64_t *)soff, (const int64_t *)voff, O, flags);
     EM_HIP(hipGetLastError());
-    EM_HIP(hipMemcpyAsync(&hf, flags, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{&hf, flags, sizeof(unsigned)}}, s);
     EM_CHECK(!(hf & 8u), MAP_EDEVICE, "a Voronoi face did not close into one loop");
     V.n = n;
 }
@@ -1206,11 +1201,10 @@ int64_t merge_sites(Workspace &ws, int64_t n_in, const double *in, const double 
     EM_HIP(hipGetLastError());
     scan_counts(ws, keep, koff, n_in, s);
     int64_t m = 0;
-    EM_HIP(hipMemcpyAsync(&m, koff + n_in, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     hipLaunchKernelGGL(k_vor_gather, dim3(vgrid(n_in, 256)), dim3(256), 0, s, n_in, in, (const int64_t *)keep,
                        (const int64_t *)koff, out);
     EM_HIP(hipGetLastError());
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{&m, koff + n_in, sizeof(int64_t)}}, s);
     return m;
 }
 
@@ -1232,8 +1226,7 @@ void site_cells(Workspace &ws, const VorGrid &V, int64_t n_in, const double *in,
                        n_list);
     EM_HIP(hipGetLastError());
     unsigned long long n_tree = 0;
-    EM_HIP(hipMemcpyAsync(&n_tree, n_list, sizeof(n_tree), hipMemcpyDeviceToHost, s));
-    EM_HIP(hipStreamSynchronize(s));
+    read_back(ws, {{&n_tree, n_list, sizeof(n_tree)}}, s);
     if (n_tree == 0) return;
     const SiteTree T = site_tree(ws, V.n, V.sites, B, true, s);
     hipLaunchKernelGGL(k_vor_site_cell, dim3(vgrid((int64_t)n_tree, 128)), dim3(128), 0, s, (int64_t)n_tree,
