@@ -1567,14 +1567,16 @@ __global__ void k_table_pack(int n0, int n1, int n2, const double *__restrict__ 
 }  // namespace
 
 // The listed cells' pairs in FP64, to the bit as pair_fraction<MAP_FP64>
-// (the per-pair FP64 form): each workgroup takes chunks of 32 of a cell's pairs (kRecBlocks workgroups
-// per cell, chunks round-robin), computes every (pair, wall) term of a chunk
-// in parallel (the wall's edge loop of pair_fraction), then one thread per
-// pair adds its walls in wall order, as pair_fraction does, so the result is
-// the FP64 path's to the bit (cells of up to 64 walls; larger ones take one
-// thread per pair).  One thread per pair left most of the
-// workgroup idle and each thread with all of its pair's edge terms in a row.
-constexpr int kRecPairs = 32, kRecBlocks = 4, kRecWalls = 64;
+// (the per-pair FP64 form): each workgroup takes chunks of up to 32 of a cell's
+// pairs (kRecBlocks workgroups per cell, chunks round-robin), computes every
+// (pair, edge) term of a chunk in parallel, then a thread per (pair, wall) adds
+// the wall's edges in order and a thread per pair its walls in order, as
+// pair_fraction does, so the result is the FP64 path's to the bit (cells of up to
+// 64 walls and kRecTerms slots; larger ones take one thread per pair).  Bound by
+// FP64 issue.  With a thread for all edges of a (pair, wall), where lanes wait for
+// the wall of the most edges, 76,574 pairs of 729 cells took 141 us and 385 pairs
+// of 9 cells 40; now 103 and 25.
+constexpr int kRecPairs = 32, kRecBlocks = 4, kRecWalls = 64, kRecTerms = 2048;
 
 __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const uint32_t *__restrict__ cells,
                                                          const int64_t *__restrict__ coff,
@@ -1587,15 +1589,17 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
                                                          unsigned long long *__restrict__ S,
                                                          unsigned long long *counters)
 {
-    static_assert(kRecPairs * kRecWalls <= 2048, "one chunk's terms in LDS");
-    __shared__ double term[kRecPairs * kRecWalls];
-    __shared__ uint8_t side[kRecPairs * kRecWalls];  // bit 0: d >= 0, bit 1: d == 0
+    __shared__ double term[kRecTerms];               // of a (pair, slot), with the edge's sign
+    __shared__ double wall[kRecPairs * kRecWalls];   // of a (pair, wall): its distance, then its sum
+    __shared__ uint8_t side[kRecPairs * kRecWalls];  // of a (pair, wall): bit 0: distance >= 0, bit 1: 0
+    __shared__ uint8_t wall_of[kRecTerms];           // of the cell's slots
     const int64_t q = blockIdx.x;
     if (q >= n_list) return;
     const int64_t c = cells[q];
     const int64_t f0 = cfo[c], nw = cfo[c + 1] - f0;
     const int64_t k0 = coff[c], np = coff[c + 1] - k0;
-    if (nw > kRecWalls) {  // cells of more walls: one thread per pair
+    const int64_t s0 = fvo[f0], ns = fvo[f0 + nw] - s0;
+    if (nw > kRecWalls || ns > kRecTerms) {  // larger cells: one thread per pair
         for (int64_t k = k0 + (int64_t)blockIdx.y * blockDim.x + threadIdx.x; k < k0 + np;
              k += (int64_t)gridDim.y * blockDim.x) {
             const int64_t a = pair_p[k];
@@ -1607,36 +1611,51 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
             f[k] = v;
         }
     } else {
-        const int W = (int)nw;
-        for (int64_t pb = (int64_t)blockIdx.y * kRecPairs; pb < np; pb += (int64_t)gridDim.y * kRecPairs) {
-            const int nc = (int)(np - pb < kRecPairs ? np - pb : kRecPairs);
+        const int W = (int)nw, slots = (int)ns;
+        for (int w = threadIdx.x; w < W; w += blockDim.x)
+            for (int64_t sl = fvo[f0 + w]; sl < fvo[f0 + w + 1]; sl++) wall_of[sl - s0] = (uint8_t)w;
+        const int per = slots > 0 ? min(kRecPairs, kRecTerms / slots) : kRecPairs;  // pairs of a chunk
+        for (int64_t pb = (int64_t)blockIdx.y * per; pb < np; pb += (int64_t)gridDim.y * per) {
+            const int nc = (int)(np - pb < per ? np - pb : per);
             __syncthreads();  // the previous chunk's sums are done
             for (int it = threadIdx.x; it < nc * W; it += blockDim.x) {
                 const int p = it / W, w = it - p * W;
                 const int64_t a = pair_p[k0 + pb + p];
                 const double px = xyz[3 * a], py = xyz[3 * a + 1], pz = xyz[3 * a + 2];
-                const double invh = 1.0 / h[a];
                 const int64_t j = f0 + w;
                 const double nx = plane[4 * j], ny = plane[4 * j + 1], nz = plane[4 * j + 2], cj = plane[4 * j + 3];
-                const double d = cj - (nx * px + ny * py + nz * pz);
-                side[it] = (uint8_t)((d >= 0.0 ? 1 : 0) | (d == 0.0 ? 2 : 0));
-                const double r0d = fabs(d) * invh;
-                double face = 0.0;
+                wall[it] = cj - (nx * px + ny * py + nz * pz);
+            }
+            __syncthreads();
+            for (int it = threadIdx.x; it < nc * slots; it += blockDim.x) {
+                const int p = it / slots, sl = it - p * slots;
+                const int64_t a = pair_p[k0 + pb + p];
+                const double invh = 1.0 / h[a];
+                const double r0d = fabs(wall[p * W + wall_of[sl]]) * invh;
+                double t = 0.0;
                 if (r0d < 2.0) {
-                    Work wk;
-                    const double Ht = pi_H<double>(r0d), dH = pi_dH<double>(r0d);
-                    for (int64_t sl = fvo[j]; sl < fvo[j + 1]; sl++) {
-                        const EdgeRec E = edges[sl];
-                        const double wx = px - E.vx, wy = py - E.vy, wz = pz - E.vz;
-                        const double rho = E.mx * wx + E.my * wy + E.mz * wz;
-                        if (rho == 0.0) continue;
+                    const EdgeRec E = edges[s0 + sl];
+                    const double wx = xyz[3 * a] - E.vx, wy = xyz[3 * a + 1] - E.vy, wz = xyz[3 * a + 2] - E.vz;
+                    const double rho = E.mx * wx + E.my * wy + E.mz * wz;
+                    if (rho != 0.0) {
+                        Work wk;
                         const double la = -(E.ex * wx + E.ey * wy + E.ez * wz) * invh;
                         const double Le = E.L * invh;
-                        const double t = edge_term(r0d, fabs(rho) * invh, la, la + Le, Le, Ht, dH, wk);
-                        face += (rho > 0.0) ? t : -t;
+                        t = edge_term(r0d, fabs(rho) * invh, la, la + Le, Le, pi_H<double>(r0d), pi_dH<double>(r0d), wk);
+                        t = (rho > 0.0) ? t : -t;
                     }
                 }
-                term[it] = face;
+                term[it] = t;
+            }
+            __syncthreads();
+            for (int it = threadIdx.x; it < nc * W; it += blockDim.x) {
+                const int p = it / W, w = it - p * W;
+                const double d = wall[it];
+                side[it] = (uint8_t)((d >= 0.0 ? 1 : 0) | (d == 0.0 ? 2 : 0));
+                const int q0 = (int)(fvo[f0 + w] - s0), q1 = (int)(fvo[f0 + w + 1] - s0);
+                double face = 0.0;
+                for (int q = q0; q < q1; q++) face += term[p * slots + q];
+                wall[it] = face;
             }
             __syncthreads();
             for (int p = threadIdx.x; p < nc; p += blockDim.x) {
@@ -1649,7 +1668,7 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
                     const bool in_j = (sd & 1) != 0;
                     inside = inside && in_j;
                     n_on += (sd >> 1) & 1;
-                    const double face = term[p * W + w];
+                    const double face = wall[p * W + w];
                     acc += in_j ? face : -face;
                 }
                 const double v = winding_term(inside, n_on, xyz[3 * a], xyz[3 * a + 1], xyz[3 * a + 2], c, cfo, fvo,
