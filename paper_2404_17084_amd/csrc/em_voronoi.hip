@@ -695,13 +695,16 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
     const int nu = __popcll(used);
     char *base = recs + r * (int64_t)vor::kRecBytes;
     int big = -1;
-    if (status == vor::ST_OK && vor::rec_bytes(nu, nt) > vor::kRecBytes) {
+    if (status == vor::ST_OK &&
+        (vor::rec_bytes(nu, nt) > vor::kRecBytes || nu > vor::kRecPlanes || nt > vor::kRecTris)) {
         if (lane == 0) big = (int)atomicAdd(big_used, 1u);
         big = __builtin_amdgcn_readfirstlane(big);
     }
     if (lane == 0) *reinterpret_cast<vor::RecHead *>(base) = vor::RecHead{nu, nt, status, big, used};
     if (status == vor::ST_OK && (big < 0 || (unsigned)big < n_big)) {  // (too many big cells: the host builds again)
-        const vor::Rec G = vor::rec_at(big < 0 ? base : bigs + big * (int64_t)vor::kBigRecBytes, nu, nt);
+        char *at = big < 0 ? base : bigs + big * (int64_t)vor::kBigRecBytes;
+        if (big >= 0 && lane == 0) *reinterpret_cast<int64_t *>(at) = r;  // whose it is, in the header's place
+        const vor::Rec G = vor::rec_at(at, nu, nt);
         if (c > 0) {
             const int k = lanes_below(used);
             G.pl[k] = W.pl[lane];
@@ -741,40 +744,50 @@ struct VorOut {
 // summed over the faces of each lane and then across the wavefront).  The
 // record is read once into LDS.  flags bit 3: a face's vertices did not close
 // into one loop.
+template <int PLANES, int TRIS>
 struct XCell {
-    vor::Plane pl[vor::kMaxPlanes];
-    double vx[vor::kMaxTris], vy[vor::kMaxTris], vz[vor::kMaxTris];
-    uint32_t tri[vor::kMaxTris];
-    int32_t src[vor::kMaxPlanes];
-    uint8_t et[vor::kMaxPlanes * vor::kMaxPlanes];  // directed edge (x, y): its triangle at 64 x + y, 0xff: none
-    uint8_t ring[vor::kMaxPlanes][64];               // ring[k][p]: the k-th triangle around plane p
+    vor::Plane pl[PLANES];
+    double vx[TRIS], vy[TRIS], vz[TRIS];
+    uint32_t tri[TRIS];
+    int32_t src[PLANES];
+    uint8_t et[PLANES * PLANES];   // directed edge (x, y): its triangle at PLANES x + y, 0xff: none
+    uint8_t ring[PLANES][PLANES];  // ring[k][p]: the k-th triangle around plane p
 };
 static_assert(vor::kMaxTris < 255 && vor::kMaxPlanes <= 64, "triangle ids in bytes, one plane per lane");
 
-__global__ void __launch_bounds__(128) k_vor_extract(int64_t n, const double *__restrict__ s,
+// BIG: one wavefront per big record (n of them); else one per input site, the
+// big ones left out.  Bound by the latency of LDS and of the records: with 14 kB
+// of LDS for every cell ten wavefronts fit a CU and 262,144 clumpy sites took
+// 1.27 ms; with 5 kB, where registers allow 16, 0.86, and 24, 0.70 ms.
+template <bool BIG>
+__global__ void __launch_bounds__(128, BIG ? 1 : 6) k_vor_extract(int64_t n, const double *__restrict__ s,
                                                      const int64_t *__restrict__ rank,
+                                                     const int32_t *__restrict__ orig,
                                                      char *__restrict__ recs, char *__restrict__ bigs,
                                                      const int64_t *__restrict__ foff, const int64_t *__restrict__ soff,
                                                      const int64_t *__restrict__ voff, VorOut O, unsigned *flags)
 {
-    __shared__ XCell xbuf[2];
+    constexpr int PLANES = BIG ? vor::kMaxPlanes : vor::kRecPlanes, TRIS = BIG ? vor::kMaxTris : vor::kRecTris;
+    __shared__ XCell<PLANES, TRIS> xbuf[2];
     const int lane = threadIdx.x & 63;
-    XCell &X = xbuf[threadIdx.x >> 6];
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (i >= n) return;  // whole wavefronts
-    char *base = recs + rank[i] * (int64_t)vor::kRecBytes;
+    XCell<PLANES, TRIS> &X = xbuf[threadIdx.x >> 6];
+    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (w >= n) return;  // whole wavefronts
+    const int64_t r = BIG ? *reinterpret_cast<const int64_t *>(bigs + w * (int64_t)vor::kBigRecBytes) : rank[w];
+    const int64_t i = BIG ? orig[r] : w;
+    char *base = recs + r * (int64_t)vor::kRecBytes;
     const vor::RecHead H = *reinterpret_cast<const vor::RecHead *>(base);
-    if (lane == 0) {
+    if (!BIG && lane == 0) {
         O.cfo[i] = foff[i];
         if (i == n - 1) O.cfo[n] = foff[n];
     }
-    if (H.status != vor::ST_OK) return;
+    if (H.status != vor::ST_OK || (H.big >= 0) != BIG) return;
     const int np = H.np, nt = H.nt;
-    const vor::Rec C = vor::rec_at(H.big < 0 ? base : bigs + H.big * (int64_t)vor::kBigRecBytes, np, nt);
+    const vor::Rec C = vor::rec_at(BIG ? bigs + w * (int64_t)vor::kBigRecBytes : base, np, nt);
     const double sx = s[3 * i], sy = s[3 * i + 1], sz = s[3 * i + 2];
     const int64_t vbase = voff[i], fbase = foff[i], sbase = soff[i];
     uint32_t *et32 = reinterpret_cast<uint32_t *>(X.et);
-    for (int k = lane; k < vor::kMaxPlanes * vor::kMaxPlanes / 4; k += 64) et32[k] = 0xffffffffu;
+    for (int k = lane; k < PLANES * PLANES / 4; k += 64) et32[k] = 0xffffffffu;
     if (lane < np) {
         X.pl[lane] = C.pl[lane];
         X.src[lane] = C.src[lane];
@@ -793,9 +806,9 @@ __global__ void __launch_bounds__(128) k_vor_extract(int64_t n, const double *__
     for (int t = lane; t < nt; t += 64) {
         const uint32_t q = X.tri[t];
         const int a = vor::tri_a(q), b = vor::tri_b(q), c = vor::tri_c(q);
-        X.et[64 * a + b] = (uint8_t)t;
-        X.et[64 * b + c] = (uint8_t)t;
-        X.et[64 * c + a] = (uint8_t)t;
+        X.et[PLANES * a + b] = (uint8_t)t;
+        X.et[PLANES * b + c] = (uint8_t)t;
+        X.et[PLANES * c + a] = (uint8_t)t;
     }
     lds_sync_wave();
     // the ring of triangles around plane p = lane, from the first that holds it
@@ -812,12 +825,12 @@ __global__ void __launch_bounds__(128) k_vor_extract(int64_t n, const double *__
     int len = 0;
     if (face) {
         int t = first;
-        while (len < nr && len < vor::kMaxPlanes) {  // (a valid cell has at most np - 1)
+        while (len < nr && len < PLANES) {  // (a valid cell has at most np - 1)
             X.ring[len][p] = (uint8_t)t;
             len++;
             const uint32_t q = X.tri[t];
             const int b = vor::tri_a(q) == p ? vor::tri_c(q) : (vor::tri_b(q) == p ? vor::tri_a(q) : vor::tri_b(q));
-            const int nx = X.et[64 * p + b];  // the triangle holding the directed edge (p, b)
+            const int nx = X.et[PLANES * p + b];  // the triangle holding the directed edge (p, b)
             if (nx == 0xff || nx == first) break;
             t = nx;
         }
@@ -1141,7 +1154,7 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
     // many as it asked for
     char *recs = static_cast<char *>(ws.get(S_VOR8, vor::kRecBytes * (size_t)n)), *bigs = nullptr;
     unsigned n_big = (unsigned)(n / 16 + 16);
-    int64_t tot[3] = {0, 0, 0};
+    int64_t tot[3] = {0, 0, 0}, n_used = 0;
     for (;;) {
         bigs = static_cast<char *>(ws.get(S_VOR15, vor::kBigRecBytes * (size_t)n_big));
         hipLaunchKernelGGL(k_vor_build_wave, dim3(vgrid(64 * n, 128)), dim3(128), 0, s, n, (const double *)ps,
@@ -1155,6 +1168,7 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
         read_back(ws, {{&tot[0], foff + n, sizeof(int64_t)}, {&tot[1], soff + n, sizeof(int64_t)},
                        {&tot[2], voff + n, sizeof(int64_t)}, {h2, flags, sizeof(h2)}}, s);
         hf = h2[0];
+        n_used = h2[1];
         if (h2[1] <= n_big) break;
         n_big = h2[1];
         fill_zero_bytes(flags, sizeof(unsigned) * 4, s);
@@ -1174,10 +1188,16 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
     O.plane = dev_alloc(V.plane, V.cap_plane, (size_t)(4 * tot[0]));
     O.fv = dev_alloc(V.fv, V.cap_fv, (size_t)tot[1]);
     O.verts = dev_alloc(V.verts, V.cap_verts, (size_t)(3 * tot[2]));
-    hipLaunchKernelGGL(k_vor_extract, dim3(vgrid(64 * n, 128)), dim3(128), 0, s, n, sites, (const int64_t *)rank,
-                       recs, bigs,
-                       (const int64_t *)foff, (const int64_t *)soff, (const int64_t *)voff, O, flags);
+    hipLaunchKernelGGL(k_vor_extract<false>, dim3(vgrid(64 * n, 128)), dim3(128), 0, s, n, sites,
+                       (const int64_t *)rank, orig, recs, bigs, (const int64_t *)foff, (const int64_t *)soff,
+                       (const int64_t *)voff, O, flags);
     EM_HIP(hipGetLastError());
+    if (n_used > 0) {
+        hipLaunchKernelGGL(k_vor_extract<true>, dim3(vgrid(64 * n_used, 128)), dim3(128), 0, s, n_used, sites,
+                           (const int64_t *)rank, orig, recs, bigs, (const int64_t *)foff, (const int64_t *)soff,
+                           (const int64_t *)voff, O, flags);
+        EM_HIP(hipGetLastError());
+    }
     read_back(ws, {{&hf, flags, sizeof(unsigned)}}, s);
     EM_CHECK(!(hf & 8u), MAP_EDEVICE, "a Voronoi face did not close into one loop");
     V.n = n;

@@ -49,6 +49,7 @@ struct RecHead {
     uint64_t used;                // the planes that are left, by the order in which they were cut
 };
 constexpr size_t kRecBytes = 2048;
+constexpr int kRecPlanes = 32, kRecTris = 64;  // more also make a cell a big one (the extraction's LDS)
 __host__ __device__ constexpr size_t rec_bytes(int np, int nt)
 {
     return sizeof(RecHead) + (size_t)np * (sizeof(Plane) + 4) + (size_t)nt * (3 * sizeof(double) + 4);
