@@ -198,6 +198,9 @@ struct IntegrateTune {
 // ---------------------------------------------------------------- primitives (em_primitives.hip)
 // Exclusive scan of int64 counts: out[0] = 0, out[i+1] = out[i] + in[i]; out has n+1 entries.
 void scan_counts(Workspace &ws, const int64_t *in, int64_t *out, int64_t n, hipStream_t s);
+// Boxes (lo, hi: 6 doubles) of the inner nodes 1 .. NL - 1 of a tree in heap
+// order from those of its NL leaves (a power of two), nodes NL .. 2 NL - 1.
+void tree_parent_boxes(double *boxes, int64_t NL, hipStream_t s);
 // Stable LSD radix sort by the low `bits` bits of 32-bit keys, carrying 32-bit values.
 // Results end in (keys, vals); (keys2, vals2) are scratch of the same size.
 void radix_sort_u32(Workspace &ws, uint32_t *keys, uint32_t *vals, uint32_t *keys2, uint32_t *vals2, int64_t n,

@@ -167,19 +167,6 @@ __global__ void k_particle_boxes(int64_t n, const double *__restrict__ xyz, cons
     }
 }
 
-__global__ void k_parent_boxes(int64_t first, int64_t count, double *nodes)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= count) return;
-    int64_t i = first + t;
-    const double *a = nodes + 6 * (2 * i), *b = nodes + 6 * (2 * i + 1);
-    double *o = nodes + 6 * i;
-    for (int d = 0; d < 3; d++) {
-        o[d] = fmin(a[d], b[d]);
-        o[3 + d] = fmax(a[3 + d], b[3 + d]);
-    }
-}
-
 __device__ __forceinline__ double box_dist2(const double *bb, double px, double py, double pz)
 {
     double dx = fmax(fmax(bb[0] - px, px - bb[3]), 0.0);
@@ -660,11 +647,7 @@ PairSet build_pairs(Workspace &ws, const DevInputs &in, const double *aabb, cons
     hipLaunchKernelGGL(k_leaf_boxes, dim3((unsigned)((NL + 255) / 256)), dim3(256), 0, s, n, NL,
                        (const uint32_t *)nullptr, (const double *)pbox, nodes);
     EM_HIP(hipGetLastError());
-    for (int64_t first = NL / 2; first >= 1; first /= 2) {
-        hipLaunchKernelGGL(k_parent_boxes, dim3((unsigned)((first + 255) / 256)), dim3(256), 0, s, first, first,
-                           nodes);
-        EM_HIP(hipGetLastError());
-    }
+    tree_parent_boxes(nodes, NL, s);
 
     // candidates per cell (tree walk with the cheap tests, particles ascending),
     // the exact test of the marked ones, and the pairs per cell.  Each cell has

@@ -522,19 +522,6 @@ __global__ void k_pt_leaf_boxes(int64_t n_pts, int64_t NL, const double4 *__rest
     }
 }
 
-// boxes of the internal nodes [first, 2 first) of the point tree (heap order)
-__global__ void k_pt_parent_boxes(int64_t first, double *__restrict__ bx)
-{
-    const int64_t i = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 2 * first) return;
-    const double *a = bx + 6 * (2 * i), *b = bx + 6 * (2 * i + 1);
-    double *o = bx + 6 * i;
-    for (int d = 0; d < 3; d++) {
-        o[d] = fmin(a[d], b[d]);
-        o[3 + d] = fmax(a[3 + d], b[3 + d]);
-    }
-}
-
 __device__ __forceinline__ double box_gap2(const double *bb, double px, double py, double pz)
 {
 #pragma clang fp contract(off)
@@ -1178,10 +1165,7 @@ int64_t walk_tree(Workspace &ws, const TreeState &TS, const DevParticles &P, con
         hipLaunchKernelGGL(k_pt_leaf_boxes, dim3(grid_of(NL)), dim3(256), 0, s, n_pts, NL, (const double4 *)pts,
                            bx);
         EM_HIP(hipGetLastError());
-        for (int64_t first = NL / 2; first >= 1; first /= 2) {
-            hipLaunchKernelGGL(k_pt_parent_boxes, dim3(grid_of(first)), dim3(256), 0, s, first, bx);
-            EM_HIP(hipGetLastError());
-        }
+        tree_parent_boxes(bx, NL, s);
         hipLaunchKernelGGL(k_hsolve, dim3(grid_of(64 * n_pts)), dim3(256), 0, s, n_pts, (const double4 *)pts,
                            (const double *)bx, NL, nleaf, (const int64_t *)pt_slot, (const int32_t *)pt_node, T,
                            (const uint32_t *)perm, P.h, par.h_fact_node, O.h, hc);

@@ -98,16 +98,6 @@ __global__ void k_vor_leaf_boxes(int64_t n, int64_t NL, const double *__restrict
     }
 }
 
-__global__ void k_vor_parent_boxes(int64_t first, double *__restrict__ bx)
-{
-    const int64_t i = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 2 * first) return;
-    for (int d = 0; d < 3; d++) {
-        bx[6 * i + d] = fmin(bx[6 * (2 * i) + d], bx[6 * (2 * i + 1) + d]);
-        bx[6 * i + 3 + d] = fmax(bx[6 * (2 * i) + 3 + d], bx[6 * (2 * i + 1) + 3 + d]);
-    }
-}
-
 // ---------------------------------------------------------------- one wavefront per cell
 // The working cell of each wavefront is in LDS: the lanes own the cell's
 // triangles (lane l: triangles l and l + 64), so a cut tests every vertex at
@@ -1118,10 +1108,7 @@ SiteTree site_tree(Workspace &ws, int64_t n, const double *sites, const VBox &B,
     double *bx = ws.get<double>(S_VOR7, (size_t)(12 * NL));
     hipLaunchKernelGGL(k_vor_leaf_boxes, dim3(vgrid(NL, 256)), dim3(256), 0, s, n, NL, (const double *)ps, bx);
     EM_HIP(hipGetLastError());
-    for (int64_t first = NL / 2; first >= 1; first /= 2) {
-        hipLaunchKernelGGL(k_vor_parent_boxes, dim3(vgrid(first, 256)), dim3(256), 0, s, first, bx);
-        EM_HIP(hipGetLastError());
-    }
+    tree_parent_boxes(bx, NL, s);
     return SiteTree{ps, orig, rank, bx, NL};
 }
 
