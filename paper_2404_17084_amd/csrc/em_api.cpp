@@ -327,7 +327,7 @@ void ensure_table(Ctx &C, hipStream_t s)
     C.table.d64 = nullptr;
     C.table.d4 = nullptr;
     EM_HIP(hipMalloc(&C.table.d64, sizeof(double) * nodes));
-    EM_HIP(hipMalloc(&C.table.d4, sizeof(float4) * nodes));
+    EM_HIP(hipMalloc(&C.table.d4, sizeof(TabNode) * nodes));
     launch_table_build(C.table.n[0], C.table.n[1], C.table.n[2], C.table.d64, C.table.d4, s);
     EM_HIP(hipStreamSynchronize(s));
     C.table.built = true;

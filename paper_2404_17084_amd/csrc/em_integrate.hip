@@ -1031,7 +1031,7 @@ __device__ __forceinline__ int job_of_tile(const JobsArg &A, int64_t t)
     int lo = 0, hi = A.n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (A.table[mid].tile_base <= t) lo = mid;
+        if (A.table[mid].wave_base <= t) lo = mid;
         else hi = mid - 1;
     }
     return lo;
@@ -1078,7 +1078,7 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
         const double *__restrict__ plane = JOB(plane);
         const int64_t *__restrict__ fvo = JOB(fvo);
         const int sh = JOB(split), part = lane & ((1 << sh) - 1);  // 2^sh neighbouring lanes share a pair
-        const int64_t k = (t - JOB(tile_base)) * (64 >> sh) + (lane >> sh);
+        const int64_t k = (t - JOB(wave_base)) * (64 >> sh) + (lane >> sh);
         const bool active = k < JOB(np);
         double px = 0.0, py = 0.0, pz = 0.0, invh = 1.0;
         int32_t s = 0, s_end = 0, j = 0;
@@ -1241,7 +1241,7 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
         const double *__restrict__ plane = JOB(plane);
         const int64_t *__restrict__ fvo = JOB(fvo);
         const int sh = JOB(split), part = lane & ((1 << sh) - 1);  // 2^sh neighbouring lanes share a pair
-        const int64_t k = (t - JOB(tile_base)) * (64 >> sh) + (lane >> sh);
+        const int64_t k = (t - JOB(wave_base)) * (64 >> sh) + (lane >> sh);
         const bool active = k < JOB(np);
         double px = 0.0, py = 0.0, pz = 0.0, invh = 1.0;
         int32_t s = 0, s_end = 0, j = 0;
@@ -1553,15 +1553,15 @@ __global__ void k_table_build(int n0, int n1, int n2, double *__restrict__ tab64
 }
 
 // The node values as the reads take them (em_table.hip).
-__global__ void k_table_pack(int n0, int n1, int n2, const double *__restrict__ tab64, float4 *__restrict__ tab4)
+__global__ void k_table_pack(int n0, int n1, int n2, const double *__restrict__ tab64, TabNode *__restrict__ tab4)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t dj = n2, di = (int64_t)n1 * n2;
     if (q >= (int64_t)n0 * di) return;
     const int j = (int)((q / n2) % n1), i = (int)(q / di);
     const bool in = i + 1 < n0 && j + 1 < n1;
-    tab4[q] = in ? make_float4((float)tab64[q], (float)tab64[q + dj], (float)tab64[q + di], (float)tab64[q + di + dj])
-                 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    tab4[q] = in ? TabNode{(float)tab64[q], (float)tab64[q + dj], (float)tab64[q + di], (float)tab64[q + di + dj]}
+                 : TabNode{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
 }  // namespace
@@ -1682,7 +1682,7 @@ __global__ void __launch_bounds__(256) k_recompute_cells(int64_t n_list, const u
     if (threadIdx.x == 0 && blockIdx.y == 0) atomicAdd(counter_copy(counters) + C_FP64_PAIRS, (unsigned long long)np);
 }
 
-void launch_table_build(int n0, int n1, int n2, double *tab64, float4 *tab4, hipStream_t s)
+void launch_table_build(int n0, int n1, int n2, double *tab64, TabNode *tab4, hipStream_t s)
 {
     const int64_t total = (int64_t)n0 * n1 * n2;
     const dim3 g((unsigned)((total + 255) / 256));
@@ -1720,12 +1720,13 @@ static void launch_queued(const IntJob *h_jobs, const IntJob *d_jobs, int n_jobs
 {
     EM_CHECK(n_jobs >= 1 && h_jobs, MAP_EINVAL, "integration launch without jobs");
     EM_CHECK(n_jobs == 1 || d_jobs, MAP_EINVAL, "integration launch of several jobs without a device table");
-    int64_t tiles = 0;
+    int64_t blocks64 = 0, tiles = 0;
     for (int i = 0; i < n_jobs; i++) {
-        EM_CHECK(h_jobs[i].tile_base == tiles && h_jobs[i].np > 0, MAP_EINVAL,
+        EM_CHECK(h_jobs[i].tile_base == blocks64 && h_jobs[i].wave_base == tiles && h_jobs[i].np > 0, MAP_EINVAL,
                  "integration job table: tile bases are not the running tile count");
         EM_CHECK(h_jobs[i].split == job_split(h_jobs[i].np, precision), MAP_EINVAL,
                  "integration job table: a job's split is not the one of its size");
+        blocks64 += (h_jobs[i].np + 63) / 64;
         tiles += job_tiles(h_jobs[i]);
     }
     JobsArg A;
@@ -1795,7 +1796,7 @@ void launch_integrate(const DevInputs &in, const EdgeRec *edges, const PairSet &
         IntJob J;
         J.np = np;
         J.split = job_split(np, precision);
-        J.tile_base = 0;
+        J.tile_base = J.wave_base = 0;
         J.pair_p = ps.pair_p;
         J.pair_c = ps.pair_c;
         J.xyz = in.xyz;

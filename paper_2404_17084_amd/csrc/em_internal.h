@@ -273,12 +273,13 @@ int64_t run_pseudo_adaptive(Workspace &ws, const DevParticles &p, const double b
                             hipEvent_t *ev);
 
 // One job of an integration launch of the task-batch kernels: its pairs
-// (cell-major), inputs, geometry tables and outputs.  tile_base is the job's
-// first tile (a wavefront's pairs) in the launch's tile space, the running sum
-// of the tiles of the jobs before it.
+// (cell-major), inputs, geometry tables and outputs.  tile_base and wave_base are
+// the running sums over the jobs before it of their tiles of 64 pairs and of
+// the tiles that the wavefronts take (64 >> split pairs): its first tile in the
+// launch's tile space.
 struct IntJob {
     int64_t np = 0;
-    int64_t tile_base = 0;
+    int64_t tile_base = 0, wave_base = 0;
     int split = 0;  // 2^split lanes share a pair, each with its part of the cell's walls (job_split)
     const uint32_t *pair_p = nullptr, *pair_c = nullptr;
     const double *xyz = nullptr, *h = nullptr;
@@ -341,11 +342,17 @@ void launch_fixup(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, 
 void launch_fixup_apply(const uint64_t *keys, const double *vals, int64_t n_fix, const uint32_t *pair_p, double *f,
                         double *S, hipStream_t s);
 
+// Four FP32 node values of the table (a type of its own: this header is also
+// compiled for the host alone).
+struct alignas(16) TabNode {
+    float x, y, z, w;
+};
+
 // em_integrate.hip: node values of the tabulated pyramid integral: FP64, and FP32 as the reads take them (per node
 // (i, j, k) the four values at i, i + 1 and j, j + 1; zeros where there is no i + 1 or j + 1)
-void launch_table_build(int n0, int n1, int n2, double *tab64, float4 *tab4, hipStream_t s);
+void launch_table_build(int n0, int n1, int n2, double *tab64, TabNode *tab4, hipStream_t s);
 // em_table.hip: raw f per pair through the table (cell-major order)
-void launch_integrate_table(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const float4 *tab, int n0,
+void launch_integrate_table(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const TabNode *tab, int n0,
                             int n1, int n2, double *f, int64_t *counters, hipStream_t s);
 
 // em_voronoi.hip: the box-clipped Voronoi grid of a site set, in the cell

@@ -51,7 +51,7 @@ struct Ctx {
         int n[3] = {64, 64, 64};
         bool built = false;
         double *d64 = nullptr;
-        float4 *d4 = nullptr;
+        TabNode *d4 = nullptr;
     } table;
 };
 

@@ -289,7 +289,7 @@ static bool launch_batch(Server &S)
             for (int prec : {MAP_FP64, MAP_MIXED}) {
                 IntJob *ht = S.h_table + (size_t)prec * S.table_cap;
                 std::vector<Job *> members;
-                int64_t tiles = 0;
+                int64_t tiles = 0, wave_tiles = 0;
                 int n = 0;
                 for (Job *j : staged) {
                     if (j->precision != prec) continue;
@@ -319,6 +319,7 @@ static bool launch_batch(Server &S)
                     e.np = js.ps.n_pairs;
                     e.split = job_split(e.np, prec);
                     e.tile_base = tiles;
+                    e.wave_base = wave_tiles;
                     e.pair_p = js.ps.pair_p;
                     e.pair_c = js.ps.pair_c;
                     e.xyz = js.in.xyz;
@@ -334,7 +335,8 @@ static bool launch_batch(Server &S)
                     e.fix_count = js.tile_ctr + 1;
                     e.fix_items = js.fix_items;
                     e.fix_cap = (unsigned)std::min<int64_t>(js.fix_cap, 0xffffffffLL);
-                    tiles += job_tiles(e);
+                    tiles += (e.np + 63) / 64;
+                    wave_tiles += job_tiles(e);
                     members.push_back(j);
                 }
                 if (n == 0) continue;

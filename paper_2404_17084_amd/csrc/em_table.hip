@@ -36,7 +36,7 @@ namespace em {
 namespace {
 
 struct TableView {
-    const float4 *__restrict__ t;  // per node (i, j, k), i < n0 - 1, j < n1 - 1: the values at (i, j), (i, j + 1), (i + 1, j), (i + 1, j + 1)
+    const TabNode *__restrict__ t;  // per node (i, j, k), i < n0 - 1, j < n1 - 1: the values at (i, j), (i, j + 1), (i + 1, j), (i + 1, j + 1)
     int n0, n1, n2;
     float s0, s1, s2;  // grid coordinates per unit of r0, R0, phi
 };
@@ -56,8 +56,8 @@ __device__ __forceinline__ float table_I(const TableView &T, float r0, float R0,
     grid_cell(r0 * T.s0, T.n0, i, a);
     grid_cell(R0 * T.s1, T.n1, j, b);
     grid_cell(phi * T.s2, T.n2, k, c);
-    const float4 *p = T.t + ((int64_t)i * T.n1 + j) * T.n2 + k;
-    const float4 A = p[0], B = p[1];
+    const TabNode *p = T.t + ((int64_t)i * T.n1 + j) * T.n2 + k;
+    const TabNode A = p[0], B = p[1];
     const float v00 = A.x + c * (B.x - A.x);
     const float v01 = A.y + c * (B.y - A.y);
     const float v10 = A.z + c * (B.z - A.z);
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) k_integrate_table(int64_t np, const uint3
 
 }  // namespace
 
-void launch_integrate_table(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const float4 *tab, int n0,
+void launch_integrate_table(const DevInputs &in, const EdgeRec *edges, const PairSet &ps, const TabNode *tab, int n0,
                             int n1, int n2, double *f, int64_t *counters, hipStream_t s)
 {
     const int64_t np = ps.n_pairs;
