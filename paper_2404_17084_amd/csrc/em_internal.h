@@ -65,7 +65,7 @@ public:
     void use_stream(hipStream_t s) { stream_ = s; }
     bool is_arena() const { return arena_base_ != nullptr; }
     // Pinned host memory (kMailboxBytes) that kernels write results to, allocated on
-    // first use; null in arena mode, which allocates nothing.
+    // first use; null in arena mode, which allocates nothing, and where there is none to be had.
     void *mailbox();
     // bytes still free in arena mode (SIZE_MAX otherwise)
     size_t arena_free() const;

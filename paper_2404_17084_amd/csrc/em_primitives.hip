@@ -21,8 +21,12 @@ Workspace::~Workspace()
 
 void *Workspace::mailbox()
 {
-    if (!mailbox_ && !arena_base_) EM_HIP(hipHostMalloc(&mailbox_, kMailboxBytes, hipHostMallocDefault));
-    return arena_base_ ? nullptr : mailbox_;
+    if (arena_base_) return nullptr;
+    if (!mailbox_ && hipHostMalloc(&mailbox_, kMailboxBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();  // the copies do without it
+        mailbox_ = nullptr;
+    }
+    return mailbox_;
 }
 
 void Workspace::use_arena(void *base, size_t bytes)
