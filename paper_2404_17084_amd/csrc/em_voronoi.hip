@@ -210,11 +210,6 @@ struct Bounds {
     double m2;
 };
 
-__device__ __forceinline__ float round_up(double v)  // v >= 0
-{
-    return (float)v * 1.0000002f;
-}
-
 __device__ __forceinline__ void bounds_of(const MyTris &T, int nt, int lane, Bounds &B)
 {
     float l[3] = {0.0f, 0.0f, 0.0f}, h[3] = {0.0f, 0.0f, 0.0f}, m = 0.0f;
