@@ -202,43 +202,55 @@ __device__ __forceinline__ void load_tris(const WCell &W, int nt, int lane, MyTr
 
 // Upper bounds of the cell about its site, wave-uniform: how far it reaches
 // along the six axis directions and the squared distance of its farthest
-// vertex, rounded up to FP32.  (The site lies in its cell, so all are >= 0.)
-// They only decide which sites need no cut, so a bound that is a little too
-// large changes nothing.
+// vertex.  (The site lies in its cell, so all are >= 0.)  They only decide
+// which sites need no cut, so a bound that is a little too large changes
+// nothing: the reduction takes the upper words of the doubles, 20 bits of
+// mantissa and the whole range of exponents, and rounds up.  (With FP32 bounds
+// and distances, cells were wrong where squared lengths leave FP32's range:
+// neighbours 2e19 units apart or more were never cut.)
 struct Bounds {
-    float lo[3], hi[3];  // reach along -x, -y, -z and +x, +y, +z
+    double lo[3], hi[3];  // reach along -x, -y, -z and +x, +y, +z
     double m2;
 };
 
+// Upper word of a double >= 0 (-0 counts as 0): orders like the value.
+__device__ __forceinline__ uint32_t upper_word(double v) { return (uint32_t)__double2hiint(v) & 0x7fffffffu; }
+
+// The lanes' largest value (all >= 0), rounded up to its upper word.
+__device__ __forceinline__ double wave_bound(double v)
+{
+    const uint32_t w = wave_umax(upper_word(v)) + 1u, inf = 0x7ff00000u;
+    return __hiloint2double((int)(w < inf ? w : inf), 0);
+}
+
 __device__ __forceinline__ void bounds_of(const MyTris &T, int nt, int lane, Bounds &B)
 {
-    float l[3] = {0.0f, 0.0f, 0.0f}, h[3] = {0.0f, 0.0f, 0.0f}, m = 0.0f;
+    double l[3] = {0.0, 0.0, 0.0}, h[3] = {0.0, 0.0, 0.0}, m = 0.0;
 #pragma unroll
     for (int u = 0; u < 2; u++)
         if (lane + 64 * u < nt) {
-            const double x = T.x[u], y = T.y[u], z = T.z[u];
-            const float f[3] = {(float)x, (float)y, (float)z};
+            const double f[3] = {T.x[u], T.y[u], T.z[u]};
             for (int d = 0; d < 3; d++) {
-                l[d] = fmaxf(l[d], -f[d]);
-                h[d] = fmaxf(h[d], f[d]);
+                l[d] = fmax(l[d], -f[d]);
+                h[d] = fmax(h[d], f[d]);
             }
-            m = fmaxf(m, (float)(x * x + y * y + z * z));
+            m = fmax(m, f[0] * f[0] + f[1] * f[1] + f[2] * f[2]);
         }
     for (int d = 0; d < 3; d++) {
-        B.lo[d] = __uint_as_float(wave_umax(__float_as_uint(l[d] + 0.0f))) * 1.0000002f;
-        B.hi[d] = __uint_as_float(wave_umax(__float_as_uint(h[d] + 0.0f))) * 1.0000002f;
+        B.lo[d] = wave_bound(l[d]);
+        B.hi[d] = wave_bound(h[d]);
     }
-    B.m2 = (double)(__uint_as_float(wave_umax(__float_as_uint(m))) * 1.0000002f);
+    B.m2 = wave_bound(m);
 }
 
 // A site at offset w reaches the cell only if some vertex v has w.v > |w|^2 /
 // 2; w.v is at most the box's reach along w (all of whose terms are >= 0).
-// FP32, with a margin above its rounding.
-__device__ __forceinline__ bool may_cut(const Bounds &B, float dx, float dy, float dz, float d2)
+// With a margin above the rounding.
+__device__ __forceinline__ bool may_cut(const Bounds &B, double dx, double dy, double dz, double d2)
 {
-    const float r = fmaxf(-dx * B.lo[0], dx * B.hi[0]) + fmaxf(-dy * B.lo[1], dy * B.hi[1]) +
-                    fmaxf(-dz * B.lo[2], dz * B.hi[2]);
-    return 0.5f * d2 < r * 1.000002f;
+    const double r = fmax(-dx * B.lo[0], dx * B.hi[0]) + fmax(-dy * B.lo[1], dy * B.hi[1]) +
+                     fmax(-dz * B.lo[2], dz * B.hi[2]);
+    return d2 < r * (2.0 + 1e-12);
 }
 
 // The candidate sites of one pass with the whole wavefront: each step takes 16
@@ -300,13 +312,13 @@ __device__ int collect_wave(WCell &W, const double *__restrict__ ps, int64_t n, 
                     const bool in = lane + 64 * u < cnt;
                     q[u] = in ? W.cand[lane + 64 * u] : 0;
                     d[u] = in ? dist2(q[u], dx, dy, dz) : INFINITY;
-                    key[u] = __float_as_uint((float)d[u]);
+                    key[u] = upper_word(d[u]);
                 }
                 auto upto = [&](uint32_t k) {
                     return __popcll(__ballot(key[0] <= k)) + __popcll(__ballot(key[1] <= k)) +
                            __popcll(__ballot(key[2] <= k));
                 };
-                uint32_t ka = 0, kb = __float_as_uint(INFINITY);  // at most half are <= ka, more than half <= kb
+                uint32_t ka = 0, kb = upper_word(INFINITY);  // at most half are <= ka, more than half <= kb
                 while (kb - ka > 1) {
                     const uint32_t km = ka + (kb - ka) / 2;
                     if (upto(km) <= kWCand / 2) ka = km;
@@ -534,8 +546,8 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
         bool more = false;
         double blo[3], bhi[3];
         for (int d = 0; d < 3; d++) {
-            blo[d] = -(double)bd.lo[d];
-            bhi[d] = (double)bd.hi[d];
+            blo[d] = -bd.lo[d];
+            bhi[d] = bd.hi[d];
         }
         int cnt = collect_wave(W, ps, n, bx, NL, r, sx, sy, sz, lo2, lo_q, hi2, blo, bhi, lane, &more);
         if (cnt < 0) {  // the serial walk, 64 at a time
@@ -554,7 +566,7 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
                 break;
             }
         }
-        // candidates lane, lane + 64, lane + 128: offsets, squared distances (bits of the FP32 value as the coarse key)
+        // candidates lane, lane + 64, lane + 128: offsets, squared distances (their upper words as the coarse key)
         double cx[3], cy[3], cz[3], cd[3];
         int32_t cq[3];
         bool left[3];
@@ -573,10 +585,9 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
             if (fresh) {
 #pragma unroll
                 for (int u = 0; u < 3; u++) {
-                    const float d2 = (float)cd[u];
                     const bool cuts = left[u] && cd[u] < 4.0 * bd.m2 && cd[u] > 0.0 &&
-                                      may_cut(bd, (float)cx[u], (float)cy[u], (float)cz[u], d2);
-                    key[u] = cuts ? __float_as_uint(d2) : ~0u;
+                                      may_cut(bd, cx[u], cy[u], cz[u], cd[u]);
+                    key[u] = cuts ? upper_word(cd[u]) : ~0u;
                 }
                 fresh = false;
             }
@@ -592,7 +603,7 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
             const bool tie = __popcll(at[0]) + __popcll(at[1]) + __popcll(at[2]) > 1;
 #pragma unroll
             for (int u = 0; u < 3; u++)
-                for (uint64_t m = at[u]; m != 0; m &= m - 1) {  // (one, but for equal FP32 distances)
+                for (uint64_t m = at[u]; m != 0; m &= m - 1) {  // (one, but for equal upper words)
                     const int l = __builtin_ctzll(m);
                     if (tie) {
                         const double d = lane_value(cd[u], l);

@@ -252,3 +252,36 @@ def test_voronoi_many_faced_cells(per_line):
             G = mp.voronoi(s, BOX)
             assert (np.abs(G.cell_volume - O["cell_volume"]) / O["cell_volume"]).max() < 1e-10
             assert _nb_sets(G, range(2 * per_line)) == _nb_sets(O, range(2 * per_line))
+
+
+@pytest.mark.parametrize("kind", ["uniform", "clumps"])
+@pytest.mark.parametrize("scale", [2.0 ** -8, 3.1e21, 2.0 ** 66, 2.0 ** 70, 2.0 ** 200])
+def test_voronoi_units_of_length(kind, scale):
+    """The same grid in other units of length, up to galaxies in centimetres and beyond, where squared lengths leave
+    FP32's range: the neighbours of the unit box, its volumes and sites times the scale.  A power of two is exact;
+    3.1e21 rounds every coordinate once, 1e-16 of the box, against cells of about 1e-3 of it in a clump: 1e-12 a
+    length, some 1e-11 a volume."""
+    say(f"case: voronoi {kind} 700, lengths times {scale:.3g}")
+    s = synth.particles(kind, 700, 81).xyz
+    with em.Mapper(device=0) as mp:
+        A = mp.voronoi(s, BOX)
+        G = mp.voronoi(s * scale, BOX * scale)
+    assert _nb_sets(G, range(700)) == _nb_sets(A, range(700))
+    tol = 1e-14 if np.log2(scale) == np.round(np.log2(scale)) else 1e-11
+    assert np.abs(G.cell_volume / scale ** 3 / A.cell_volume - 1.0).max() < tol
+    assert np.abs(G.centroid / scale - A.centroid).max() < 10 * tol
+    assert abs(G.cell_volume.sum() / scale ** 3 - 1.0) < 1e-11
+
+
+def test_voronoi_sites_far_closer_than_the_box():
+    """A cluster of sites 1e-30 of the box wide: the squared distances and reaches of its cells are 1e-60 of the
+    box's.  The cells that a box of seven units does not clip are the same in the large one."""
+    say("case: voronoi cluster in a box of 1e30")
+    s = np.random.default_rng(12).random((300, 3))
+    O = oracle.voronoi(s, np.array([-3.0] * 3 + [4.0] * 3))
+    with em.Mapper(device=0) as mp:
+        G = mp.voronoi(s, np.array([-1e30] * 3 + [1e30] * 3))
+    inner = [i for i, nb in enumerate(_nb_sets(O, range(300))) if nb[0] >= 0]
+    assert len(inner) > 50
+    assert [_nb_sets(G, [i]) for i in inner] == [_nb_sets(O, [i]) for i in inner]
+    assert np.abs(G.cell_volume[inner] / O["cell_volume"][inner] - 1.0).max() < 1e-10
