@@ -343,7 +343,10 @@ __global__ void __launch_bounds__(256) k_candidates(
 // D decides when |D - r^2| exceeds a bound on its rounding, tol = 1e-6 (r + 2
 // rc)^2 (every vector involved is shorter than r + 2 rc, FP32 rounding of D is
 // below 10 u (r + 2 rc)^2); (4) D within tol of r^2, and cells of more than 64
-// walls, run the exact test.  Cells too large for the staging area are read
+// walls, run the exact test.  Lengths are rounded to FP32 in a unit near the
+// cell's size, a power of two, so that their squares stay in FP32's range
+// whatever the caller's unit; a support 1e15 cells wide leaves it and takes
+// the exact test.  Cells too large for the staging area are read
 // from the global tables throughout.
 //
 // Bound by latency: 70 % of the wavefronts' time is waits (the cell's records,
@@ -356,16 +359,16 @@ __global__ void __launch_bounds__(256) k_candidates(
 constexpr uint32_t kNoCand = 0xffffffffu;
 
 // One slot of the tested cell as the screened test takes it: edge start (about
-// the cell centre) and length, edge direction, in-wall normal.  From the staged
+// the cell centre) and length in the cell's unit, edge direction, in-wall normal.  From the staged
 // cell, or for a cell too large for it from its records.
 struct SlotF {
     float ax, ay, az, len, ex, ey, ez, mx, my, mz;
 };
 
-__device__ __forceinline__ SlotF slot_of(const EdgeRec &E, double gx, double gy, double gz)
+__device__ __forceinline__ SlotF slot_of(const EdgeRec &E, double gx, double gy, double gz, double per_unit)
 {
-    return SlotF{(float)(E.vx - gx), (float)(E.vy - gy), (float)(E.vz - gz), (float)E.L, (float)E.ex, (float)E.ey,
-                 (float)E.ez, (float)E.mx, (float)E.my, (float)E.mz};
+    return SlotF{(float)((E.vx - gx) * per_unit), (float)((E.vy - gy) * per_unit), (float)((E.vz - gz) * per_unit),
+                 (float)(E.L * per_unit), (float)E.ex, (float)E.ey, (float)E.ez, (float)E.mx, (float)E.my, (float)E.mz};
 }
 
 // squared FP32 distance from q (about the cell centre) to wall j of the cell: d2 (its plane's distance) when q's foot
@@ -414,6 +417,8 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
         const bool screen = nf <= 64 && ns < 65536;  // (a bit per wall, 16-bit slot offsets)
         const bool fits = nf <= kExactMaxFaces && ns <= kExactMaxSlots;
         const double gx = centre[3 * c], gy = centre[3 * c + 1], gz = centre[3 * c + 2], rc2 = 2.0 * radii[2 * c + 1];
+        const int ex = min(max(__builtin_amdgcn_frexp_exp(rc2), -1000), 1000);
+        const double unit = __builtin_amdgcn_ldexp(1.0, ex), per_unit = __builtin_amdgcn_ldexp(1.0, -ex);
         int64_t pairs = 0;
         bool staged = false;
         int waiting = 0;
@@ -423,7 +428,7 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
                 if (fits) {
                     for (int q = lane; q < 4 * (int)nf; q += 64) L.pl_[q >> 2][q & 3] = plane[4 * j0 + q];
                     for (int q = lane; q < (int)ns; q += 64) {
-                        const SlotF E = slot_of(edges[s0 + q], gx, gy, gz);
+                        const SlotF E = slot_of(edges[s0 + q], gx, gy, gz, per_unit);
                         L.a_[q] = make_float4(E.ax, E.ay, E.az, E.len);
                         L.b_[q] = make_float4(E.ex, E.ey, E.ez, E.mx);
                         L.c_[q] = make_float2(E.my, E.mz);
@@ -438,7 +443,7 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
                     const float2 C = L.c_[k];
                     return SlotF{A.x, A.y, A.z, A.w, B.x, B.y, B.z, B.w, C.x, C.y};
                 };
-                auto rec = [&](int k) { return slot_of(edges[s0 + k], gx, gy, gz); };
+                auto rec = [&](int k) { return slot_of(edges[s0 + k], gx, gy, gz, per_unit); };
                 const int k0 = L.so_[j], k1 = L.so_[j + 1];
                 return fits ? wall_dist2(lds, k0, k1, qx, qy, qz, d2, in_poly)
                             : wall_dist2(rec, k0, k1, qx, qy, qz, d2, in_poly);
@@ -466,14 +471,20 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
                 }
                 hit = valid && inside;
                 bool open = valid && !inside && !(far * far > r2 * (1.0 + 1e-9));
-                const double rr = r + rc2, tol = 1e-6 * rr * rr;
-                const float qx = (float)(px - gx), qy = (float)(py - gy), qz = (float)(pz - gz);
+                const double rs = r * per_unit, rs2 = rs * rs, rr = rs + rc2 * per_unit, tol = 1e-6 * rr * rr;
+                if (open && !(rr < 1e15)) {
+                    exact = true;
+                    open = false;
+                }
+                const float qx = (float)((px - gx) * per_unit), qy = (float)((py - gy) * per_unit),
+                            qz = (float)((pz - gz) * per_unit);
+                const double fs = far * per_unit;
                 float D = INFINITY;
                 if (open) {
                     bool in_poly;
-                    D = wall(jf, qx, qy, qz, (float)(far * far), in_poly);
+                    D = wall(jf, qx, qy, qz, (float)(fs * fs), in_poly);
                     seen &= in_poly ? 0ull : ~(1ull << jf);
-                    if ((double)D < r2 - tol) {
+                    if ((double)D < rs2 - tol) {
                         hit = true;
                         open = false;
                     }
@@ -490,7 +501,8 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
                         if (lane < m) {
                             const int o = L.task_[at + lane] >> 8, j = L.task_[at + lane] & 255;
                             const float x = L.p_[o][0], y = L.p_[o][1], z = L.p_[o][2];
-                            const double d = pl(j, 3) - (pl(j, 0) * (gx + x) + pl(j, 1) * (gy + y) + pl(j, 2) * (gz + z));
+                            const double d = (pl(j, 3) - (pl(j, 0) * (gx + x * unit) + pl(j, 1) * (gy + y * unit) +
+                                                          pl(j, 2) * (gz + z * unit))) * per_unit;
                             bool in_poly;
                             const float Dj = wall(j, x, y, z, (float)(d * d), in_poly);
                             atomicMin(&L.dmin_[o], __float_as_uint(Dj));
@@ -511,8 +523,8 @@ __global__ void __launch_bounds__(64 * kExactWaves) k_exact(
                     D = __uint_as_float(L.dmin_[lane]);
                 }
                 if (open) {
-                    if ((double)D < r2 - tol) hit = true;
-                    else if (!((double)D > r2 + tol)) exact = true;
+                    if ((double)D < rs2 - tol) hit = true;
+                    else if (!((double)D > rs2 + tol)) exact = true;
                 }
             }
             if (exact) hit = cell_meets(px, py, pz, r2, c, cfo, fvo, edges, plane);

@@ -33,3 +33,30 @@ def test_pair_set(n, scale, order):
     with em.Mapper(device=0) as mp:
         pp, pc = mp.pairs(q, c)
     assert np.array_equal(pp, ref["pair_p"]) and np.array_equal(pc, ref["pair_c"])
+
+
+@pytest.mark.parametrize("walls", [16, 48])
+@pytest.mark.parametrize("scale", [2.0 ** -100, 2.0 ** -80, 1.0, 2.0 ** 66, 2.0 ** 70, 2.0 ** 200])
+def test_pair_set_in_other_units(scale, walls):
+    """Lengths times a power of two, which is exact: the pairs are those of the unit box, also where squared lengths
+    leave FP32's range.  One cell among `walls` others on a sphere about it: fewer walls than the test stages in LDS
+    (40), and more."""
+    import oracle
+    import paper_2404_17084_amd as em
+    import synth
+
+    k = np.arange(walls) + 0.5
+    ph, th = np.arccos(1 - 2 * k / walls), np.pi * (1 + 5 ** 0.5) * k
+    s = 0.5 + 0.25 * np.stack([np.cos(th) * np.sin(ph), np.sin(th) * np.sin(ph), np.cos(ph)], 1)
+    s = np.concatenate([[[0.5, 0.5, 0.5]], s + 1e-3 * np.random.default_rng(1).standard_normal(s.shape)])
+    c = synth.voronoi_cells(s)
+    assert np.diff(c.cell_face_off).max() == walls
+    x = np.random.default_rng(2).random((3000, 3))
+    p = synth.Particles(x, np.full(3000, 1 / 3000.0), np.full(3000, 0.03))
+    ref = oracle.map_particles(p, c)
+    q = synth.Particles(x * scale, p.m, p.h * scale)
+    cs = synth.Cells(c.cell_face_off, c.face_vert_off, c.face_vert, c.face_plane * np.array([1.0, 1.0, 1.0, scale]),
+                     c.face_nb, c.verts * scale, c.cell_volume * scale ** 3, tuple(scale * np.array(synth.BOX)))
+    with em.Mapper(device=0) as mp:
+        pp, pc = mp.pairs(q, cs)
+    assert np.array_equal(pp, ref["pair_p"]) and np.array_equal(pc, ref["pair_c"])
