@@ -1112,8 +1112,8 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued(JobsArg A, unsign
                 if (s < s_end) {
                     j++;
                     face_end = (int32_t)fvo[j + 1];
-                    const double d =
-                        plane[4 * j + 3] - (plane[4 * j] * px + plane[4 * j + 1] * py + plane[4 * j + 2] * pz);
+                    const double *pl = plane + plane_at(j);
+                    const double d = pl[3] - (pl[0] * px + pl[1] * py + pl[2] * pz);
                     wk.faces++;
                     const bool in_j = d >= 0.0;
                     at_walls = (at_walls + (d == 0.0)) | (in_j ? 0u : 0x80000000u);
@@ -1275,8 +1275,8 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
                 if (s < s_end) {
                     j++;
                     face_end = (int32_t)fvo[j + 1];
-                    const double d =
-                        plane[4 * j + 3] - (plane[4 * j] * px + plane[4 * j + 1] * py + plane[4 * j + 2] * pz);
+                    const double *pl = plane + plane_at(j);
+                    const double d = pl[3] - (pl[0] * px + pl[1] * py + pl[2] * pz);
                     wk.faces++;
                     const bool in_j = d >= 0.0;
                     at_walls = (at_walls + (d == 0.0)) | (in_j ? 0u : 0x80000000u);

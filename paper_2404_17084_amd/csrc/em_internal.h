@@ -174,6 +174,10 @@ constexpr int kCounterCopies = 16, kCounterStride = 16;
 // tiles of each XCD's eighth, a cache line each.
 constexpr int kXcdCtr = 32, kXcdCtrStride = 32, kLaunchCtrs = kXcdCtr + 8 * kXcdCtrStride;
 
+// First of the four values of wall j in a plane array, in 64 bits also for the
+// 32-bit wall indices of the kernels: 2^29 walls have 2^31 values.
+constexpr int64_t plane_at(int64_t j) { return 4 * j; }
+
 // Device-resident view of one job's inputs.
 struct DevInputs {
     int64_t n = 0;

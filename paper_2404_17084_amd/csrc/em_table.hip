@@ -122,8 +122,8 @@ __global__ void __launch_bounds__(256) k_integrate_table(int64_t np, const uint3
             face = 0.0;
             j++;
             face_end = (int32_t)fvo[j + 1];
-            const double nx = plane[4 * (int64_t)j], ny = plane[4 * (int64_t)j + 1], nz = plane[4 * (int64_t)j + 2],
-                         cj = plane[4 * (int64_t)j + 3];
+            const double *pl = plane + plane_at(j);
+            const double nx = pl[0], ny = pl[1], nz = pl[2], cj = pl[3];
             const double d = cj - (nx * px + ny * py + nz * pz);
             n_faces++;
             in_j = d >= 0.0;
