@@ -300,14 +300,22 @@ __device__ __forceinline__ double part_len(double x, double y, double la, double
 
 // The angle of two parts [a1, b1], [a2, b2] at the foot point as the argument
 // of the product of their complex numbers (R0^2 + a b) + i R0 (b - a) (the sum
-// stays below pi).
+// stays below pi).  Where the product overflows (edges that reach 1e76 h and
+// more from the foot point) the numbers are scaled down first.
 __device__ __forceinline__ void angle_product(double R0, double a1, double b1, double a2, double b2, double &y,
                                               double &x)
 {
     const double R02 = R0 * R0;
-    const double x1 = fma(a1, b1, R02), y1 = R0 * (b1 - a1), x2 = fma(a2, b2, R02), y2 = R0 * (b2 - a2);
+    double x1 = fma(a1, b1, R02), y1 = R0 * (b1 - a1), x2 = fma(a2, b2, R02), y2 = R0 * (b2 - a2);
     x = fma(x1, x2, -(y1 * y2));
     y = fma(x1, y2, x2 * y1);
+    if (!(y + fabs(x) <= 0x1p1000)) {
+        const double s1 = fmax(fabs(x1), y1) > 0x1p480 ? 0x1p-540 : 1.0, s2 = fmax(fabs(x2), y2) > 0x1p480 ? 0x1p-540 : 1.0;
+        x1 *= s1, y1 *= s1;
+        x2 *= s2, y2 *= s2;
+        x = fma(x1, x2, -(y1 * y2));
+        y = fma(x1, y2, x2 * y1);
+    }
 }
 
 // Closed form of one piece over one edge part [a, a + L]: the integral along it
