@@ -192,9 +192,10 @@ __device__ __forceinline__ double box_dist2(const double *bb, double px, double 
 // the cell's whole bounding box lies within (1 - 1e-6) 2h of the particle, or
 // when the ball about the cell's interior point g (radius rin) comes closer
 // than (1 - 1e-9) 2h; dropped when the ball about g that contains the cell
-// (radius rc) stays (1 + 1e-9) 2h or more away.  The margins exceed the
-// rounding of every distance involved, so these decisions are the exact
-// test's.  The rest are marked for the exact test.
+// (radius rc) stays (1 + 1e-9) 2h or more away; the balls' radii have a margin
+// of 1e-14 of their own, for supports far smaller than the cell.  The margins
+// exceed the rounding of every distance involved, so these decisions are the
+// exact test's.  The rest are marked for the exact test.
 // A cell has room for K candidates (particle index, bit 31 = marked), from c K
 // on.  A cell with more has all of them in the overflow list, from ovf_off[c]
 // on, which a second walk of those cells writes (SECOND).
@@ -293,7 +294,8 @@ __global__ void __launch_bounds__(256) k_candidates(
                 const double fz = fmax(fabs(cb[2] - pz), fabs(cb[5] - pz));
                 const double dx = centre[3 * c] - px, dy = centre[3 * c + 1] - py, dz = centre[3 * c + 2] - pz;
                 const double dg2 = dx * dx + dy * dy + dz * dz;
-                const double ri = r * (1.0 - 1e-9) + radii[2 * c], ro = r * (1.0 + 1e-9) + radii[2 * c + 1];
+                const double ri = r * (1.0 - 1e-9) + radii[2 * c] * (1.0 - 1e-14);
+                const double ro = r * (1.0 + 1e-9) + radii[2 * c + 1] * (1.0 + 1e-14);
                 const bool ok = fx * fx + fy * fy + fz * fz < r2 * 0.999998 || dg2 < ri * ri;
                 const bool cand = in_reach && (ok || dg2 < ro * ro);
                 const unsigned long long mc = __ballot(cand);

@@ -60,3 +60,27 @@ def test_pair_set_in_other_units(scale, walls):
     with em.Mapper(device=0) as mp:
         pp, pc = mp.pairs(q, cs)
     assert np.array_equal(pp, ref["pair_p"]) and np.array_equal(pc, ref["pair_c"])
+
+
+@pytest.mark.parametrize("h", [1e-6, 1e-14, 1e-18, 1e-30])
+def test_particles_on_the_vertices(h):
+    """Particles on the cells' own vertices, supports down to far below the rounding of the cells' coordinates: the
+    ball about a cell ends at its farthest vertex, whose particle must not be dropped for the rounding of its
+    distance.  Pairs of a particle with the cell whose vertex it is on, as the oracle's test of all pairs has them."""
+    import oracle
+    import paper_2404_17084_amd as em
+    import synth
+
+    c = synth.voronoi_cells(np.random.default_rng(8).random((200, 3)))
+    own = np.full(c.n_verts, -1)
+    for i in range(c.n_cells):
+        a, b = c.face_vert_off[c.cell_face_off[i]], c.face_vert_off[c.cell_face_off[i + 1]]
+        own[c.face_vert[a:b]] = i
+    n = c.n_verts
+    p = synth.Particles(c.verts.copy(), np.full(n, 1.0 / n), np.full(n, h))
+    pp, pc = oracle.pairs(p.xyz, p.h, c, brute=True)
+    want = set(pp[own[pp] == pc].tolist())
+    with em.Mapper(device=0) as mp:
+        gp, gc = mp.pairs(p, c)
+    got = set(gp[own[gp] == gc].tolist())
+    assert len(want) > n // 4 and want - got == set()
