@@ -11,6 +11,7 @@
 // (faces counter-clockwise about outward unit normals, vertices per cell),
 // the site or wall across each face, the volumes and the centroids.  A Lloyd
 // step moves every site to its cell's centroid and builds the grid again.
+#include <algorithm>
 #include <cmath>
 
 #include "em_internal.h"
@@ -1143,10 +1144,11 @@ void build_voronoi(Workspace &ws, VorGrid &V, int64_t n, const double *sites, co
     int64_t *soff = ws.get<int64_t>(S_VOR13, (size_t)n + 1);
     int64_t *voff = ws.get<int64_t>(S_VOR14, (size_t)n + 1);
     unsigned *big_used = flags + 1;
-    // the cells' records, and big ones for one cell in 16; a grid with more big cells is built again with as
-    // many as it asked for
+    // the cells' records, and big ones for one cell in 16, or as many as there is room for from the grid before; a
+    // grid with more big cells is built again with as many as it asked for
     char *recs = static_cast<char *>(ws.get(S_VOR8, vor::kRecBytes * (size_t)n)), *bigs = nullptr;
-    unsigned n_big = (unsigned)(n / 16 + 16);
+    unsigned n_big = (unsigned)std::min<int64_t>(
+        n, std::max<int64_t>(n / 16 + 16, (int64_t)(ws.held(S_VOR15) / vor::kBigRecBytes)));
     int64_t tot[3] = {0, 0, 0}, n_used = 0;
     for (;;) {
         bigs = static_cast<char *>(ws.get(S_VOR15, vor::kBigRecBytes * (size_t)n_big));

@@ -285,3 +285,26 @@ def test_voronoi_sites_far_closer_than_the_box():
     assert len(inner) > 50
     assert [_nb_sets(G, [i]) for i in inner] == [_nb_sets(O, [i]) for i in inner]
     assert np.abs(G.cell_volume[inner] / O["cell_volume"][inner] - 1.0).max() < 1e-10
+
+
+def test_voronoi_many_faced_grids_are_built_once():
+    """Half the cells with more faces than a usual record holds (two skew lines of 20 sites in each of 4^3 boxes): the
+    first grid finds too few large records and is built again; the next grids, Lloyd steps among them, find the
+    buffer and are built once."""
+    say("case: voronoi many-faced grid, kernels of the second call")
+    from torch.profiler import ProfilerActivity, profile
+
+    q, rng = np.linspace(0.3, 0.7, 20), np.random.default_rng(1)
+    mid = np.full_like(q, 0.5)
+    g = np.stack(np.meshgrid([0.25, 0.75], [0.25, 0.75], [0.25, 0.75], indexing="ij"), -1).reshape(-1, 3)
+    one = np.concatenate([np.stack([q, mid, mid - 0.1], 1), np.stack([mid, q, mid + 0.1], 1), g])
+    s = np.concatenate([(one + 1e-3 * rng.standard_normal(one.shape) + i) / 4 for i in np.ndindex(4, 4, 4)])
+    with em.Mapper(device=0) as mp:
+        G = mp.voronoi(s, BOX)
+        assert np.mean(np.diff(G.cell_face_off) > 23) > 0.25
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            H = mp.voronoi(s, BOX, lloyd_iters=2)
+    builds = sum(e.count for e in prof.key_averages() if "k_vor_build_wave" in e.key)
+    say(f"  {builds} builds for a grid and two Lloyd steps")
+    assert builds == 3
+    assert H.cell_volume.sum() == pytest.approx(1.0, rel=1e-12)
