@@ -106,7 +106,7 @@ __device__ __forceinline__ double sqrt_f64(double x)
     return x > 0.0 ? g : 0.0;
 }
 
-// atan2(y, x) for y >= 0, result in [0, pi]; (0, 0) gives 0.  Three ranges of
+// atan2(y, x) for y >= 0, |x| + y < 2^1022; result in [0, pi], (0, 0) gives 0.  Three ranges of
 // y / |x|, cut at tan(pi/8) and tan(3 pi/8): the angle is k pi/4 + atan(q) with
 // q = y / |x|, (y - |x|) / (y + |x|) or -|x| / y, |q| <= tan(pi/8), one division
 // for all three; x < 0 mirrors it to (4 - k) pi/4 - atan(q).  atan q = q + q z
@@ -116,7 +116,7 @@ __device__ __forceinline__ double atan2_f64(double y, double x)
     const double ax = fabs(x);
     const bool low = y <= 0.41421356237309503 * ax, steep = y > 2.4142135623730951 * ax;
     const double num = low ? y : (steep ? -ax : y - ax);
-    const double den = (low ? ax : (steep ? y : y + ax)) + 1e-300;  // (0, 0): 0 / 1e-300
+    const double den = fmax(low ? ax : (steep ? y : y + ax), 0x1p-1022);  // (0, 0): 0 / 2^-1022
     double k = low ? 0.0 : (steep ? 2.0 : 1.0);
     k = x < 0.0 ? 4.0 - k : k;
     const double q = div_f64(x < 0.0 ? -num : num, den), z = q * q;

@@ -345,7 +345,7 @@ __device__ __forceinline__ double part_term(double r0, double R0, double a0, dou
     const bool mirror = a0 + b0 < 0.0;
     const double a = mirror ? -b0 : a0, b = mirror ? -a0 : b0;
     const double A = r0 * r0, R02 = R0 * R0;
-    const double c2 = fmax(A + R02, 1e-290);
+    const double c2 = A + R02;
     const double Sa = sqrt_f64(fma(a, a, c2)), Sb = sqrt_f64(fma(b, b, c2));
     const double ab = a * b, SS = Sa * Sb, Ssum = Sa + Sb;
     const double rs = div_f64(1.0, Ssum);
@@ -356,7 +356,8 @@ __device__ __forceinline__ double part_term(double r0, double R0, double a0, dou
     const double Dbeta = 2.0 * atan2_f64(yb, xb);
     const double u = L * fma(a + b, rs, 1.0);
     const bool an = a < 0.0;
-    const double Da = log1p_ratio_f64(an ? u * (Sa - a) : u, an ? c2 : a + Sa);
+    // (c^2 may round to 0, the logarithm then is finite and multiplied by it)
+    const double Da = log1p_ratio_f64(an ? u * (Sa - a) : u, fmax(an ? c2 : a + Sa, 1e-290));
     const double t = a * (a + b) * rs;
     const double DxS = L * (Sb + t);
     const double DxS3 = L * fma(t, fma(Sa, Sa, fma(Sb, Sb, SS)), Sb * Sb * Sb);

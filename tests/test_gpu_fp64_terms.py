@@ -46,3 +46,26 @@ def test_cells_far_larger_than_the_support(h, dist):
         r = mp.map(p, c, want_pairs=True)
     assert np.abs(r["f"] - 0.5).max() < 1e-12 and r["f"].size == 4
     assert np.abs(r["M"] - 0.5).max() < 1e-12
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("dist", [0, 3])
+def test_particles_next_to_an_edge(precision, dist):
+    """Particles beside the common edge of four cells, down to distances whose squares, or that themselves, are near
+    the smallest doubles: each cell holds a quarter (to the distance), and a particle on a wall plane beside the edge
+    as much as one off it.  1e-12 as above; mixed 1e-6, some 40 FP32 terms of order one."""
+    import paper_2404_17084_amd as em
+    import synth
+
+    c = synth.voronoi_cells(np.array([[x, y, 0.0] for x in (-.25, .25) for y in (-.25, .25)]),
+                            (-.5, -.5, -.5, .5, .5, .5))
+    prec = em.MAP_FP64 if precision == "fp64" else em.MAP_MIXED
+    e = [0.0, 1e-20, 1e-100, 1e-146, 1e-170, 1e-250, 1e-280, 1e-290, 1e-300, 1e-310]
+    xyz = np.array([[a, b, z] for a in e for b in e for z in (0.0, 0.1)])
+    n = len(xyz)
+    p = synth.Particles(xyz, np.full(n, 1.0 / n), np.full(n, 0.1))
+    with em.Mapper(device=0, precision=prec) as mp:
+        em.map_set_tune(mp.ctx, prec, waves=0 if dist == 0 else (3 if precision == "fp64" else 6), persistent=dist)
+        r = mp.map(p, c, want_pairs=True)
+    assert r["f"].size == 4 * n
+    assert np.abs(r["f"] - 0.25).max() < (1e-12 if precision == "fp64" else 1e-6)
