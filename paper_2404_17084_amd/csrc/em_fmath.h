@@ -71,7 +71,9 @@ __device__ __forceinline__ float log1p_f32(float u)
 // ---------------------------------------------------------------- FP64
 // The library's double functions cost several times these (argument classes
 // the edge terms never meet, correctly rounded divisions, extended-precision
-// intermediate sums).  Each form below is within 3 ulp over its stated domain.
+// intermediate sums).  Each form below is within 3 ulp over its stated domain
+// (largest errors found over all exponents and at the cuts: division and square
+// root 0.5, arctangent 3.0, logarithm 2.4).
 
 // p z + c with c kept in its register.  The compiler forms the steps of a
 // Horner sum as a move of the coefficient and a two-operand v_fmac_f64, one
@@ -134,30 +136,33 @@ __device__ __forceinline__ double atan2_f64(double y, double x)
 }
 
 // log(1 + n / d) for n >= 0, d > 0: the ratio of N = d + n and d as 2^k M / D
-// with M / D in [sqrt(1/2), sqrt(2)], log(M / D) = 2 atanh(s), s = (M - D) /
-// (M + D), |s| <= 0.1716 (n / (N + d), with n exact, when k = 0); atanh s =
-// s + s^3 P(s^2), P fitted for least maximum relative error (Remez; 2e-18).
-// One division for the ratio and the logarithm.
+// with M / D in [5/6, 5/3], log(M / D) = 2 atanh(s), s = (M - D) / (M + D),
+// |s| <= 1/4 (n / (2 d + n) when k = 0); atanh s = s + s^3 P(s^2),
+// P fitted for least maximum relative error (Remez; 1e-17).  The rounding of N
+// is an absolute error where k > 0; with the ratio cut at 5/3 the result is
+// above 1/2 there, so that this is one unit (two at a cut of sqrt(2), 3.6 with
+// the rest).  One division for the ratio and the logarithm.
 __device__ __forceinline__ double log1p_ratio_f64(double n, double d)
 {
     const double N = d + n;
     int k = __builtin_amdgcn_frexp_exp(N) - __builtin_amdgcn_frexp_exp(d);
     double M = __builtin_amdgcn_frexp_mant(N), D = __builtin_amdgcn_frexp_mant(d);
-    if (M > 1.4142135623730951 * D) {
+    if (M > 1.6666666666666667 * D) {
         D += D;
         k += 1;
-    } else if (D > 1.4142135623730951 * M) {
+    } else if (M < 0.83333333333333337 * D) {
         M += M;
         k -= 1;
     }
-    const double s = div_f64(k == 0 ? n : M - D, k == 0 ? N + d : M + D), z = s * s;
-    double p = 0.074054223133321661683;
-    p = horner_f64(p, z, 0.07656206821538370732);
-    p = horner_f64(p, z, 0.090918181095641508513);
-    p = horner_f64(p, z, 0.11111098483779897497);
-    p = horner_f64(p, z, 0.14285714380770156303);
-    p = horner_f64(p, z, 0.19999999999649014241);
-    p = horner_f64(p, z, 0.33333333333333826701);
+    const double s = div_f64(k == 0 ? n : M - D, k == 0 ? fma(2.0, d, n) : M + D), z = s * s;
+    double p = 0.07598479913953453;
+    p = horner_f64(p, z, 0.06457231710210651);
+    p = horner_f64(p, z, 0.07705714463987434);
+    p = horner_f64(p, z, 0.09090416066032425);
+    p = horner_f64(p, z, 0.11111121626402759);
+    p = horner_f64(p, z, 0.14285714161962293);
+    p = horner_f64(p, z, 0.2000000000070331);
+    p = horner_f64(p, z, 0.33333333333331966);
     const double s2 = s + s;
     return fma((double)k, 0.69314718055994531, fma(s2 * z, p, s2));
 }
