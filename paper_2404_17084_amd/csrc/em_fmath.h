@@ -95,8 +95,8 @@ __device__ __forceinline__ double div_f64(double n, double d)
     return fma(fma(-d, q, n), y, q);
 }
 
-// sqrt(x), x >= 0 and not denormal (0 gives 0): the hardware reciprocal square
-// root and two coupled Newton steps.
+// sqrt(x) (0 and infinity are themselves, NaN for NaN and x < 0): the hardware
+// reciprocal square root and two coupled Newton steps.
 __device__ __forceinline__ double sqrt_f64(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
@@ -105,7 +105,7 @@ __device__ __forceinline__ double sqrt_f64(double x)
     g = fma(g, r, g);
     h = fma(h, r, h);
     g = fma(fma(-g, g, x), h, g);
-    return x > 0.0 ? g : 0.0;
+    return __builtin_amdgcn_class(x, 0x260) ? x : g;  // -0, +0, +infinity
 }
 
 // atan2(y, x) for y >= 0, |x| + y < 2^1022; result in [0, pi], (0, 0) gives 0.  Three ranges of

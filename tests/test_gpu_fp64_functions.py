@@ -62,6 +62,12 @@ def test_square_root(lo, hi):
     assert e < 3.0
 
 
+def test_square_root_special_values():
+    x = np.array([0.0, -0.0, np.inf, np.nan, -1.0, -np.inf])
+    r = run(SQRT, x)
+    assert np.array_equal(r[:3], [0.0, 0.0, np.inf]) and np.signbit(r[1]) and np.isnan(r[3:]).all()
+
+
 @pytest.mark.parametrize("kind", ["any", "tan(pi/8)", "tan(3 pi/8)", "one", "small angles", "near pi", "tiny", "huge"])
 def test_arctangent(kind):
     rng = np.random.default_rng(3)
