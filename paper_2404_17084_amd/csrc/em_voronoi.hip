@@ -285,7 +285,7 @@ __device__ int collect_wave(WCell &W, const double *__restrict__ ps, int64_t n, 
         dx = ps[3 * q] - sx;
         dy = ps[3 * q + 1] - sy;
         dz = ps[3 * q + 2] - sz;
-        return dx * dx + dy * dy + dz * dz;
+        return vor::length2(dx, dy, dz);
     };
     int sp = 0, nl = 0, cnt = 0;  // inner nodes, leaves, candidates
     auto push = [&](bool v, int64_t node) {  // false: no room
@@ -578,7 +578,7 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
             cx[u] = ps[3 * (int64_t)cq[u]] - sx;
             cy[u] = ps[3 * (int64_t)cq[u] + 1] - sy;
             cz[u] = ps[3 * (int64_t)cq[u] + 2] - sz;
-            cd[u] = cx[u] * cx[u] + cy[u] * cy[u] + cz[u] * cz[u];
+            cd[u] = vor::length2(cx[u], cy[u], cz[u]);
         }
         bool fresh = true;  // the bounds have changed
         uint32_t key[3] = {~0u, ~0u, ~0u};
@@ -631,7 +631,7 @@ __global__ void __launch_bounds__(128, 4) k_vor_build_wave(int64_t n, const doub
             if (bu == 0) take(0);
             else if (bu == 1) take(1);
             else take(2);
-            P.d = 0.5 * fma(P.nz, P.nz, fma(P.nx, P.nx, P.ny * P.ny));
+            P.d = 0.5 * vor::length2(P.nx, P.ny, P.nz);
             if (wclip(W, np, nt, status, P, orig[q], lane, T)) {
                 bounds_of(T, nt, lane, bd);
                 fresh = true;

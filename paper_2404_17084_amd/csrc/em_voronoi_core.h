@@ -103,6 +103,11 @@ __host__ __device__ inline double box_gap2(const double *bb, double px, double p
     return dx * dx + dy * dy + dz * dz;
 }
 
+// Squared length of a site's offset, wherever it is a key or a plane's offset:
+// written out, so that it rounds alike everywhere (a site whose key differed
+// between the walk that lists it and the pass that follows could be lost).
+__host__ __device__ inline double length2(double x, double y, double z) { return fma(z, z, fma(x, x, y * y)); }
+
 // Key order of the candidate sites: squared distance, then sorted index.
 __host__ __device__ inline bool key_less(double d2, int64_t q, double e2, int64_t r)
 {
@@ -185,7 +190,7 @@ __host__ __device__ inline int collect(CellT &C, const double *ps, int64_t n, co
         for (int64_t q = kLeaf * j; q < kLeaf * (j + 1) && q < n; q++) {
             if (q == self) continue;
             const double dx = ps[3 * q] - sx, dy = ps[3 * q + 1] - sy, dz = ps[3 * q + 2] - sz;
-            const double d2 = dx * dx + dy * dy + dz * dz;
+            const double d2 = length2(dx, dy, dz);
             if (!(d2 < hi2) || !key_less(lo2, lo_q, d2, q) || !(0.5 * d2 < reach(blo, bhi, dx, dy, dz))) continue;
             if (cnt < kMaxCand) {  // push, sift up
                 int k = cnt++;
