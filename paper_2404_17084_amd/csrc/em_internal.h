@@ -205,8 +205,8 @@ void scan_counts(Workspace &ws, const int64_t *in, int64_t *out, int64_t n, hipS
 // Boxes (lo, hi: 6 doubles) of the inner nodes 1 .. NL - 1 of a tree in heap
 // order from those of its NL leaves (a power of two), nodes NL .. 2 NL - 1.
 void tree_parent_boxes(double *boxes, int64_t NL, hipStream_t s);
-// Stable LSD radix sort by the low `bits` bits of 32-bit keys, carrying 32-bit values.
-// Results end in (keys, vals); (keys2, vals2) are scratch of the same size.
+// Stable sort of 32-bit keys below 2^bits, carrying 32-bit values.  Results end
+// in (keys, vals); (keys2, vals2) are scratch of the same size.
 void radix_sort_u32(Workspace &ws, uint32_t *keys, uint32_t *vals, uint32_t *keys2, uint32_t *vals2, int64_t n,
                     int bits, hipStream_t s);
 // The same for 64-bit keys.

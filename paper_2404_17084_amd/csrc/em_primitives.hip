@@ -400,11 +400,7 @@ void scan_counts(Workspace &ws, const int64_t *in, int64_t *out, int64_t n, hipS
     scan_rec(tmp, in, out, n, s);
 }
 
-// ---------------------------------------------------------------- radix sort
-// LSD radix sort with digits of up to 10 bits: a key width of b bits takes
-// ceil(b / 10) passes, the width split evenly between them (18-bit keys: two
-// passes of 9 bits, so the result lands back in the input buffers).  Short
-// lists are sorted by counting instead.
+// ---------------------------------------------------------------- box trees
 // A workgroup takes 256 parents of one level and goes up the subtree above them,
 // nine levels a launch; one launch per level took 2.4 us each, 84 of them for a
 // grid of 30,011 sites with five Lloyd steps.
@@ -437,6 +433,11 @@ void tree_parent_boxes(double *boxes, int64_t NL, hipStream_t s)
     }
 }
 
+// ---------------------------------------------------------------- radix sort
+// LSD radix sort with digits of up to 10 bits: a key width of b bits takes
+// ceil(b / 10) passes, the width split evenly between them (18-bit keys: two
+// passes of 9 bits, so the result lands back in the input buffers).  Short
+// lists are sorted by counting instead.
 constexpr int RS_BLOCK = 256;
 constexpr int RS_WAVES = RS_BLOCK / 64;
 constexpr int RS_MAX_BITS = 10;
@@ -560,9 +561,10 @@ __global__ void __launch_bounds__(RS_BLOCK) k_rs_scatter(const K *__restrict__ k
 // whose (key, index) is less.  A workgroup takes 64 items; each of its 16
 // wavefronts counts over a sixteenth of the list, whose keys it reads as
 // wave-uniform values (scalar loads; a compare and an add per key), and the
-// counts meet in LDS.  6,900 64-bit keys take 16 us and 30,011 with values 70 us;
-// the 29 launches of seven radix passes take 250 and 160 (and 165 for 40,000
-// keys, where counting would take 120 and grows with the square).
+// counts meet in LDS.  The work grows with the square of the list, so the line
+// lies a little below the crossing: octrees (63-bit keys with values, whole build)
+// of 1,000 particles 117 us by counting and 168 by seven radix passes, 16,384 154
+// and 249, 32,768 217 and 272, 40,000 267 and 268, 65,536 403 and 280.
 constexpr int64_t kSmallSort = 32768;
 constexpr int kRankParts = 16;
 
