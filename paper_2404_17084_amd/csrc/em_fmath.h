@@ -85,6 +85,14 @@ __device__ __forceinline__ double horner_f64(double p, double z, double c)
     return r;
 }
 
+// The larger of x and c (fmax quiets its operands by instructions of their own).
+__device__ __forceinline__ double max_f64(double x, double c)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "s"(c));
+    return r;
+}
+
 // n / d for d of ordinary size (no overflow of 1/d): the hardware reciprocal
 // (24 bits), one Newton step (48 bits) and a residual correction.
 __device__ __forceinline__ double div_f64(double n, double d)
@@ -118,7 +126,7 @@ __device__ __forceinline__ double atan2_f64(double y, double x)
     const double ax = fabs(x);
     const bool low = y <= 0.41421356237309503 * ax, steep = y > 2.4142135623730951 * ax;
     const double num = low ? y : (steep ? -ax : y - ax);
-    const double den = fmax(low ? ax : (steep ? y : y + ax), 0x1p-1022);  // (0, 0): 0 / 2^-1022
+    const double den = max_f64(low ? ax : (steep ? y : y + ax), 0x1p-1022);  // (0, 0): 0 / 2^-1022
     double k = low ? 0.0 : (steep ? 2.0 : 1.0);
     k = x < 0.0 ? 4.0 - k : k;
     const double q = div_f64(x < 0.0 ? -num : num, den), z = q * q;

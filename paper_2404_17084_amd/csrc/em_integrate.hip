@@ -357,7 +357,7 @@ __device__ __forceinline__ double part_term(double r0, double R0, double a0, dou
     const double u = L * fma(a + b, rs, 1.0);
     const bool an = a < 0.0;
     // (c^2 may round to 0, the logarithm then is finite and multiplied by it)
-    const double Da = log1p_ratio_f64(an ? u * (Sa - a) : u, fmax(an ? c2 : a + Sa, 1e-290));
+    const double Da = log1p_ratio_f64(an ? u * (Sa - a) : u, max_f64(an ? c2 : a + Sa, 1e-290));
     const double t = a * (a + b) * rs;
     const double DxS = L * (Sb + t);
     const double DxS3 = L * fma(t, fma(Sa, Sa, fma(Sb, Sb, SS)), Sb * Sb * Sb);
