@@ -300,22 +300,31 @@ __device__ __forceinline__ double part_len(double x, double y, double la, double
 
 // The angle of two parts [a1, b1], [a2, b2] at the foot point as the argument
 // of the product of their complex numbers (R0^2 + a b) + i R0 (b - a) (the sum
-// stays below pi).  Where the product overflows (edges that reach 1e76 h and
-// more from the foot point) the numbers are scaled down first.
+// stays below pi).  Lengths below kFarLength.
 __device__ __forceinline__ void angle_product(double R0, double a1, double b1, double a2, double b2, double &y,
                                               double &x)
 {
     const double R02 = R0 * R0;
-    double x1 = fma(a1, b1, R02), y1 = R0 * (b1 - a1), x2 = fma(a2, b2, R02), y2 = R0 * (b2 - a2);
+    const double x1 = fma(a1, b1, R02), y1 = R0 * (b1 - a1), x2 = fma(a2, b2, R02), y2 = R0 * (b2 - a2);
     x = fma(x1, x2, -(y1 * y2));
     y = fma(x1, y2, x2 * y1);
-    if (!(y + fabs(x) <= 0x1p1000)) {
-        const double s1 = fmax(fabs(x1), y1) > 0x1p480 ? 0x1p-540 : 1.0, s2 = fmax(fabs(x2), y2) > 0x1p480 ? 0x1p-540 : 1.0;
-        x1 *= s1, y1 *= s1;
-        x2 *= s2, y2 *= s2;
-        x = fma(x1, x2, -(y1 * y2));
-        y = fma(x1, y2, x2 * y1);
-    }
+}
+
+// The same for an edge that may reach further from the foot point (in units of
+// h: a cell so much larger than the support): the product would overflow, so
+// the numbers are scaled down first.
+constexpr double kFarLength = 0x1p250;
+
+__device__ __forceinline__ void angle_product_far(double R0, double a1, double b1, double a2, double b2, double &y,
+                                                  double &x)
+{
+    const double R02 = R0 * R0;
+    double x1 = fma(a1, b1, R02), y1 = R0 * (b1 - a1), x2 = fma(a2, b2, R02), y2 = R0 * (b2 - a2);
+    const double s1 = fmax(fabs(x1), y1) > 0x1p480 ? 0x1p-540 : 1.0, s2 = fmax(fabs(x2), y2) > 0x1p480 ? 0x1p-540 : 1.0;
+    x1 *= s1, y1 *= s1;
+    x2 *= s2, y2 *= s2;
+    x = fma(x1, x2, -(y1 * y2));
+    y = fma(x1, y2, x2 * y1);
 }
 
 // Closed form of one piece over one edge part [a, a + L]: the integral along it
@@ -386,6 +395,7 @@ __device__ __forceinline__ double edge_term(double r0, double R0, double la, dou
     if (la < P.ca || P.cb < lb) {
         double y, x;
         angle_product(R0, la, P.ca, P.cb, lb, y, x);
+        if (!(fmax(R0, fmax(-la, lb)) < kFarLength)) angle_product_far(R0, la, P.ca, P.cb, lb, y, x);
         tot -= Ht * atan2_f64(y, x);
         wk.angles++;
     }
@@ -1267,6 +1277,7 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
             s = (int32_t)fvo[from];
             s_end = (int32_t)fvo[f0 + ((walls * (part + 1)) >> sh)];
         }
+        const bool far = mask_of(invh > JOB(far_invh)) != 0;  // edges beyond kFarLength may be among the tile's
         W.acc[lane] = 0.0;
         int32_t face_end = s;
         const int n_steps = __builtin_amdgcn_readfirstlane(wave_max((int)(s_end - s)));
@@ -1326,6 +1337,7 @@ __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsi
                 const double b1 = lane_in(has_b) ? P.ca : P.ia, a2 = lane_in(has_b) ? P.cb : P.ib;
                 double y, x;
                 angle_product(R0, la, b1, a2, lb, y, x);
+                if (far) angle_product_far(R0, la, b1, a2, lb, y, x);
                 const double w = lane_in(has_b) ? nHt : (lane_in(has_s) ? dH : 0.0);
                 const double v = flip_sign(w, sbit) * atan2_f64(y, x);
                 acc_in += lane_in(live) ? v : 0.0;
@@ -1808,6 +1820,7 @@ void launch_integrate(const DevInputs &in, const EdgeRec *edges, const PairSet &
         J.tile_base = J.wave_base = 0;
         J.pair_p = ps.pair_p;
         J.pair_c = ps.pair_c;
+        J.far_invh = far_invh(in.box);
         J.xyz = in.xyz;
         J.h = in.h;
         J.cfo = in.cfo;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <string>
@@ -285,6 +286,7 @@ struct IntJob {
     int64_t np = 0;
     int64_t tile_base = 0, wave_base = 0;
     int split = 0;  // 2^split lanes share a pair, each with its part of the cell's walls (job_split)
+    double far_invh = 0.0;  // 1 / h from which on a vertex of its cells may be 2^250 h or more from the particle
     const uint32_t *pair_p = nullptr, *pair_c = nullptr;
     const double *xyz = nullptr, *h = nullptr;
     const int64_t *cfo = nullptr, *fvo = nullptr;
@@ -309,6 +311,12 @@ struct IntJob {
 // so that a pair's result does not depend on the launch.
 inline int job_split(int64_t np, int precision) { return np <= (precision == MAP_FP64 ? 196608 : 98304) ? 2 : 0; }
 inline int64_t job_tiles(const IntJob &j) { return (j.np + (64 >> j.split) - 1) / (64 >> j.split); }
+// IntJob::far_invh: a particle lies within 2 h of its cells, so their vertices
+// are at most the diagonal of the cells' box and 2 h away.
+inline double far_invh(const double box[6])
+{
+    return 0x1p249 / (std::fabs(box[3] - box[0]) + std::fabs(box[4] - box[1]) + std::fabs(box[5] - box[2]));
+}
 // Kernel argument: one job by value (n = 1) or a device table of n jobs.
 struct JobsArg {
     const IntJob *table;

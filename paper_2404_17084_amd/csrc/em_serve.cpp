@@ -322,6 +322,7 @@ static bool launch_batch(Server &S)
                     e.wave_base = wave_tiles;
                     e.pair_p = js.ps.pair_p;
                     e.pair_c = js.ps.pair_c;
+                    e.far_invh = far_invh(js.in.box);
                     e.xyz = js.in.xyz;
                     e.h = js.in.h;
                     e.cfo = js.in.cfo;
