@@ -38,8 +38,8 @@ FLOP_FACE, FLOP_EDGE, FLOP_ETERM, FLOP_MOMENT, FLOP_QPOINT, FLOP_ANGLE = 7, 19, 
 # (profiles/traffic_integrate_queued_clumps262144.md, profiles/valu_integrate_queued_clumps262144.md); null
 # once the source has changed.
 COUNTER_SOURCE = "paper_2404_17084_amd/csrc/em_integrate.hip"
-COUNTER_SHA256_PREFIX = "38095a5d60b62c6c"
-TRAFFIC_BYTES = 3.253e9
+COUNTER_SHA256_PREFIX = "950e0d7d94db237f"
+TRAFFIC_BYTES = 3.242e9
 VALU_FLOPS_PER_LAUNCH = 5.518e11
 
 PEAK_FP64 = 78.6   # TFLOP/s, MI355X FP64 vector

@@ -183,7 +183,9 @@ int map_set_precision(map_ctx *ctx, int precision);
  * integrals from it (no FP64 fixups); S_a then deviates from 1 in the interior
  * by the table's error and the sum-to-one normalisation keeps the total mass.
  * map_set_table: each size in [8, 1024] and at most 2^27 nodes (default
- * 64 x 64 x 64); the table is rebuilt on the next MAP_TABLE mapping.
+ * 64 x 64 x 64); the table is rebuilt on the next MAP_TABLE mapping.  Device
+ * memory: 24 bytes per node (the FP64 value, and four FP32 ones: a node is read
+ * with its neighbours along r0 and R0), 3 GiB at 2^27 nodes.
  * map_get_table: the FP64 node values of the current size (host memory,
  * n0 n1 n2 doubles; built if needed).
  */

@@ -1231,12 +1231,12 @@ __device__ __forceinline__ void run_stack64(WaveStacks64 &W, int &count, int lan
 }
 
 // Bound by FP64 VALU issue: 0.20 vector instructions per SIMD and clock (a
-// dense FMA stream reaches 0.235), 81 % of the lanes active; 10.2e6 pairs of a
-// clumpy cloud take 9.8 ms (10.1 with lane predicates instead of masks), and took
-// 20.2 ms with two closed-form points per part, an angle task per part and the
-// library's double functions.  WPE:
-// resident wavefronts per SIMD the register budget is cut for (3: 167 VGPRs;
-// 2 waves 12.2 ms; a budget for 4 spills 60 to 100 registers, 27.7 ms).
+// dense FMA stream reaches 0.235), 79 % of the lanes active; 10.2e6 pairs of a
+// clumpy cloud take 8.7 ms, and took 20.2 ms with two closed-form points per part,
+// an angle task per part and the library's double functions.  WPE:
+// resident wavefronts per SIMD the register budget is cut for (3: 168 VGPRs;
+// when it took 10.1 ms, 2 waves took 12.2, and a budget for 4, which spills 60 to
+// 100 registers, 27.7).
 template <int WPE, bool MULTI>
 __global__ void __launch_bounds__(256, WPE) k_integrate_queued64(JobsArg A, unsigned *tile_ctr)
 {

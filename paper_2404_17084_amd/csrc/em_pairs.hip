@@ -204,7 +204,7 @@ __device__ __forceinline__ double box_dist2(const double *bb, double px, double 
 // chips, by the FP64 tests.  One lane per cell over a packet of 64 cells (the
 // lanes walking together, one node at a time) was a chain of several hundred
 // loads on 1/64 of the wavefronts: 0.57 -> 0.038 ms for 4,096 uniform particles,
-// 1.38 -> 0.26 ms for 65,537 and 2.18 -> 0.82 ms for 262,144 clumpy ones.
+// 1.38 -> 0.23 ms for 65,537 and 2.18 -> 0.74 ms for 262,144 clumpy ones.
 // kCells = 4: more cells share a walk but test more particles that only the
 // others need.
 constexpr int kCells = 4;
@@ -344,20 +344,21 @@ __global__ void __launch_bounds__(256) k_candidates(
 // become tasks (lane, wall) that the lanes share, and D is the least of all.
 // D decides when |D - r^2| exceeds a bound on its rounding, tol = 1e-6 (r + 2
 // rc)^2 (every vector involved is shorter than r + 2 rc, FP32 rounding of D is
-// below 10 u (r + 2 rc)^2); (4) D within tol of r^2, and cells of more than 64
+// below 10 u (r + 2 rc)^2, and the tasks' wall distance, taken from the rounded
+// particle, below 4 u (r + 2 rc)^2 more: 14 u = 0.8e-6); (4) D within tol of r^2, and cells of more than 64
 // walls, run the exact test.  Lengths are rounded to FP32 in a unit near the
 // cell's size, a power of two, so that their squares stay in FP32's range
 // whatever the caller's unit; a support 1e15 cells wide leaves it and takes
 // the exact test.  Cells too large for the staging area are read
 // from the global tables throughout.
 //
-// Bound by latency: 70 % of the wavefronts' time is waits (the cell's records,
-// gathers from LDS), vector instructions at 0.09 per SIMD and clock with half
+// Bound by latency: 58 % of the wavefronts' time is waits (the cell's records,
+// gathers from LDS), vector instructions at 0.12 per SIMD and clock with half
 // of the lanes active.  With 64 list entries per wavefront (two or three cells
 // each, staged one after the other, a third of the lanes each), every lane
 // looping over all walls it sees, and the candidates gathered into lists of
 // their own first, 262,144 clumpy particles took 2.22 ms here and 0.37 ms around
-// it; 1.73 and 0.13 ms now.
+// it; 1.55 and 0.13 ms now.
 constexpr uint32_t kNoCand = 0xffffffffu;
 
 // One slot of the tested cell as the screened test takes it: edge start (about

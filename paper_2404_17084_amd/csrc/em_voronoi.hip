@@ -112,8 +112,8 @@ __global__ void k_vor_leaf_boxes(int64_t n, int64_t NL, const double *__restrict
 // arrays with a different index on every lane, so that each access fetches a
 // cache line per lane.
 //
-// Bound by vector issue and latency together (10,200 vector instructions per
-// cell, 0.17 per SIMD and clock at 4 wavefronts per SIMD): 6.4 ms for 262,144
+// Bound by vector issue and latency together (9,600 vector instructions per
+// cell, 0.16 per SIMD and clock at 4 wavefronts per SIMD): 6.3 ms for 262,144
 // clumpy sites.  It was 18.7 ms with 26,300 instructions per cell: each leaf's 8
 // sites by one lane, the candidate list sorted and every candidate's plane
 // taken in turn, the reductions of every cut through the LDS crossbar, the
