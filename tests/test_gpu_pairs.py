@@ -84,3 +84,21 @@ def test_particles_on_the_vertices(h):
         gp, gc = mp.pairs(p, c)
     got = set(gp[own[gp] == gc].tolist())
     assert len(want) > n // 4 and want - got == set()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed", "table"])
+def test_mapping_in_other_units(precision):
+    """A whole mapping with lengths times a power of two: the same bits of the masses and of S_a."""
+    import paper_2404_17084_amd as em
+    import synth
+
+    prec = {"fp64": em.MAP_FP64, "mixed": em.MAP_MIXED, "table": em.MAP_TABLE}[precision]
+    p, c = synth.workload("clumps", 1000, 5)
+    with em.Mapper(device=0, precision=prec) as mp:
+        ref = mp.map(p, c)
+        for scale in (2.0 ** -80, 2.0 ** 70, 2.0 ** 200):
+            cs = synth.Cells(c.cell_face_off, c.face_vert_off, c.face_vert,
+                             c.face_plane * np.array([1.0, 1.0, 1.0, scale]), c.face_nb, c.verts * scale,
+                             c.cell_volume * scale ** 3, tuple(scale * np.array(synth.BOX)))
+            r = mp.map(synth.Particles(p.xyz * scale, p.m, p.h * scale), cs)
+            assert np.array_equal(r["M"], ref["M"]) and np.array_equal(r["S"], ref["S"])
